@@ -74,6 +74,22 @@ def test_geometry_sweep(geom, bf16, backend):
         assert n == p.o.Ho * p.o.Wo
 
 
+# Strided dilation: the even bits of two windows (stride 2), every s-th bit of s windows (3 - 64), one window per
+# output (beyond); output rows of less and more than a word, filters of up to 31 columns, maps whose staged part of
+# the input map fits the workgroup's LDS and maps whose does not (the large strides).
+@pytest.mark.parametrize("geom", [(2, 3, 5, 2, 2, 61, 331), (2, 2, 1, 2, 0, 33, 257), (2, 3, 7, 3, 3, 100, 410),
+                                  (1, 2, 3, 4, 1, 70, 601), (1, 2, 31, 5, 15, 80, 903), (1, 2, 4, 64, 1, 130, 8400),
+                                  (1, 2, 3, 70, 1, 290, 4600), (1, 2, 5, 8, 31, 900, 700)])
+def test_strided_dilation(geom):
+    C, O, k, s, pd, H, W = geom
+    _say(f"strided dilation {geom}")
+    spec, frames = syn.random_layer_case(sum(geom), C, O, k, s, pd, H, W, 4, change_prob=0.003, relu=True)
+    p = Pair(spec, H, W, backend=1)
+    for t, f in enumerate(frames):
+        _, n = p.step(f, 0.02, tag=f"{geom} frame {t}")
+    assert n < p.o.Ho * p.o.Wo or H * W > 1000000
+
+
 @pytest.mark.parametrize("backend", [1, 2])
 def test_nonsquare_kernel(backend):
     rng = np.random.default_rng(5)
