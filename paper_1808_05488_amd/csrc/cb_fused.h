@@ -22,15 +22,7 @@ constexpr int FUSED_ZERO_TAP = 60;      // tap index of the zero rows that pad K
 constexpr int FUSED_TAB_PAD = 64;       // entries of length 0 that close the chunk table: a group of gather rounds (up to 4 rounds of 16 fetchers) may read this far past the last chunk
 
 // Channel-last variant (C a power of two: >= 16 float32, >= 32 bfloat16; layers that keep an input state): the
-// gather reads a pixel-major shadow of the state, K is walked tap-major, no chunk table.
-constexpr int FUSED_CL_LOADS = 12;      // 16-byte gather loads a thread holds per stage at most
-// floats per column of its B stage ([n][k'] in LDS) for a tile of bn columns: the LDS window
-// divided by the columns, less 28, which makes the pitch 4 mod 32 (conflict-free 16-byte reads)
-__host__ __device__ constexpr int fused_cl_pitch(int bn) { return FUSED_LDS_BYTES / (bn * 4) - 28; }
-__host__ __device__ constexpr int fused_cl_units(int bn)
-{
-    return fused_cl_pitch(bn) / KC < FUSED_CL_LOADS / (bn / 16) ? fused_cl_pitch(bn) / KC : FUSED_CL_LOADS / (bn / 16);
-}
+// gather reads a pixel-major shadow of the state, K is walked tap-major, no chunk table (cb_fused_cl.hip).
 
 // Chunk table.  The rows of X' that belong to one input channel c and one filter row j,
 // r = (c*kh + j)*kw + i for i = 0..kw-1 (construction of X below Eq. 2), are kw consecutive
@@ -132,10 +124,10 @@ size_t fused_table_bytes(const Geom& g);
 hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, bool channel_last, hipStream_t st,
                          FusedPlan* plan);
 // src: the channel-first source of the gather (input state, or a producer's output); shadow: the
-// pixel-major copy of that source (used, and required, when plan.cl is set); OUT2: null, or the
+// pixel-major copy of that source (used, and required, when plan.cl is set); KT: the transposed filter matrix (R x Opad); OUT2: null, or the
 // pixel-major copy of the cached output (Po x O; O a multiple of 16), which receives the same updates as OUT
 hipError_t launch_fused(const Geom& g, const FusedPlan& plan, const void* src, const void* shadow, const int32_t* idx,
-                        const int* count, const void* KF, const void* tab, const float* bias, int relu, void* OUT,
+                        const int* count, const void* KF, const void* KT, const void* tab, const float* bias, int relu, void* OUT,
                         void* OUT2, hipStream_t st, Tm tm = Tm());
 
 // launches of the two element types (cb_fused_f32.hip, cb_fused_bf16.hip, cb_fused_cl.hip)
@@ -143,8 +135,10 @@ hipError_t launch_fused_f32(const Geom& g, const FusedPlan& plan, const float* s
                             const int* count, const void* KF, const int2* tab, const float* bias, int relu,
                             float* OUT, float* OUT2, hipStream_t st, Tm tm);
 hipError_t launch_fused_f32_cl(const Geom& g, const FusedPlan& plan, const float* shadow, const int32_t* idx,
-                               const int* count, const void* KF, const float* bias, int relu, float* OUT, float* OUT2,
-                               hipStream_t st, Tm tm);
+                               const int* count, const void* KF, const float* KT, const float* bias, int relu, float* OUT,
+                               float* OUT2, hipStream_t st, Tm tm);
+// its filter matrix: three bfloat16 terms per value, in fragment order (fused_pack_bytes)
+hipError_t launch_pack_fused_split(const Geom& g, const float* w, void* KF, hipStream_t st);
 hipError_t launch_fused_bf16_cl(const Geom& g, const FusedPlan& plan, const uint16_t* shadow, const int32_t* idx,
                                 const int* count, const void* KF, const float* bias, int relu, uint16_t* OUT, uint16_t* OUT2,
                                 hipStream_t st, Tm tm);

@@ -33,31 +33,6 @@ __global__ __launch_bounds__(256) void pack_fused_f32_kernel(Geom g, int Mt16, i
     }
 }
 
-// Channel-last variant: K is walked tap-major, k' = (j*kw + i)*C + c, and a lane's four values of a
-// k-group are four consecutive k':
-//   KF[((mtile*KG + kgroup)*64 + lane)].{x,y,z,w}[kk] = K(m, c*kh*kw + tap) with k' = kgroup*16 + 4*(lane/16) + kk,
-//   tap = k' / C, c = k' mod C; zero outside O x R.
-__global__ __launch_bounds__(256) void pack_fused_f32_cl_kernel(Geom g, int Mt16, int KG, const float* __restrict__ w,
-                                                                float4* __restrict__ KF)
-{
-    const long n = (long)Mt16 * KG * 64;
-    const int taps = g.kh * g.kw;
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
-        const int lane = (int)(e & 63);
-        const long gk = e >> 6;
-        const int kgroup = (int)(gk % KG), mtile = (int)(gk / KG);
-        const int m = mtile * 16 + (lane & 15);
-        float v[4];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const int k = kgroup * 16 + 4 * (lane >> 4) + kk;
-            const int tap = k / g.C, c = k - tap * g.C;
-            v[kk] = (m < g.O && k < g.R) ? w[(size_t)m * g.R + (size_t)c * taps + tap] : 0.f;
-        }
-        KF[e] = make_float4(v[0], v[1], v[2], v[3]);
-    }
-}
-
 // Filter matrix in fragment order for v_mfma_f32_16x16x32_bf16:
 //   KF[(mtile*KG + kgroup)*64 + lane] = 8 bf16: K(m = mtile*16 + lane%16, k = kgroup*32 + 8*(lane/16) + 0..7)
 __global__ __launch_bounds__(256) void pack_fused_bf16_kernel(Geom g, int Mt16, int KG, const uint16_t* __restrict__ w,
@@ -181,6 +156,8 @@ size_t fused_pack_bytes(const Geom& g)
     const size_t Rpad = g.bf16 ? (size_t)(g.R + 127) / 128 * 128 : (size_t)(g.R + KC - 1) / KC * KC;
     const size_t Mt16 = (size_t)(g.O + 127) / 128 * 8;     // 16-row tiles, padded to the largest row tile
     // 16 bytes per lane per k-group: 16 rows of float32, 32 rows of bfloat16
+    // (float32, channel-last: three bfloat16 terms, 16 bytes each per lane and 32 rows)
+    if (fused_channel_last(g) && !g.bf16) return Mt16 * (Rpad / 32) * 3 * 64 * 16;
     return Mt16 * (Rpad / (g.bf16 ? 32 : 16)) * 64 * 16;
 }
 
@@ -228,34 +205,22 @@ hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, 
     else if (g.bf16)
         hipLaunchKernelGGL(pack_fused_bf16_kernel, dim3(grid), dim3(256), 0, st, g, Mt16, KG, (const uint16_t*)w,
                            (uint4*)KF);
-    else if (plan->cl)
-        hipLaunchKernelGGL(pack_fused_f32_cl_kernel, dim3(grid), dim3(256), 0, st, g, Mt16, KG, (const float*)w,
-                           (float4*)KF);
+    else if (plan->cl) {
+        const hipError_t ep = launch_pack_fused_split(g, (const float*)w, KF, st);
+        if (ep != hipSuccess) return ep;
+    }
     else
         hipLaunchKernelGGL(pack_fused_f32_kernel, dim3(grid), dim3(256), 0, st, g, Mt16, KG, (const float*)w,
                            (float4*)KF);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (plan->cl) {
-        // no table; units per stage from the LDS window and the gather's register budget
+        // no table, and the stages are the kernel's own (cb_fused_cl.hip)
         plan->cw = 4;
         plan->ntab = 0;
-        plan->nunits = g.bf16 ? (g.R + 127) / 128 : (g.R + KC - 1) / KC;   // 256-byte units of a column
+        plan->nunits = 0;
         plan->tab_lds = 0;
-        int bm, bns, bnl;
-        fused_shape(g.O, bm, bns, bnl);
-        auto units = [&](int cap, int pf) {
-            int gu = cap < plan->nunits ? cap : plan->nunits;
-            const int rounded = gu - gu % pf;    // a multiple of the prefetch depth, unless that costs a stage
-            if (rounded >= pf && (plan->nunits + rounded - 1) / rounded == (plan->nunits + gu - 1) / gu) gu = rounded;
-            return gu;
-        };
-        plan->gu_small = units(bns == 64 ? fused_cl_units(64) : bns == 32 ? fused_cl_units(32) : fused_cl_units(16),
-                               g.O > 64 ? 2 : 4);
-        plan->gu_large = units(bnl == 128 ? fused_cl_units(128) : fused_cl_units(64), 2);
-        // (the 32-column tile at any length of K, both element types: a stage change is cheap in this kernel)
-        plan->gu_mid = (g.O > 32) ? units(fused_cl_units(32), 2) : 0;
-        plan->lds_bytes = FUSED_LDS_BYTES;
+        plan->lds_bytes = 0;
         return hipSuccess;                       // nothing built on the host: the packing kernel runs in stream order
     }
 
@@ -310,7 +275,7 @@ hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, 
 }
 
 hipError_t launch_fused(const Geom& g, const FusedPlan& plan, const void* src, const void* shadow, const int32_t* idx,
-                        const int* count, const void* KF, const void* tab, const float* bias, int relu, void* OUT,
+                        const int* count, const void* KF, const void* KT, const void* tab, const float* bias, int relu, void* OUT,
                         void* OUT2, hipStream_t st, Tm tm)
 {
     if (OUT2 && (g.O & 15) != 0) return hipErrorInvalidValue;
@@ -319,7 +284,8 @@ hipError_t launch_fused(const Geom& g, const FusedPlan& plan, const void* src, c
         if (g.bf16)
             return launch_fused_bf16_cl(g, plan, (const uint16_t*)shadow, idx, count, KF, bias, relu, (uint16_t*)OUT,
                                         (uint16_t*)OUT2, st, tm);
-        return launch_fused_f32_cl(g, plan, (const float*)shadow, idx, count, KF, bias, relu, (float*)OUT, (float*)OUT2, st, tm);
+        return launch_fused_f32_cl(g, plan, (const float*)shadow, idx, count, KF, (const float*)KT, bias, relu, (float*)OUT, (float*)OUT2,
+                                   st, tm);
     }
     if (g.bf16)
         return launch_fused_bf16(g, plan, (const uint16_t*)src, idx, count, KF, (const int2*)tab, bias, relu,

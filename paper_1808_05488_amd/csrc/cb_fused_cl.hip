@@ -1,449 +1,264 @@
-// Fused back end, float32 and bfloat16, gathering from the channel-last shadow of the input
-// state (Sec. III-A, last three processing steps in one kernel, like
-// cb_fused_f32.hip).  The shadow holds the C values of a pixel side by side, so a
-// filter tap of a listed pixel is C contiguous elements: sixteen lanes fetch 256
-// contiguous bytes with one 16-byte load each -- fully coalesced, no chunk table,
-// and one 16-byte LDS store per load.  (Written for float32; the bfloat16 form is
-// the same kernel in bytes: a 256-byte unit of a column is 128 rows of K instead of
-// 64, a 16-byte piece eight elements instead of four, and a lane's 16-byte B
-// fragment feeds ONE v_mfma_f32_16x16x32_bf16 instead of four v_mfma_f32_16x16x4_f32.)
+// Fused back end, float32 and bfloat16, gathering from the channel-last shadow of the input state (Sec. III-A, last
+// three processing steps in one kernel, like cb_fused_f32.hip).  The shadow holds the C values of a pixel side by
+// side, so a filter tap of a listed pixel is C contiguous elements: fully coalesced 16-byte loads, no chunk table.
 //
-// K is walked tap-major: row k' = (j*kw + i)*C + c.  The order of the contraction is free as
-// long as both operands agree; the filter matrix is packed in this order at layer creation
-// (pack_fused_*_cl_kernel).  Requires C to be a power of two >= 16.
+// Work item = BN listed columns x BM output channels x all of K; four wavefronts, WGM x WGN, each
+// (16*TM) x (16*TN).  K is walked tap-major, k' = (j*kw + i)*C + c (C a power of two), in groups of 32 (one step of
+// v_mfma_f32_16x16x32_bf16), UKG groups = one stage.
+//   B operand: a thread fetches 16-byte pieces of a column (consecutive lanes: consecutive pieces) and stores them to
+//     LDS, [column][k], column pitch 4 mod 32 words, so that the 16-byte fragment reads of sixteen columns fall
+//     into different banks.  Two stage buffers alternate; stage u+1 is stored and a later one requested ahead of
+//     the MFMAs of stage u, one barrier per stage.  Narrow tiles, whose MFMAs are short, take long stages (the same
+//     number of loads in flight whatever the tile width) and keep two of them in flight (GD).
+//   A operand: packed in MFMA fragment order at layer creation, read from L2 into a ring of D groups of registers,
+//     refilled as soon as a group's MFMAs are issued.
+// The grid is persistent; N is read from device memory; each XCD takes a contiguous range of column tiles.
 //
-//   B operand: LDS tile [n][k'] (k' contiguous, row pitch LDK floats with LDK = 4 mod 32, so that
-//     the 16-byte fragment reads of sixteen columns fall into different banks).  A lane reads
-//     the four consecutive k' of its quarter of a 16-row k-group with ONE 16-byte LDS read and
-//     uses them in four successive MFMAs: MFMA step kk of k-group kg contracts the rows
-//     16*kg + 4*q + kk, q = 0..3 (q = lane / 16).
-//   A operand, tile shapes, persistent grid, XCD-contiguous tile ranges, rolling prefetch of
-//     the filter fragments, epilogue: as in cb_fused_f32.hip.
+// float32 runs on the bfloat16 matrix cores as well.  A float32 product on v_mfma_f32_16x16x4_f32 costs sixteen
+// times the matrix-core time of a bfloat16 one, and float32 layers were bound by exactly that (256 -> 256, 3x3, every
+// output of 92x164: 166 us with or without the gather, the filter loads and the output stores).  Both operands are
+// split into three bfloat16 terms, x = h + m + l, each the round-to-nearest bfloat16 of what the terms before it
+// left over.  24 significant bits fit 3 x 8, so the split is exact, and the six products down to 2^-16 of the
+// leading one,
+//     h*h + (h*m + m*h) + (h*l + m*m + l*h),
+// are accumulated in float32: 6/16 of the matrix-core time.  What is left out (m*l, l*m, l*l) is below 2^-24 of the
+// product; the sum over K is rounded 6 times per 32 products instead of up to 32 times.  Error against float64 over
+// whole layers, before -> now: 64 -> 64 3x3 4.4e-7 -> 3.6e-7, 128 -> 128 3x3 5.7e-7 -> 4.8e-7, 256 -> 256 3x3 8.1e-7 ->
+// 7.0e-7.  The terms of an infinity or a NaN, and of a value that rounds up to infinity, do not add up to it; any
+// such operand makes the accumulated sum non-finite, and the epilogue recomputes every non-finite sum in plain
+// float32 from the state and the unsplit filter matrix (exact_dot), so that infinities and NaNs come out as they do
+// in float32 arithmetic.
 #include "cb_fused.h"
+
+#include <type_traits>
 
 namespace cb {
 
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 
-template <typename T, int WGM, int WGN, int TM, int TN>
-__device__ __forceinline__ void fused_cl_body(const Geom& g, const T* __restrict__ S2,
-                                                  const int32_t* __restrict__ idx, const int N,
-                                                  const float4* __restrict__ KF, const float* __restrict__ bias,
-                                                  int relu, T* __restrict__ OUT, T* __restrict__ OUT2, const int GUin)
+// two neighbouring values -> their three bfloat16 terms, packed
+__device__ __forceinline__ void split2(float a, float b, unsigned& h, unsigned& m, unsigned& l)
 {
-    constexpr bool BF = sizeof(T) == 2;
-    constexpr int UK = BF ? 128 : KC;            // rows of K in a 256-byte unit of a column
-    constexpr int EPV = BF ? 8 : 4;              // elements per 16-byte piece
-    constexpr unsigned ESZ = (unsigned)sizeof(T);
-    static_assert(WGM * WGN == 4, "four wavefronts per workgroup");
-    constexpr int BM = 16 * TM * WGM, BN = 16 * TN * WGN;
-    constexpr int NP = BN / 16;                  // columns per thread: column (tid / 16) + 16 * p
-    constexpr int GUMAX = FUSED_CL_LOADS / NP;   // units per stage at most (register budget of the gather)
-    constexpr int LDK = fused_cl_pitch(BN);      // floats per column of the B stage
-    static_assert(GUMAX >= 1 && GUMAX * KC <= LDK, "a stage fits its LDS column");
-    const int GU = GUin < 1 ? 1 : (GUin < GUMAX ? GUin : GUMAX);
-    constexpr bool TWO = TM * TN < 4;            // second accumulator chain where a wavefront has few tiles
-    constexpr int PF = TM * TN >= 2 ? 2 : 4;     // units of filter fragments in flight (register budget)
-    __shared__ int qs[BN];
-    extern __shared__ float4 dyn_lds4[];
-    float* const Bs = reinterpret_cast<float*>(dyn_lds4);
+    h = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
+    a -= __uint_as_float(h << 16);
+    b -= __uint_as_float(h & 0xFFFF0000u);
+    m = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
+    a -= __uint_as_float(m << 16);
+    b -= __uint_as_float(m & 0xFFFF0000u);
+    l = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
+}
 
-    const int nunits = (g.R + UK - 1) / UK;      // 256-byte units of K
-    const int lc = 31 - __builtin_clz((unsigned)g.C);          // C = 1 << lc
-    const unsigned inv_kw = (65536u + (unsigned)g.kw - 1u) / (unsigned)g.kw;   // tap / kw = tap * inv_kw >> 16 for tap < 64
-    // raw buffer over the shadow: 32-bit byte offsets; an offset beyond the end reads as 0
+// One output in plain float32 arithmetic: the receptive field of listed pixel q times filter row m (KT: the
+// filter matrix transposed, row (c*kh + j)*kw + i).  Only for sums that came out non-finite.
+__device__ __forceinline__ float exact_dot(const Geom& g, const float* __restrict__ S2, const float* __restrict__ KT, int q, int m)
+{
+    const int yo = q / g.Wo, xo = q - yo * g.Wo;
+    const int y0 = yo * g.s - g.p, x0 = xo * g.s - g.p;
+    const int kk = g.kh * g.kw;
+    float v = 0.f;
+    for (int j = 0; j < g.kh; ++j)
+        for (int i = 0; i < g.kw; ++i) {
+            const bool in = (unsigned)(y0 + j) < (unsigned)g.H && (unsigned)(x0 + i) < (unsigned)g.W;
+            const float* px = S2 + (in ? ((size_t)(y0 + j) * g.W + (x0 + i)) * g.C : 0);
+            const float* kt = KT + (size_t)(j * g.kw + i) * g.Opad + m;
+            // (a padding tap is a zero that takes part: zero times an infinite filter value is no number)
+            for (int c = 0; c < g.C; ++c) v = fmaf(in ? px[c] : 0.f, kt[(size_t)c * kk * g.Opad], v);
+        }
+    return v;
+}
+
+// k-groups per stage for a tile of bn columns (float32: 1 / 2 / 4 from 128 / 64 / 32 columns on).  Longer stages mean fewer
+// barriers, shorter ones less padding of K and an earlier first MFMA.  bfloat16, twice as long: 64 -> 64 at 307 200
+// listed pixels 70 against 50 us, 32 -> 32 43 against 28 us.
+// (wgk: wavefronts that share a tile's K; each takes every wgk-th group of a stage)
+template <typename T> __host__ __device__ constexpr int cl_groups(int bn, int wgk = 1)
+{
+    if (wgk > 1) return sizeof(T) == 4 ? 8 : 16;
+    return sizeof(T) == 4 ? (bn >= 128 ? 1 : bn == 64 ? 2 : 4) : (bn >= 128 ? 2 : bn == 64 ? 4 : 8);
+}
+// bytes per column of a stage buffer, dynamic LDS (two buffers and the listed pixels; float32 three, bfloat16 four workgroups in 160 KB)
+template <typename T> __host__ __device__ constexpr unsigned cl_pitch(int bn, int wgk = 1)
+{
+    return (unsigned)cl_groups<T>(bn, wgk) * (sizeof(T) == 4 ? 192u : 64u) + 16u;
+}
+template <typename T> __host__ __device__ constexpr unsigned cl_lds(int bn, int wgk = 1) { return 2u * (unsigned)bn * cl_pitch<T>(bn, wgk) + 4u * (unsigned)bn; }
+constexpr unsigned CL_LDS_F32 = cl_lds<float>(128), CL_LDS_BF16 = cl_lds<uint16_t>(128);
+static_assert(3 * CL_LDS_F32 <= 163840 && cl_lds<float>(64) <= CL_LDS_F32 && cl_lds<float>(32) <= CL_LDS_F32 && cl_lds<float>(16) <= CL_LDS_F32 &&
+              4 * CL_LDS_BF16 <= 163840 && cl_lds<uint16_t>(64) <= CL_LDS_BF16 && cl_lds<uint16_t>(32) <= CL_LDS_BF16 &&
+              cl_lds<uint16_t>(16) <= CL_LDS_BF16 && cl_lds<float>(16, 4) <= CL_LDS_F32 && cl_lds<uint16_t>(16, 4) <= CL_LDS_BF16,
+              "the widest tile takes the most LDS");
+
+// Divisions by layer constants.  q / Wo = q * inv_wo >> 42, exact while q * Wo < 2^42, which Wo < 4096 makes sure of (0:
+// divide); tap / kw = tap * inv_kw >> 16 for the few taps there are.
+struct ClDiv { unsigned long long inv_wo; unsigned inv_kw; };
+
+template <typename T, int WGM, int WGN, int TM, int TN, int WGK = 1>
+__device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, const T* __restrict__ S2,
+                                                 const int32_t* __restrict__ idx, const int N,
+                                                 const uint4* __restrict__ KF, const float* __restrict__ KT,
+                                                 const float* __restrict__ bias, int relu, T* __restrict__ OUT,
+                                                 T* __restrict__ OUT2)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr int TERMS = F32 ? 3 : 1;           // bfloat16 terms per value
+    constexpr int EPV = 16 / (int)sizeof(T);     // elements per 16-byte piece
+    constexpr unsigned ESZ = (unsigned)sizeof(T);
+    static_assert(WGM * WGN * WGK == 4, "four wavefronts per workgroup");
+    constexpr int BM = 16 * TM * WGM, BN = 16 * TN * WGN;
+    constexpr int UKG = cl_groups<T>(BN, WGK);   // k-groups of 32 per stage
+    constexpr int UKW = UKG / WGK;               // ... of one wavefront
+    constexpr int UK = 32 * UKG;
+    constexpr int PPC = UK / EPV;                // 16-byte pieces of a column in a stage
+    constexpr int CPP = 256 / PPC;               // columns one round of loads covers
+    constexpr int NP = BN / CPP;                 // loads per thread and stage
+    static_assert(PPC <= 256 && NP * CPP == BN, "pieces come out even");
+    // k-groups of filter fragments in flight: an L2 latency's worth of MFMAs, as far as the registers go
+    constexpr int DMAX = F32 ? (TM == 1 ? 4 : 2)
+                          : (TM * TN <= 2 ? 8 : 4);
+    constexpr int D = DMAX < 4 * UKW ? DMAX : 4 * UKW;
+    constexpr int GD = F32 && TM * TN <= 2 ? 2 : 1;     // stages of gathered pieces in flight
+    // stages per round of the stage loop: ring slot and register set are compile-time indexes
+    constexpr int UU = D / UKW > GD ? D / UKW : GD;
+    static_assert(UU * UKW % D == 0 && UU % GD == 0, "a round of stages is whole rings");
+    constexpr unsigned PITCH = cl_pitch<T>(BN, WGK), BUF = BN * PITCH;
+    constexpr unsigned PLANE = UKG * 64u;        // bytes of one term of a column
+    constexpr bool TWO = TM * TN < 4;            // second accumulator chain where a wavefront has few tiles
+    extern __shared__ uint4 dyn_lds4[];          // two stage buffers, then the listed pixel of every column
+    char* const Bs = reinterpret_cast<char*>(dyn_lds4);
+    int* const qs = reinterpret_cast<int*>(Bs + 2 * BUF);
+
+    const int nkg = F32 ? (g.R + 63) / 64 * 2 : (g.R + 127) / 128 * 4;       // k-groups of the packed filter matrix
+    const int nunits = (nkg + UKG - 1) / UKG;
+    const int lc = 31 - __builtin_clz((unsigned)g.C);
     const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<T*>(S2), 0, (int)((unsigned)g.C * (unsigned)g.P * ESZ), 0x00020000);
     constexpr unsigned NOWHERE = 0xFFFFFFF0u;
-    const int KG = nunits * 4;                   // 16-row groups of the packed filter matrix
-    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float4*>(KF), 0, (int)((unsigned)((g.O + 127) / 128 * 8) * (unsigned)KG * 1024u), 0x00020000);
-    const int NT = (N + BN - 1) / BN;
-    const int MT = (g.O + BM - 1) / BM;
-    const int per_xcd = (NT + 7) / 8;
-    const long total = (long)per_xcd * 8 * MT;
+    // tiles: every XCD (workgroup number mod 8) walks its own range of column tiles, all row tiles of one column tile in
+    // turn.  (32 bits: the outputs of 2^31 such tiles would not fit any memory.)
+    const unsigned NT = ((unsigned)N + BN - 1u) / BN;
+    const unsigned MT = ((unsigned)g.O + BM - 1u) / BM;
+    const unsigned per_xcd = (NT + 7u) / 8u, total = per_xcd * MT;
+    const unsigned xcd0 = (blockIdx.x & 7u) * per_xcd;
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int wm = wv / WGN, wn = wv % WGN;
+    const int wk = __builtin_amdgcn_readfirstlane(wv % WGK);
+    const int wm = wv / WGK / WGN, wn = wv / WGK % WGN;
     const int wm_s = __builtin_amdgcn_readfirstlane(wm);
     const int l16 = lane & 15, lq = lane >> 4;
-    const int gc = tid >> 4, ch = tid & 15;      // first column of this thread, its 16-byte piece of a 64-row unit
-    // a unit holds 64 / C taps when C < 64: this thread's piece lies in tap dt of the unit, channels cl .. cl + 3
+    const int gc = tid / PPC, ch = tid % PPC;    // first column of this thread, its piece of a stage
     const int dt = (EPV * ch) >> lc, cl = (EPV * ch) & (g.C - 1);
 
-    // the listed pixels of this thread's columns are requested one tile ahead
     int qnext[NP];
-    auto fetch_q = [&](long tt, int (&q)[NP]) {
-        const int ntt = (int)(tt & 7) * per_xcd + (int)((tt >> 3) / MT);
+    auto fetch_q = [&](unsigned u, int (&q)[NP]) {
+        const unsigned ntt = xcd0 + u / MT;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            const int n = ntt * BN + gc + 16 * p;
-            q[p] = (tt < total && ntt < NT && n < N) ? idx[n] : -1;
+            const unsigned n = ntt * BN + gc + CPP * p;
+            q[p] = (u < total && n < (unsigned)N) ? idx[n] : -1;
         }
     };
-    fetch_q(blockIdx.x, qnext);
+    fetch_q(blockIdx.x >> 3, qnext);
 
-    for (long t = blockIdx.x; t < total; t += gridDim.x) {
-        const int xcd = (int)(t & 7);
-        const long u = t >> 3;
-        const int mt = (int)(u % MT);
-        const int nt = xcd * per_xcd + (int)(u / MT);
+    for (unsigned uq = blockIdx.x >> 3; uq < total; uq += gridDim.x >> 3) {
+        const int mt = (int)(uq % MT);
+        const unsigned nt = xcd0 + uq / MT;
         int q[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) q[p] = qnext[p];
-        fetch_q(t + gridDim.x, qnext);
+        fetch_q(uq + (gridDim.x >> 3), qnext);
         if (nt >= NT) continue;
         const int m0 = mt * BM;
-        const int uend = nunits;
 
-        float4 areg[PF][TM][4];
-        auto aload = [&](int c, float4 (&dst)[TM][4]) {
+        // ring of filter fragments: [k-group mod D][row tile][term].  The resource covers this tile's rows.
+        const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint4*>(KF) + (size_t)(m0 >> 4) * nkg * (TERMS * 64), 0,
+            (int)((unsigned)(BM / 16) * (unsigned)nkg * (TERMS * 1024u)), 0x00020000);
+        uint4 areg[D][TM][TERMS];
+        auto aload = [&](int kg, uint4 (&dst)[TM][TERMS]) {
+            const int kc = kg < nkg ? kg : nkg - 1;
 #pragma unroll
             for (int a = 0; a < TM; ++a) {
-                const unsigned soff = (unsigned)(((m0 >> 4) + wm_s * TM + a) * KG + c * 4) * 1024u;
+                const unsigned soff = (unsigned)((wm_s * TM + a) * nkg + kc) * (TERMS * 1024u);
 #pragma unroll
-                for (int kg = 0; kg < 4; ++kg)
-                    dst[a][kg] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, lane * 16 + kg * 1024, (int)soff, 0));
+                for (int e = 0; e < TERMS; ++e)
+                    dst[a][e] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, lane * 16 + e * 1024, (int)soff, 0));
             }
         };
-        const bool ring = GU % PF == 0;
-#pragma unroll
-        for (int p = 0; p < PF; ++p) aload(p < uend - 1 ? p : uend - 1, areg[p]);
 
-        // per column: which taps lie inside the image, and the byte offset of the top-left tap's
-        // channel cl in the shadow (it may wrap below zero for pixels at the border: only taps
-        // inside the image are fetched, and for those the sum is a valid offset again)
-        unsigned long long ok[NP];
-        unsigned base[NP];
+        // per column: which filter rows and columns lie inside the image (all clear for a column without a pixel), and the
+        // byte offset of the top-left tap's channel cl in the shadow (it may wrap below zero at the border: only
+        // taps inside are fetched, and for those the sum is a valid offset again)
+        unsigned okr[NP], okc[NP], base[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const bool colv = q[p] >= 0;
             const int qq = colv ? q[p] : 0;
-            const int yo = qq / g.Wo, xo = qq - yo * g.Wo;
+            const int yo = div.inv_wo ? (int)(((unsigned long long)(unsigned)qq * div.inv_wo) >> 42) : qq / g.Wo;
+            const int xo = qq - yo * g.Wo;
             const int y0 = yo * g.s - g.p, x0 = xo * g.s - g.p;
-            ok[p] = taps_inside(g, colv, y0, x0);
+            // bits max(0, -y0) .. min(kh, H - y0) - 1
+            auto inside = [](int o, int k, int size) -> unsigned {
+                const int lo = o < 0 ? -o : 0, hi = size - o < k ? size - o : k;
+                return hi > lo ? ((1u << hi) - 1u) & ~((1u << lo) - 1u) : 0u;
+            };
+            okr[p] = colv ? inside(y0, g.kh, g.H) : 0u;
+            okc[p] = inside(x0, g.kw, g.W);
             base[p] = (((unsigned)(y0 * g.W + x0) << lc) + (unsigned)cl) * ESZ;
         }
-        __syncthreads();                          // the previous tile's epilogue has read qs
-        if (ch == 0) {
-#pragma unroll
-            for (int p = 0; p < NP; ++p) qs[gc + 16 * p] = q[p];
-        }
 
-        // One stage = up to GU units: all its loads are issued together, parked in registers
-        // and stored to LDS behind one barrier pair.  Unit u0 + r of column p: rows
-        // (u0 + r)*64 + 4*ch .. + 3 of K, i.e. tap ((u0 + r)*64 >> lc) + dt, channels
-        // ((u0 + r)*64 mod C) + cl .. + 3.  Taps outside the image, taps beyond the filter (the
-        // rows that pad K to a multiple of 64) and columns without a pixel read as 0.
-        float4 breg[GUMAX][NP];
-        auto gload_stage = [&](int u0) {
-            const int ucount = uend - u0 < GU ? uend - u0 : GU;
+        uint4 breg[GD][NP];
+        auto gload = [&](int u, uint4 (&dst)[NP]) {
+            const unsigned kb = (unsigned)u * (unsigned)UK;
+            const unsigned tap = (kb >> lc) + (unsigned)dt;
+            const unsigned j = (tap * div.inv_kw) >> 16, i = tap - j * (unsigned)g.kw;
+            const unsigned toff = (((j * (unsigned)g.W + i) << lc) + (kb & (unsigned)(g.C - 1))) * ESZ;
+            // (rows that pad K have j >= kh, whose bit is clear, as bit 31 is for any j beyond it: kh, kw <= 31)
+            const unsigned jj = j < 31u ? j : 31u;
 #pragma unroll
-            for (int r = 0; r < GUMAX; ++r) {
-                if (r < ucount) {
-                    const unsigned kb = (unsigned)(u0 + r) * (unsigned)UK;
-                    const unsigned tap = (kb >> lc) + (unsigned)dt;
-                    const unsigned j = (tap * inv_kw) >> 16, i = tap - j * (unsigned)g.kw;
-                    const unsigned toff = (((j * (unsigned)g.W + i) << lc) + (kb & (unsigned)(g.C - 1))) * ESZ;
-#pragma unroll
-                    for (int p = 0; p < NP; ++p) {
-                        const bool in = ((ok[p] >> tap) & 1ull) != 0ull;     // tap < 64 always
-                        breg[r][p] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(
-                            srsrc, (int)(in ? base[p] + toff : NOWHERE), 0, 0));
-                    }
-                }
+            for (int p = 0; p < NP; ++p) {
+                const bool in = (((okr[p] >> jj) & (okc[p] >> i)) & 1u) != 0u;
+                dst[p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                    srsrc, (int)(in ? base[p] + toff : NOWHERE), 0, 0));
             }
         };
-        auto lds_store_stage = [&](int u0) {
-            const int ucount = uend - u0 < GU ? uend - u0 : GU;
-            float* Bst = Bs + gc * LDK + 4 * ch;
+        auto lds_store = [&](int buf, const uint4 (&v)[NP]) {
+            char* dst = Bs + buf * BUF + gc * PITCH + (F32 ? 8 : 16) * ch;
 #pragma unroll
-            for (int r = 0; r < GUMAX; ++r) {
-                if (r < ucount) {
-#pragma unroll
-                    for (int p = 0; p < NP; ++p)
-                        *reinterpret_cast<float4*>(Bst + 16 * p * LDK + r * KC) = breg[r][p];
-                }
+            for (int p = 0; p < NP; ++p) {
+                if constexpr (F32) {
+                    uint2 h, m, l;
+                    split2(__uint_as_float(v[p].x), __uint_as_float(v[p].y), h.x, m.x, l.x);
+                    split2(__uint_as_float(v[p].z), __uint_as_float(v[p].w), h.y, m.y, l.y);
+                    *reinterpret_cast<uint2*>(dst + CPP * p * PITCH) = h;
+                    *reinterpret_cast<uint2*>(dst + CPP * p * PITCH + PLANE) = m;
+                    *reinterpret_cast<uint2*>(dst + CPP * p * PITCH + 2 * PLANE) = l;
+                } else
+                    *reinterpret_cast<uint4*>(dst + CPP * p * PITCH) = v[p];
             }
         };
 
-        floatx4 acc[TM][TN], acc1[TWO ? TM : 1][TWO ? TN : 1];
+        floatx4 acc[TM][TN], acc1[TM][TN];         // (acc1: unused unless TWO)
 #pragma unroll
         for (int a = 0; a < TM; ++a)
 #pragma unroll
             for (int b = 0; b < TN; ++b) {
                 acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (TWO) acc1[a][b] = acc[a][b];
+                acc1[a][b] = acc[a][b];
             }
 
-        // One unit = four k-groups of four MFMA steps.  The B fragments of the next k-group are
-        // requested from LDS before the MFMAs of the current one are issued; the first k-group of
-        // a unit is requested during the last k-group of the unit before it (same stage).
-        // (wide tiles have no registers left for the carried fragments, and 128 MFMAs per k-group to hide
-        // one exposed LDS read per unit behind)
-        constexpr bool CARRY = TN < 4;
-        float4 bcarry[CARRY ? TN : 1];
-        auto compute = [&](int uu, const float4 (&af)[TM][4], bool first, bool more) {
-            const float* Bu = Bs + (wn * TN * 16 + l16) * LDK + uu * KC + lq * 4;
-            float4 bfr[2][TN];
-            auto bload = [&](const float* base_, int kg, float4 (&dst)[TN]) {
+        // (the loads in flight at the stage loop's entry are in the order of those in flight at its back edge: where
+        // the two differ the compiler waits for the longer of the two queues)
+        gload(0, breg[0]);
+        if constexpr (GD == 2) {
+            gload(1, breg[1]);
 #pragma unroll
-                for (int b = 0; b < TN; ++b) dst[b] = *reinterpret_cast<const float4*>(base_ + b * 16 * LDK + kg * 16);
-            };
-            if (first || !CARRY) bload(Bu, 0, bfr[0]);
-            else {
-#pragma unroll
-                for (int b = 0; b < TN; ++b) bfr[0][b] = bcarry[CARRY ? b : 0];
-            }
-#pragma unroll
-            for (int kg = 0; kg < 4; ++kg) {
-                if (kg + 1 < 4) bload(Bu, kg + 1, bfr[(kg + 1) & 1]);
-                else if (CARRY && more) {
-#pragma unroll
-                    for (int b = 0; b < TN; ++b)
-                        bcarry[CARRY ? b : 0] = *reinterpret_cast<const float4*>(Bu + KC + b * 16 * LDK);
-                }
-                if (TN >= 4) __builtin_amdgcn_sched_barrier(0);
-                if constexpr (BF) {
-#pragma unroll
-                    for (int a = 0; a < TM; ++a)
-#pragma unroll
-                        for (int b = 0; b < TN; ++b) {
-                            const bf16x8 av = __builtin_bit_cast(bf16x8, af[a][kg]), bv = __builtin_bit_cast(bf16x8, bfr[kg & 1][b]);
-                            if (TWO && (kg & 1))
-                                acc1[TWO ? a : 0][TWO ? b : 0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                    av, bv, acc1[TWO ? a : 0][TWO ? b : 0], 0, 0, 0);
-                            else
-                                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[a][b], 0, 0, 0);
-                        }
-                } else {
-#pragma unroll
-                    for (int k4 = 0; k4 < 4; ++k4) {
-#pragma unroll
-                        for (int a = 0; a < TM; ++a) {
-                            const float av = k4 == 0 ? af[a][kg].x : k4 == 1 ? af[a][kg].y : k4 == 2 ? af[a][kg].z : af[a][kg].w;
-#pragma unroll
-                            for (int b = 0; b < TN; ++b) {
-                                const float4& bq = bfr[kg & 1][b];
-                                const float bv = k4 == 0 ? bq.x : k4 == 1 ? bq.y : k4 == 2 ? bq.z : bq.w;
-                                if (TWO && (k4 & 1))
-                                    acc1[TWO ? a : 0][TWO ? b : 0] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                        av, bv, acc1[TWO ? a : 0][TWO ? b : 0], 0, 0, 0);
-                                else
-                                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[a][b], 0, 0, 0);
-                            }
-                        }
-                    }
-                }
-                if (TN >= 4) __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-
-        gload_stage(0);
-        for (int u0 = 0; u0 < uend; u0 += GU) {
-            const int ucount = uend - u0 < GU ? uend - u0 : GU;
-            const int ulast = u0 + ucount - 1;
-            __syncthreads();                      // the previous stage's fragments have been read (first stage: qs is written)
-            lds_store_stage(u0);
-            __syncthreads();
-            if (!ring && u0 != 0) {
-#pragma unroll
-                for (int p = 0; p < PF; ++p) aload(u0 + p < ulast ? u0 + p : ulast, areg[p]);
-            }
-            if (u0 + GU < uend) gload_stage(u0 + GU);   // in flight during this stage's MFMAs
-            const int alast = ring ? uend - 1 : ulast;
-            const int nfull = ucount / PF;
-            for (int grp = 0; grp < nfull; ++grp) {
-#pragma unroll
-                for (int p = 0; p < PF; ++p) {
-                    const int uu = grp * PF + p;
-                    compute(uu, areg[p], uu == 0, uu + 1 < ucount);
-                    aload(u0 + uu + PF < alast ? u0 + uu + PF : alast, areg[p]);
-                }
-            }
-#pragma unroll
-            for (int p = 0; p < PF - 1; ++p)
-                if (nfull * PF + p < ucount) compute(nfull * PF + p, areg[p], nfull * PF + p == 0, nfull * PF + p + 1 < ucount);
+            for (int s = 0; s < D; ++s) aload(s * WGK + wk, areg[s]);
         }
-
-        if (TWO) {
-#pragma unroll
-            for (int a = 0; a < TM; ++a)
-#pragma unroll
-                for (int b = 0; b < TN; ++b) acc[a][b] += acc1[TWO ? a : 0][TWO ? b : 0];
-        }
-        // output update: bias + ReLU, written at the listed pixels only
-#pragma unroll
-        for (int b = 0; b < TN; ++b) {
-            const int qn = qs[(wn * TN + b) * 16 + l16];
-            if (qn < 0) continue;
-#pragma unroll
-            for (int a = 0; a < TM; ++a) {
-                const int mb = m0 + (wm * TM + a) * 16 + lq * 4;
-                float v4[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int m = mb + r;
-                    v4[r] = 0.f;
-                    if (m < g.O) {
-                        float v = acc[a][b][r] + bias[m];
-                        if (relu) v = v > 0.f ? v : 0.f;
-                        st_out(OUT + (size_t)m * g.Po + qn, v);
-                        v4[r] = v;
-                    }
-                }
-                // (a layer that keeps the pixel-major copy has a multiple of 16 output channels)
-                if (OUT2 && mb < g.O) st_out4(OUT2 + (size_t)qn * g.O + mb, v4);
-            }
-        }
-    }
-}
-
-// Wide tiles with a double-buffered B stage (layers with more than 64 output channels, from 16 384
-// listed pixels on).  The workgroup tile is 128 x 128 (128 x 64 while the wider tiles would number
-// fewer than the 512 workgroups that run at a time); a wavefront owns 32 rows x all columns, so every
-// filter fragment is loaded by exactly one wavefront of the workgroup.  A stage is ONE 256-byte unit of
-// every column, and two stage buffers alternate: the gathered unit u+1 is stored into the free buffer
-// at the start of unit u and the loads of unit u+2 are issued right behind it, so that the only thing
-// between the MFMAs of two units is one barrier.  The filter fragments run in a ring of four
-// k-groups (one unit), each refilled for the next unit as soon as its MFMAs are issued.  No
-// conditional loads in the unit loop: units beyond the end of K are gathered from nowhere (zeros) and
-// never multiplied.  Per tile, everything with a memory round trip in it is requested at the start:
-// the listed pixels (a tile ahead), the bias, and no integer division per column.
-constexpr int FUSED_DB_PITCH = 272;               // bytes per column of a stage buffer: 256 + 16, i.e. 4 mod 32 banks
-__host__ __device__ constexpr unsigned fused_db_lds(int bn) { return 2u * (unsigned)bn * FUSED_DB_PITCH; }
-
-template <typename T, int WGM, int WGN, int TM, int TN>
-__device__ __forceinline__ void fused_cl_db_body(const Geom& g, const T* __restrict__ S2,
-                                                 const int32_t* __restrict__ idx, const int N,
-                                                 const float4* __restrict__ KF, const float* __restrict__ bias,
-                                                 int relu, T* __restrict__ OUT, T* __restrict__ OUT2)
-{
-    constexpr bool BF = sizeof(T) == 2;
-    constexpr int UK = BF ? 128 : KC;            // rows of K in a 256-byte unit of a column
-    constexpr int EPV = BF ? 8 : 4;              // elements per 16-byte piece
-    constexpr unsigned ESZ = (unsigned)sizeof(T);
-    static_assert(WGM * WGN == 4, "four wavefronts per workgroup");
-    constexpr int BM = 16 * TM * WGM, BN = 16 * TN * WGN;
-    constexpr int NP = BN / 16;                  // columns per thread: column (tid / 16) + 16 * p
-    constexpr int BUF = BN * FUSED_DB_PITCH;     // bytes of one stage buffer
-    __shared__ int qs[BN];
-    extern __shared__ float4 dyn_lds4[];
-    char* const Bs = reinterpret_cast<char*>(dyn_lds4);
-
-    const int nunits = (g.R + UK - 1) / UK;
-    const int lc = 31 - __builtin_clz((unsigned)g.C);
-    // q / Wo for 0 <= q < 2^30 without a division: floor(q * ceil(2^42 / Wo) / 2^42) is exact while
-    // q * Wo < 2^42, and Wo < 2^12 here (the launcher checks)
-    const unsigned long long inv_wo = ((1ull << 42) + (unsigned)g.Wo - 1ull) / (unsigned)g.Wo;
-    const unsigned inv_kw = (65536u + (unsigned)g.kw - 1u) / (unsigned)g.kw;
-    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<T*>(S2), 0, (int)((unsigned)g.C * (unsigned)g.P * ESZ), 0x00020000);
-    constexpr unsigned NOWHERE = 0xFFFFFFF0u;
-    const int KG = nunits * 4;
-    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float4*>(KF), 0, (int)((unsigned)((g.O + 127) / 128 * 8) * (unsigned)KG * 1024u), 0x00020000);
-    const int NT = (N + BN - 1) / BN;
-    const int MT = (g.O + BM - 1) / BM;
-    const int per_xcd = (NT + 7) / 8;
-    const long total = (long)per_xcd * 8 * MT;
-
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int wm = wv / WGN, wn = wv % WGN;
-    const int wm_s = __builtin_amdgcn_readfirstlane(wm);
-    const int l16 = lane & 15, lq = lane >> 4;
-    const int gc = tid >> 4, ch = tid & 15;
-    const int dt = (EPV * ch) >> lc, cl = (EPV * ch) & (g.C - 1);
-
-    int qnext[NP];
-    auto fetch_q = [&](long tt, int (&q)[NP]) {
-        const int ntt = (int)(tt & 7) * per_xcd + (int)((tt >> 3) / MT);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const int n = ntt * BN + gc + 16 * p;
-            q[p] = (tt < total && ntt < NT && n < N) ? idx[n] : -1;
-        }
-    };
-    fetch_q(blockIdx.x, qnext);
-
-    for (long t = blockIdx.x; t < total; t += gridDim.x) {
-        const int xcd = (int)(t & 7);
-        const long uq = t >> 3;
-        const int mt = (int)(uq % MT);
-        const int nt = xcd * per_xcd + (int)(uq / MT);
-        int q[NP];
-#pragma unroll
-        for (int p = 0; p < NP; ++p) q[p] = qnext[p];
-        fetch_q(t + gridDim.x, qnext);
-        if (nt >= NT) continue;
-        const int m0 = mt * BM;
-
-        // ring of filter fragments: k-group kg of the unit being multiplied, TM row tiles
-        float4 areg[4][TM];
-        auto aload = [&](int u, int kg) {
-            const int uc = u < nunits ? u : nunits - 1;
-#pragma unroll
-            for (int a = 0; a < TM; ++a) {
-                const unsigned soff = (unsigned)(((m0 >> 4) + wm_s * TM + a) * KG + uc * 4 + kg) * 1024u;
-                areg[kg][a] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, lane * 16, (int)soff, 0));
-            }
-        };
-
-        // per column: which filter rows (bits 0..15) and filter columns (bits 16..31) lie inside the
-        // image (all clear for a column without a pixel), and the byte offset of the top-left tap's
-        // channel cl in the shadow (may wrap below zero at the border: only taps inside are fetched)
-        unsigned ok[NP];
-        unsigned base[NP];
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const bool colv = q[p] >= 0;
-            const int qq = colv ? q[p] : 0;
-            const int yo = (int)(((unsigned long long)(unsigned)qq * inv_wo) >> 42), xo = qq - yo * g.Wo;
-            const int y0 = yo * g.s - g.p, x0 = xo * g.s - g.p;
-            unsigned m = 0;
-            if (colv) {
-                for (int j = 0; j < g.kh; ++j) m |= ((unsigned)(y0 + j) < (unsigned)g.H ? 1u : 0u) << j;
-                for (int i = 0; i < g.kw; ++i) m |= ((unsigned)(x0 + i) < (unsigned)g.W ? 0x10000u : 0u) << i;
-            }
-            ok[p] = m;
-            base[p] = (((unsigned)(y0 * g.W + x0) << lc) + (unsigned)cl) * ESZ;
-        }
-
-        float4 breg[NP];
-        auto gload = [&](int u) {
-            const unsigned kb = (unsigned)u * (unsigned)UK;
-            const unsigned tap = (kb >> lc) + (unsigned)dt;
-            const unsigned j = (tap * inv_kw) >> 16, i = tap - j * (unsigned)g.kw;
-            const unsigned toff = (((j * (unsigned)g.W + i) << lc) + (kb & (unsigned)(g.C - 1))) * ESZ;
-            // (rows that pad K to a whole unit have j >= kh: their bit is clear)
-            const unsigned need = u < nunits && j < 16u ? (1u << j) | (0x10000u << i) : 0xFFFFFFFFu;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const bool in = (ok[p] & need) == need;
-                breg[p] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(
-                    srsrc, (int)(in ? base[p] + toff : NOWHERE), 0, 0));
-            }
-        };
-        auto lds_store = [&](int buf) {
-            char* dst = Bs + buf * BUF + gc * FUSED_DB_PITCH + 16 * ch;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) *reinterpret_cast<float4*>(dst + 16 * p * FUSED_DB_PITCH) = breg[p];
-        };
-
-        floatx4 acc[TM][TN];
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-            for (int b = 0; b < TN; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-        // (the loads in flight at the loop's entry are the ones in flight at its back edge, in the same
-        // order -- eight gathered pieces, then the filter fragments: where the two differ the compiler
-        // waits for the longer of the two queues)
-        gload(0);
-        // bias of this wavefront's rows: requested now, used in the epilogue
-        float bv[TM][4];
+        float bv[TM][4];                          // bias of this wavefront's rows
 #pragma unroll
         for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -454,176 +269,289 @@ __device__ __forceinline__ void fused_cl_db_body(const Geom& g, const T* __restr
         __syncthreads();                          // the previous tile has read its last stage and its qs
         if (ch == 0) {
 #pragma unroll
-            for (int p = 0; p < NP; ++p) qs[gc + 16 * p] = q[p];
+            for (int p = 0; p < NP; ++p) qs[gc + CPP * p] = q[p];
         }
-        lds_store(0);
-        gload(1);
+        lds_store(0, breg[0]);
+        gload(GD, breg[0]);
+        if constexpr (GD == 1) {
 #pragma unroll
-        for (int kg = 0; kg < 4; ++kg) aload(0, kg);
+            for (int s = 0; s < D; ++s) aload(s * WGK + wk, areg[s]);
+        }
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
 
-        const char* const Bw = Bs + (wn * TN * 16 + l16) * FUSED_DB_PITCH + lq * 16;
-        for (int u = 0; u < nunits; ++u) {
+        const char* const Bw = Bs + (wn * TN * 16 + l16) * PITCH + lq * 16;
+        // SI: stage modulo UU
+        auto stage = [&](int u, auto si) {
+            constexpr int SI = decltype(si)::value;
+            constexpr int S0 = SI * UKW % D;      // ring slot of the stage's first k-group
             const int cur = u & 1;
-            // unit u+1 goes into the buffer that unit u-1 was read from; unit u+2 is requested
-            lds_store(cur ^ 1);
-            gload(u + 2);
-            // (left to itself the compiler sinks these loads to the end of the unit, to re-use their
-            // registers in between, and the next unit then starts by waiting for them)
+            // stage u+1 goes into the buffer that stage u-1 was read from; stage u+1+GD is requested
+            if (u + 1 < nunits) lds_store(cur ^ 1, breg[(SI + 1) % GD]);
+            gload(u + 1 + GD, breg[(SI + 1) % GD]);
+            // (left to itself the compiler sinks these loads to the end of the stage)
             __builtin_amdgcn_sched_barrier(0);
             const char* const Bu = Bw + cur * BUF;
-            // One set of B fragments: the MFMAs run column tile by column tile, and a column tile's
-            // fragment of the next k-group is requested as soon as its TM MFMAs have been issued (the
-            // other column tiles' MFMAs cover the LDS latency).
-            float4 bfr[TN];
+            // the fragment of the next column tile is requested ahead of the MFMAs of this one
+            uint4 bfr[2][TERMS];
+            auto bload = [&](int kgi, int b, uint4 (&dst)[TERMS]) {
 #pragma unroll
-            for (int b = 0; b < TN; ++b) bfr[b] = *reinterpret_cast<const float4*>(Bu + b * 16 * FUSED_DB_PITCH);
+                for (int e = 0; e < TERMS; ++e) dst[e] = *reinterpret_cast<const uint4*>(Bu + b * 16 * PITCH + e * PLANE + (kgi * WGK + wk) * 64);
+            };
+            bload(0, 0, bfr[0]);
 #pragma unroll
-            for (int kg = 0; kg < 4; ++kg) {
+            for (int kgi = 0; kgi < UKW; ++kgi) {
+                const int kg = u * UKG + kgi * WGK + wk;
+                if ((WGK > 1 || kgi > 0) && kg >= nkg) break;        // the last stage may be short
+                uint4 (&af)[TM][TERMS] = areg[(S0 + kgi) % D];
 #pragma unroll
                 for (int b = 0; b < TN; ++b) {
-                    if constexpr (BF) {
-                        const bf16x8 bv = __builtin_bit_cast(bf16x8, bfr[b]);
+                    const int cb_ = (kgi * TN + b) & 1;
+                    if (b + 1 < TN) bload(kgi, b + 1, bfr[cb_ ^ 1]);
+                    else if (kgi + 1 < UKW) bload(kgi + 1, 0, bfr[cb_ ^ 1]);
+                    auto mul = [&](int ea, int eb, floatx4 (&d)[TM][TN]) {
 #pragma unroll
                         for (int a = 0; a < TM; ++a)
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, areg[kg][a]), bv,
-                                                                                acc[a][b], 0, 0, 0);
-                    } else {
-                        const float4 bq = bfr[b];
-#pragma unroll
-                        for (int k4 = 0; k4 < 4; ++k4) {
-                            const float bv = k4 == 0 ? bq.x : k4 == 1 ? bq.y : k4 == 2 ? bq.z : bq.w;
-#pragma unroll
-                            for (int a = 0; a < TM; ++a) {
-                                const float4& aq = areg[kg][a];
-                                const float av = k4 == 0 ? aq.x : k4 == 1 ? aq.y : k4 == 2 ? aq.z : aq.w;
-                                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[a][b], 0, 0, 0);
-                            }
-                        }
-                    }
-                    if (kg + 1 < 4)
-                        bfr[b] = *reinterpret_cast<const float4*>(Bu + b * 16 * FUSED_DB_PITCH + (kg + 1) * 64);
+                            d[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[a][ea]),
+                                                                              __builtin_bit_cast(bf16x8, bfr[cb_][eb]), d[a][b], 0, 0, 0);
+                    };
+                    if constexpr (F32) {
+                        // smallest terms first; a chain of their own where a wavefront has few tiles
+                        floatx4 (&rest)[TM][TN] = TWO ? acc1 : acc;
+                        mul(2, 0, rest); mul(1, 1, rest); mul(0, 2, rest); mul(1, 0, rest); mul(0, 1, rest);
+                        mul(0, 0, acc);
+                    } else
+                        mul(0, 0, TWO && (kgi & 1) ? acc1 : acc);
                 }
-                aload(u + 1, kg);                 // the same k-group of the next unit
+                aload(kg + D * WGK, af);
                 __builtin_amdgcn_sched_barrier(0);
             }
             __syncthreads();
+        };
+        for (int u = 0; u < nunits; u += UU) {
+            stage(u, std::integral_constant<int, 0>());
+            if constexpr (UU >= 2) if (u + 1 < nunits) stage(u + 1, std::integral_constant<int, 1>());
+            if constexpr (UU >= 4) {
+                if (u + 2 < nunits) stage(u + 2, std::integral_constant<int, 2>());
+                if (u + 3 < nunits) stage(u + 3, std::integral_constant<int, 3>());
+            }
+            static_assert(UU == 1 || UU == 2 || UU == 4, "stages per round");
         }
 
+        if (TWO) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b) acc[a][b] += acc1[a][b];
+        }
+        if constexpr (WGK > 1) {
+            // the partial sums of the other wavefronts, through the (now free) stage buffers, added in their order
+            float* const red = reinterpret_cast<float*>(Bs) + lane;
+            constexpr int PER = TM * TN * 4 * 64;
+            static_assert((unsigned)(4 * PER) * 4u <= 2u * BUF, "partial sums fit the stage buffers");
+            if (wk) {
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) red[wv * PER + ((a * TN + b) * 4 + r) * 64] = acc[a][b][r];
+            }
+            __syncthreads();
+            if (wk) continue;
+#pragma unroll
+            for (int w = 1; w < WGK; ++w)
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[a][b][r] += red[(wv + w) * PER + ((a * TN + b) * 4 + r) * 64];
+        }
         // output update: bias + ReLU, written at the listed pixels only
+        unsigned long long bad = 0;               // float32: sums to recompute, bit (b*TM + a)*4 + r
+        const int mw = m0 + wm_s * TM * 16;       // first row of this wavefront
+        T* const orow = OUT + (size_t)(mw + lq * 4) * g.Po;
+        const bool whole = mw + 16 * TM <= g.O;
 #pragma unroll
         for (int b = 0; b < TN; ++b) {
             const int qn = qs[(wn * TN + b) * 16 + l16];
             if (qn < 0) continue;
+            T* const o = orow + qn;
+            auto rows = [&](bool all) {
 #pragma unroll
-            for (int a = 0; a < TM; ++a) {
-                const int mb = m0 + (wm * TM + a) * 16 + lq * 4;
-                float v4[4];
+                for (int a = 0; a < TM; ++a) {
+                    const int mb = mw + a * 16 + lq * 4;
+                    float v4[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int m = mb + r;
-                    float v = acc[a][b][r] + bv[a][r];
-                    if (relu) v = v > 0.f ? v : 0.f;
-                    if (m < g.O) st_out(OUT + (size_t)m * g.Po + qn, v);
-                    v4[r] = v;
+                    for (int r = 0; r < 4; ++r) {
+                        float v = acc[a][b][r] + bv[a][r];
+                        if (F32 && !(fabsf(acc[a][b][r]) < __builtin_inff()) && (all || mb + r < g.O)) bad |= 1ull << ((b * TM + a) * 4 + r);
+                        if (relu) v = v > 0.f ? v : 0.f;
+                        if (all || mb + r < g.O) st_out(o + (size_t)(a * 16 + r) * g.Po, v);
+                        v4[r] = v;
+                    }
+                    // (a layer that keeps the pixel-major copy has a multiple of 16 output channels)
+                    if (OUT2 && (all || mb < g.O)) st_out4(OUT2 + (size_t)qn * g.O + mb, v4);
                 }
-                // (a layer that keeps the pixel-major copy has a multiple of 16 output channels)
-                if (OUT2 && mb < g.O) st_out4(OUT2 + (size_t)qn * g.O + mb, v4);
+            };
+            if (whole) rows(true);
+            else rows(false);
+        }
+        if constexpr (F32) {
+            while (bad) {
+                const int e = __builtin_ctzll(bad);
+                bad &= bad - 1ull;
+                const int b = e / (4 * TM), a = (e >> 2) % TM, r = e & 3;
+                const int qn = qs[(wn * TN + b) * 16 + l16];
+                const int m = mw + a * 16 + lq * 4 + r;
+                float v = exact_dot(g, S2, KT, qn, m) + bias[m];
+                if (relu) v = v > 0.f ? v : 0.f;
+                OUT[(size_t)m * g.Po + qn] = v;
+                if (OUT2) OUT2[(size_t)qn * g.O + m] = v;
             }
         }
     }
 }
 
-// tile shapes chosen from N on the device, as in the channel-first kernel
-template <typename T, int WGM, int WGN, int TM, int TNS, int TNL, int TMH, int TNM, bool DB>
-__global__ __launch_bounds__(256, 2) void fused_cl_kernel(Geom g, const T* __restrict__ S2,
-                                                           const int32_t* __restrict__ idx,
-                                                           const int* __restrict__ count,
-                                                           const float4* __restrict__ KF,
-                                                           const float* __restrict__ bias, int relu,
-                                                           T* __restrict__ OUT, T* __restrict__ OUT2, int gu_small, int gu_large, int gu_mid)
+// Filter matrix of the float32 kernel: for every 16-row tile and k-group of 32, three fragments (terms h, m, l) of 64 x 16
+// bytes: lane's 8 values are K(m = mtile*16 + lane%16, k' = kgroup*32 + 8*(lane/16) + 0..7), k' = (j*kw + i)*C + c; zero
+// outside O x R.
+__global__ __launch_bounds__(256) void pack_fused_split_kernel(Geom g, int Mt16, int KG, const float* __restrict__ w,
+                                                               uint4* __restrict__ KF)
+{
+    const long n = (long)Mt16 * KG * 64;
+    const int taps = g.kh * g.kw;
+    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
+        const int lane = (int)(e & 63);
+        const long gk = e >> 6;
+        const int kgroup = (int)(gk % KG), mtile = (int)(gk / KG);
+        const int m = mtile * 16 + (lane & 15);
+        unsigned t[3][4];
+#pragma unroll
+        for (int q2 = 0; q2 < 4; ++q2) {
+            float v[2];
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                const int k = kgroup * 32 + 8 * (lane >> 4) + 2 * q2 + o;
+                const int tap = k / g.C, c = k - tap * g.C;
+                v[o] = (m < g.O && k < g.R) ? w[(size_t)m * g.R + (size_t)c * taps + tap] : 0.f;
+            }
+            split2(v[0], v[1], t[0][q2], t[1][q2], t[2][q2]);
+        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s) KF[(gk * 3 + s) * 64 + lane] = make_uint4(t[s][0], t[s][1], t[s][2], t[s][3]);
+    }
+}
+
+// Which tile finishes a frame first, in ns.  The kernel takes as long as the compute unit with the most tiles, and n tiles
+// on it take about max(latency of one, n * its share of a busy unit) beyond the launch; both grow with the k-groups of the
+// layer.  Fitted to every tile forced in turn (K = 288 to 12 544, 24 to 307 200 listed pixels, O = 8 to 512, both types):
+// the choice is within a few percent of the best tile.
+template <int BM, int BN> __device__ __forceinline__ unsigned cl_cost(int N, int O, unsigned nkg, unsigned l0, unsigned l1, unsigned c0, unsigned c1)
+{
+    const unsigned tiles = (((unsigned)N + BN - 1u) / BN) * (((unsigned)O + BM - 1u) / BM);
+    const unsigned lat = l0 + l1 * nkg, busy = (tiles + 255u) / 256u * (c0 + c1 * nkg);
+    return busy > lat ? busy : lat;
+}
+
+template <typename T, int SHAPE>
+// (wavefronts per SIMD: as many as the widest tile's registers allow.  They are worth more than wider tiles: bfloat16, O > 64
+// at 76 800 listed pixels 45 us with two, 40 us with four.)
+__global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(Geom g, ClDiv div, const T* __restrict__ S2,
+                                                          const int32_t* __restrict__ idx, const int* __restrict__ count,
+                                                          const uint4* __restrict__ KF, const float* __restrict__ KT,
+                                                          const float* __restrict__ bias, int relu,
+                                                          T* __restrict__ OUT, T* __restrict__ OUT2)
 {
     const int N = *count;
     if (N <= 0) return;
-    // The 32-column tile halves what the MFMAs read of the filter matrix and costs about 1.75 narrow
-    // tiles (bfloat16, where that traffic weighs more: about 1.25; 512 -> 512 at 3 645 listed pixels
-    // 57.7 -> 36.6 us, 64 -> 64 at 13 480: 12.8 -> 9.4 us).  512 workgroups run at a time, and the kernel takes as many rounds as the busiest slot
-    // has tiles: the wider tile is used where rounds x cost comes out lower (7 706 listed pixels,
-    // 256 -> 256, K = 2304: 98 -> 93 us; 8 828 pixels, 64 -> 256, K = 3136, where 552 wide tiles are
-    // two rounds: 160 us narrow, 173 us wide).
-    const long tiles_m = (g.O + 16 * TM * WGM - 1) / (16 * TM * WGM);
-    const long tiles_narrow = (long)((N + 16 * TNS * WGN - 1) / (16 * TNS * WGN)) * tiles_m;
-    const long tiles_mid = TNM > 0 ? (long)((N + 16 * TNM * WGN - 1) / (16 * TNM * WGN)) * tiles_m : 0;
-    if (TNM > 0 && gu_mid > 0 && N < FUSED_LARGE_N && tiles_narrow > FUSED_MID_TILES &&
-        ((tiles_mid + 511) / 512) * (sizeof(T) == 2 ? 5 : 7) < ((tiles_narrow + 511) / 512) * 4) {
-        if constexpr (DB) fused_cl_db_body<T, WGM, WGN, TM, (TNM > 0 ? TNM : TNS)>(g, S2, idx, N, KF, bias, relu, OUT, OUT2);
-        else fused_cl_body<T, WGM, WGN, TM, (TNM > 0 ? TNM : TNS)>(g, S2, idx, N, KF, bias, relu, OUT, OUT2, gu_mid);
-    } else if (N < FUSED_LARGE_N) {
-        if (TMH > 0 && fused_half_rows(N, g.O, 16 * TNS * WGN, 16 * TM * WGM)) {
-            if constexpr (DB) fused_cl_db_body<T, WGM, WGN, (TMH > 0 ? TMH : TM), TNS>(g, S2, idx, N, KF, bias, relu, OUT, OUT2);
-            else fused_cl_body<T, WGM, WGN, (TMH > 0 ? TMH : TM), TNS>(g, S2, idx, N, KF, bias, relu, OUT, OUT2, gu_small);
-        } else {
-            if constexpr (DB) fused_cl_db_body<T, WGM, WGN, TM, TNS>(g, S2, idx, N, KF, bias, relu, OUT, OUT2);
-            else fused_cl_body<T, WGM, WGN, TM, TNS>(g, S2, idx, N, KF, bias, relu, OUT, OUT2, gu_small);
-        }
-    } else if constexpr (DB) {
-        // 128 x 128, double-buffered stage; 128 x 64 while the wider tiles would leave workgroup slots empty
-        if ((long)((N + 127) / 128) * tiles_m < 512)
-            fused_cl_db_body<T, WGM, WGN, TM, TNL>(g, S2, idx, N, KF, bias, relu, OUT, OUT2);
-        else
-            fused_cl_db_body<T, WGM, WGN, TM, 2 * TNL>(g, S2, idx, N, KF, bias, relu, OUT, OUT2);
-    } else
-        fused_cl_body<T, WGM, WGN, TM, TNL>(g, S2, idx, N, KF, bias, relu, OUT, OUT2, gu_large);
+#define CB_BODY(...) fused_cl_body<T, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2)
+    constexpr bool F32 = sizeof(T) == 4;
+    // (literal arguments, not a table: a table would be fetched from memory ahead of everything else)
+    const unsigned nkg = ((unsigned)g.R + 31u) / 32u;
+#define CB_COST(bm, bn, a0, a1, a2, a3, b0, b1, b2, b3) \
+    (F32 ? cl_cost<bm, bn>(N, g.O, nkg, a0, a1, a2, a3) : cl_cost<bm, bn>(N, g.O, nkg, b0, b1, b2, b3))
+    // 16 x 16, the four wavefronts sharing K: four times the tiles of the others where few pixels are listed, a quarter of
+    // the serial chain (256 -> 8, 7x7, 3 322 pixels: 104 -> 43 us; 64 -> 9, 3x3: 8.7 -> 6.5 us)
+    // (filters beyond one XCD's 4 MB of L2 come in more slowly than its four wavefronts ask for them: 512 -> 512, 324 pixels
+    // 42 us, 33 us with 64 x 16)
+    const bool far = F32 && (unsigned long long)g.O * (unsigned)g.R > 700000ull;
+    const unsigned k = CB_COST(16, 16, 100, 94, 1260, (far ? 80 : 49), 200, 30, 870, 16);
+    if constexpr (SHAPE == 16) {
+        const unsigned a = CB_COST(16, 64, 0, 330, 1100, 222, 200, 110, 1000, 60), b = CB_COST(16, 128, 0, 700, 1300, 440, 300, 200, 1300, 110);
+        if (k <= a && k <= b) CB_BODY(1, 1, 1, 1, 4);
+        else if (a <= b) CB_BODY(1, 4, 1, 1);
+        else CB_BODY(1, 4, 1, 2);
+    } else if constexpr (SHAPE == 32) {
+        const unsigned a = CB_COST(32, 32, 200, 230, 1250, 155, 200, 70, 850, 50), b = CB_COST(32, 64, 600, 390, 1200, 290, 400, 120, 800, 85),
+                       c = CB_COST(32, 128, 1000, 800, 1500, 550, 900, 220, 900, 130);
+        if (k <= a && k <= b && k <= c) CB_BODY(1, 1, 1, 1, 4);
+        else if (a <= b && a <= c) CB_BODY(2, 2, 1, 1);
+        else if (b <= c) CB_BODY(2, 2, 1, 2);
+        else CB_BODY(2, 2, 1, 4);
+    } else if constexpr (SHAPE == 64) {
+        const unsigned a = CB_COST(64, 16, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, 1600, 310, 1400, 200, 400, 83, 1100, 48),
+                       c = CB_COST(64, 64, 1300, 530, 800, 395, 1000, 148, 800, 100);
+        if (k <= a && k <= b && k <= c) CB_BODY(1, 1, 1, 1, 4);
+        else if (a <= b && a <= c) CB_BODY(4, 1, 1, 1);
+        else if (b <= c) CB_BODY(4, 1, 1, 2);
+        else CB_BODY(4, 1, 1, 4);
+    } else {
+        const unsigned a = CB_COST(64, 16, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, 1000, 300, 1400, 203, 400, 80, 1100, 47),
+                       c = CB_COST(128, 32, 0, 400, 1000, 320, 0, 115, 100, 96), d = CB_COST(128, 64, 900, 745, 2900, 510, 700, 205, 1000, 140),
+                       ab = a < b ? a : b, cd = c < d ? c : d;
+        if (k <= ab && k <= cd) CB_BODY(1, 1, 1, 1, 4);
+        else if (ab <= cd) { if (a <= b) CB_BODY(4, 1, 1, 1); else CB_BODY(4, 1, 1, 2); }
+        else if (c <= d) CB_BODY(4, 1, 2, 2);
+        else CB_BODY(4, 1, 2, 4);
+    }
+#undef CB_COST
+#undef CB_BODY
 }
 
 template <typename T>
 hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow, const int32_t* idx, const int* count,
-                           const void* KF, const float* bias, int relu, T* OUT, T* OUT2, hipStream_t st, Tm tm)
+                           const void* KF, const float* KT, const float* bias, int relu, T* OUT, T* OUT2, hipStream_t st, Tm tm)
 {
     if (!plan.cl || (g.C & (g.C - 1)) != 0 || g.C < 16 || g.bf16 != (sizeof(T) == 2)) return hipErrorInvalidValue;
-    const dim3 grid(1024), block(256);
-    const float4* kf = (const float4*)KF;
-#define CB_FUSED_CL(wgm, wgn, tm_, tns, tnl, tmh, tnm, db)                                                             \
-    hipExtLaunchKernelGGL((fused_cl_kernel<T, wgm, wgn, tm_, tns, tnl, tmh, tnm, db>), grid, block, lds, st,           \
-                          tm.start, tm.stop, 0, g, shadow, idx, count, kf, bias, relu, OUT, OUT2, plan.gu_small,       \
-                          plan.gu_large, plan.gu_mid)
-    unsigned lds = plan.lds_bytes;
-    const bool db_ok = g.kh <= 16 && g.kw <= 16 && g.Wo < 4096;      // what the double-buffered body's tap masks and reciprocal hold
-    // tile shapes (rows x columns): narrow | wide
-    if (g.O <= 32 && db_ok && fused_db_lds(256) > lds) lds = fused_db_lds(256);
-    if (g.O <= 16 && !db_ok)      CB_FUSED_CL(1, 4, 1, 1, 2, 0, 0, false);      // 16 x 64  |  16 x 128
-    else if (g.O <= 16)           CB_FUSED_CL(1, 4, 1, 1, 2, 0, 0, true);       //   ... / 16 x 256, double-buffered stage
-    else if (g.O <= 32 && !db_ok) CB_FUSED_CL(2, 2, 1, 1, 2, 0, 0, false);      // 32 x 32  |  32 x 64
-    else if (g.O <= 32)           CB_FUSED_CL(2, 2, 1, 1, 2, 0, 0, true);       //   ... / 32 x 128, double-buffered stage
-    else if (g.O <= 64 && !db_ok) CB_FUSED_CL(4, 1, 1, 1, 4, 0, 2, false);   // 64 x 16  |  64 x 64
-    else if (g.O <= 64) {                                             // 64 x 16  |  64 x 64 / 64 x 128, double-buffered stage
-        if (fused_db_lds(128) > lds) lds = fused_db_lds(128);
-        CB_FUSED_CL(4, 1, 1, 1, 4, 0, 2, true);
-    }
-    else if (!db_ok) CB_FUSED_CL(4, 1, 2, 1, 4, 1, 2, false);         // 128 x 16 | 128 x 64
-    else {                                                            // 128 x 16 | 128 x 128, double-buffered stage
-        if (fused_db_lds(128) > lds) lds = fused_db_lds(128);         // (its tap masks hold 16 filter rows and columns)
-        CB_FUSED_CL(4, 1, 2, 1, 4, 1, 2, true);
-    }
-#undef CB_FUSED_CL
+    const ClDiv div = {g.Wo < 4096 ? ((1ull << 42) + (unsigned)g.Wo - 1ull) / (unsigned)g.Wo : 0ull,
+                       (65536u + (unsigned)g.kw - 1u) / (unsigned)g.kw};
+#define CB_CL(shape)                                                                                                     \
+    hipExtLaunchKernelGGL((fused_cl_kernel<T, shape>), dim3(1024), dim3(256), sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16, st, tm.start, tm.stop, 0, g, \
+                          div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)
+    if (g.O <= 16)      CB_CL(16);
+    else if (g.O <= 32) CB_CL(32);
+    else if (g.O <= 64) CB_CL(64);
+    else                CB_CL(128);
+#undef CB_CL
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_fused_f32_cl(const Geom& g, const FusedPlan& plan, const float* shadow, const int32_t* idx,
-                               const int* count, const void* KF, const float* bias, int relu, float* OUT, float* OUT2,
-                               hipStream_t st, Tm tm)
+hipError_t launch_pack_fused_split(const Geom& g, const float* w, void* KF, hipStream_t st)
 {
-    return launch_fused_cl<float>(g, plan, shadow, idx, count, KF, bias, relu, OUT, OUT2, st, tm);
+    const int KG = (g.R + 63) / 64 * 2, Mt16 = (g.O + 127) / 128 * 8;
+    const long n = (long)Mt16 * KG * 64;
+    unsigned grid = (unsigned)((n + 255) / 256);
+    if (grid > 2048) grid = 2048;
+    hipLaunchKernelGGL(pack_fused_split_kernel, dim3(grid), dim3(256), 0, st, g, Mt16, KG, w, (uint4*)KF);
+    return hipGetLastError();
+}
+
+hipError_t launch_fused_f32_cl(const Geom& g, const FusedPlan& plan, const float* shadow, const int32_t* idx,
+                               const int* count, const void* KF, const float* KT, const float* bias, int relu, float* OUT,
+                               float* OUT2, hipStream_t st, Tm tm)
+{
+    return launch_fused_cl<float>(g, plan, shadow, idx, count, KF, KT, bias, relu, OUT, OUT2, st, tm);
 }
 
 hipError_t launch_fused_bf16_cl(const Geom& g, const FusedPlan& plan, const uint16_t* shadow, const int32_t* idx,
                                 const int* count, const void* KF, const float* bias, int relu, uint16_t* OUT, uint16_t* OUT2,
                                 hipStream_t st, Tm tm)
 {
-    return launch_fused_cl<uint16_t>(g, plan, shadow, idx, count, KF, bias, relu, OUT, OUT2, st, tm);
+    return launch_fused_cl<uint16_t>(g, plan, shadow, idx, count, KF, nullptr, bias, relu, OUT, OUT2, st, tm);
 }
 
 }  // namespace cb

@@ -273,7 +273,7 @@ int run_back_end(cb_layer* L, const void* src, bool have_list)
     }
     if (L->fused) {
         CB_HIP(cb::launch_fused(g, L->plan, src, L->d.gather_channel_last ? L->ext_cl : L->S2(), L->cur_idx, L->cur_count,
-                                L->KF(), L->rowtab(), L->bias(), L->d.relu, L->OUT(), L->OUT2(), L->st,
+                                L->KF(), L->KT(), L->rowtab(), L->bias(), L->d.relu, L->OUT(), L->OUT2(), L->st,
                                 next_tm(L, CB_STEP_FUSED)));
         L->primed = true;
         L->frames++;

@@ -251,6 +251,57 @@ def test_channel_last_shadow(geom, bf16):
     p.step(frames[4], 0.02, tag=f"shadow {geom} frame 4")
 
 
+# The channel-last kernel picks its tile from the number of listed pixels: every width it has for each range of output
+# channels, with ragged row and column tiles and a K that fills its last stage only in part.
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("geom", [
+    (32, 13, 1, 241, 251), (32, 16, 3, 61, 67), (32, 24, 3, 31, 33), (32, 30, 1, 183, 179), (32, 32, 1, 411, 421),
+    (32, 50, 5, 53, 57), (32, 64, 1, 143, 141), (32, 60, 1, 213, 217), (64, 100, 3, 17, 19), (32, 140, 1, 97, 93),
+    (32, 140, 3, 71, 97), (32, 72, 1, 207, 201)])
+def test_channel_last_tile_shapes(geom, bf16):
+    C, O, k, H, W = geom
+    _say(f"tile shapes {geom} bf16={bf16}")
+    spec, frames = syn.random_layer_case(sum(geom) + 5, C, O, k, 1, k // 2, H, W, 2, change_prob=0.03, relu=False, noise_std=0.004)
+    p = Pair(spec, H, W, bf16=bf16, backend=2)
+    _, n = p.step(frames[0], 0.02, tag=f"tile shapes {geom} full update")
+    assert n == H * W
+    p.step(frames[1], 0.02, tag=f"tile shapes {geom} frame 1")
+
+
+# The float32 channel-last kernel multiplies bfloat16 terms of its operands.  Values without such a decomposition
+# (infinities, NaN, finite values that round up to infinity in bfloat16) have to come out as in float32 arithmetic.
+@pytest.mark.parametrize("where", ["input", "weight"])
+@pytest.mark.parametrize("geom", [(16, 12, 3, 1, 9, 11), (32, 70, 3, 2, 20, 23), (64, 64, 1, 1, 30, 31)])
+def test_channel_last_special_values(geom, where):
+    C, O, k, s, H, W = geom
+    _say(f"special values {geom} {where}")
+    rng = np.random.default_rng(C + O)
+    x = rng.uniform(-1, 1, (C, H, W)).astype(np.float32)
+    w = (rng.uniform(-1, 1, (O, C, k, k)) / (C * k * k)).astype(np.float32)
+    w[:, 1] = 0.0                                    # zero weights: 0 * inf is no number
+    special = [np.inf, -np.inf, np.nan, np.float32(3.4e38), np.float32(-3.3961776e38), np.float32(1e-41)]
+    t = x if where == "input" else w
+    flat = t.reshape(-1)
+    for v, i in zip(special, rng.choice(flat.size, len(special), replace=False)):
+        flat[i] = v
+    b = rng.uniform(-1, 1, O).astype(np.float32)
+    L = cb.Layer(to_dev(w, False), to_dev(b, False), s, k // 2, H, W, False, backend=2)
+    got = to_host(L.process_frame(to_dev(x, False), 0.0)).astype(np.float64)
+    with np.errstate(all="ignore"):
+        ref = torch.nn.functional.conv2d(torch.from_numpy(x)[None].double(), torch.from_numpy(w).double(),
+                                         torch.from_numpy(b).double(), s, k // 2)[0].numpy()
+    assert np.abs(ref[np.isfinite(ref)]).max() < 3.4e38           # nothing overflows on the way in float32 either
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    assert np.isfinite(got[fin]).all()
+    # |x . w| rounded at most K + 1 times, each by 2^-24 of a partial sum bounded by the sum of magnitudes
+    with np.errstate(all="ignore"):
+        mag = torch.nn.functional.conv2d(torch.from_numpy(x)[None].double().abs(), torch.from_numpy(w).double().abs(),
+                                         torch.from_numpy(b).double().abs(), s, k // 2)[0].numpy()
+    assert (np.abs(got[fin] - ref[fin]) <= (C * k * k + 1) * 2.0 ** -24 * mag[fin]).all()
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("geom", [(3, 4, 5, 1, 2, 200, 181), (2, 5, 3, 2, 1, 370, 361), (5, 3, 1, 1, 0, 190, 175)])
 def test_explicit_gather_with_many_columns(geom, bf16):
