@@ -17,6 +17,8 @@ namespace cb {
 
 namespace {
 
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+
 __device__ __forceinline__ float widen(float v) { return v; }
 __device__ __forceinline__ float widen(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
 
@@ -53,6 +55,30 @@ template <typename V> __device__ __forceinline__ V ld_once(const V* p)
     } else {
         return __builtin_nontemporal_load(p);
     }
+}
+
+// The VEC pixels of a channel at p.  bfloat16: at any alignment (a plane of an odd number of pixels leaves every other
+// channel unaligned; global memory takes such loads, at the price of one more cache line per wavefront).
+template <typename T, int VEC> struct PxMem { typedef typename Pack<T, VEC>::type type; };
+typedef unsigned PxMem2x4 __attribute__((ext_vector_type(2), aligned(2)));
+template <> struct PxMem<uint16_t, 4> { typedef PxMem2x4 type; };
+template <typename T, int VEC, bool ONCE> __device__ __forceinline__ typename Pack<T, VEC>::type ld_px(const T* p)
+{
+    typedef typename Pack<T, VEC>::type V;
+    typedef typename PxMem<T, VEC>::type M;
+    if constexpr (sizeof(T) == 2 && VEC > 1) {
+        if constexpr (ONCE) return __builtin_bit_cast(V, (uintx2)__builtin_nontemporal_load(reinterpret_cast<const M*>(p)));
+        else return __builtin_bit_cast(V, (uintx2)*reinterpret_cast<const M*>(p));
+    } else {
+        if constexpr (ONCE) return ld_once(reinterpret_cast<const V*>(p));
+        else return *reinterpret_cast<const V*>(p);
+    }
+}
+template <typename T, int VEC> __device__ __forceinline__ void st_px(T* p, const typename Pack<T, VEC>::type& v)
+{
+    typedef typename PxMem<T, VEC>::type M;
+    if constexpr (sizeof(T) == 2 && VEC > 1) *reinterpret_cast<M*>(p) = __builtin_bit_cast(uintx2, v);
+    else *reinterpret_cast<M*>(p) = v;
 }
 
 // Workgroup barrier that orders LDS accesses only.  __syncthreads() also waits until every global
@@ -198,8 +224,14 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
     const int tid = threadIdx.x;
     const int g = tid / PL;
     const int pl = tid - g * PL;
-    const long p0 = ((long)blockIdx.x * PL + pl) * VEC;
-    const bool valid = p0 < P;
+    // The lane's pixels are pw .. pw + VEC - 1.  Where the image ends among them it loads the image's last VEC pixels
+    // (p0 .. P - 1) instead, of which only those from pw on are its own.
+    const long pw = ((long)blockIdx.x * PL + pl) * VEC;
+    const bool valid = pw < P;
+    constexpr bool RAGGED = sizeof(T) == 2 && VEC > 1;      // (float32 takes several pixels per lane only where P is a multiple)
+    const int over = RAGGED && valid && pw + VEC > P ? (int)(pw + VEC - P) : 0;
+    const long p0 = pw - over;
+    const unsigned own = valid ? (ALL << over) & ALL : 0u;
 
     V xv[CPT];
     unsigned bits = 0;
@@ -208,7 +240,7 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
 #pragma unroll
             for (int q = 0; q < CPT; ++q) {
                 const int c = SH ? g * CPT + q : g + q * CS;
-                if (c < C) xv[q] = *reinterpret_cast<const V*>(x + (size_t)c * P + p0);
+                if (c < C) xv[q] = ld_px<T, VEC, false>(x + (size_t)c * P + p0);
             }
             // (first frame only.  Without this wait the compiler assumes these loads may still be in flight
             // in the other branch, and waits there between loads.)
@@ -220,9 +252,8 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
                 const int c = SH ? g * CPT + q : g + q * CS;
                 if (c < C) {
                     const size_t off = (size_t)c * P + p0;
-                    xv[q] = ld_once(reinterpret_cast<const V*>(x + off));
-                    sv[q] = (flags & DET_STREAM_STATE) ? ld_once(reinterpret_cast<const V*>(S + off))
-                                                       : *reinterpret_cast<const V*>(S + off);
+                    xv[q] = ld_px<T, VEC, true>(x + off);
+                    sv[q] = (flags & DET_STREAM_STATE) ? ld_px<T, VEC, true>(S + off) : ld_px<T, VEC, false>(S + off);
                 }
             }
             // every load is issued before the first compare waits for one: the kernel lives on loads in flight
@@ -250,15 +281,16 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
 #pragma unroll
         for (int q = 0; q < CS; ++q) bits |= sflag[q * PL + pl];
     }
-    if (flags & DET_FORCE_ALL) bits = valid ? ALL : 0u;
+    bits = (flags & DET_FORCE_ALL) ? own : bits & own;
 
     if (g == 0) {
         const int lane = tid & 63;
         const long wave_p0 = ((long)blockIdx.x * PL + (pl & ~63)) * VEC;
         const long w0 = wave_p0 >> 6;
+        const unsigned mapped = bits >> over;
         if (VEC == 4) {
-            uint64_t b0 = __ballot(bits & 1u), b1 = __ballot(bits & 2u);
-            uint64_t b2 = __ballot(bits & 4u), b3 = __ballot(bits & 8u);
+            uint64_t b0 = __ballot(mapped & 1u), b1 = __ballot(mapped & 2u);
+            uint64_t b2 = __ballot(mapped & 4u), b3 = __ballot(mapped & 8u);
             if (lane < 4 && w0 + lane < nwords) {
                 const int sh = 16 * lane;
                 uint64_t w = spread4((b0 >> sh) & 0xFFFF) | (spread4((b1 >> sh) & 0xFFFF) << 1) |
@@ -286,7 +318,7 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
         }
     }
 
-    unsigned upd = (flags & DET_NO_UPDATE) ? 0u : (flags & DET_COPY_ALL) ? (valid ? ALL : 0u) : bits;
+    unsigned upd = (flags & DET_NO_UPDATE) ? 0u : (flags & DET_COPY_ALL) ? own : bits;
     if (upd) {
 #pragma unroll
         for (int q = 0; q < CPT; ++q) {
@@ -295,7 +327,7 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
                 const size_t off = (size_t)c * P + p0;
                 const T* xe = reinterpret_cast<const T*>(&xv[q]);
                 if (upd == ALL) {
-                    *reinterpret_cast<V*>(S + off) = xv[q];
+                    st_px<T, VEC>(S + off, xv[q]);
                 } else {
 #pragma unroll
                     for (int v = 0; v < VEC; ++v)
@@ -736,8 +768,13 @@ hipError_t launch_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int
     // 44.9 -> 42.4 - 42.7 us (two pixels per lane: 43.1 - 43.4 us); the kernel itself 26.9 -> 24.1 - 25.2 us.  No gain
     // for 128 channels (1080p) or for the first layers' 3 channels, so only here.
     const bool one_px = sizeof(T) == 4 && g.C > 32 && g.C <= 64;
-    const bool vec4 = (P % 4 == 0) && ((uintptr_t)x % valign == 0) && ((uintptr_t)S % valign == 0) && P >= 65536 &&
-                      !(S2 != nullptr && g.C > 128 && g.C <= 512) && !one_px;
+    // Four pixels per lane otherwise, from 65 536 pixels on.  bfloat16, whose single pixels are 2-byte loads, from 32 768 on
+    // and whatever the alignment (64 channels at 271x435 13.8 -> 7.5 us, 128 channels at 1053x1822 398 -> 184 us; at 140x141
+    // pixels one pixel per lane is still the faster one, 7.3 against 7.8 us).  float32 gains nothing from unaligned loads
+    // (32 channels at 557x803: 25.1 us either way), and the looped variant for more than 128 channels wants aligned ones.
+    const bool aligned = P % 4 == 0 && (uintptr_t)x % valign == 0 && (uintptr_t)S % valign == 0;
+    const bool vec4 = P >= (sizeof(T) == 4 ? 65536 : 32768) && !one_px &&
+                      (aligned || (sizeof(T) == 2 && g.C <= 128)) && (g.C <= 128 || (P >= 65536 && !(S2 != nullptr && g.C <= 512)));
     if (vec4) launch_v<T, 4>(x, S, S2, mbits, ctl, g.C, P, tau, flags, st, tm);
     else      launch_v<T, 1>(x, S, S2, mbits, ctl, g.C, P, tau, flags, st, tm);
     return hipGetLastError();

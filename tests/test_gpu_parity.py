@@ -251,6 +251,31 @@ def test_channel_last_shadow(geom, bf16):
     p.step(frames[4], 0.02, tag=f"shadow {geom} frame 4")
 
 
+# bfloat16 change detection takes four pixels per lane at any alignment from 32 768 pixels on.  Planes of 4n + 1 .. 3 pixels, the
+# last lane's first pixel at the start of a workgroup (256 or 1024 pixels) or inside one; every number of channel groups; frames
+# that start one element off a word; full, closed-loop and feed-forward updates.
+@pytest.mark.parametrize("feed_forward", [False, True])
+@pytest.mark.parametrize("geom", [(64, 25, 1321), (3, 7, 4681), (40, 163, 203), (20, 187, 179), (7, 173, 191), (128, 2, 16387), (100, 131, 257), (32, 129, 255)])
+def test_detect_bfloat16_ragged_planes(geom, feed_forward):
+    C, H, W = geom
+    assert H * W >= 32768 - 1024
+    _say(f"ragged planes {geom} feed_forward={feed_forward}")
+    spec, frames = syn.random_layer_case(sum(geom), C, 3, 1, 1, 0, H, W, 3, change_prob=0.02, relu=False, noise_std=0.004)
+    frames[1][:, -1, -3:] += np.float32(0.5)          # the pixels of the last lane
+    frames[2][:, -1, -4:-2] += np.float32(0.25)
+    p = Pair(spec, H, W, bf16=True, feed_forward=feed_forward)
+    for t, f in enumerate(frames):
+        p.step(f, 0.02, tag=f"ragged planes {geom} frame {t}")
+    x = to_dev(prep(frames[0], True), True)
+    buf = torch.empty(x.numel() + 1, dtype=torch.bfloat16, device="cuda")
+    buf[1:] = x.reshape(-1)
+    out = to_host(p.g.process_frame(buf[1:].view(C, H, W), 0.02))
+    p.o.process(prep(frames[0], True), 0.02)
+    assert np.array_equal(p.g.changes_host()[0], p.o.m)
+    assert np.array_equal(to_host(p.g.state()), p.o.state)
+    assert_close(out, p.o.out, True, f"ragged planes {geom} frame one element off a word")
+
+
 # The channel-last kernel picks its tile from the number of listed pixels: every width it has for each range of output
 # channels, with ragged row and column tiles and a K that fills its last stage only in part.
 @pytest.mark.parametrize("bf16", [False, True])
