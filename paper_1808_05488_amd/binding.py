@@ -302,6 +302,21 @@ def _view(owner: torch.Tensor, ptr: int, shape, dtype) -> torch.Tensor:
     return owner[off:off + nbytes].view(dtype).view(*shape)
 
 
+class _Views:
+    """Tensor views of elements of the byte buffer `owner`, one torch operation each (slicing the bytes and viewing them
+    as elements and as a shape is three, on every frame)."""
+
+    def __init__(self, owner: torch.Tensor, dtype):
+        self.elems = owner.view(dtype)
+        self.ptr, self.first, self.size = owner.data_ptr(), self.elems.storage_offset(), self.elems.element_size()
+
+    def __call__(self, ptr: int, shape) -> torch.Tensor:
+        c, h, w = shape
+        off = (ptr - self.ptr) // self.size
+        assert 0 <= off and off + c * h * w <= self.elems.numel(), "pointer outside its owner buffer"
+        return self.elems.as_strided(shape, (h * w, w, 1), self.first + off)
+
+
 class Layer:
     """A cb_layer with its buffers held by torch tensors (memory plumbing only)."""
 
@@ -332,6 +347,7 @@ class Layer:
         self.C, self.H, self.W = Cc, h_in, w_in
         self.O, self.Ho, self.Wo = cb_layer_out_shape(self.handle)
         self._keep = (weight, bias)
+        self._views = _Views(self.state_buf, _TORCH_DT[self.dtype])
 
     def close(self):
         if getattr(self, "handle", None):
@@ -348,7 +364,7 @@ class Layer:
         assert x.is_cuda and x.is_contiguous() and x.dtype == _TORCH_DT[self.dtype]
         assert tuple(x.shape[-3:]) == (self.C, self.H, self.W), (tuple(x.shape), (self.C, self.H, self.W))
         p = cb_process_frame(self.handle, x, tau)
-        return _view(self.state_buf, p, (self.O, self.Ho, self.Wo), _TORCH_DT[self.dtype])
+        return self._views(p, (self.O, self.Ho, self.Wo))
 
     def process_frame_chained(self, x: torch.Tensor, producer, tau: float) -> torch.Tensor:
         assert x.is_cuda and x.is_contiguous() and x.dtype == _TORCH_DT[self.dtype]
@@ -357,7 +373,7 @@ class Layer:
             p = cb_process_frame_chained(self.handle, x, None, producer.handle, tau)
         else:
             p = cb_process_frame_chained(self.handle, x, producer.handle, None, tau)
-        return _view(self.state_buf, p, (self.O, self.Ho, self.Wo), _TORCH_DT[self.dtype])
+        return self._views(p, (self.O, self.Ho, self.Wo))
 
     def process_frame_propagated(self, x: torch.Tensor, producer) -> torch.Tensor:
         assert x.is_cuda and x.is_contiguous() and x.dtype == _TORCH_DT[self.dtype]
@@ -366,7 +382,7 @@ class Layer:
             p = cb_process_frame_propagated(self.handle, x, None, producer.handle)
         else:
             p = cb_process_frame_propagated(self.handle, x, producer.handle, None)
-        return _view(self.state_buf, p, (self.O, self.Ho, self.Wo), _TORCH_DT[self.dtype])
+        return self._views(p, (self.O, self.Ho, self.Wo))
 
     def changes(self):
         """(m, m~, idx, N) of the last frame as device tensors (idx is sliced to N on the host)."""
@@ -385,7 +401,7 @@ class Layer:
         return m_t, mt_t, idx.astype(np.int32), n
 
     def state(self) -> torch.Tensor:
-        return _view(self.state_buf, cb_layer_state(self.handle), (self.C, self.H, self.W), _TORCH_DT[self.dtype])
+        return self._views(cb_layer_state(self.handle), (self.C, self.H, self.W))
 
     def export_state(self):
         """(input state or None for a CB_PROPAGATE layer, cached output) as new tensors."""
@@ -474,7 +490,7 @@ class Network:
             self.stages[s].pool = self.pools[s].handle if self.pools[s] is not None else None
         last = self.pools[-1] if self.pools[-1] is not None else self.layers[-1]
         self.out_shape = (last.O, last.Hp, last.Wp) if self.pools[-1] is not None else (last.O, last.Ho, last.Wo)
-        self._out_buf = last.state_buf
+        self._views = last._views
         self.dtype = self.layers[-1].dtype
         self.device = self.layers[0].device
 
@@ -487,7 +503,7 @@ class Network:
         t = (C.c_float * self.n)(*[float(v) for v in taus])
         out = C.c_void_p()
         _check(lib().cb_network_forward(self.stages, self.n, _ptr(x), t, C.byref(out)), "cb_network_forward")
-        return _view(self._out_buf, out.value, self.out_shape, _TORCH_DT[self.dtype])
+        return self._views(out.value, self.out_shape)
 
     def select_thresholds(self, sequences, tau0: float, factor: float, max_loss, max_steps: int = 200):
         """Sec. III-F threshold selection over `sequences` (lists of equally many device frames).
@@ -520,6 +536,7 @@ class Pool:
         self.dtype = producer.dtype
         self.stream_handle = producer.stream_handle
         self.device = producer.device
+        self._views = _Views(self.state_buf, _TORCH_DT[self.dtype])
 
     def close(self):
         if getattr(self, "handle", None):
@@ -534,7 +551,7 @@ class Pool:
 
     def process(self) -> torch.Tensor:
         p = cb_pool_process(self.handle)
-        return _view(self.state_buf, p, (self.O, self.Hp, self.Wp), _TORCH_DT[self.dtype])
+        return self._views(p, (self.O, self.Hp, self.Wp))
 
     def changes(self) -> torch.Tensor:
         return _view(self.state_buf, cb_pool_changes(self.handle), (self.Hp, self.Wp), torch.uint8)

@@ -382,8 +382,7 @@ hipError_t launch_fused_bf16(const Geom& g, const FusedPlan& plan, const uint16_
     const dim3 grid(1024), block(256);
     const uint4* kf = (const uint4*)KF;
 #define CB_FUSED(wgm, wgn, tm_, tns, tnl, cw, tmh)                                                                     \
-    hipExtLaunchKernelGGL((fused_bf16_kernel<wgm, wgn, tm_, tns, tnl, cw, tmh>), grid, block, plan.lds_bytes, st, tm.start, \
-                          tm.stop, 0, g, src, idx, count, kf, tab, plan.ntab, bias, relu, OUT, OUT2, plan.gu_small,      \
+    CB_LAUNCH_LDS((fused_bf16_kernel<wgm, wgn, tm_, tns, tnl, cw, tmh>), grid, block, plan.lds_bytes, st, tm, g, src, idx, count, kf, tab, plan.ntab, bias, relu, OUT, OUT2, plan.gu_small,      \
                           plan.gu_large)
     // tile shapes (rows x columns): narrow | wide
     if (plan.cw == 1) {

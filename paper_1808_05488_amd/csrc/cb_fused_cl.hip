@@ -518,7 +518,7 @@ hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow
     const ClDiv div = {g.Wo < 4096 ? ((1ull << 42) + (unsigned)g.Wo - 1ull) / (unsigned)g.Wo : 0ull,
                        (65536u + (unsigned)g.kw - 1u) / (unsigned)g.kw};
 #define CB_CL(shape)                                                                                                     \
-    hipExtLaunchKernelGGL((fused_cl_kernel<T, shape>), dim3(1024), dim3(256), sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16, st, tm.start, tm.stop, 0, g, \
+    CB_LAUNCH_LDS((fused_cl_kernel<T, shape>), dim3(1024), dim3(256), sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16, st, tm, g, \
                           div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)
     if (g.O <= 16)      CB_CL(16);
     else if (g.O <= 32) CB_CL(32);

@@ -436,8 +436,7 @@ hipError_t launch_fused_f32(const Geom& g, const FusedPlan& plan, const float* s
     const dim3 grid(1024), block(256);
     const float4* kf = (const float4*)KF;
 #define CB_FUSED(wgm, wgn, tm_, tns, tnl, cw, tmh, tnm)                                                                   \
-    hipExtLaunchKernelGGL((fused_f32_kernel<wgm, wgn, tm_, tns, tnl, cw, tmh, tnm>), grid, block, plan.lds_bytes, st, tm.start, \
-                          tm.stop, 0, g, src, idx, count, kf, tab, plan.ntab, bias, relu, OUT, OUT2, plan.gu_small,      \
+    CB_LAUNCH_LDS((fused_f32_kernel<wgm, wgn, tm_, tns, tnl, cw, tmh, tnm>), grid, block, plan.lds_bytes, st, tm, g, src, idx, count, kf, tab, plan.ntab, bias, relu, OUT, OUT2, plan.gu_small,      \
                           plan.gu_large, plan.gu_mid)
     // tile shapes (rows x columns): narrow | wide
     if (plan.cw == 1) {

@@ -13,8 +13,13 @@ namespace cb {
 struct Tm {
     hipEvent_t start = nullptr, stop = nullptr;
 };
-#define CB_LAUNCH(kernel, grid, block, st, tm, ...) \
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, st, (tm).start, (tm).stop, 0, __VA_ARGS__)
+// (the extended entry takes about 1 us more per launch on the host: a frame of three launches 11.7 -> 8.8 us without it)
+#define CB_LAUNCH_LDS(kernel, grid, block, lds, st, tm, ...)                                                    \
+    do {                                                                                                        \
+        if ((tm).start) hipExtLaunchKernelGGL(kernel, grid, block, lds, st, (tm).start, (tm).stop, 0, __VA_ARGS__); \
+        else hipLaunchKernelGGL(kernel, grid, block, lds, st, __VA_ARGS__);                                     \
+    } while (0)
+#define CB_LAUNCH(kernel, grid, block, st, tm, ...) CB_LAUNCH_LDS(kernel, grid, block, 0, st, tm, __VA_ARGS__)
 
 // Geometry shared by all kernels of one layer (passed by value).
 struct Geom {
