@@ -337,6 +337,21 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
         }
     }
 
+    // Shadow of a first layer: its few channels are in this lane's registers, a pixel is one 16-byte store.
+    if constexpr (CS == 1 && CPT * sizeof(T) <= 16) {
+        if (S2 != nullptr && upd) {
+            constexpr int EPV = 16 / (int)sizeof(T);
+#pragma unroll
+            for (int v = 0; v < VEC; ++v)
+                if (upd & (1u << v)) {
+                    __attribute__((aligned(16))) T e[EPV];
+#pragma unroll
+                    for (int j = 0; j < EPV; ++j) e[j] = j < CPT && j < C ? reinterpret_cast<const T*>(&xv[j < CPT ? j : 0])[v] : (T)0;
+                    *reinterpret_cast<uint4*>(S2 + (size_t)(p0 + v) * EPV) = *reinterpret_cast<const uint4*>(e);
+                }
+        }
+    }
+
     // Channel-last shadow of the state (pixel-major: the C values of a pixel side by side), kept for
     // the gather of the fused back end.  The values of a changed pixel sit in CS different lanes of
     // CS different wavefronts.  The changed pixels of the workgroup are numbered (lane-major, from
@@ -519,7 +534,7 @@ __global__ __launch_bounds__(256) void state_apply_kernel(const T* __restrict__ 
 // The whole shadow from the state: S (C x P) -> S2 (P x C), 64 x 64 tiles through LDS.  For a state that
 // arrives from outside (an imported checkpoint); not on the per-frame path.
 template <typename T>
-__global__ __launch_bounds__(256) void shadow_rebuild_kernel(const T* __restrict__ S, T* __restrict__ S2, int C, int P)
+__global__ __launch_bounds__(256) void shadow_rebuild_kernel(const T* __restrict__ S, T* __restrict__ S2, int C, int Cs, int P)
 {
     __shared__ T tile[64][65];
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
@@ -533,7 +548,7 @@ __global__ __launch_bounds__(256) void shadow_rebuild_kernel(const T* __restrict
             if (c0 + r < C && p0 + tx < P) tile[r][tx] = S[(size_t)(c0 + r) * P + p0 + tx];
         __syncthreads();
         for (int r = ty; r < 64; r += 4)                   // row = pixel, lane = channel
-            if (c0 + tx < C && p0 + r < P) S2[(size_t)(p0 + r) * C + c0 + tx] = tile[tx][r];
+            if (c0 + tx < C && p0 + r < P) S2[(size_t)(p0 + r) * Cs + c0 + tx] = tile[tx][r];
         __syncthreads();
     }
 }
@@ -552,7 +567,7 @@ void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int P
             return;
         }
     }
-    CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX>), dim3(grid), dim3(PL * CS), st, tm, x, S, (T*)nullptr, mbits,
+    CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX>), dim3(grid), dim3(PL * CS), st, tm, x, S, CS == 1 && CPT * sizeof(T) <= 16 ? S2 : (T*)nullptr, mbits,
               ctl, C, P, (P + 63) / 64, tau, flags);
 }
 
@@ -602,7 +617,7 @@ __global__ __launch_bounds__(CS * PLC) void detect_listed_kernel(const T* __rest
                                                                  int* __restrict__ ctl,
                                                                  const int32_t* __restrict__ cand,
                                                                  const int* __restrict__ cand_count, int cand_cap,
-                                                                 int C, int P, int W, float tau, int flags, int pool_w,
+                                                                 int C, int Cpx, int P, int W, float tau, int flags, int pool_w,
                                                                  int cand_W)
 {
     constexpr int U = 8;                          // channels per lane held in registers (all of them when C <= 8*CS)
@@ -677,14 +692,14 @@ __global__ __launch_bounds__(CS * PLC) void detect_listed_kernel(const T* __rest
                 const int c = g + u * CS;
                 if (c < C) {
                     S[(size_t)c * P + q] = xr[u];
-                    if (!SH && S2) S2[(size_t)q * C + c] = xr[u];
+                    if (!SH && S2) S2[(size_t)q * Cpx + c] = xr[u];
                 }
             }
             for (int c = g + U * CS; c < C; c += CS) {
                 const size_t off = (size_t)c * P + q;
                 const T xc = x[off];
                 S[off] = xc;
-                if (S2) S2[(size_t)q * C + c] = xc;
+                if (S2) S2[(size_t)q * Cpx + c] = xc;
             }
         }
         if (SH) {
@@ -734,15 +749,15 @@ hipError_t launch_listed_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbi
 #define CB_LISTED(cs, plc)                                                                                          \
     do {                                                                                                            \
         {                                                                                                           \
-            if (S2 != nullptr) {                                                                                    \
+            if (S2 != nullptr && g.Cs == g.C && g.C >= 16) {                                                        \
                 CB_LAUNCH((detect_listed_kernel<T, cs, plc, true>), dim3(std::min(2048, (cand_cap + plc - 1) / plc)), \
-                          dim3(cs * plc), st, tm, x, S, S2, mbits, ctl, cand, cand_count, cand_cap, g.C, g.P, g.W, tau, \
+                          dim3(cs * plc), st, tm, x, S, S2, mbits, ctl, cand, cand_count, cand_cap, g.C, g.Cs, g.P, g.W, tau, \
                           flags, pool_w, cand_W);                                                                   \
                 break;                                                                                              \
             }                                                                                                       \
         }                                                                                                           \
         CB_LAUNCH((detect_listed_kernel<T, cs, plc>), dim3(std::min(2048, (cand_cap + plc - 1) / plc)), dim3(cs * plc), \
-                  st, tm, x, S, S2, mbits, ctl, cand, cand_count, cand_cap, g.C, g.P, g.W, tau, flags, pool_w, cand_W); \
+                  st, tm, x, S, S2, mbits, ctl, cand, cand_count, cand_cap, g.C, g.Cs, g.P, g.W, tau, flags, pool_w, cand_W); \
     } while (0)
     if (g.C <= 32)       CB_LISTED(4, 64);
     else if (g.C <= 64)  CB_LISTED(8, 32);
@@ -786,7 +801,7 @@ hipError_t launch_detect(const Geom& g, const void* x, void* S, void* S2, uint64
                          float tau, int flags, hipStream_t st, Tm tm)
 {
     // a shadow is kept for layers with a power-of-two channel count (see fused_channel_last)
-    if (S2 && (g.C < (g.bf16 ? 32 : 16) || (g.C & (g.C - 1)) != 0)) return hipErrorInvalidValue;
+    if (S2 && g.Cs == g.C && g.C > (g.bf16 ? 8 : 4) && (g.C < (g.bf16 ? 32 : 16) || (g.C & (g.C - 1)) != 0)) return hipErrorInvalidValue;
     if (g.bf16)
         return launch_t<uint16_t>(g, (const uint16_t*)x, (uint16_t*)S, (uint16_t*)S2, mbits, ctl, tau, flags,
                                   st, tm);
@@ -813,9 +828,9 @@ hipError_t launch_shadow_rebuild(const Geom& g, const void* S, void* S2, hipStre
     const unsigned grid = (unsigned)std::min(tiles, 8192L);
     if (g.bf16)
         hipLaunchKernelGGL(shadow_rebuild_kernel<uint16_t>, dim3(grid), dim3(256), 0, st, (const uint16_t*)S, (uint16_t*)S2,
-                           g.C, g.P);
+                           g.C, g.Cs, g.P);
     else
-        hipLaunchKernelGGL(shadow_rebuild_kernel<float>, dim3(grid), dim3(256), 0, st, (const float*)S, (float*)S2, g.C, g.P);
+        hipLaunchKernelGGL(shadow_rebuild_kernel<float>, dim3(grid), dim3(256), 0, st, (const float*)S, (float*)S2, g.C, g.Cs, g.P);
     return hipGetLastError();
 }
 

@@ -119,6 +119,8 @@ __device__ __forceinline__ void st_out4(uint16_t* p, const float (&v)[4])
 bool fused_supported(const Geom& g);
 // whether a layer of this geometry that keeps an input state uses the channel-last variant
 bool fused_channel_last(const Geom& g);
+// ... or pads the pixels of its shadow to 16 bytes for it (up to 4 float32 / 8 bfloat16 channels: first layers)
+bool fused_padded(const Geom& g);
 size_t fused_pack_bytes(const Geom& g);
 size_t fused_table_bytes(const Geom& g);
 hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, bool channel_last, hipStream_t st,

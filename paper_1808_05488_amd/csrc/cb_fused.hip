@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void pack_fused_bf16_kernel(Geom g, int Mt16, 
     }
 }
 
-// Channel-last variant, bfloat16: 8 consecutive k' per lane, k' = (j*kw + i)*C + c.
+// Channel-last variant, bfloat16: 8 consecutive k' per lane, k' = (j*kw + i)*Cs + c (zero for the channels c >= C of a padded pixel).
 __global__ __launch_bounds__(256) void pack_fused_bf16_cl_kernel(Geom g, int Mt16, int KG, const uint16_t* __restrict__ w,
                                                                  uint4* __restrict__ KF)
 {
@@ -70,8 +70,8 @@ __global__ __launch_bounds__(256) void pack_fused_bf16_cl_kernel(Geom g, int Mt1
 #pragma unroll
         for (int qk = 0; qk < 8; ++qk) {
             const int k = kgroup * 32 + 8 * (lane >> 4) + qk;
-            const int tap = k / g.C, c = k - tap * g.C;
-            const uint32_t h = (m < g.O && k < g.R) ? w[(size_t)m * g.R + (size_t)c * taps + tap] : 0u;
+            const int tap = k / g.Cs, c = k - tap * g.Cs;
+            const uint32_t h = (m < g.O && tap < taps && c < g.C) ? w[(size_t)m * g.R + (size_t)c * taps + tap] : 0u;
             v[qk >> 1] |= h << ((qk & 1) * 16);
         }
         KF[e] = make_uint4(v[0], v[1], v[2], v[3]);
@@ -153,11 +153,12 @@ int stage_units(const Geom& g, int cw, int bn, unsigned tab_lds, const std::vect
 size_t fused_pack_bytes(const Geom& g)
 {
     // (bfloat16: padded to 128 rows, the unit of the channel-last kernel)
-    const size_t Rpad = g.bf16 ? (size_t)(g.R + 127) / 128 * 128 : (size_t)(g.R + KC - 1) / KC * KC;
+    const size_t Rs = fused_padded(g) ? (size_t)g.Cs * g.kh * g.kw : (size_t)g.R;
+    const size_t Rpad = g.bf16 ? (Rs + 127) / 128 * 128 : (Rs + KC - 1) / KC * KC;
     const size_t Mt16 = (size_t)(g.O + 127) / 128 * 8;     // 16-row tiles, padded to the largest row tile
     // 16 bytes per lane per k-group: 16 rows of float32, 32 rows of bfloat16
     // (float32, channel-last: three bfloat16 terms, 16 bytes each per lane and 32 rows)
-    if (fused_channel_last(g) && !g.bf16) return Mt16 * (Rpad / 32) * 3 * 64 * 16;
+    if ((fused_channel_last(g) || fused_padded(g)) && !g.bf16) return Mt16 * (Rpad / 32) * 3 * 64 * 16;
     return Mt16 * (Rpad / (g.bf16 ? 32 : 16)) * 64 * 16;
 }
 
@@ -189,12 +190,17 @@ bool fused_channel_last(const Geom& g)
     return g.C >= (g.bf16 ? 32 : 16) && (g.C & (g.C - 1)) == 0 && fused_supported(g);
 }
 
+bool fused_padded(const Geom& g)
+{
+    return g.C <= (g.bf16 ? 8 : 4) && fused_supported(g) && (unsigned long long)g.P * 16 <= 0xFFFFFF00ull;
+}
+
 hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, bool channel_last, hipStream_t st,
                          FusedPlan* plan)
 {
-    plan->cl = channel_last && fused_channel_last(g);
+    plan->cl = channel_last && (fused_channel_last(g) || fused_padded(g));
     // 16-row (float32) / 32-row (bfloat16) groups of K; the channel-last bfloat16 kernel walks K in units of 128 rows
-    const int KG = (plan->cl && g.bf16) ? (g.R + 127) / 128 * 4 : (g.R + KC - 1) / KC * KC / (g.bf16 ? 32 : 16);
+    const int KG = (plan->cl && g.bf16) ? (g.Cs * g.kh * g.kw + 127) / 128 * 4 : (g.R + KC - 1) / KC * KC / (g.bf16 ? 32 : 16);
     const int Mt16 = (g.O + 127) / 128 * 8;
     long n = (long)Mt16 * KG * 64;
     unsigned grid = (unsigned)((n + 255) / 256);

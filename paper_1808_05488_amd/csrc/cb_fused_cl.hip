@@ -3,7 +3,8 @@
 // side, so a filter tap of a listed pixel is C contiguous elements: fully coalesced 16-byte loads, no chunk table.
 //
 // Work item = BN listed columns x BM output channels x all of K; four wavefronts, WGM x WGN, each
-// (16*TM) x (16*TN).  K is walked tap-major, k' = (j*kw + i)*C + c (C a power of two), in groups of 32 (one step of
+// (16*TM) x (16*TN).  K is walked tap-major, k' = (j*kw + i)*Cs + c (Cs a power of two: C, or the 16
+// bytes to which the pixels of a first layer's shadow are padded), in groups of 32 (one step of
 // v_mfma_f32_16x16x32_bf16), UKG groups = one stage.
 //   B operand: a thread fetches 16-byte pieces of a column (consecutive lanes: consecutive pieces) and stores them to
 //     LDS, [column][k], column pitch 4 mod 32 words, so that the 16-byte fragment reads of sixteen columns fall
@@ -63,7 +64,7 @@ __device__ __forceinline__ float exact_dot(const Geom& g, const float* __restric
     for (int j = 0; j < g.kh; ++j)
         for (int i = 0; i < g.kw; ++i) {
             const bool in = (unsigned)(y0 + j) < (unsigned)g.H && (unsigned)(x0 + i) < (unsigned)g.W;
-            const float* px = S2 + (in ? ((size_t)(y0 + j) * g.W + (x0 + i)) * g.C : 0);
+            const float* px = S2 + (in ? ((size_t)(y0 + j) * g.W + (x0 + i)) * g.Cs : 0);
             const float* kt = KT + (size_t)(j * g.kw + i) * g.Opad + m;
             // (a padding tap is a zero that takes part: zero times an infinite filter value is no number)
             for (int c = 0; c < g.C; ++c) v = fmaf(in ? px[c] : 0.f, kt[(size_t)c * kk * g.Opad], v);
@@ -131,11 +132,11 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     char* const Bs = reinterpret_cast<char*>(dyn_lds4);
     int* const qs = reinterpret_cast<int*>(Bs + 2 * BUF);
 
-    const int nkg = F32 ? (g.R + 63) / 64 * 2 : (g.R + 127) / 128 * 4;       // k-groups of the packed filter matrix
+    const int nkg = F32 ? (g.Cs * g.kh * g.kw + 63) / 64 * 2 : (g.Cs * g.kh * g.kw + 127) / 128 * 4;       // k-groups of the packed filter matrix
     const int nunits = (nkg + UKG - 1) / UKG;
-    const int lc = 31 - __builtin_clz((unsigned)g.C);
+    const int lc = 31 - __builtin_clz((unsigned)g.Cs);
     const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<T*>(S2), 0, (int)((unsigned)g.C * (unsigned)g.P * ESZ), 0x00020000);
+        const_cast<T*>(S2), 0, (int)((unsigned)g.Cs * (unsigned)g.P * ESZ), 0x00020000);
     constexpr unsigned NOWHERE = 0xFFFFFFF0u;
     // tiles: every XCD (workgroup number mod 8) walks its own range of column tiles, all row tiles of one column tile in
     // turn.  (32 bits: the outputs of 2^31 such tiles would not fit any memory.)
@@ -150,7 +151,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     const int wm_s = __builtin_amdgcn_readfirstlane(wm);
     const int l16 = lane & 15, lq = lane >> 4;
     const int gc = tid / PPC, ch = tid % PPC;    // first column of this thread, its piece of a stage
-    const int dt = (EPV * ch) >> lc, cl = (EPV * ch) & (g.C - 1);
+    const int dt = (EPV * ch) >> lc, cl = (EPV * ch) & (g.Cs - 1);
 
     int qnext[NP];
     auto fetch_q = [&](unsigned u, int (&q)[NP]) {
@@ -215,7 +216,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             const unsigned kb = (unsigned)u * (unsigned)UK;
             const unsigned tap = (kb >> lc) + (unsigned)dt;
             const unsigned j = (tap * div.inv_kw) >> 16, i = tap - j * (unsigned)g.kw;
-            const unsigned toff = (((j * (unsigned)g.W + i) << lc) + (kb & (unsigned)(g.C - 1))) * ESZ;
+            const unsigned toff = (((j * (unsigned)g.W + i) << lc) + (kb & (unsigned)(g.Cs - 1))) * ESZ;
             // (rows that pad K have j >= kh, whose bit is clear, as bit 31 is for any j beyond it: kh, kw <= 31)
             const unsigned jj = j < 31u ? j : 31u;
 #pragma unroll
@@ -415,8 +416,8 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 }
 
 // Filter matrix of the float32 kernel: for every 16-row tile and k-group of 32, three fragments (terms h, m, l) of 64 x 16
-// bytes: lane's 8 values are K(m = mtile*16 + lane%16, k' = kgroup*32 + 8*(lane/16) + 0..7), k' = (j*kw + i)*C + c; zero
-// outside O x R.
+// bytes: lane's 8 values are K(m = mtile*16 + lane%16, k' = kgroup*32 + 8*(lane/16) + 0..7), k' = (j*kw + i)*Cs + c; zero
+// outside the filter matrix and for the channels c >= C of a padded pixel.
 __global__ __launch_bounds__(256) void pack_fused_split_kernel(Geom g, int Mt16, int KG, const float* __restrict__ w,
                                                                uint4* __restrict__ KF)
 {
@@ -434,8 +435,8 @@ __global__ __launch_bounds__(256) void pack_fused_split_kernel(Geom g, int Mt16,
 #pragma unroll
             for (int o = 0; o < 2; ++o) {
                 const int k = kgroup * 32 + 8 * (lane >> 4) + 2 * q2 + o;
-                const int tap = k / g.C, c = k - tap * g.C;
-                v[o] = (m < g.O && k < g.R) ? w[(size_t)m * g.R + (size_t)c * taps + tap] : 0.f;
+                const int tap = k / g.Cs, c = k - tap * g.Cs;
+                v[o] = (m < g.O && tap < taps && c < g.C) ? w[(size_t)m * g.R + (size_t)c * taps + tap] : 0.f;
             }
             split2(v[0], v[1], t[0][q2], t[1][q2], t[2][q2]);
         }
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(G
 #define CB_BODY(...) fused_cl_body<T, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2)
     constexpr bool F32 = sizeof(T) == 4;
     // (literal arguments, not a table: a table would be fetched from memory ahead of everything else)
-    const unsigned nkg = ((unsigned)g.R + 31u) / 32u;
+    const unsigned nkg = ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u;
 #define CB_COST(bm, bn, a0, a1, a2, a3, b0, b1, b2, b3) \
     (F32 ? cl_cost<bm, bn>(N, g.O, nkg, a0, a1, a2, a3) : cl_cost<bm, bn>(N, g.O, nkg, b0, b1, b2, b3))
     // 16 x 16, the four wavefronts sharing K: four times the tiles of the others where few pixels are listed, a quarter of
@@ -514,7 +515,7 @@ template <typename T>
 hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow, const int32_t* idx, const int* count,
                            const void* KF, const float* KT, const float* bias, int relu, T* OUT, T* OUT2, hipStream_t st, Tm tm)
 {
-    if (!plan.cl || (g.C & (g.C - 1)) != 0 || g.C < 16 || g.bf16 != (sizeof(T) == 2)) return hipErrorInvalidValue;
+    if (!plan.cl || (g.Cs & (g.Cs - 1)) != 0 || g.Cs < 16 / (int)sizeof(T) || g.bf16 != (sizeof(T) == 2)) return hipErrorInvalidValue;
     const ClDiv div = {g.Wo < 4096 ? ((1ull << 42) + (unsigned)g.Wo - 1ull) / (unsigned)g.Wo : 0ull,
                        (65536u + (unsigned)g.kw - 1u) / (unsigned)g.kw};
 #define CB_CL(shape)                                                                                                     \
@@ -532,7 +533,7 @@ hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow
 
 hipError_t launch_pack_fused_split(const Geom& g, const float* w, void* KF, hipStream_t st)
 {
-    const int KG = (g.R + 63) / 64 * 2, Mt16 = (g.O + 127) / 128 * 8;
+    const int KG = (g.Cs * g.kh * g.kw + 63) / 64 * 2, Mt16 = (g.O + 127) / 128 * 8;
     const long n = (long)Mt16 * KG * 64;
     unsigned grid = (unsigned)((n + 255) / 256);
     if (grid > 2048) grid = 2048;

@@ -30,6 +30,7 @@ struct Geom {
     int WWo;          // 64-bit words per output row of the bit-packed dilated map
     int Opad;         // O rounded up to 16: row pitch of the transposed filter matrix
     int bf16;         // element type: 0 float, 1 bfloat16 bit patterns
+    int Cs;           // channels of a pixel in the channel-last shadow: C, or the channels of 16 bytes where C is fewer
 };
 
 // Small device-resident control block of a layer (int32 slots).
@@ -55,8 +56,8 @@ enum { DET_FORCE_ALL = 1,      // mark every pixel as changed (first frame)
                                // non-temporally too (1080p, 128 channels: 374 -> 318 us; a state that fits loses)
        DET_NO_UPDATE = 8 };    // compare and write the map only; launch_state_apply updates the state (and shadow)
 
-// S2: null, or the channel-last shadow of the state (pixel-major, C values per pixel; C >= 16), which
-// receives the same updates as S.
+// S2: null, or the channel-last shadow of the state (pixel-major, Cs values per pixel: a power of two C >= 16, or the
+// 16 bytes that hold the few channels of a first layer, zero behind them), which receives the same updates as S.
 // mbits: the layer's two input maps, used by alternate frames and interleaved word by word (64-bit word w
 // of the map of frame parity p at index 2*w + p: the index extraction, which does not know p when it
 // starts, fetches both candidates with one 16-byte load); the frame count in ctl[CTL_FRAME] selects
@@ -69,7 +70,7 @@ hipError_t launch_detect(const Geom& g, const void* x, void* S, void* S2, uint64
 hipError_t launch_state_apply(const Geom& g, const void* x, void* S, void* S2, const uint64_t* mbits, const int* ctl,
                               hipStream_t st, Tm tm = Tm());
 
-// S2 = the channel-last copy of the whole state S (for a state that was written from outside).
+// S2 = the channel-last copy of the whole state S (for a state that was written from outside; padding channels are left alone).
 hipError_t launch_shadow_rebuild(const Geom& g, const void* S, void* S2, hipStream_t st);
 
 // Eq. 3 restricted to candidate pixels: the entries of a producer's index list (mapped through

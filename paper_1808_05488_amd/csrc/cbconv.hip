@@ -69,6 +69,7 @@ int validate(const cb_layer_desc* d, cb::Geom* g)
     const int bm = cb::gemm_bm(d->c_out);
     g->Opad = (d->c_out + bm - 1) / bm * bm;
     g->bf16 = d->dtype == CB_BF16;
+    g->Cs = g->C <= (g->bf16 ? 8 : 4) ? (g->bf16 ? 8 : 4) : g->C;
     if (d->backend == CB_BACKEND_FUSED && !cb::fused_supported(*g)) return CB_EINVAL;
     const bool fused = d->backend != CB_BACKEND_EXPLICIT && cb::fused_supported(*g);
     // the pixel-major copy of the cached output is written by the fused kernel's epilogue, four channels at a time
@@ -84,12 +85,13 @@ bool use_fused(const cb_layer_desc* d, const cb::Geom& g)
     return d->backend == CB_BACKEND_FUSED || (d->backend == CB_BACKEND_AUTO && cb::fused_supported(g));
 }
 
-// Closed-loop layers on the fused back end whose channel count allows it keep a second,
+// Closed-loop layers on the fused back end whose channel count allows it (16 and more: a power of two; first layers: as
+// many as 16 bytes hold, padded to that) keep a second,
 // pixel-major copy of the input state for the gather of the fused kernel.  Not feed-forward
 // layers, which rewrite the whole state every frame.
 bool use_shadow(const cb_layer_desc* d, const cb::Geom& g)
 {
-    return use_fused(d, g) && d->mode == CB_CLOSED_LOOP && cb::fused_channel_last(g);
+    return use_fused(d, g) && d->mode == CB_CLOSED_LOOP && (cb::fused_channel_last(g) || cb::fused_padded(g));
 }
 
 StateLayout state_layout(const cb_layer_desc* d, const cb::Geom& g)
@@ -100,7 +102,7 @@ StateLayout state_layout(const cb_layer_desc* d, const cb::Geom& g)
     // (the input state, or the cached output when a CB_PROPAGATE consumer reads it)
     size_t o = 256;
     L.S = o;      o += d->mode == CB_PROPAGATE ? 0 : align256((size_t)g.C * g.P * b);
-    L.S2 = o;     o += use_shadow(d, g) ? align256((size_t)g.C * g.P * b) : 0;
+    L.S2 = o;     o += use_shadow(d, g) ? align256((size_t)g.Cs * g.P * b) : 0;
     L.OUT = o;    o += align256((size_t)g.O * g.Po * b);
     L.OUT2 = o;   o += d->keep_output_channel_last ? align256((size_t)g.O * g.Po * b) : 0;
     L.mbits = o;  o += align256(((size_t)(g.P + 63) / 64 + 4) * 16);  // two maps, word-interleaved: frames alternate between them
@@ -306,7 +308,7 @@ int detect_and_update(cb_layer* L, const void* input_dev, float tau, const int32
         CB_HIP(cb::launch_detect_listed(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau,
                                         flags, cand, cand_count, cand_cap, pool_w, cand_W, L->st,
                                         next_tm(L, CB_STEP_DETECT)));
-    else if (L->shadow && L->primed && !L->g.bf16 && (flags & cb::DET_STREAM_STATE)) {
+    else if (L->shadow && L->g.C >= 16 && L->primed && !L->g.bf16 && (flags & cb::DET_STREAM_STATE)) {
         // a float32 state beyond the caches, with a shadow: detection as a pure stream, the update of the changed
         // pixels (state and shadow) in a kernel of its own (1080p x 128 channels: the detection variant that
         // updates the shadow itself costs 17 us more even when nothing changes, this one 0 - 10 us up to 1 % changed;
@@ -609,7 +611,7 @@ int cb_layer_import_state(cb_layer_t* L, const void* state_in_dev, const void* o
     CB_HIP(hipMemcpyAsync(L->OUT(), output_in_dev, nO, hipMemcpyDeviceToDevice, L->st));
     if (L->OUT2()) {
         cb::Geom go = g;                      // the same transposition, on the output's shape
-        go.C = g.O; go.P = g.Po;
+        go.C = go.Cs = g.O; go.P = g.Po;
         CB_HIP(cb::launch_shadow_rebuild(go, L->OUT(), L->OUT2(), L->st));
     }
     // the change set of "the last frame" is empty: both input maps, the dilated map, N and the two counters of M

@@ -251,6 +251,41 @@ def test_channel_last_shadow(geom, bf16):
     p.step(frames[4], 0.02, tag=f"shadow {geom} frame 4")
 
 
+# First layers (up to 4 float32 / 8 bfloat16 channels) keep a shadow padded to 16 bytes per pixel for the channel-last kernel:
+# whole and partial updates, a state that comes from outside, and detection at a producer's listed pixels.
+@pytest.mark.parametrize("bf16,C", [(False, 1), (False, 3), (False, 4), (True, 1), (True, 3), (True, 5), (True, 8)])
+@pytest.mark.parametrize("geom", [(16, 7, 1, 61, 67), (70, 3, 2, 45, 52), (33, 5, 1, 260, 256), (5, 1, 1, 40, 31)])
+def test_padded_shadow(geom, bf16, C):
+    O, k, s, H, W = geom
+    _say(f"padded shadow {geom} C={C} bf16={bf16}")
+    spec, frames = syn.random_layer_case(sum(geom) + C, C, O, k, s, k // 2, H, W, 5, change_prob=0.03, relu=True, noise_std=0.004)
+    p = Pair(spec, H, W, bf16=bf16, backend=2)
+    for t in range(3):
+        p.step(frames[t], 0.02, tag=f"padded shadow {geom} frame {t}")
+    st, out = p.g.export_state()
+    q = Pair(spec, H, W, bf16=bf16, backend=2)
+    q.step(frames[4], 0.02, tag="another state")
+    q.g.import_state(st, out)
+    for f in frames[3:]:
+        x = to_dev(prep(f, bf16), bf16)
+        a, b = p.g.process_frame(x, 0.02), q.g.process_frame(x, 0.02)
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)) and torch.equal(p.g.state(), q.g.state())
+    dt = torch.bfloat16 if bf16 else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(C)
+    w1 = (torch.rand((C, 4, 3, 3), generator=g, device="cuda") - 0.5).to(dt)
+    prod = cb.Layer(w1, None, 1, 1, H, W, True)
+    w2 = to_dev(p.w, bf16)
+    chained, plain = (cb.Layer(w2, None, s, k // 2, H, W, False, backend=2) for _ in range(2))
+    x = torch.rand((4, H, W), generator=g, device="cuda").to(dt)
+    for t in range(4):
+        x = x.clone()
+        x[:, 5 * t:5 * t + 9, 3 * t:3 * t + 11] = torch.rand((4, 9, 11), generator=g, device="cuda").to(dt)
+        mid = prod.process_frame(x, 0.02)
+        a, b = chained.process_frame_chained(mid, prod, 0.02), plain.process_frame(mid.clone(), 0.02)
+        assert torch.equal(chained.state(), plain.state()) and torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
 # bfloat16 change detection takes four pixels per lane at any alignment from 32 768 pixels on.  Planes of 4n + 1 .. 3 pixels, the
 # last lane's first pixel at the start of a workgroup (256 or 1024 pixels) or inside one; every number of channel groups; frames
 # that start one element off a word; full, closed-loop and feed-forward updates.
