@@ -246,8 +246,9 @@ __device__ __forceinline__ void expand_words(uint64_t word, int off, int pixbase
 // nothing to clear.
 __device__ __forceinline__ int frame_parity(const int* ctl, int own_map) { return own_map ? (ctl[CTL_FRAME] & 1) : 0; }
 // the other map and the other counter start the next frame empty
-__device__ __forceinline__ void clear_other_map(uint64_t* maps, int par, int clear_words, int first, int step)
+__device__ __forceinline__ void clear_other_map(uint64_t* maps, int* ctl, int par, int clear_words, int first, int step)
 {
+    if (first < NIN_SLOTS) *nin_counter(ctl, (unsigned)first, par ^ 1) = 0;
     for (int i = first; i < clear_words; i += step) maps[2 * i + (par ^ 1)] = 0;
 }
 
@@ -273,20 +274,18 @@ __global__ __launch_bounds__(256) void dilate_kernel(Geom g, const uint64_t* __r
     const int items = g.Ho * g.WWo;
     const int it = blockIdx.x * 256 + threadIdx.x;
     const int par = frame_parity(ctl, own_map);
-    const int clear_slot = own_map ? CTL_NIN_A + (par ^ 1) : -1;
     uint64_t word = 0;
     if (!full) word = dilated_block_word<256, MAP_STAGE>(g, in_bits, pitch, (int)blockIdx.x * 256, items, own_map, par, s_map);
     if (it < items) {
         if (full) word = full_word(g, it);
         mt_bits[it] = word;
     }
-    if (own_map) clear_other_map(const_cast<uint64_t*>(in_bits), par, clear_words, it, (int)gridDim.x * 256);
+    if (own_map) clear_other_map(const_cast<uint64_t*>(in_bits), ctl, par, clear_words, it, (int)gridDim.x * 256);
     int s = wave_sum(__popcll(word));
     if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
         blk_cnt[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-        if (blockIdx.x == 0 && clear_slot >= 0) ctl[clear_slot] = 0;
     }
 }
 
@@ -370,7 +369,6 @@ __global__ __launch_bounds__(256) void dilate_compact_kernel(Geom g, const uint6
 {
     // (needed only after the map words have been requested: both candidates come with one load)
     const int par = frame_parity(ctl, own_map);
-    const int clear_slot = own_map ? CTL_NIN_A + (par ^ 1) : -1;
     __shared__ unsigned s_epoch;
     __shared__ int wtot[4];
     __shared__ int red[4];
@@ -393,7 +391,7 @@ __global__ __launch_bounds__(256) void dilate_compact_kernel(Geom g, const uint6
         pixbase = yo * g.Wo + 64 * wo;
     }
     // housekeeping for the next frame: the other input map starts out empty
-    if (own_map) clear_other_map(const_cast<uint64_t*>(in_bits), par, clear_words, bid * 256 + tid, nblk * 256);
+    if (own_map) clear_other_map(const_cast<uint64_t*>(in_bits), ctl, par, clear_words, bid * 256 + tid, nblk * 256);
     const int cnt = __popcll(word);
     const int inc = wave_inclusive_scan(cnt);                  // inclusive scan inside the wavefront
     if (lane == 63) wtot[wv] = inc;
@@ -433,7 +431,6 @@ __global__ __launch_bounds__(256) void dilate_compact_kernel(Geom g, const uint6
     expand_words<false>(word, off, pixbase, idx, lane);
 
     if (tid == 0) {
-        if (bid == 0 && clear_slot >= 0) ctl[clear_slot] = 0;
         if (atomicAdd(&ctl[CTL_DONE], 1) == nblk - 1) {      // everybody has read the epoch and the frame count
             ctl[CTL_DONE] = 0;
             ctl[CTL_EPOCH] = (int)epoch;
@@ -452,7 +449,6 @@ __global__ __launch_bounds__(1024) void dilate_compact_small_kernel(Geom g, cons
                                                                     int own_map, int clear_words)
 {
     const int par = frame_parity(ctl, own_map);
-    const int clear_slot = own_map ? CTL_NIN_A + (par ^ 1) : -1;
     __shared__ int wtot[16];
     __shared__ int carry;
     __shared__ uint64_t s_map[MAP_STAGE_SMALL];
@@ -487,11 +483,10 @@ __global__ __launch_bounds__(1024) void dilate_compact_small_kernel(Geom g, cons
         __syncthreads();                 // everyone has read carry
         if (tid == 0) carry += round_total;
     }
-    if (own_map) clear_other_map(const_cast<uint64_t*>(in_bits), par, clear_words, tid, 1024);
+    if (own_map) clear_other_map(const_cast<uint64_t*>(in_bits), ctl, par, clear_words, tid, 1024);
     __syncthreads();
     if (tid == 0) {
         ctl[CTL_COUNT] = carry;
-        if (clear_slot >= 0) ctl[clear_slot] = 0;
         if (own_map) ctl[CTL_FRAME] = ctl[CTL_FRAME] + 1;    // (one workgroup: everybody is past its reads)
     }
 }

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void detect_kernel(const T* __restrict__ x, T*
     typedef typename Pack<T, VEC>::type V;
     const int par = ctl[CTL_FRAME] & 1;          // which of the two map buffers and counters this frame fills
     uint64_t* __restrict__ mbits = mbits0 + par;  // the two maps are interleaved: word w of this frame's map at [2 * w]
-    int* __restrict__ nin = ctl + CTL_NIN_A + par;
+    int* __restrict__ nin = nin_counter(ctl, blockIdx.x, par);
     constexpr int PL = 256 / CS;
     constexpr unsigned ALL = (1u << VEC) - 1u;
     const int tid = threadIdx.x;
@@ -216,7 +216,7 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
     // number of frames captured
     const int par = ctl[CTL_FRAME] & 1;
     uint64_t* __restrict__ mbits = mbits0 + par;  // the two maps are interleaved: word w of this frame's map at [2 * w]
-    int* __restrict__ nin = ctl + CTL_NIN_A + par;
+    int* __restrict__ nin = nin_counter(ctl, blockIdx.x, par);
     constexpr int PL = PLX ? PLX : (CS >= 4 ? 64 : 256 / CS);
     static_assert(PLX == 0 || (PLX == 16 && VEC == 1 && CS > 1), "narrow workgroups: 16 lanes of one pixel each");
     constexpr int NT = PL * CS;
@@ -623,7 +623,7 @@ __global__ __launch_bounds__(CS * PLC) void detect_listed_kernel(const T* __rest
     constexpr int U = 8;                          // channels per lane held in registers (all of them when C <= 8*CS)
     const int par = ctl[CTL_FRAME] & 1;           // which of the two map buffers and counters this frame fills
     uint64_t* __restrict__ mbits = mbits0 + par;  // the two maps are interleaved: word w of this frame's map at [2 * w]
-    int* __restrict__ nin = ctl + CTL_NIN_A + par;
+    int* __restrict__ nin = nin_counter(ctl, blockIdx.x, par);
     __shared__ unsigned sflag[CS * PLC];
     constexpr int PITCH = CS * U + 1;             // staged values per candidate: candidates a lane apart fall into different banks
     // (one buffer and a barrier at the end of the round where two would not fit)

@@ -36,8 +36,6 @@ struct Geom {
 // Small device-resident control block of a layer (int32 slots).
 enum Ctl {
     CTL_COUNT = 0,     // N of the current frame
-    CTL_NIN_A = 1,     // changed-input counter, even frames
-    CTL_NIN_B = 2,     // changed-input counter, odd frames
     CTL_LD = 3,        // leading dimension of X'/Y' of the last chunk
     CTL_NCOLS = 4,     // columns of the last chunk
     CTL_NSPLIT = 5,    // k-splits (partial products stacked in Y') of the last chunk
@@ -46,8 +44,20 @@ enum Ctl {
     CTL_FRAME = 10,    // frames processed by a layer that detects its own changes: its parity selects the input-map
                        //   buffer and the changed-pixel counter of the frame (advanced by the index extraction)
     CTL_RECOUNTS = 9,  //   predecessor counts a workgroup recomputed itself after its bounded wait ran out
-    CTL_SLOTS = 64
+    CTL_SLOTS = 64,
+    // Behind the slots: the changed-input counters, NIN_SLOTS pairs (even / odd frames) on lines of their own; their sum is the
+    // count.  Every wavefront of change detection that found something adds to one of them: to a single counter these
+    // additions queue up behind each other, at memory, for about 11 ns each (3 channels at 1080p with every
+    // pixel changed: 98 us, 9 us without a change).
+    NIN_SLOTS = 64,
+    NIN_STRIDE = 32,
+    CTL_WORDS = CTL_SLOTS + NIN_SLOTS * NIN_STRIDE
 };
+// counter of the frame parity `par` for workgroup b
+__device__ __forceinline__ int* nin_counter(int* ctl, unsigned b, int par)
+{
+    return ctl + CTL_SLOTS + (b % NIN_SLOTS) * NIN_STRIDE + par;
+}
 
 // flags for detect
 enum { DET_FORCE_ALL = 1,      // mark every pixel as changed (first frame)

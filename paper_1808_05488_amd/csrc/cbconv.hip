@@ -108,7 +108,7 @@ StateLayout state_layout(const cb_layer_desc* d, const cb::Geom& g)
     L.mbits = o;  o += align256(((size_t)(g.P + 63) / 64 + 4) * 16);  // two maps, word-interleaved: frames alternate between them
     L.mtbits = o; o += align256(((size_t)g.Ho * g.WWo + 4) * 8);
     L.idx = o;    o += align256((size_t)g.Po * 4);
-    L.ctl = o;    o += align256(cb::CTL_SLOTS * 4);
+    L.ctl = o;    o += align256(cb::CTL_WORDS * 4);
     L.look = o;   o += align256(cb::compact_one_pass_bytes(g));
     L.KT = o;     o += align256((size_t)g.R * g.Opad * b);
     L.bias = o;   o += align256((size_t)g.Opad * 4);
@@ -617,7 +617,8 @@ int cb_layer_import_state(cb_layer_t* L, const void* state_in_dev, const void* o
     // the change set of "the last frame" is empty: both input maps, the dilated map, N and the two counters of M
     CB_HIP(cb::launch_fill32((uint32_t*)L->mbits(), ((size_t)(g.P + 63) / 64) * 4, 0u, L->st));
     CB_HIP(cb::launch_fill32((uint32_t*)L->mtbits(), (size_t)g.Ho * g.WWo * 2, 0u, L->st));
-    CB_HIP(cb::launch_fill32((uint32_t*)L->ctl(), 3, 0u, L->st));       // CTL_COUNT, CTL_NIN_A, CTL_NIN_B
+    CB_HIP(cb::launch_fill32((uint32_t*)L->ctl() + cb::CTL_COUNT, 1, 0u, L->st));
+    CB_HIP(cb::launch_fill32((uint32_t*)L->ctl() + cb::CTL_SLOTS, cb::CTL_WORDS - cb::CTL_SLOTS, 0u, L->st));
     L->cur_in_bits = L->mbits();
     L->cur_in_pitch = g.W;
     L->cur_in_own = has_state;
@@ -681,14 +682,17 @@ int cb_layer_stats(cb_layer_t* L, cb_stats* stats)
     std::memset(stats, 0, sizeof(*stats));
     CB_HIP(hipStreamSynchronize(L->st));
     if (!L->primed) return CB_OK;
-    int ctl[cb::CTL_SLOTS];
+    int ctl[cb::CTL_WORDS];
     CB_HIP(hipMemcpy(ctl, L->ctl(), sizeof(ctl), hipMemcpyDeviceToHost));
     stats->scan_recounts = ctl[cb::CTL_RECOUNTS];
     int n = 0;
     CB_HIP(hipMemcpy(&n, L->cur_count, sizeof(int), hipMemcpyDeviceToHost));
     stats->n_changed_out = n;
-    // (the counter of the last frame: the one that the frame count, already advanced, selected for it)
-    stats->n_changed_in = L->d.mode == CB_PROPAGATE ? -1 : ctl[cb::CTL_NIN_A + ((ctl[cb::CTL_FRAME] - 1) & 1)];
+    // (the counters of the last frame: the ones that the frame count, already advanced, selected for it)
+    stats->n_changed_in = L->d.mode == CB_PROPAGATE ? -1 : 0;
+    if (L->d.mode != CB_PROPAGATE)
+        for (int s = 0; s < cb::NIN_SLOTS; ++s)
+            stats->n_changed_in += ctl[cb::CTL_SLOTS + s * cb::NIN_STRIDE + ((ctl[cb::CTL_FRAME] - 1) & 1)];
     stats->ops = 2LL * L->g.O * L->g.R * (long long)n;
     if (L->timing && L->ev_used >= 2) {
         // each pair holds the begin and end time stamps of one kernel dispatch
