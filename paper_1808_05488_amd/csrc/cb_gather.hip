@@ -7,7 +7,7 @@
 // lane owns one column n (so consecutive lanes write consecutive addresses of a
 // row of X', and -- because the index list is sorted and changes are spatially
 // clustered -- mostly read consecutive addresses of the state).  A work item is
-// 256 columns x a group of input channels.  The rows of one channel and one
+// 256 columns x a group of filter rows of input channels.  The rows of one channel and one
 // filter row are kw consecutive elements of the state: a lane fetches them as
 // runs of up to four (float32) / three (bfloat16) elements with ONE load each --
 // the vector memory pipeline's cost is per load and cache line touched, not per
@@ -20,7 +20,7 @@
 // counter, so a wavefront that keeps both in flight has to drain everything at
 // every wait.  The grid is persistent and strides over the work items; the
 // number of columns is read from device memory (no host round trip), and the
-// channel-group size is chosen there so that a few thousand columns still give
+// group size is chosen there so that a few thousand columns still give
 // every compute unit work.
 #include "cb_kernels.h"
 
@@ -198,13 +198,16 @@ __global__ __launch_bounds__(256) void gather_kernel(Geom g, const T* __restrict
         return;
     }
     const int tiles_n = ld >> 8;
-    // channel groups: about 1024 work items when there are few column tiles
+    // groups of (channel, filter row) pairs: about 1024 work items when there are few column tiles.  (Groups of whole channels
+    // were few and long: 3 -> 256, 9x9, 4 960 listed pixels 13 -> 6 us, 32 -> 32, 4 240 pixels 17 -> 13 us.)
     int groups = (1024 + tiles_n - 1) / tiles_n;
-    if (groups > g.C) groups = g.C;
-    const int cg = (g.C + groups - 1) / groups;
-    groups = (g.C + cg - 1) / cg;
+    const int nrows = g.C * g.kh;
+    if (groups > nrows) groups = nrows;
+    int rg = (nrows + groups - 1) / groups;
+    // (whole channels where they are enough items: 64 channels, 19 200 pixels 70 us, 77 in pieces of channels)
+    if ((long)tiles_n * g.C >= 1024) rg = (rg + g.kh - 1) / g.kh * g.kh;
+    groups = (nrows + rg - 1) / rg;
     const long total = (long)tiles_n * groups;
-    const int kk = g.kh * g.kw;
     const int npc = (g.kw + LEN - 1) / LEN;      // runs per filter row
     // Workgroup b runs on XCD b mod 8; every XCD takes a contiguous range of work items, so that
     // tiles that are neighbours in the (sorted) index list, and therefore read the same rows of
@@ -216,8 +219,9 @@ __global__ __launch_bounds__(256) void gather_kernel(Geom g, const T* __restrict
         if (t >= total) break;
         const int gi = (int)(t / tiles_n);
         const int n = (int)(t - (long)gi * tiles_n) * 256 + threadIdx.x;
-        const int c0 = gi * cg, c1 = c0 + cg < g.C ? c0 + cg : g.C;
-        T* xr = X + (size_t)c0 * kk * ld + n;
+        const int r0 = gi * rg, r1 = r0 + rg < nrows ? r0 + rg : nrows;
+        const int c0 = r0 / g.kh, j0 = r0 - c0 * g.kh;
+        T* xr = X + (size_t)r0 * g.kw * ld + n;
         // a lane beyond the last column still runs (it writes the zero padding columns that
         // the GEMM tiles read): all its taps count as padding
         const bool colv = n < ncols;
@@ -229,12 +233,12 @@ __global__ __launch_bounds__(256) void gather_kernel(Geom g, const T* __restrict
             for (int j = 0; j < g.kh; ++j) rowmask |= ((unsigned)(y0 + j) < (unsigned)g.H ? 1u : 0u) << j;
             for (int i = 0; i < g.kw; ++i) colmask |= ((unsigned)(x0 + i) < (unsigned)g.W ? 1u : 0u) << i;
         }
-        const int nruns = (c1 - c0) * g.kh * npc;
+        const int nruns = (r1 - r0) * npc;
         // wave-uniform position of the next run to load / to store: channel, filter row, first tap
-        int jl = 0, il = 0, js = 0, is = 0;
+        int jl = j0, il = 0, js = j0, is = 0;
         unsigned cbl = ((unsigned)c0 * (unsigned)g.P + (unsigned)(y0 * g.W + x0)) * esz + (unsigned)GUARD;
-        unsigned rbl = cbl;                      // byte offset of tap (j, 0) of the run being loaded
-        size_t rows = 0;                         // row of X' (relative to c0*kk) of the run being stored
+        unsigned rbl = cbl + (unsigned)(j0 * g.W) * esz;   // byte offset of tap (j, 0) of the run being loaded
+        size_t rows = 0;                         // row of X' (relative to the item's first) of the run being stored
         for (int e0 = 0; e0 < nruns; e0 += NB) {
             Run<T> v[NB];
             unsigned offs[NB];

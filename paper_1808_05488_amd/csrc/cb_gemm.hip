@@ -297,16 +297,16 @@ hipError_t launch_gemm(const Geom& g, const void* KT, const void* X, void* Y, co
                        int col0, int cap, int* ctl, hipStream_t st, Tm tm)
 {
     const int bm = gemm_bm(g.O);
-    const dim3 grid(1024), block(256);   // grid: multiple of 8 (XCD mapping), a few workgroups per CU
+    const dim3 grid(g.O <= 32 ? 2048 : 1024), block(256);   // grid: multiple of 8 (XCD mapping), a few workgroups per CU
     if (g.bf16) {
         const uint16_t* k = (const uint16_t*)KT; const uint16_t* x = (const uint16_t*)X; float* y = (float*)Y;
-        if (bm == 16)      CB_LAUNCH((gemm_bf16_kernel<16, 256, 1, 4>), grid, block, st, tm, g.O, g.Opad, g.R, k, x, y, count, col0, cap, ctl);
-        else if (bm == 32) CB_LAUNCH((gemm_bf16_kernel<32, 128, 1, 4>), grid, block, st, tm, g.O, g.Opad, g.R, k, x, y, count, col0, cap, ctl);
+        if (bm == 16)      CB_LAUNCH((gemm_bf16_kernel<16, 128, 1, 4>), grid, block, st, tm, g.O, g.Opad, g.R, k, x, y, count, col0, cap, ctl);
+        else if (bm == 32) CB_LAUNCH((gemm_bf16_kernel<32, 64, 1, 4>), grid, block, st, tm, g.O, g.Opad, g.R, k, x, y, count, col0, cap, ctl);
         else               CB_LAUNCH((gemm_bf16_kernel<64, 64, 2, 2>), grid, block, st, tm, g.O, g.Opad, g.R, k, x, y, count, col0, cap, ctl);
     } else {
         const float* k = (const float*)KT; const float* x = (const float*)X; float* y = (float*)Y;
-        if (bm == 16)      CB_LAUNCH((gemm_f32_kernel<16, 256, 1, 4>), grid, block, st, tm, g.O, g.Opad, g.R, k, x, y, count, col0, cap, ctl);
-        else if (bm == 32) CB_LAUNCH((gemm_f32_kernel<32, 128, 1, 4>), grid, block, st, tm, g.O, g.Opad, g.R, k, x, y, count, col0, cap, ctl);
+        if (bm == 16)      CB_LAUNCH((gemm_f32_kernel<16, 128, 1, 4>), grid, block, st, tm, g.O, g.Opad, g.R, k, x, y, count, col0, cap, ctl);
+        else if (bm == 32) CB_LAUNCH((gemm_f32_kernel<32, 64, 1, 4>), grid, block, st, tm, g.O, g.Opad, g.R, k, x, y, count, col0, cap, ctl);
         else               CB_LAUNCH((gemm_f32_kernel<64, 64, 2, 2>), grid, block, st, tm, g.O, g.Opad, g.R, k, x, y, count, col0, cap, ctl);
     }
     return hipGetLastError();

@@ -134,13 +134,15 @@ hipError_t launch_gemm(const Geom& g, const void* KT, const void* X, void* Y, co
 // k-splits it uses for a chunk of ncols columns (the output update sums the
 // partial products in a fixed order, so results do not depend on scheduling).
 __host__ __device__ inline int gemm_bm(int O) { return O <= 16 ? 16 : (O <= 32 ? 32 : 64); }
-__host__ __device__ inline int gemm_bn(int O) { return O <= 16 ? 256 : (O <= 32 ? 128 : 64); }
+// (tiles of 128 columns for 17 - 32 and 256 for up to 16 output channels left a few thousand columns too few workgroups: 32 -> 32, 9x9,
+// 4 240 columns 20 -> 14 us, 64 -> 16, 3 936 columns 54 -> 33 us, bfloat16 94 -> 38 us)
+__host__ __device__ inline int gemm_bn(int O) { return O <= 16 ? 128 : 64; }
 __host__ __device__ inline int gemm_nsplit(int ncols, int R, int O, int Opad, int cap)
 {
     const int bm = gemm_bm(O), bn = gemm_bn(O);
     const int ld = (ncols + 255) & ~255;
     const int tiles = ((ncols + bn - 1) / bn) * (Opad / bm);
-    int s = 512 / tiles;                 // aim at two workgroups per compute unit
+    int s = (O <= 32 ? 1024 : 512) / tiles;   // aim at two workgroups per compute unit, of the small tiles at four
     if (s > 8) s = 8;
     if (s > R / 128) s = R / 128;        // at least 128 rows of K per split
     if (s > cap / ld) s = cap / ld;      // partial products must fit the Y' buffer

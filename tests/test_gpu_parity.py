@@ -251,6 +251,19 @@ def test_channel_last_shadow(geom, bf16):
     p.step(frames[4], 0.02, tag=f"shadow {geom} frame 4")
 
 
+# Explicit back end: matrix generation in groups of filter rows (groups that start and end inside a channel), and the tiles and
+# k-splits of the product for up to 16, 32 and more output channels.
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("geom", [(3, 16, 9, 1, 60, 70), (5, 7, 9, 2, 75, 83), (7, 32, 5, 1, 120, 130), (11, 31, 7, 1, 33, 35), (2, 70, 9, 1, 24, 27)])
+def test_explicit_row_groups(geom, bf16):
+    C, O, k, s, H, W = geom
+    _say(f"row groups {geom} bf16={bf16}")
+    spec, frames = syn.random_layer_case(sum(geom) + 1, C, O, k, s, k // 2, H, W, 3, change_prob=0.01, relu=True, noise_std=0.004)
+    p = Pair(spec, H, W, bf16=bf16, backend=1)
+    for t, f in enumerate(frames):
+        p.step(f, 0.02, tag=f"row groups {geom} frame {t}")
+
+
 # First layers (up to 4 float32 / 8 bfloat16 channels) keep a shadow padded to 16 bytes per pixel for the channel-last kernel:
 # whole and partial updates, a state that comes from outside, and detection at a producer's listed pixels.
 @pytest.mark.parametrize("bf16,C", [(False, 1), (False, 3), (False, 4), (True, 1), (True, 3), (True, 5), (True, 8)])
