@@ -59,14 +59,14 @@ template <typename V> __device__ __forceinline__ V ld_once(const V* p)
 
 // The VEC pixels of a channel at p.  bfloat16: at any alignment (a plane of an odd number of pixels leaves every other
 // channel unaligned; global memory takes such loads, at the price of one more cache line per wavefront).
-template <typename T, int VEC, bool ANY> struct PxMem { typedef typename Pack<T, VEC>::type type; };
+template <typename T, int VEC> struct PxMem { typedef typename Pack<T, VEC>::type type; };
 typedef unsigned PxMem2x4 __attribute__((ext_vector_type(2), aligned(2)));
-template <> struct PxMem<uint16_t, 4, true> { typedef PxMem2x4 type; };
-template <typename T, int VEC, bool ANY, bool ONCE> __device__ __forceinline__ typename Pack<T, VEC>::type ld_px(const T* p)
+template <> struct PxMem<uint16_t, 4> { typedef PxMem2x4 type; };
+template <typename T, int VEC, bool ONCE> __device__ __forceinline__ typename Pack<T, VEC>::type ld_px(const T* p)
 {
     typedef typename Pack<T, VEC>::type V;
-    typedef typename PxMem<T, VEC, ANY>::type M;
-    if constexpr (ANY) {
+    typedef typename PxMem<T, VEC>::type M;
+    if constexpr (sizeof(T) == 2 && VEC > 1) {
         if constexpr (ONCE) return __builtin_bit_cast(V, (uintx2)__builtin_nontemporal_load(reinterpret_cast<const M*>(p)));
         else return __builtin_bit_cast(V, (uintx2)*reinterpret_cast<const M*>(p));
     } else {
@@ -74,10 +74,10 @@ template <typename T, int VEC, bool ANY, bool ONCE> __device__ __forceinline__ t
         else return *reinterpret_cast<const V*>(p);
     }
 }
-template <typename T, int VEC, bool ANY> __device__ __forceinline__ void st_px(T* p, const typename Pack<T, VEC>::type& v)
+template <typename T, int VEC> __device__ __forceinline__ void st_px(T* p, const typename Pack<T, VEC>::type& v)
 {
-    typedef typename PxMem<T, VEC, ANY>::type M;
-    if constexpr (ANY) *reinterpret_cast<M*>(p) = __builtin_bit_cast(uintx2, v);
+    typedef typename PxMem<T, VEC>::type M;
+    if constexpr (sizeof(T) == 2 && VEC > 1) *reinterpret_cast<M*>(p) = __builtin_bit_cast(uintx2, v);
     else *reinterpret_cast<M*>(p) = v;
 }
 
@@ -203,10 +203,9 @@ __global__ __launch_bounds__(256) void detect_kernel(const T* __restrict__ x, T*
 // PLX = 16 (one pixel per lane only): 16 instead of 64 pixel lanes per workgroup, for maps with so
 // few pixels that 64-pixel workgroups would leave most compute units idle; such a workgroup owns a
 // quarter of a 64-pixel word of the bit map and stores it as a half word.
-// ANY (bfloat16, several pixels per lane): planes of any size and alignment.
 // SH: the layer keeps a channel-last shadow of its state (S2), C == CS*CPT, and channel q of group g is
 // g*CPT + q instead of g + q*CS, so that a lane's channels are neighbours in the shadow.
-template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false, bool ANY = sizeof(T) == 2 && (VEC > 1)>
+template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false>
 __global__ __launch_bounds__((PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS)
 void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2, uint64_t* __restrict__ mbits0,
                        int* __restrict__ ctl, int C, int P, int nwords, float tau, int flags)
@@ -229,7 +228,8 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
     // (p0 .. P - 1) instead, of which only those from pw on are its own.
     const long pw = ((long)blockIdx.x * PL + pl) * VEC;
     const bool valid = pw < P;
-    const int over = ANY && valid && pw + VEC > P ? (int)(pw + VEC - P) : 0;
+    constexpr bool RAGGED = sizeof(T) == 2 && VEC > 1;      // (float32 takes several pixels per lane only where P is a multiple)
+    const int over = RAGGED && valid && pw + VEC > P ? (int)(pw + VEC - P) : 0;
     const long p0 = pw - over;
     const unsigned own = valid ? (ALL << over) & ALL : 0u;
 
@@ -240,7 +240,7 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
 #pragma unroll
             for (int q = 0; q < CPT; ++q) {
                 const int c = SH ? g * CPT + q : g + q * CS;
-                if (c < C) xv[q] = ld_px<T, VEC, ANY, false>(x + (size_t)c * P + p0);
+                if (c < C) xv[q] = ld_px<T, VEC, false>(x + (size_t)c * P + p0);
             }
             // (first frame only.  Without this wait the compiler assumes these loads may still be in flight
             // in the other branch, and waits there between loads.)
@@ -252,8 +252,8 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
                 const int c = SH ? g * CPT + q : g + q * CS;
                 if (c < C) {
                     const size_t off = (size_t)c * P + p0;
-                    xv[q] = ld_px<T, VEC, ANY, true>(x + off);
-                    sv[q] = (flags & DET_STREAM_STATE) ? ld_px<T, VEC, ANY, true>(S + off) : ld_px<T, VEC, ANY, false>(S + off);
+                    xv[q] = ld_px<T, VEC, true>(x + off);
+                    sv[q] = (flags & DET_STREAM_STATE) ? ld_px<T, VEC, true>(S + off) : ld_px<T, VEC, false>(S + off);
                 }
             }
             // every load is issued before the first compare waits for one: the kernel lives on loads in flight
@@ -327,7 +327,7 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
                 const size_t off = (size_t)c * P + p0;
                 const T* xe = reinterpret_cast<const T*>(&xv[q]);
                 if (upd == ALL) {
-                    st_px<T, VEC, ANY>(S + off, xv[q]);
+                    st_px<T, VEC>(S + off, xv[q]);
                 } else {
 #pragma unroll
                     for (int v = 0; v < VEC; ++v)
@@ -561,14 +561,6 @@ void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int P
     const unsigned grid = (unsigned)((P + px_per_block - 1) / px_per_block);
     if constexpr (CS >= 4 && (CPT * sizeof(T)) % 16 == 0) {
         // (launch_t only passes a shadow on when the variant's registers hold exactly C channels)
-        // (128 bfloat16 channels, whose aligned planes the unaligned loads read 3 % more slowly: 173 against 167 us at 1080p; with 64
-        // channels they are the faster ones at any alignment, 73 against 85 us)
-        if constexpr (sizeof(T) == 2 && VEC == 4 && CS == 16)
-            if (S2 != nullptr && C == CS * CPT && P % 4 == 0 && (uintptr_t)x % 8 == 0 && (uintptr_t)S % 8 == 0) {
-                CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX, true, false>), dim3(grid), dim3(PL * CS), st, tm, x, S, S2, mbits,
-                          ctl, C, P, (P + 63) / 64, tau, flags);
-                return;
-            }
         if (S2 != nullptr && C == CS * CPT) {
             CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX, true>), dim3(grid), dim3(PL * CS), st, tm, x, S, S2, mbits,
                       ctl, C, P, (P + 63) / 64, tau, flags);
