@@ -30,6 +30,7 @@
 // float32 from the state and the unsplit filter matrix (exact_dot), so that infinities and NaNs come out as they do
 // in float32 arithmetic.
 #include "cb_fused.h"
+#include "cb_cl_rules.h"
 
 #include <type_traits>
 
@@ -92,10 +93,6 @@ static_assert(3 * CL_LDS_F32 <= 163840 && cl_lds<float>(64) <= CL_LDS_F32 && cl_
               4 * CL_LDS_BF16 <= 163840 && cl_lds<uint16_t>(64) <= CL_LDS_BF16 && cl_lds<uint16_t>(32) <= CL_LDS_BF16 &&
               cl_lds<uint16_t>(16) <= CL_LDS_BF16 && cl_lds<float>(16, 4) <= CL_LDS_F32 && cl_lds<uint16_t>(16, 4) <= CL_LDS_BF16,
               "the widest tile takes the most LDS");
-
-// Divisions by layer constants.  q / Wo = q * inv_wo >> 42, exact while q * Wo < 2^42, which Wo < 4096 makes sure of (0:
-// divide); tap / kw = tap * inv_kw >> 16 for the few taps there are.
-struct ClDiv { unsigned long long inv_wo; unsigned inv_kw; };
 
 template <typename T, int WGM, int WGN, int TM, int TN, int WGK = 1>
 __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, const T* __restrict__ S2,
@@ -198,7 +195,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
         for (int p = 0; p < NP; ++p) {
             const bool colv = q[p] >= 0;
             const int qq = colv ? q[p] : 0;
-            const int yo = div.inv_wo ? (int)(((unsigned long long)(unsigned)qq * div.inv_wo) >> 42) : qq / g.Wo;
+            const int yo = cl_row(div, qq, g.Wo);
             const int xo = qq - yo * g.Wo;
             const int y0 = yo * g.s - g.p, x0 = xo * g.s - g.p;
             // bits max(0, -y0) .. min(kh, H - y0) - 1
@@ -516,8 +513,7 @@ hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow
                            const void* KF, const float* KT, const float* bias, int relu, T* OUT, T* OUT2, hipStream_t st, Tm tm)
 {
     if (!plan.cl || (g.Cs & (g.Cs - 1)) != 0 || g.Cs < 16 / (int)sizeof(T) || g.bf16 != (sizeof(T) == 2)) return hipErrorInvalidValue;
-    const ClDiv div = {g.Wo < 4096 ? ((1ull << 42) + (unsigned)g.Wo - 1ull) / (unsigned)g.Wo : 0ull,
-                       (65536u + (unsigned)g.kw - 1u) / (unsigned)g.kw};
+    const ClDiv div = cl_div(g.Wo, g.Ho, g.kw);
 #define CB_CL(shape)                                                                                                     \
     CB_LAUNCH_LDS((fused_cl_kernel<T, shape>), dim3(1024), dim3(256), sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16, st, tm, g, \
                           div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)

@@ -299,6 +299,24 @@ def test_padded_shadow(geom, bf16, C):
         assert torch.equal(chained.state(), plain.state()) and torch.equal(a.view(torch.uint8), b.view(torch.uint8))
 
 
+# Output maps of more than 2^22 rows, where the channel-last kernel divides by the map's width (below, it multiplies by a
+# reciprocal whose product would leave 64 bits there): a signal of one column, and one of two.
+@pytest.mark.parametrize("bf16,C,W", [(False, 1, 1), (False, 3, 2), (True, 2, 1)])
+def test_more_than_2_to_22_output_rows(bf16, C, W):
+    H = (1 << 22) + 70
+    _say(f"tall map {H}x{W} C={C} bf16={bf16}")
+    rng = np.random.default_rng(C + W)
+    spec = syn.ConvSpec(C, 2, 3, 1, 1, weight=(rng.standard_normal((2, C, 3, 3)) * 0.3).astype(np.float32))
+    f0 = rng.uniform(0, 1, (C, H, W)).astype(np.float32)
+    f1 = f0.copy()
+    for y in (0, 12345, (1 << 22) - 2, (1 << 22) + 1, H - 1):
+        f1[:, y, -1] += np.float32(0.5)
+    p = Pair(spec, H, W, bf16=bf16, backend=2)
+    _, n = p.step(f0, 0.02, tag="tall map full update")
+    assert n == H * W
+    p.step(f1, 0.02, tag="tall map frame 1")
+
+
 # bfloat16 change detection takes four pixels per lane at any alignment from 32 768 pixels on.  Planes of 4n + 1 .. 3 pixels, the
 # last lane's first pixel at the start of a workgroup (256 or 1024 pixels) or inside one; every number of channel groups; frames
 # that start one element off a word; full, closed-loop and feed-forward updates.
