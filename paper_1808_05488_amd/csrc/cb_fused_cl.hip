@@ -27,7 +27,7 @@
 // whole layers, before -> now: 64 -> 64 3x3 4.4e-7 -> 3.6e-7, 128 -> 128 3x3 5.7e-7 -> 4.8e-7, 256 -> 256 3x3 8.1e-7 ->
 // 7.0e-7.  The terms of an infinity or a NaN, and of a value that rounds up to infinity, do not add up to it; any
 // such operand makes the accumulated sum non-finite, and the epilogue recomputes every non-finite sum in plain
-// float32 from the state and the unsplit filter matrix (exact_dot), so that infinities and NaNs come out as they do
+// float32 from the state and the unsplit filter matrix (exact_tiles), so that infinities and NaNs come out as they do
 // in float32 arithmetic.
 #include "cb_fused.h"
 #include "cb_cl_rules.h"
@@ -54,23 +54,86 @@ __device__ __forceinline__ void split2(float a, float b, unsigned& h, unsigned& 
     l = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
 }
 
-// One output in plain float32 arithmetic: the receptive field of listed pixel q times filter row m (KT: the
-// filter matrix transposed, row (c*kh + j)*kw + i).  Only for sums that came out non-finite.
-__device__ __forceinline__ float exact_dot(const Geom& g, const float* __restrict__ S2, const float* __restrict__ KT, int q, int m)
+// bits max(0, -o) .. min(k, size - o) - 1: which of a filter's k rows (columns), the first at o, lie inside the image
+__device__ __forceinline__ unsigned taps_within(int o, int k, int size)
 {
-    const int yo = q / g.Wo, xo = q - yo * g.Wo;
-    const int y0 = yo * g.s - g.p, x0 = xo * g.s - g.p;
-    const int kk = g.kh * g.kw;
-    float v = 0.f;
-    for (int j = 0; j < g.kh; ++j)
-        for (int i = 0; i < g.kw; ++i) {
-            const bool in = (unsigned)(y0 + j) < (unsigned)g.H && (unsigned)(x0 + i) < (unsigned)g.W;
-            const float* px = S2 + (in ? ((size_t)(y0 + j) * g.W + (x0 + i)) * g.Cs : 0);
-            const float* kt = KT + (size_t)(j * g.kw + i) * g.Opad + m;
-            // (a padding tap is a zero that takes part: zero times an infinite filter value is no number)
-            for (int c = 0; c < g.C; ++c) v = fmaf(in ? px[c] : 0.f, kt[(size_t)c * kk * g.Opad], v);
+    const int lo = o < 0 ? -o : 0, hi = size - o < k ? size - o : k;
+    return hi > lo ? ((1u << hi) - 1u) & ~((1u << lo) - 1u) : 0u;
+}
+
+// Sums whose split came out non-finite, in plain float32: TM 16 x 16 tiles of outputs on v_mfma_f32_16x16x4_f32, lane l16 =
+// listed pixel q (-1: none) and filter row m + 16 * a (the wavefront's row tile at + a of krsrc).  A lane holds eight
+// consecutive k' of a k-group: of the shadow as they are, of the filter matrix as the sum of its terms, which is the
+// filter value again; where it is not finite the value itself is fetched (KT: the filter matrix transposed, row (c*kh + j)*kw + i).
+// A padding tap is a zero that takes part: zero times an infinite filter value is no number.
+// Bound by the latency of its loads (few such sums) or the float32 matrix instruction (many).  Full updates, us, finite / one NaN /
+// every value infinite: 64 -> 64, 3x3, 480x640 227 / 258 / 669, 256 -> 256, 3x3, 92x164 120 / 173 / 410.  A lane that walks K by itself
+// for each of its sums took 547 / 28 100 and 2 606 / 16 960 for the latter two; a kernel on the float32 instruction throughout 330 and 180 for each.
+template <int TM>
+__device__ __forceinline__ void exact_tiles(const Geom& g, const ClDiv& div, const __amdgpu_buffer_rsrc_t srsrc, const __amdgpu_buffer_rsrc_t krsrc,
+                                            const float* __restrict__ KT, int nkg, int at, int lane, int q, int m, floatx4 (&sum)[TM])
+{
+    constexpr int U = 2;                         // k-groups in flight (nkg is even)
+    const int lq = lane >> 4;
+    const int lc = 31 - __builtin_clz((unsigned)g.Cs);
+    const unsigned taps = (unsigned)(g.kh * g.kw);
+    const int qq = q < 0 ? 0 : q;
+    const int yo = cl_row(div, qq, g.Wo);
+    const int y0 = yo * g.s - g.p, x0 = (qq - yo * g.Wo) * g.s - g.p;
+    const unsigned okr = q < 0 ? 0u : taps_within(y0, g.kh, g.H), okc = taps_within(x0, g.kw, g.W);
+    const unsigned base = (unsigned)(y0 * g.W + x0) << lc;
+#pragma unroll
+    for (int a = 0; a < TM; ++a) sum[a] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int kg = 0; kg < nkg; kg += U) {
+        uint4 b[U][2], w[U][TM][3];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const unsigned k = (unsigned)(32 * (kg + u) + 8 * lq + 4 * h), tap = k >> lc;
+                const unsigned j = (tap * div.inv_kw) >> 16, i = tap - j * (unsigned)g.kw;
+                const bool in = (((okr >> (j < 31u ? j : 31u)) & (okc >> i)) & 1u) != 0u;
+                const unsigned off = (base + ((j * (unsigned)g.W + i) << lc) + (k & (unsigned)(g.Cs - 1))) * 4u;
+                b[u][h] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(srsrc, (int)(in ? off : 0xFFFFFFF0u), 0, 0));
+            }
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    w[u][a][e] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                        krsrc, lane * 16 + e * 1024, (int)((unsigned)((at + a) * nkg + kg + u) * 3072u), 0));
         }
-    return v;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = __uint_as_float(reinterpret_cast<const unsigned*>(&b[u][e >> 2])[e & 3]);
+#pragma unroll
+            for (int a = 0; a < TM; ++a) {
+                float v[8];
+                bool odd = false;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    auto term = [&](int t) {
+                        const unsigned p = reinterpret_cast<const unsigned*>(&w[u][a][t])[e >> 1];
+                        return __uint_as_float(e & 1 ? p & 0xFFFF0000u : p << 16);
+                    };
+                    v[e] = term(0) + (term(1) + term(2));
+                    odd |= !(fabsf(v[e]) < __builtin_inff());
+                }
+                if (__ballot(odd)) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const unsigned k = (unsigned)(32 * (kg + u) + 8 * lq + e), tap = k >> lc, c = k & (unsigned)(g.Cs - 1);
+                        if (!(fabsf(v[e]) < __builtin_inff())) v[e] = KT[((size_t)c * taps + tap) * g.Opad + m + 16 * a];
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sum[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e], x[e], sum[a], 0, 0, 0);
+            }
+        }
+    }
 }
 
 // k-groups per stage for a tile of bn columns (float32: 1 / 2 / 4 from 128 / 64 / 32 columns on).  Longer stages mean fewer
@@ -198,13 +261,8 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             const int yo = cl_row(div, qq, g.Wo);
             const int xo = qq - yo * g.Wo;
             const int y0 = yo * g.s - g.p, x0 = xo * g.s - g.p;
-            // bits max(0, -y0) .. min(kh, H - y0) - 1
-            auto inside = [](int o, int k, int size) -> unsigned {
-                const int lo = o < 0 ? -o : 0, hi = size - o < k ? size - o : k;
-                return hi > lo ? ((1u << hi) - 1u) & ~((1u << lo) - 1u) : 0u;
-            };
-            okr[p] = colv ? inside(y0, g.kh, g.H) : 0u;
-            okc[p] = inside(x0, g.kw, g.W);
+            okr[p] = colv ? taps_within(y0, g.kh, g.H) : 0u;
+            okc[p] = taps_within(x0, g.kw, g.W);
             base[p] = (((unsigned)(y0 * g.W + x0) << lc) + (unsigned)cl) * ESZ;
         }
 
@@ -397,17 +455,26 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             else rows(false);
         }
         if constexpr (F32) {
-            while (bad) {
-                const int e = __builtin_ctzll(bad);
-                bad &= bad - 1ull;
-                const int b = e / (4 * TM), a = (e >> 2) % TM, r = e & 3;
-                const int qn = qs[(wn * TN + b) * 16 + l16];
-                const int m = mw + a * 16 + lq * 4 + r;
-                float v = exact_dot(g, S2, KT, qn, m) + bias[m];
-                if (relu) v = v > 0.f ? v : 0.f;
-                OUT[(size_t)m * g.Po + qn] = v;
-                if (OUT2) OUT2[(size_t)qn * g.O + m] = v;
-            }
+            if (__ballot(bad != 0ull))
+#pragma unroll 1
+                for (int b = 0; b < TN; ++b) {
+                    const unsigned mine = (unsigned)(bad >> (4 * TM * b)) & ((1u << (4 * TM)) - 1u);
+                    if (!__ballot(mine != 0u)) continue;
+                    const int qn = qs[(wn * TN + b) * 16 + l16];
+                    floatx4 sum[TM];
+                    exact_tiles<TM>(g, div, srsrc, krsrc, KT, nkg, wm_s * TM, lane, qn, mw + l16, sum);
+#pragma unroll
+                    for (int a = 0; a < TM; ++a)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (mine & (1u << (4 * a + r))) {
+                                const int m = mw + a * 16 + lq * 4 + r;
+                                float v = sum[a][r] + bias[m];
+                                if (relu) v = v > 0.f ? v : 0.f;
+                                OUT[(size_t)m * g.Po + qn] = v;
+                                if (OUT2) OUT2[(size_t)qn * g.O + m] = v;
+                            }
+                }
         }
     }
 }

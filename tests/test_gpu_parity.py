@@ -362,7 +362,10 @@ def test_channel_last_tile_shapes(geom, bf16):
 # The float32 channel-last kernel multiplies bfloat16 terms of its operands.  Values without such a decomposition
 # (infinities, NaN, finite values that round up to infinity in bfloat16) have to come out as in float32 arithmetic.
 @pytest.mark.parametrize("where", ["input", "weight"])
-@pytest.mark.parametrize("geom", [(16, 12, 3, 1, 9, 11), (32, 70, 3, 2, 20, 23), (64, 64, 1, 1, 30, 31)])
+@pytest.mark.parametrize("geom", [(16, 12, 3, 1, 9, 11), (32, 70, 3, 2, 20, 23), (64, 64, 1, 1, 30, 31),
+                                  # first layers (padded pixels), wide tiles of every range of output channels
+                                  (3, 16, 7, 1, 61, 67), (4, 33, 3, 2, 45, 52), (32, 13, 1, 1, 241, 251), (32, 30, 1, 1, 183, 179),
+                                  (32, 60, 1, 1, 213, 217), (32, 140, 1, 1, 97, 93), (64, 100, 3, 1, 97, 93)])
 def test_channel_last_special_values(geom, where):
     C, O, k, s, H, W = geom
     _say(f"special values {geom} {where}")
@@ -391,6 +394,38 @@ def test_channel_last_special_values(geom, where):
         mag = torch.nn.functional.conv2d(torch.from_numpy(x)[None].double().abs(), torch.from_numpy(w).double().abs(),
                                          torch.from_numpy(b).double().abs(), s, k // 2)[0].numpy()
     assert (np.abs(got[fin] - ref[fin]) <= (C * k * k + 1) * 2.0 ** -24 * mag[fin]).all()
+
+
+# ... at a cost that stays within a small factor of a finite frame's.  Measured: one NaN 1.4, every value infinite 3.4 times the full
+# update of a finite frame (a lane that walks K by itself instead of a wavefront computing whole tiles: 21 and 138).  The bounds
+# leave a factor of three for what else the machine does.
+def test_cost_of_non_finite_sums():
+    C = O = 256
+    H, W = 92, 164
+    _say("cost of non-finite sums")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    x = torch.rand((C, H, W), generator=g, device="cuda")
+    one = x.clone()
+    one[1, H // 2, W // 2] = float("nan")
+    w = torch.randn((O, C, 3, 3), generator=g, device="cuda") * 0.02
+    L = cb.Layer(w, None, 1, 1, H, W, True, backend=2)
+
+    def cost(frame):
+        best = 1e9
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            L.reset()
+            a.record()
+            L.process_frame(frame, 0.02)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    finite = cost(x)
+    assert cost(one) < 4.5 * finite
+    assert cost(torch.full_like(x, float("inf"))) < 10 * finite
 
 
 @pytest.mark.parametrize("bf16", [False, True])
