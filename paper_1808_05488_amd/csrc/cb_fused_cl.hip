@@ -18,16 +18,19 @@
 // float32 runs on the bfloat16 matrix cores as well.  A float32 product on v_mfma_f32_16x16x4_f32 costs sixteen
 // times the matrix-core time of a bfloat16 one, and float32 layers were bound by exactly that (256 -> 256, 3x3, every
 // output of 92x164: 166 us with or without the gather, the filter loads and the output stores).  Both operands are
-// split into three bfloat16 terms, x = h + m + l, each the round-to-nearest bfloat16 of what the terms before it
-// left over.  24 significant bits fit 3 x 8, so the split is exact, and the six products down to 2^-16 of the
+// split into three bfloat16 terms, x * 2^24 = h + m + l, each the round-to-nearest bfloat16 of what the terms before it
+// left over.  24 significant bits fit 3 x 8, and 2^24 in front keeps the last bit of float32's smallest numbers (2^-149) inside
+// bfloat16's normal range, so the split is exact for every value below 2^104.  The six products down to 2^-16 of the
 // leading one,
 //     h*h + (h*m + m*h) + (h*l + m*m + l*h),
 // are accumulated in float32: 6/16 of the matrix-core time.  What is left out (m*l, l*m, l*l) is below 2^-24 of the
 // product; the sum over K is rounded 6 times per 32 products instead of up to 32 times.  Error against float64 over
 // whole layers, before -> now: 64 -> 64 3x3 4.4e-7 -> 3.6e-7, 128 -> 128 3x3 5.7e-7 -> 4.8e-7, 256 -> 256 3x3 8.1e-7 ->
-// 7.0e-7.  The terms of an infinity or a NaN, and of a value that rounds up to infinity, do not add up to it; any
-// such operand makes the accumulated sum non-finite, and the epilogue recomputes every non-finite sum in plain
-// float32 from the state and the unsplit filter matrix (exact_tiles), so that infinities and NaNs come out as they do
+// 7.0e-7.  The epilogue takes the 2^48 out again, exactly, together with the bias.  (Without the 2^24, values below 2^-110 lost
+// their last term: 4e-6 of the result at 2^-116, 1e-3 at 2^-124.)
+// The terms of an infinity, a NaN or a value of 2^104 and more do not add up to it, and sums beyond 2^80 overflow; any
+// such makes the accumulated sum non-finite, and the epilogue recomputes every non-finite sum in plain
+// float32 from the state and the filter matrix (exact_tiles), so that infinities, NaNs and large numbers come out as they do
 // in float32 arithmetic.
 #include "cb_fused.h"
 #include "cb_cl_rules.h"
@@ -42,9 +45,14 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 
-// two neighbouring values -> their three bfloat16 terms, packed
+// in front of both operands of a float32 product, and what takes them out of a sum of products
+constexpr float SPLIT_SCALE = 0x1p24f, SPLIT_UNSCALE = 0x1p-48f;
+
+// two neighbouring values (times SPLIT_SCALE) -> their three bfloat16 terms, packed
 __device__ __forceinline__ void split2(float a, float b, unsigned& h, unsigned& m, unsigned& l)
 {
+    a *= SPLIT_SCALE;
+    b *= SPLIT_SCALE;
     h = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
     a -= __uint_as_float(h << 16);
     b -= __uint_as_float(h & 0xFFFF0000u);
@@ -63,7 +71,7 @@ __device__ __forceinline__ unsigned taps_within(int o, int k, int size)
 
 // Sums whose split came out non-finite, in plain float32: TM 16 x 16 tiles of outputs on v_mfma_f32_16x16x4_f32, lane l16 =
 // listed pixel q (-1: none) and filter row m + 16 * a (the wavefront's row tile at + a of krsrc).  A lane holds eight
-// consecutive k' of a k-group: of the shadow as they are, of the filter matrix as the sum of its terms, which is the
+// consecutive k' of a k-group: of the shadow as they are, of the filter matrix as the sum of its terms, which is the scaled
 // filter value again; where it is not finite the value itself is fetched (KT: the filter matrix transposed, row (c*kh + j)*kw + i).
 // A padding tap is a zero that takes part: zero times an infinite filter value is no number.
 // Bound by the latency of its loads (few such sums) or the float32 matrix instruction (many).  Full updates, us, finite / one NaN /
@@ -119,7 +127,7 @@ __device__ __forceinline__ void exact_tiles(const Geom& g, const ClDiv& div, con
                         const unsigned p = reinterpret_cast<const unsigned*>(&w[u][a][t])[e >> 1];
                         return __uint_as_float(e & 1 ? p & 0xFFFF0000u : p << 16);
                     };
-                    v[e] = term(0) + (term(1) + term(2));
+                    v[e] = (term(0) + (term(1) + term(2))) * (1.f / SPLIT_SCALE);
                     odd |= !(fabsf(v[e]) < __builtin_inff());
                 }
                 if (__ballot(odd)) {
@@ -441,7 +449,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                     float v4[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        float v = acc[a][b][r] + bv[a][r];
+                        float v = F32 ? fmaf(acc[a][b][r], SPLIT_UNSCALE, bv[a][r]) : acc[a][b][r] + bv[a][r];
                         if (F32 && !(fabsf(acc[a][b][r]) < __builtin_inff()) && (all || mb + r < g.O)) bad |= 1ull << ((b * TM + a) * 4 + r);
                         if (relu) v = v > 0.f ? v : 0.f;
                         if (all || mb + r < g.O) st_out(o + (size_t)(a * 16 + r) * g.Po, v);
@@ -479,7 +487,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     }
 }
 
-// Filter matrix of the float32 kernel: for every 16-row tile and k-group of 32, three fragments (terms h, m, l) of 64 x 16
+// Filter matrix of the float32 kernel: for every 16-row tile and k-group of 32, three fragments (terms h, m, l of the scaled value) of 64 x 16
 // bytes: lane's 8 values are K(m = mtile*16 + lane%16, k' = kgroup*32 + 8*(lane/16) + 0..7), k' = (j*kw + i)*Cs + c; zero
 // outside the filter matrix and for the channels c >= C of a padded pixel.
 __global__ __launch_bounds__(256) void pack_fused_split_kernel(Geom g, int Mt16, int KG, const float* __restrict__ w,

@@ -29,6 +29,14 @@ def assert_close(got: np.ndarray, ref: np.ndarray, bf16: bool, what: str = "out"
                              f"got {got.reshape(-1)[k]!r} ref {ref.reshape(-1)[k]!r}")
 
 
+def split_bound(K: int) -> float:
+    """Bound on the relative 2-norm error of a float32 layer whose products run as six bfloat16 products of three-term
+    splits.  A sum is rounded six times per 32 products; each rounding is at most 2^-24 of a partial sum, the partial sums of
+    zero-mean data are at most of the whole sum's size, and the roundings are independent: 2^-24 * sqrt(6 K / 32).  (Measured
+    with one chain of sums: 3.6e-7 of 6.2e-7 at K = 576, 7.0e-7 of 1.2e-6 at K = 2 304.)"""
+    return 2.0 ** -24 * float(np.sqrt(max(6.0 * K / 32.0, 1.0)))
+
+
 def to_dev(a: np.ndarray, bf16: bool) -> torch.Tensor:
     t = torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
     return t.to(torch.bfloat16).contiguous() if bf16 else t

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 if torch.cuda.is_available():
     import paper_1808_05488_amd as cb
     from oracle import cb_oracle as orc
-    from parity import Pair, assert_close, to_dev, to_host, prep
+    from parity import Pair, assert_close, split_bound, to_dev, to_host, prep
 
 
 def _say(msg):
@@ -394,6 +394,28 @@ def test_channel_last_special_values(geom, where):
         mag = torch.nn.functional.conv2d(torch.from_numpy(x)[None].double().abs(), torch.from_numpy(w).double().abs(),
                                          torch.from_numpy(b).double().abs(), s, k // 2)[0].numpy()
     assert (np.abs(got[fin] - ref[fin]) <= (C * k * k + 1) * 2.0 ** -24 * mag[fin]).all()
+
+
+# Accuracy of the float32 channel-last kernel on whole layers against float64, over the whole range of float32: K shared by the wavefronts
+# (few pixels) and wide tiles, padded first layers, operands so small or so large that a term of their split would leave bfloat16's
+# range, products down to float32's smallest numbers (each then rounded to a multiple of 2^-149).
+@pytest.mark.parametrize("scale", [(0, 0), (-124, 0), (0, -124), (-124, 100), (100, -124), (-140, 20), (-75, -60), (60, 40), (100, 20)])
+@pytest.mark.parametrize("geom", [(64, 64, 3, 17, 19), (64, 64, 3, 143, 141), (256, 100, 3, 12, 13), (256, 130, 3, 60, 61), (3, 16, 7, 61, 67),
+                                  (32, 24, 1, 183, 179)])
+def test_float32_accuracy(geom, scale):
+    C, O, k, H, W = geom
+    _say(f"float32 accuracy {geom} scale={scale}")
+    g = torch.Generator()
+    g.manual_seed(C + O)
+    K = C * k * k
+    x = torch.randn((C, H, W), generator=g) * 2.0 ** scale[0]
+    w = torch.randn((O, C, k, k), generator=g) / K ** 0.5 * 2.0 ** scale[1]
+    y = cb.Layer(w.cuda(), None, 1, k // 2, H, W, False, backend=2).process_frame(x.cuda(), 0.0).double().cpu()
+    ref = torch.nn.functional.conv2d(x[None].double(), w.double(), None, 1, k // 2)[0]
+    # (sums beyond 2^80 are those of the float32 instruction: a rounding per product)
+    bound = split_bound(K) if scale[0] + scale[1] < 80 else 2.0 ** -24 * K ** 0.5
+    assert torch.isfinite(y).all()
+    assert (y - ref).norm() <= bound * ref.norm() + 2.0 ** -149 * y.numel() ** 0.5
 
 
 # ... at a cost that stays within a small factor of a finite frame's.  Measured: one NaN 1.4, every value infinite 3.4 times the full
