@@ -102,9 +102,7 @@ StateLayout state_layout(const cb_layer_desc* d, const cb::Geom& g)
     // (the input state, or the cached output when a CB_PROPAGATE consumer reads it)
     size_t o = 256;
     L.S = o;      o += d->mode == CB_PROPAGATE ? 0 : align256((size_t)g.C * g.P * b);
-    // (first layers: 16 bytes a pixel whatever the mode, so that a first layer's buffer serves both ways of detecting)
-    const bool padded = use_fused(d, g) && d->mode != CB_PROPAGATE && cb::fused_padded(g);
-    L.S2 = o;     o += use_shadow(d, g) || padded ? align256((size_t)g.Cs * g.P * b) : 0;
+    L.S2 = o;     o += use_shadow(d, g) ? align256((size_t)g.Cs * g.P * b) : 0;
     L.OUT = o;    o += align256((size_t)g.O * g.Po * b);
     L.OUT2 = o;   o += d->keep_output_channel_last ? align256((size_t)g.O * g.Po * b) : 0;
     L.mbits = o;  o += align256(((size_t)(g.P + 63) / 64 + 4) * 16);  // two maps, word-interleaved: frames alternate between them

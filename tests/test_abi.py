@@ -62,20 +62,29 @@ def test_workspace_sizes_follow_the_geometry():
 
 
 def test_which_layers_keep_a_channel_last_shadow_of_the_state():
-    """Closed-loop layers on the fused back end with a power-of-two channel count from 16 (float32) / 32 (bfloat16) on
-    keep a second, pixel-major copy of the input state: one more C*P*b bytes."""
+    """Closed-loop layers on the fused back end keep a second, pixel-major copy of the input state: C*P*b more bytes with a
+    power-of-two channel count from 16 (float32) / 32 (bfloat16) on, 16*P with up to 4 / 8 channels (pixels padded to 16 bytes),
+    none with other counts.  Feed-forward layers keep none."""
     def state_bytes(C, H=120, W=160, **kw):
         return cb.cb_layer_workspace_bytes(cb.make_desc(C, 32, 3, 3, 1, 1, H, W, backend=cb.CB_BACKEND_FUSED, **kw))[0]
     P = 120 * 160
     for C in (16, 32, 64, 128, 256, 512):
         extra = state_bytes(C) - state_bytes(C, mode=cb.CB_FEED_FORWARD)
         assert C * P * 4 <= extra < C * P * 4 + 4096, C
-    for C in (3, 8, 24, 48, 96):
+    for dtype, few in ((cb.CB_F32, (1, 3, 4)), (cb.CB_BF16, (1, 3, 5, 8))):
+        for C in few:
+            extra = state_bytes(C, dtype=dtype) - state_bytes(C, dtype=dtype, mode=cb.CB_FEED_FORWARD)
+            assert extra == P * 16, (C, dtype)
+    for C in (5, 8, 24, 48, 96):
         assert state_bytes(C) == state_bytes(C, mode=cb.CB_FEED_FORWARD), C
+    for C in (9, 16, 24, 48, 96):
+        assert state_bytes(C, dtype=cb.CB_BF16) == state_bytes(C, dtype=cb.CB_BF16, mode=cb.CB_FEED_FORWARD), C
+    # a feed-forward first layer holds its state, output, maps and index list, and its filters: nothing else
+    first = state_bytes(3, 1080, 1920, mode=cb.CB_FEED_FORWARD)
+    assert first < 1080 * 1920 * ((3 + 32) * 4 + 4 + 2 + 1) + (1 << 20)
     # bfloat16 layers from 32 channels on (half the bytes); layers on the explicit back end keep none
     extra = state_bytes(64, dtype=cb.CB_BF16) - state_bytes(64, dtype=cb.CB_BF16, mode=cb.CB_FEED_FORWARD)
     assert 64 * P * 2 <= extra < 64 * P * 2 + 4096
-    assert state_bytes(16, dtype=cb.CB_BF16) == state_bytes(16, dtype=cb.CB_BF16, mode=cb.CB_FEED_FORWARD)
     de = [cb.cb_layer_workspace_bytes(cb.make_desc(64, 32, 3, 3, 1, 1, 120, 160, backend=cb.CB_BACKEND_EXPLICIT, mode=m))[0]
           for m in (cb.CB_CLOSED_LOOP, cb.CB_FEED_FORWARD)]
     assert de[0] == de[1]
