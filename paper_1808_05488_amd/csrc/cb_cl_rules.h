@@ -2,6 +2,8 @@
 // from host code and kernels alike.
 #pragma once
 
+#include <type_traits>
+
 #ifdef __HIPCC__
 #define CB_HD __host__ __device__ __forceinline__
 #else
@@ -24,5 +26,69 @@ inline ClDiv cl_div(int Wo, int Ho, int kw)
 }
 
 CB_HD int cl_row(const ClDiv& d, int q, int Wo) { return d.inv_wo ? (int)(((unsigned long long)(unsigned)q * d.inv_wo) >> 42) : q / Wo; }
+
+// Rows of the widest tile for O output channels, which names the kernel's instance.
+inline int cl_shape(int O) { return O <= 16 ? 16 : O <= 32 ? 32 : O <= 64 ? 64 : 128; }
+
+// Tiles (rows x columns) of instance `shape`: number 0 is 16 x 16 with the four wavefronts sharing K, the others follow.
+//   16: 16 x 64, 16 x 128    32: 32 x 32, 32 x 64, 32 x 128    64: 64 x 16, 64 x 32, 64 x 64    128: 64 x 16, 64 x 32, 128 x 32, 128 x 64
+CB_HD constexpr int cl_tiles(int shape) { return shape == 16 ? 3 : shape == 128 ? 5 : 4; }
+
+// Which tile finishes a frame first, in ns.  The kernel takes as long as the compute unit with the most tiles, and n tiles
+// on it take about max(latency of one, n * its share of a busy unit) beyond the launch; both grow with the k-groups of the
+// layer.  Fitted to every tile forced in turn (K = 288 to 12 544, 24 to 307 200 listed pixels, O = 8 to 512, both types):
+// the choice is within a few percent of the best tile.
+template <int BM, int BN> CB_HD unsigned cl_cost(int N, int O, unsigned nkg, unsigned l0, unsigned l1, unsigned c0, unsigned c1)
+{
+    const unsigned tiles = (((unsigned)N + BN - 1u) / BN) * (((unsigned)O + BM - 1u) / BM);
+    const unsigned lat = l0 + l1 * nkg, busy = (tiles + 255u) / 256u * (c0 + c1 * nkg);
+    return busy > lat ? busy : lat;
+}
+
+// run(number of the tile, a compile-time constant) for N listed pixels, O output channels, Cs channels of a pixel in the shadow,
+// taps of the filter, R values of a filter.  (A function that returns the number instead cost the kernel registers: 128 -> 128
+// bfloat16 at 1080p 453 -> 458 us.)
+template <bool F32, int SHAPE, typename FN> CB_HD void cl_tile(int N, int O, int Cs, int taps, int R, FN&& run)
+{
+    // (literal arguments, not a table: a table would be fetched from memory ahead of everything else)
+    const unsigned nkg = ((unsigned)(Cs * taps) + 31u) / 32u;
+#define CB_COST(bm, bn, a0, a1, a2, a3, b0, b1, b2, b3) \
+    (F32 ? cl_cost<bm, bn>(N, O, nkg, a0, a1, a2, a3) : cl_cost<bm, bn>(N, O, nkg, b0, b1, b2, b3))
+    // 16 x 16, the four wavefronts sharing K: four times the tiles of the others where few pixels are listed, a quarter of
+    // the serial chain (256 -> 8, 7x7, 3 322 pixels: 104 -> 43 us; 64 -> 9, 3x3: 8.7 -> 6.5 us)
+    // (filters beyond one XCD's 4 MB of L2 come in more slowly than its four wavefronts ask for them: 512 -> 512, 324 pixels
+    // 42 us, 33 us with 64 x 16)
+    const bool far = F32 && (unsigned long long)O * (unsigned)R > 700000ull;
+    const unsigned k = CB_COST(16, 16, 100, 94, 1260, (far ? 80 : 49), 200, 30, 870, 16);
+    if constexpr (SHAPE == 16) {
+        const unsigned a = CB_COST(16, 64, 0, 330, 1100, 222, 200, 110, 1000, 60), b = CB_COST(16, 128, 0, 700, 1300, 440, 300, 200, 1300, 110);
+        if (k <= a && k <= b) run(std::integral_constant<int, 0>());
+        else if (a <= b) run(std::integral_constant<int, 1>());
+        else run(std::integral_constant<int, 2>());
+    } else if constexpr (SHAPE == 32) {
+        const unsigned a = CB_COST(32, 32, 200, 230, 1250, 155, 200, 70, 850, 50), b = CB_COST(32, 64, 600, 390, 1200, 290, 400, 120, 800, 85),
+                       c = CB_COST(32, 128, 1000, 800, 1500, 550, 900, 220, 900, 130);
+        if (k <= a && k <= b && k <= c) run(std::integral_constant<int, 0>());
+        else if (a <= b && a <= c) run(std::integral_constant<int, 1>());
+        else if (b <= c) run(std::integral_constant<int, 2>());
+        else run(std::integral_constant<int, 3>());
+    } else if constexpr (SHAPE == 64) {
+        const unsigned a = CB_COST(64, 16, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, 1600, 310, 1400, 200, 400, 83, 1100, 48),
+                       c = CB_COST(64, 64, 1300, 530, 800, 395, 1000, 148, 800, 100);
+        if (k <= a && k <= b && k <= c) run(std::integral_constant<int, 0>());
+        else if (a <= b && a <= c) run(std::integral_constant<int, 1>());
+        else if (b <= c) run(std::integral_constant<int, 2>());
+        else run(std::integral_constant<int, 3>());
+    } else {
+        const unsigned a = CB_COST(64, 16, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, 1000, 300, 1400, 203, 400, 80, 1100, 47),
+                       c = CB_COST(128, 32, 0, 400, 1000, 320, 0, 115, 100, 96), d = CB_COST(128, 64, 900, 745, 2900, 510, 700, 205, 1000, 140),
+                       ab = a < b ? a : b, cd = c < d ? c : d;
+        if (k <= ab && k <= cd) run(std::integral_constant<int, 0>());
+        else if (ab <= cd) { if (a <= b) run(std::integral_constant<int, 1>()); else run(std::integral_constant<int, 2>()); }
+        else if (c <= d) run(std::integral_constant<int, 3>());
+        else run(std::integral_constant<int, 4>());
+    }
+#undef CB_COST
+}
 
 }  // namespace cb

@@ -517,17 +517,6 @@ __global__ __launch_bounds__(256) void pack_fused_split_kernel(Geom g, int Mt16,
     }
 }
 
-// Which tile finishes a frame first, in ns.  The kernel takes as long as the compute unit with the most tiles, and n tiles
-// on it take about max(latency of one, n * its share of a busy unit) beyond the launch; both grow with the k-groups of the
-// layer.  Fitted to every tile forced in turn (K = 288 to 12 544, 24 to 307 200 listed pixels, O = 8 to 512, both types):
-// the choice is within a few percent of the best tile.
-template <int BM, int BN> __device__ __forceinline__ unsigned cl_cost(int N, int O, unsigned nkg, unsigned l0, unsigned l1, unsigned c0, unsigned c1)
-{
-    const unsigned tiles = (((unsigned)N + BN - 1u) / BN) * (((unsigned)O + BM - 1u) / BM);
-    const unsigned lat = l0 + l1 * nkg, busy = (tiles + 255u) / 256u * (c0 + c1 * nkg);
-    return busy > lat ? busy : lat;
-}
-
 template <typename T, int SHAPE>
 // (wavefronts per SIMD: as many as the widest tile's registers allow.  They are worth more than wider tiles: bfloat16, O > 64
 // at 76 800 listed pixels 45 us with two, 40 us with four.)
@@ -540,46 +529,16 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(G
     const int N = *count;
     if (N <= 0) return;
 #define CB_BODY(...) fused_cl_body<T, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2)
-    constexpr bool F32 = sizeof(T) == 4;
-    // (literal arguments, not a table: a table would be fetched from memory ahead of everything else)
-    const unsigned nkg = ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u;
-#define CB_COST(bm, bn, a0, a1, a2, a3, b0, b1, b2, b3) \
-    (F32 ? cl_cost<bm, bn>(N, g.O, nkg, a0, a1, a2, a3) : cl_cost<bm, bn>(N, g.O, nkg, b0, b1, b2, b3))
-    // 16 x 16, the four wavefronts sharing K: four times the tiles of the others where few pixels are listed, a quarter of
-    // the serial chain (256 -> 8, 7x7, 3 322 pixels: 104 -> 43 us; 64 -> 9, 3x3: 8.7 -> 6.5 us)
-    // (filters beyond one XCD's 4 MB of L2 come in more slowly than its four wavefronts ask for them: 512 -> 512, 324 pixels
-    // 42 us, 33 us with 64 x 16)
-    const bool far = F32 && (unsigned long long)g.O * (unsigned)g.R > 700000ull;
-    const unsigned k = CB_COST(16, 16, 100, 94, 1260, (far ? 80 : 49), 200, 30, 870, 16);
-    if constexpr (SHAPE == 16) {
-        const unsigned a = CB_COST(16, 64, 0, 330, 1100, 222, 200, 110, 1000, 60), b = CB_COST(16, 128, 0, 700, 1300, 440, 300, 200, 1300, 110);
-        if (k <= a && k <= b) CB_BODY(1, 1, 1, 1, 4);
-        else if (a <= b) CB_BODY(1, 4, 1, 1);
-        else CB_BODY(1, 4, 1, 2);
-    } else if constexpr (SHAPE == 32) {
-        const unsigned a = CB_COST(32, 32, 200, 230, 1250, 155, 200, 70, 850, 50), b = CB_COST(32, 64, 600, 390, 1200, 290, 400, 120, 800, 85),
-                       c = CB_COST(32, 128, 1000, 800, 1500, 550, 900, 220, 900, 130);
-        if (k <= a && k <= b && k <= c) CB_BODY(1, 1, 1, 1, 4);
-        else if (a <= b && a <= c) CB_BODY(2, 2, 1, 1);
-        else if (b <= c) CB_BODY(2, 2, 1, 2);
-        else CB_BODY(2, 2, 1, 4);
-    } else if constexpr (SHAPE == 64) {
-        const unsigned a = CB_COST(64, 16, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, 1600, 310, 1400, 200, 400, 83, 1100, 48),
-                       c = CB_COST(64, 64, 1300, 530, 800, 395, 1000, 148, 800, 100);
-        if (k <= a && k <= b && k <= c) CB_BODY(1, 1, 1, 1, 4);
-        else if (a <= b && a <= c) CB_BODY(4, 1, 1, 1);
-        else if (b <= c) CB_BODY(4, 1, 1, 2);
-        else CB_BODY(4, 1, 1, 4);
-    } else {
-        const unsigned a = CB_COST(64, 16, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, 1000, 300, 1400, 203, 400, 80, 1100, 47),
-                       c = CB_COST(128, 32, 0, 400, 1000, 320, 0, 115, 100, 96), d = CB_COST(128, 64, 900, 745, 2900, 510, 700, 205, 1000, 140),
-                       ab = a < b ? a : b, cd = c < d ? c : d;
-        if (k <= ab && k <= cd) CB_BODY(1, 1, 1, 1, 4);
-        else if (ab <= cd) { if (a <= b) CB_BODY(4, 1, 1, 1); else CB_BODY(4, 1, 1, 2); }
-        else if (c <= d) CB_BODY(4, 1, 2, 2);
-        else CB_BODY(4, 1, 2, 4);
-    }
-#undef CB_COST
+    // (the tiles of cb_cl_rules.h)
+    cl_tile<sizeof(T) == 4, SHAPE>(N, g.O, g.Cs, g.kh * g.kw, g.R, [&](auto tile) __attribute__((always_inline)) {
+        constexpr int t = decltype(tile)::value;
+        static_assert(t < cl_tiles(SHAPE), "a tile of this instance");
+        if constexpr (t == 0) CB_BODY(1, 1, 1, 1, 4);
+        else if constexpr (SHAPE == 16) CB_BODY(1, 4, 1, t);
+        else if constexpr (SHAPE == 32) CB_BODY(2, 2, 1, 1 << (t - 1));
+        else if constexpr (SHAPE == 64 || t <= 2) CB_BODY(4, 1, 1, 1 << (t - 1));
+        else CB_BODY(4, 1, 2, 1 << (t - 2));
+    });
 #undef CB_BODY
 }
 
@@ -592,10 +551,12 @@ hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow
 #define CB_CL(shape)                                                                                                     \
     CB_LAUNCH_LDS((fused_cl_kernel<T, shape>), dim3(1024), dim3(256), sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16, st, tm, g, \
                           div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)
-    if (g.O <= 16)      CB_CL(16);
-    else if (g.O <= 32) CB_CL(32);
-    else if (g.O <= 64) CB_CL(64);
-    else                CB_CL(128);
+    switch (cl_shape(g.O)) {
+        case 16: CB_CL(16); break;
+        case 32: CB_CL(32); break;
+        case 64: CB_CL(64); break;
+        default: CB_CL(128);
+    }
 #undef CB_CL
     return hipGetLastError();
 }

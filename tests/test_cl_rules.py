@@ -6,12 +6,29 @@ import subprocess
 
 import pytest
 
+from cl_tiles import TILE_CASES
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1808_05488_amd", "csrc")
 
 SOURCE = r"""
 #include "cb_cl_rules.h"
 extern "C" int row(int q, int Wo, int Ho, int kw) { return cb::cl_row(cb::cl_div(Wo, Ho, kw), q, Wo); }
 extern "C" unsigned inv_kw(int kw) { return cb::cl_div(1, 1, kw).inv_kw; }
+template <bool F32> int tile(int N, int O, int Cs, int taps, int R)
+{
+    int t = -1;
+    auto run = [&](auto tile) { t = decltype(tile)::value; };
+    switch (cb::cl_shape(O)) {
+        case 16: cb::cl_tile<F32, 16>(N, O, Cs, taps, R, run); break;
+        case 32: cb::cl_tile<F32, 32>(N, O, Cs, taps, R, run); break;
+        case 64: cb::cl_tile<F32, 64>(N, O, Cs, taps, R, run); break;
+        default: cb::cl_tile<F32, 128>(N, O, Cs, taps, R, run);
+    }
+    return t;
+}
+extern "C" int tile(int bf16, int N, int O, int Cs, int taps, int R) { return bf16 ? tile<false>(N, O, Cs, taps, R) : tile<true>(N, O, Cs, taps, R); }
+extern "C" int shape(int O) { return cb::cl_shape(O); }
+extern "C" int tiles(int shape) { return cb::cl_tiles(shape); }
 """
 
 
@@ -42,3 +59,15 @@ def test_filter_row_of_a_tap(rules):
         inv = rules.inv_kw(kw)
         for tap in range(31 * kw + 256):
             assert (tap * inv) >> 16 == tap // kw, (kw, tap)
+
+
+def test_tile_cases_cover_every_tile(rules):
+    """Each layer picks the tile it stands for, and together they pick every tile of every instance: a change of the rule
+    that moves one shows up here."""
+    for shape, tile, bf16, c, o, k, h, w in TILE_CASES:
+        pixel = 16 // (2 if bf16 else 4)
+        cs = pixel if c <= pixel else c
+        assert rules.shape(o) == shape
+        assert rules.tile(bf16, h * w, o, cs, k * k, c * k * k) == tile, (shape, tile, bf16, c, o, k, h, w)
+    every = {(s, t, b) for s in (16, 32, 64, 128) for t in range(rules.tiles(s)) for b in (False, True)}
+    assert {(s, t, b) for s, t, b, *_ in TILE_CASES} == every

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import synth_inputs as syn
+from cl_tiles import TILE_CASES
 
 pytestmark = pytest.mark.gpu
 
@@ -74,6 +75,19 @@ def test_geometry_sweep(geom, bf16, backend):
         assert n == p.o.Ho * p.o.Wo
 
 
+# The same geometries in feed-forward mode: such layers keep no shadow and run the channel-first fused kernels, first layers too.
+@pytest.mark.parametrize("geom", GEOMS)
+@pytest.mark.parametrize("bf16", [False, True])
+def test_geometry_sweep_channel_first(geom, bf16):
+    C, O, k, s, pd, H, W = geom
+    _say(f"channel-first sweep {geom} bf16={bf16}")
+    spec, frames = syn.random_layer_case(sum(geom) + 2, C, O, k, s, pd, H, W, 3, change_prob=0.04, relu=True, noise_std=0.004)
+    p = Pair(spec, H, W, bf16=bf16, feed_forward=True, backend=2)
+    for t, f in enumerate(frames + [frames[-1]]):
+        _, n = p.step(f, 0.02, tag=f"{geom} frame {t}")
+    assert n == 0
+
+
 # Strided dilation: the even bits of two windows (stride 2), every s-th bit of s windows (3 - 64), one window per
 # output (beyond); output rows of less and more than a word, filters of up to 31 columns, maps whose staged part of
 # the input map fits the workgroup's LDS and maps whose does not (the large strides).
@@ -108,10 +122,10 @@ def test_nonsquare_kernel(backend):
                                    (64, 40, 2, 18, 1, 50, 120),      # 33 - 64
                                    (32, 24, 1, 1, 0, 2, 4100)])      # an output row of more than 4 095 pixels
 def test_channel_last_layers_beyond_the_double_buffered_kernels_limits(shape, bf16):
-    """Filters of more than 16 rows or columns, and maps wider than 4 095 pixels, run the channel-last kernel's
-    older body (stages of several units behind a barrier pair; tap masks of 64 bits, a division per column)."""
+    """Long and thin filters of up to 18 rows or columns on the channel-last kernel, and a map wider than 4 095 pixels, where
+    it divides by the map's width instead of multiplying by a reciprocal."""
     C, O, kh, kw, pd, H, W = shape
-    _say(f"channel-last, outside the double-buffered body: {shape} bf16={bf16}")
+    _say(f"channel-last, long filters and wide maps: {shape} bf16={bf16}")
     rng = np.random.default_rng(kh * 100 + kw)
     spec = syn.ConvSpec(C, O, kh, 1, pd, True, False,
                         (rng.standard_normal((O, C, kh, kw)) * np.sqrt(2.0 / (C * kh * kw))).astype(np.float32),
@@ -183,7 +197,8 @@ def test_fused_long_k(geom, bf16):
 # takes four pixels), and the 64-column tile of the fused kernels for 17 - 32 output channels (16 384 listed pixels
 # and more).
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("geom", [(520, 6, 1, 1, 0, 10, 12), (136, 4, 1, 1, 0, 256, 260), (3, 24, 3, 1, 1, 150, 130)])
+@pytest.mark.parametrize("geom", [(520, 6, 1, 1, 0, 10, 12), (136, 4, 1, 1, 0, 256, 260), (3, 24, 3, 1, 1, 150, 130),
+                                  (9, 24, 3, 1, 1, 150, 130)])      # (the channel-first kernels; 3 channels run the channel-last one)
 def test_rarely_taken_kernel_variants(geom, bf16):
     C, O, k, s, pd, H, W = geom
     _say(f"variant {geom} bf16={bf16}")
@@ -200,7 +215,9 @@ def test_rarely_taken_kernel_variants(geom, bf16):
 # narrow tiles would number more than 512 and fewer than 16 384 pixels are listed: full-update frames of these maps.
 # K = 72 / 100 / 8 leave padding rows in the last unit, which that kernel clears itself when it gathers runs of taps.
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("geom", [(8, 64, 3, 100, 120), (4, 130, 5, 64, 150), (8, 48, 1, 90, 101)])
+@pytest.mark.parametrize("geom", [(8, 64, 3, 100, 120), (4, 130, 5, 64, 150), (8, 48, 1, 90, 101),
+                                  # (up to 4 float32 / 8 bfloat16 channels run the channel-last kernel, these do not)
+                                  (9, 64, 3, 100, 120), (5, 130, 5, 64, 150), (9, 130, 3, 64, 150), (10, 48, 1, 90, 101)])
 def test_fused_mid_column_tile(geom, bf16):
     C, O, k, H, W = geom
     _say(f"mid tile {geom} bf16={bf16}")
@@ -218,17 +235,16 @@ def test_fused_mid_column_tile(geom, bf16):
 SHADOW_GEOMS = [
     # C, O, k, stride, pad, H, W -- power-of-two channel counts from 16 (float32) / 32 (bfloat16) on: closed-loop layers
     # on the fused back end keep a channel-last shadow of the state.  One case per change-detection variant that updates it
-    # (channel groups x channels per lane; four pixels per lane from 65 536 pixels on; 16-pixel workgroups below
-    # 8 192 pixels) and per tile shape of the fused kernel that reads it.
+    # (channel groups x channels per lane; four pixels per lane from 65 536 pixels on, bfloat16 from 32 768; 16-pixel
+    # workgroups below 8 192 pixels), strides, filter sizes and numbers of output channels of the fused kernel that reads it.
     (16, 8, 3, 1, 1, 70, 90), (32, 24, 5, 2, 2, 61, 77), (64, 40, 3, 1, 1, 256, 260), (128, 72, 3, 1, 1, 40, 50),
     (128, 130, 1, 1, 0, 96, 100), (256, 20, 3, 1, 1, 30, 40), (256, 16, 1, 1, 0, 100, 90), (512, 12, 3, 1, 0, 20, 24),
     (512, 8, 1, 1, 0, 92, 90), (16, 70, 7, 1, 3, 50, 60), (32, 33, 3, 1, 1, 64, 64), (128, 8, 1, 1, 0, 256, 260),
     (16, 8, 1, 1, 0, 256, 260), (32, 8, 1, 1, 0, 256, 260), (64, 64, 3, 1, 1, 100, 120),
     (1024, 8, 1, 1, 0, 12, 16),      # more channels than the register-resident detection variants hold: looped variant
-    (16, 24, 1, 1, 0, 130, 130),     # 17-32 output channels on more than 16 384 pixels: 32 x 64 tiles
-    (32, 130, 3, 1, 1, 60, 100),     # 128 x 32 tiles (6 000 pixels, two row tiles: one round of wide tiles against two)
-    # more than 64 output channels on more than 16 384 pixels: bfloat16 runs 128 x 128 tiles with two alternating
-    # stage buffers (ragged row tiles, ragged last column tile, several taps per 256-byte unit, stride 2, 1x1)
+    (16, 24, 1, 1, 0, 130, 130),     # 17-32 output channels on more than 16 384 pixels
+    (32, 130, 3, 1, 1, 60, 100),     # two row tiles of 128
+    # more than 64 output channels on more than 16 384 pixels: ragged row tiles, ragged last column tile, stride 2, 1x1
     (32, 72, 3, 1, 1, 130, 140), (64, 130, 3, 1, 1, 129, 131), (32, 96, 5, 2, 2, 270, 262), (128, 128, 1, 1, 0, 130, 130),
 ]
 
@@ -342,8 +358,20 @@ def test_detect_bfloat16_ragged_planes(geom, feed_forward):
     assert_close(out, p.o.out, True, f"ragged planes {geom} frame one element off a word")
 
 
-# The channel-last kernel picks its tile from the number of listed pixels: every width it has for each range of output
-# channels, with ragged row and column tiles and a K that fills its last stage only in part.
+# The channel-last kernel picks its tile from the number of listed pixels: every tile it has (cl_tiles.py), with ragged row and
+# column tiles and a K that fills its last stage only in part ...
+@pytest.mark.parametrize("case", TILE_CASES)
+def test_every_channel_last_tile(case):
+    _, _, bf16, C, O, k, H, W = case
+    _say(f"tile {case}")
+    spec, frames = syn.random_layer_case(sum(case[3:]), C, O, k, 1, k // 2, H, W, 2, change_prob=0.03, relu=False, noise_std=0.004)
+    p = Pair(spec, H, W, bf16=bf16, backend=2)
+    _, n = p.step(frames[0], 0.02, tag=f"tile {case} full update")
+    assert n == H * W
+    p.step(frames[1], 0.02, tag=f"tile {case} frame 1")
+
+
+# ... and, around the sizes where the rule changes from one tile to the next, other channel counts and filter sizes.
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("geom", [
     (32, 13, 1, 241, 251), (32, 16, 3, 61, 67), (32, 24, 3, 31, 33), (32, 30, 1, 183, 179), (32, 32, 1, 411, 421),
