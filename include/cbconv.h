@@ -133,10 +133,17 @@ typedef struct {
  *  state_bytes   : per-layer, lives as long as the layer (input state, cached
  *                  output, bit-packed change maps, index list, repacked filter
  *                  matrix -- the "variables to be stored per-layer" of Fig. 2;
- *                  closed-loop layers on the fused back end with a power-of-two
- *                  number of input channels -- float32 from 16 on, bfloat16
- *                  from 32 on -- keep a second, pixel-major copy of the input
- *                  state for the gather).
+ *                  closed-loop layers on the fused back end keep a second,
+ *                  pixel-major copy of the input state for the gather if their
+ *                  number of input channels is a power of two, float32 from 16
+ *                  and bfloat16 from 32 on, or, padded to 16 bytes a pixel, up
+ *                  to 4 / 8.  Such layers, and those that gather from a
+ *                  producer's pixel-major output, multiply float32 values as six
+ *                  bfloat16 products of exact three-term splits, accumulated in
+ *                  float32; their repacked filters take 6 bytes a value.  Sums
+ *                  that are not finite or beyond 2^80 are computed again with
+ *                  the float32 matrix instruction, which costs time where there
+ *                  are many).
  *  scratch_bytes : X' and Y' matrices and block counters; may be shared by
  *                  layers that run on the same stream (Sec. III-B).  This is the
  *                  recommended size; cb_layer_create accepts any size not below

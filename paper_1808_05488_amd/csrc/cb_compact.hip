@@ -5,8 +5,8 @@
 // and compacts with a library stream-compaction call.  Here the map is held as
 // 64-pixel words: one thread produces one word of the dilated map from at most
 // three input words per filter row (shifts and ORs), the words' popcounts are
-// scanned (wavefront shuffles + LDS), and set bits are expanded into the ordered
-// index list a word at a time by a whole wavefront (one-workgroup kernel: by its lane).  Two kernels, no atomics on
+// scanned (wavefront moves + LDS), and set bits are expanded into the ordered
+// index list a word at a time by a whole wavefront (one-workgroup kernel: sparse words by their lane).  No atomics on
 // the ordering path, so the list is strictly ascending by construction.
 //
 //   dilate_kernel : word (yo, wo) of the dilated map + per-block popcount
@@ -260,8 +260,9 @@ __device__ __forceinline__ uint64_t full_word(const Geom& g, int it)
 }
 
 // Words of the input map a workgroup can stage: 256 output words of a 1080p layer with stride 1 and a 31-row
-// filter need 1 200 words, of a VGA layer with stride 4 and 7 rows 1 100 (16 KB; the one-workgroup kernel, 1024
-// output words, four times that).
+// filter need 1 200 words, of a VGA layer with stride 2 and 7 rows 1 092 (16 KB).  The one-workgroup kernel, up to 1024
+// output words, stages maps of up to 4 605 words whole (36 KB); that of a VGA layer with stride 3 or 4, 4 802 words, is
+// read from memory.
 constexpr int MAP_STAGE = 2048, MAP_STAGE_SMALL = 4608;
 
 __global__ __launch_bounds__(256) void dilate_kernel(Geom g, const uint64_t* __restrict__ in_bits,
@@ -333,8 +334,8 @@ __global__ __launch_bounds__(256) void compact_kernel(Geom g, const uint64_t* __
 // words and then adds up what its predecessors published, so nobody waits for a chain of prefixes.
 // Progress: a workgroup publishes its own count before it waits for anybody, and it only waits for
 // workgroups with lower numbers, which were dispatched no later than itself and publish before they
-// wait in turn; on an idle GPU the whole grid (at most 1024 workgroups of 256 threads, a few dozen
-// registers, 40 bytes of LDS) is resident at once anyway.  Correctness does not rest on either: the
+// wait in turn; on an idle GPU the whole grid (at most 1024 workgroups of 256 threads, 93 registers and
+// 16.4 KB of LDS: five per compute unit, 1 280 on the chip) is resident at once anyway.  Correctness does not rest on either: the
 // wait is bounded (spin_limit polls per predecessor), and a thread whose wait runs out -- other
 // streams or processes may hold the compute units the predecessor is waiting for -- recomputes that
 // predecessor's count itself from the input map (recount_block), which needs nobody else.  The list

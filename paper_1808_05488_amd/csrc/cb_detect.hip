@@ -784,8 +784,9 @@ hipError_t launch_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int
     // for 128 channels (1080p) or for the first layers' 3 channels, so only here.
     const bool one_px = sizeof(T) == 4 && g.C > 32 && g.C <= 64;
     // Four pixels per lane otherwise, from 65 536 pixels on.  bfloat16, whose single pixels are 2-byte loads, from 32 768 on
-    // and whatever the alignment (64 channels at 271x435 13.8 -> 7.5 us, 128 channels at 1053x1822 398 -> 184 us; at 140x141
-    // pixels one pixel per lane is still the faster one, 7.3 against 7.8 us).  float32 gains nothing from unaligned loads
+    // and whatever the alignment (64 channels at 271x435 13.8 -> 7.5 us, 128 channels at 1053x1822 398 -> 184 us).  One against
+    // four pixels per lane on either side of that line, odd planes: 128 channels 8.0 against 9.5 us at 171x171, 12.0 against 8.5 at
+    // 181x182, 12.7 against 8.7 at 200x201; 64 channels 6.3 / 6.7, 6.5 / 6.0, 6.7 / 6.1; up to 16 channels no difference.  float32 gains nothing from unaligned loads
     // (32 channels at 557x803: 25.1 us either way), and the looped variant for more than 128 channels wants aligned ones.
     const bool aligned = P % 4 == 0 && (uintptr_t)x % valign == 0 && (uintptr_t)S % valign == 0;
     const bool vec4 = P >= (sizeof(T) == 4 ? 65536 : 32768) && !one_px &&
@@ -800,7 +801,7 @@ hipError_t launch_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int
 hipError_t launch_detect(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
                          float tau, int flags, hipStream_t st, Tm tm)
 {
-    // a shadow is kept for layers with a power-of-two channel count (see fused_channel_last)
+    // a shadow is kept for layers with a power-of-two channel count, and padded for first layers (fused_channel_last, fused_padded)
     if (S2 && g.Cs == g.C && g.C > (g.bf16 ? 8 : 4) && (g.C < (g.bf16 ? 32 : 16) || (g.C & (g.C - 1)) != 0)) return hipErrorInvalidValue;
     if (g.bf16)
         return launch_t<uint16_t>(g, (const uint16_t*)x, (uint16_t*)S, (uint16_t*)S2, mbits, ctl, tau, flags,

@@ -21,8 +21,9 @@ constexpr int FUSED_GUARD = 128;        // bytes readable ahead of the gather so
 constexpr int FUSED_ZERO_TAP = 60;      // tap index of the zero rows that pad K (never inside the image)
 constexpr int FUSED_TAB_PAD = 64;       // entries of length 0 that close the chunk table: a group of gather rounds (up to 4 rounds of 16 fetchers) may read this far past the last chunk
 
-// Channel-last variant (C a power of two: >= 16 float32, >= 32 bfloat16; layers that keep an input state): the
-// gather reads a pixel-major shadow of the state, K is walked tap-major, no chunk table (cb_fused_cl.hip).
+// Channel-last variant (C a power of two: >= 16 float32, >= 32 bfloat16; or up to 4 / 8, padded to 16 bytes a pixel): the
+// gather reads a pixel-major shadow of the state (or a producer's pixel-major output), K is walked tap-major, no chunk
+// table (cb_fused_cl.hip).
 
 // Chunk table.  The rows of X' that belong to one input channel c and one filter row j,
 // r = (c*kh + j)*kw + i for i = 0..kw-1 (construction of X below Eq. 2), are kw consecutive

@@ -7,8 +7,8 @@
 // bytes to which the pixels of a first layer's shadow are padded), in groups of 32 (one step of
 // v_mfma_f32_16x16x32_bf16), UKG groups = one stage.
 //   B operand: a thread fetches 16-byte pieces of a column (consecutive lanes: consecutive pieces) and stores them to
-//     LDS, [column][k], column pitch 4 mod 32 words, so that the 16-byte fragment reads of sixteen columns fall
-//     into different banks.  Two stage buffers alternate; stage u+1 is stored and a later one requested ahead of
+//     LDS, [column][k], column pitch 4 mod 32 words (128 float32 columns: 20), so that the 16-byte fragment reads of eight
+//     neighbouring columns cover all 32 banks.  Two stage buffers alternate; stage u+1 is stored and a later one requested ahead of
 //     the MFMAs of stage u, one barrier per stage.  Narrow tiles, whose MFMAs are short, take long stages (the same
 //     number of loads in flight whatever the tile width) and keep two of them in flight (GD).
 //   A operand: packed in MFMA fragment order at layer creation, read from L2 into a ring of D groups of registers,

@@ -135,7 +135,7 @@ hipError_t launch_gemm(const Geom& g, const void* KT, const void* X, void* Y, co
 // partial products in a fixed order, so results do not depend on scheduling).
 __host__ __device__ inline int gemm_bm(int O) { return O <= 16 ? 16 : (O <= 32 ? 32 : 64); }
 // (tiles of 128 columns for 17 - 32 and 256 for up to 16 output channels left a few thousand columns too few workgroups: 32 -> 32, 9x9,
-// 4 240 columns 20 -> 14 us, 64 -> 16, 3 936 columns 54 -> 33 us, bfloat16 94 -> 38 us)
+// 4 240 columns 20 -> 16 us, 64 -> 16, 3 936 columns 54 -> 33 us, bfloat16 94 -> 38 us)
 __host__ __device__ inline int gemm_bn(int O) { return O <= 16 ? 128 : 64; }
 __host__ __device__ inline int gemm_nsplit(int ncols, int R, int O, int Opad, int cap)
 {
