@@ -61,6 +61,8 @@ template <typename V> __device__ __forceinline__ V ld_once(const V* p)
 // channel unaligned; global memory takes such loads, at the price of one more cache line per wavefront).
 template <typename T, int VEC> struct PxMem { typedef typename Pack<T, VEC>::type type; };
 typedef unsigned PxMem2x4 __attribute__((ext_vector_type(2), aligned(2)));
+// (a type of its own for the loads that are not marked: of two loads of one type and address the compiler makes one, without the mark)
+typedef unsigned long long PxMem64 __attribute__((aligned(2)));
 template <> struct PxMem<uint16_t, 4> { typedef PxMem2x4 type; };
 template <typename T, int VEC, bool ONCE> __device__ __forceinline__ typename Pack<T, VEC>::type ld_px(const T* p)
 {
@@ -68,7 +70,7 @@ template <typename T, int VEC, bool ONCE> __device__ __forceinline__ typename Pa
     typedef typename PxMem<T, VEC>::type M;
     if constexpr (sizeof(T) == 2 && VEC > 1) {
         if constexpr (ONCE) return __builtin_bit_cast(V, (uintx2)__builtin_nontemporal_load(reinterpret_cast<const M*>(p)));
-        else return __builtin_bit_cast(V, (uintx2)*reinterpret_cast<const M*>(p));
+        else return __builtin_bit_cast(V, (unsigned long long)*reinterpret_cast<const PxMem64*>(p));
     } else {
         if constexpr (ONCE) return ld_once(reinterpret_cast<const V*>(p));
         else return *reinterpret_cast<const V*>(p);
@@ -208,7 +210,7 @@ __global__ __launch_bounds__(256) void detect_kernel(const T* __restrict__ x, T*
 template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false>
 __global__ __launch_bounds__((PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS)
 void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2, uint64_t* __restrict__ mbits0,
-                       int* __restrict__ ctl, int C, int P, int nwords, float tau, int flags)
+                       int* __restrict__ ctl, int C, int P, int nwords, float tau, int flags, int2 stream)
 {
     typedef typename Pack<T, VEC>::type V;
     // which of the two map buffers and counters this frame fills: the frame count lives on the device
@@ -233,6 +235,13 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
     const long p0 = pw - over;
     const unsigned own = valid ? (ALL << over) & ALL : 0u;
 
+    // (stream: from and below which count of the frame before, still in place, the state is read once; float32 does not ask)
+    bool once = (flags & DET_STREAM_STATE) != 0;
+    if constexpr (sizeof(T) == 2) {
+        const int before = __builtin_amdgcn_readfirstlane(ctl[CTL_COUNT]);
+        once = once && before >= stream.x && before < stream.y;
+    }
+
     V xv[CPT];
     unsigned bits = 0;
     if (valid) {
@@ -253,7 +262,7 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
                 if (c < C) {
                     const size_t off = (size_t)c * P + p0;
                     xv[q] = ld_px<T, VEC, true>(x + off);
-                    sv[q] = (flags & DET_STREAM_STATE) ? ld_px<T, VEC, true>(S + off) : ld_px<T, VEC, false>(S + off);
+                    sv[q] = once ? ld_px<T, VEC, true>(S + off) : ld_px<T, VEC, false>(S + off);
                 }
             }
             // every load is issued before the first compare waits for one: the kernel lives on loads in flight
@@ -554,7 +563,7 @@ __global__ __launch_bounds__(256) void shadow_rebuild_kernel(const T* __restrict
 }
 
 template <typename T, int VEC, int CS, int CPT, int PLX = 0>
-void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int P, float tau, int flags, hipStream_t st, Tm tm)
+void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int P, float tau, int flags, int2 stream, hipStream_t st, Tm tm)
 {
     constexpr int PL = PLX ? PLX : (CS >= 4 ? 64 : 256 / CS);
     const long px_per_block = (long)PL * VEC;
@@ -563,31 +572,31 @@ void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int P
         // (launch_t only passes a shadow on when the variant's registers hold exactly C channels)
         if (S2 != nullptr && C == CS * CPT) {
             CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX, true>), dim3(grid), dim3(PL * CS), st, tm, x, S, S2, mbits,
-                      ctl, C, P, (P + 63) / 64, tau, flags);
+                      ctl, C, P, (P + 63) / 64, tau, flags, stream);
             return;
         }
     }
     CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX>), dim3(grid), dim3(PL * CS), st, tm, x, S, CS == 1 && CPT * sizeof(T) <= 16 ? S2 : (T*)nullptr, mbits,
-              ctl, C, P, (P + 63) / 64, tau, flags);
+              ctl, C, P, (P + 63) / 64, tau, flags, stream);
 }
 
 template <typename T, int VEC>
-void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int P, float tau, int flags, hipStream_t st, Tm tm)
+void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int P, float tau, int flags, int2 stream, hipStream_t st, Tm tm)
 {
     // channel groups CS and channels per lane CPT with CS*CPT >= C
-    if (C <= 4)        launch_reg<T, VEC, 1, 4>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
-    else if (C <= 8)   launch_reg<T, VEC, 1, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
-    else if (C <= 16)  launch_reg<T, VEC, 4, 4>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
-    else if (C <= 32)  launch_reg<T, VEC, 4, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
-    else if (C <= 64)  launch_reg<T, VEC, 8, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
+    if (C <= 4)        launch_reg<T, VEC, 1, 4>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    else if (C <= 8)   launch_reg<T, VEC, 1, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    else if (C <= 16)  launch_reg<T, VEC, 4, 4>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    else if (C <= 32)  launch_reg<T, VEC, 4, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    else if (C <= 64)  launch_reg<T, VEC, 8, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
     // maps of fewer than 128 x 64 pixels with many channels: 16-pixel workgroups reach every compute unit
-    else if (VEC == 1 && P < 8192 && C <= 128) launch_reg<T, 1, 16, 8, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
-    else if (VEC == 1 && P < 8192 && C <= 256) launch_reg<T, 1, 16, 16, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
-    else if (VEC == 1 && P < 8192 && C <= 512) launch_reg<T, 1, 16, 32, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
-    else if (C <= 128) launch_reg<T, VEC, 16, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
+    else if (VEC == 1 && P < 8192 && C <= 128) launch_reg<T, 1, 16, 8, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    else if (VEC == 1 && P < 8192 && C <= 256) launch_reg<T, 1, 16, 16, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    else if (VEC == 1 && P < 8192 && C <= 512) launch_reg<T, 1, 16, 32, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    else if (C <= 128) launch_reg<T, VEC, 16, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
     // one pixel per lane leaves registers for more channels per lane (deep layers: many channels, few pixels)
-    else if (VEC == 1 && C <= 256) launch_reg<T, 1, 16, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
-    else if (VEC == 1 && C <= 512) launch_reg<T, 1, 16, 32>(x, S, S2, mbits, ctl, C, P, tau, flags, st, tm);
+    else if (VEC == 1 && C <= 256) launch_reg<T, 1, 16, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    else if (VEC == 1 && C <= 512) launch_reg<T, 1, 16, 32>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
     else {
         // more channels than the register-resident variants hold: looped variant
         const long px_per_block = 64L * VEC;
@@ -768,11 +777,30 @@ hipError_t launch_listed_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbi
     return hipGetLastError();
 }
 
+// DET_STREAM_STATE for bfloat16, whose detection stores state and shadow itself: the counts of listed pixels of the frame before,
+// from .x to below .y, behind which the state is read past the last-level cache (256 MB).  Behind a frame that wrote most of
+// that cache (output, state, shadow; a pixel changed for every 1.25 listed), a state read past it gains nothing and the
+// stores of this frame are the slower ones; a state that is not much larger than the cache is better kept in
+// it unless a large output pushes it out.  Frames, us, past the cache / through it: 128 -> 128, 3x3, 1080p (531 MB) 170 / 182 at 0.1 %
+// of the pixels changed, 220 / 242 at 1, 341 / 377 at 6, 450 / 454 at 10, 641 / 598 at 20, 977 / 909 at 50; at 900x1600 (368 MB) 128 / 136
+// at 0.2 %, 298 / 332 at 10, 384 / 387 at 15, 543 / 506 at 30; 64 -> 128 at 1080p (265 MB) 97 / 89 at 0.2 %, 120 / 116 at 1, 154 / 157 at 3,
+// 251 / 302 at 10, 367 / 360 at 15, 504 / 475 at 30; 32 -> 64 at 1440x2560 (236 MB) 106 / 90 at 1 %, 140 / 130 at 3, 177 / 184 at 6, 214 / 256
+// at 10, 436 / 411 at 30; 128 -> 64 at 720x1280 (236 MB) 106 / 86 at 1 %, 172 / 156 at 10; 64 -> 64 at 900x1280 (147 MB) 69 / 61 at 1 %,
+// 120 / 100 at 10, 195 / 176 at 30.
+int2 state_read_once(const Geom& g, int esz, bool shadow)
+{
+    const double state = (double)g.C * g.P * esz, out_px = (double)g.O * esz;
+    const double from = state >= 300e6 ? 0.0 : state >= 200e6 ? 25e6 / out_px : 2e9;
+    const double below = 160e6 / (out_px + 0.8 * g.C * esz * (shadow ? 2 : 1));
+    return make_int2((int)std::min(from, 2e9), (int)std::min(below, 2e9));
+}
+
 template <typename T>
 hipError_t launch_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, float tau, int flags,
                     hipStream_t st, Tm tm)
 {
     const int P = g.P;
+    const int2 stream = state_read_once(g, sizeof(T), S2 != nullptr);
     const size_t valign = 4 * sizeof(T);
     // few pixels: one pixel per lane keeps more wavefronts busy than four
     // (with a shadow to update, more than 128 channels take the one-pixel-per-lane variants, which
@@ -791,8 +819,8 @@ hipError_t launch_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int
     const bool aligned = P % 4 == 0 && (uintptr_t)x % valign == 0 && (uintptr_t)S % valign == 0;
     const bool vec4 = P >= (sizeof(T) == 4 ? 65536 : 32768) && !one_px &&
                       (aligned || (sizeof(T) == 2 && g.C <= 128)) && (g.C <= 128 || (P >= 65536 && !(S2 != nullptr && g.C <= 512)));
-    if (vec4) launch_v<T, 4>(x, S, S2, mbits, ctl, g.C, P, tau, flags, st, tm);
-    else      launch_v<T, 1>(x, S, S2, mbits, ctl, g.C, P, tau, flags, st, tm);
+    if (vec4) launch_v<T, 4>(x, S, S2, mbits, ctl, g.C, P, tau, flags, stream, st, tm);
+    else      launch_v<T, 1>(x, S, S2, mbits, ctl, g.C, P, tau, flags, stream, st, tm);
     return hipGetLastError();
 }
 

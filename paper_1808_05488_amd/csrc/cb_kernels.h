@@ -63,7 +63,8 @@ __device__ __forceinline__ int* nin_counter(int* ctl, unsigned b, int par)
 enum { DET_FORCE_ALL = 1,      // mark every pixel as changed (first frame)
        DET_COPY_ALL = 2,       // copy every pixel into the state (feed-forward)
        DET_STREAM_STATE = 4,   // the state is larger than the caches hold from one frame to the next: read it
-                               // non-temporally too (1080p, 128 channels: 374 -> 318 us; a state that fits loses)
+                               // non-temporally too (1080p, 128 channels: 374 -> 318 us; a state that fits loses; bfloat16: where
+                               // state_read_once in cb_detect.hip says so)
        DET_NO_UPDATE = 8 };    // compare and write the map only; launch_state_apply updates the state (and shadow)
 
 // S2: null, or the channel-last shadow of the state (pixel-major, Cs values per pixel: a power of two C >= 16, or the
