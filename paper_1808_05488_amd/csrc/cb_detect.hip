@@ -237,10 +237,11 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
 
     // (stream: from and below which count of the frame before, still in place, the state is read once; float32 does not ask)
     bool once = (flags & DET_STREAM_STATE) != 0;
-    if constexpr (sizeof(T) == 2) {
-        const int before = __builtin_amdgcn_readfirstlane(ctl[CTL_COUNT]);
-        once = once && before >= stream.x && before < stream.y;
-    }
+    if constexpr (sizeof(T) == 2)
+        if (once) {
+            const int before = __builtin_amdgcn_readfirstlane(ctl[CTL_COUNT]);
+            once = before >= stream.x && before < stream.y;
+        }
 
     V xv[CPT];
     unsigned bits = 0;
