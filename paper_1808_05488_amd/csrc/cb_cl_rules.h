@@ -27,12 +27,18 @@ inline ClDiv cl_div(int Wo, int Ho, int kw)
 
 CB_HD int cl_row(const ClDiv& d, int q, int Wo) { return d.inv_wo ? (int)(((unsigned long long)(unsigned)q * d.inv_wo) >> 42) : q / Wo; }
 
-// Rows of the widest tile for O output channels, which names the kernel's instance.
-inline int cl_shape(int O) { return O <= 16 ? 16 : O <= 32 ? 32 : O <= 64 ? 64 : 128; }
+// The kernel's instance: rows of its widest tile for O output channels, and 129 for bfloat16 layers whose maps (Po outputs) hold four
+// 128 x 128 tiles per compute unit: the one with that tile.  (It needs registers that the narrow tiles then lack: 128 -> 96, 3x3, 92x164,
+// 612 listed pixels 17.5 -> 19.1 us a frame with it.)
+inline int cl_shape(int O, int Po, bool f32)
+{
+    return O <= 16 ? 16 : O <= 32 ? 32 : O <= 64 ? 64 : !f32 && (Po + 127LL) / 128 * ((O + 127LL) / 128) >= 1024 ? 129 : 128;
+}
 
 // Tiles (rows x columns) of instance `shape`: number 0 is 16 x 16 with the four wavefronts sharing K, the others follow.
 //   16: 16 x 64, 16 x 128    32: 32 x 32, 32 x 64, 32 x 128    64: 64 x 16, 64 x 32, 64 x 64    128: 64 x 16, 64 x 32, 128 x 32, 128 x 64
-CB_HD constexpr int cl_tiles(int shape) { return shape == 16 ? 3 : shape == 128 ? 5 : 4; }
+//   129: these and 128 x 128
+CB_HD constexpr int cl_tiles(int shape) { return shape == 16 ? 3 : shape == 128 ? 5 : shape == 129 ? 6 : 4; }
 
 // Which tile finishes a frame first, in ns.  The kernel takes as long as the compute unit with the most tiles, and n tiles
 // on it take about max(latency of one, n * its share of a busy unit) beyond the launch; both grow with the k-groups of the
@@ -83,7 +89,14 @@ template <bool F32, int SHAPE, typename FN> CB_HD void cl_tile(int N, int O, int
         const unsigned a = CB_COST(64, 16, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, 1000, 300, 1400, 203, 400, 80, 1100, 47),
                        c = CB_COST(128, 32, 0, 400, 1000, 320, 0, 115, 100, 96), d = CB_COST(128, 64, 900, 745, 2900, 510, 700, 205, 1000, 140),
                        ab = a < b ? a : b, cd = c < d ? c : d;
-        if (k <= ab && k <= cd) run(std::integral_constant<int, 0>());
+        // 128 x 128 halves what a column costs in filter fragments and gathers; from two tiles per compute unit on, so that they
+        // have others to run beside.  us, 128 x 64 / 128 x 128: 64 -> 128, 1x1, 101 376 pixels 33 / 20; 128 -> 256, 1x1, 41 216 in blocks 29 / 18;
+        // 64 -> 96, 3x3, 122 187 56 / 34; 128 -> 512, 3x3, 233 661 420 / 358; 64 -> 256, 7x7, 151 306 294 / 254; 64 -> 128, 3x3, 1080p, 5 %
+        // changed 64 / 51.  (float32 has no registers for it.  The cost is compared with that of 128 x 64 alone: those of the narrower
+        // tiles miss what many listed pixels pay for their stores, 1x1 above all.)
+        if (SHAPE == 129 && (((unsigned)N + 127u) / 128u) * (((unsigned)O + 127u) / 128u) >= 512u && cl_cost<128, 128>(N, O, nkg, 1500, 420, 1000, 250) <= d)
+            run(std::integral_constant<int, SHAPE == 129 ? 5 : 4>());
+        else if (k <= ab && k <= cd) run(std::integral_constant<int, 0>());
         else if (ab <= cd) { if (a <= b) run(std::integral_constant<int, 1>()); else run(std::integral_constant<int, 2>()); }
         else if (c <= d) run(std::integral_constant<int, 3>());
         else run(std::integral_constant<int, 4>());

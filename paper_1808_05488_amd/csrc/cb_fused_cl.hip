@@ -187,7 +187,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     static_assert(PPC <= 256 && NP * CPP == BN, "pieces come out even");
     // k-groups of filter fragments in flight: an L2 latency's worth of MFMAs, as far as the registers go
     constexpr int DMAX = F32 ? (TM == 1 ? 4 : 2)
-                          : (TM * TN <= 2 ? 8 : 4);
+                          : (TM * TN <= 2 ? 8 : TM * TN <= 8 ? 4 : 2);
     constexpr int D = DMAX < 4 * UKW ? DMAX : 4 * UKW;
     constexpr int GD = F32 && TM * TN <= 2 ? 2 : 1;     // stages of gathered pieces in flight
     // stages per round of the stage loop: ring slot and register set are compile-time indexes
@@ -195,6 +195,8 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     static_assert(UU * UKW % D == 0 && UU % GD == 0, "a round of stages is whole rings");
     constexpr unsigned PITCH = cl_pitch<T>(BN, WGK), BUF = BN * PITCH;
     constexpr unsigned PLANE = UKG * 64u;        // bytes of one term of a column
+    // the largest tile has no registers for what can be fetched when it is used: the next tile's pixels, the bias, a longer ring
+    constexpr bool LEAN = TM * TN > 8;
     constexpr bool TWO = TM * TN < 4;            // second accumulator chain where a wavefront has few tiles
     extern __shared__ uint4 dyn_lds4[];          // two stage buffers, then the listed pixel of every column
     char* const Bs = reinterpret_cast<char*>(dyn_lds4);
@@ -230,15 +232,16 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             q[p] = (u < total && n < (unsigned)N) ? idx[n] : -1;
         }
     };
-    fetch_q(blockIdx.x >> 3, qnext);
+    if constexpr (!LEAN) fetch_q(blockIdx.x >> 3, qnext);
 
     for (unsigned uq = blockIdx.x >> 3; uq < total; uq += gridDim.x >> 3) {
         const int mt = (int)(uq % MT);
         const unsigned nt = xcd0 + uq / MT;
         int q[NP];
 #pragma unroll
-        for (int p = 0; p < NP; ++p) q[p] = qnext[p];
-        fetch_q(uq + (gridDim.x >> 3), qnext);
+        for (int p = 0; p < NP; ++p) q[p] = LEAN ? 0 : qnext[p];
+        if constexpr (LEAN) fetch_q(uq, q);
+        else fetch_q(uq + (gridDim.x >> 3), qnext);
         if (nt >= NT) continue;
         const int m0 = mt * BM;
 
@@ -328,7 +331,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = m0 + (wm * TM + a) * 16 + lq * 4 + r;
-                bv[a][r] = bias[m < g.O ? m : g.O - 1];
+                bv[a][r] = LEAN ? 0.f : bias[m < g.O ? m : g.O - 1];
             }
         __syncthreads();                          // the previous tile has read its last stage and its qs
         if (ch == 0) {
@@ -431,6 +434,15 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                     for (int b = 0; b < TN; ++b)
 #pragma unroll
                         for (int r = 0; r < 4; ++r) acc[a][b][r] += red[(wv + w) * PER + ((a * TN + b) * 4 + r) * 64];
+        }
+        if constexpr (LEAN) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int m = m0 + (wm * TM + a) * 16 + lq * 4 + r;
+                    bv[a][r] = bias[m < g.O ? m : g.O - 1];
+                }
         }
         // output update: bias + ReLU, written at the listed pixels only
         unsigned long long bad = 0;               // float32: sums to recompute, bit (b*TM + a)*4 + r
@@ -537,6 +549,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(G
         else if constexpr (SHAPE == 16) CB_BODY(1, 4, 1, t);
         else if constexpr (SHAPE == 32) CB_BODY(2, 2, 1, 1 << (t - 1));
         else if constexpr (SHAPE == 64 || t <= 2) CB_BODY(4, 1, 1, 1 << (t - 1));
+        else if constexpr (t == 5) CB_BODY(4, 1, 2, 8);
         else CB_BODY(4, 1, 2, 1 << (t - 2));
     });
 #undef CB_BODY
@@ -551,10 +564,11 @@ hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow
 #define CB_CL(shape)                                                                                                     \
     CB_LAUNCH_LDS((fused_cl_kernel<T, shape>), dim3(1024), dim3(256), sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16, st, tm, g, \
                           div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)
-    switch (cl_shape(g.O)) {
+    switch (cl_shape(g.O, g.Po, sizeof(T) == 4)) {
         case 16: CB_CL(16); break;
         case 32: CB_CL(32); break;
         case 64: CB_CL(64); break;
+        case 129: if constexpr (sizeof(T) == 2) CB_CL(129); break;
         default: CB_CL(128);
     }
 #undef CB_CL

@@ -17,4 +17,10 @@ TILE_CASES = [
     (64, 3, True, 64, 50, 3, 91, 99),
     (128, 0, True, 32, 72, 3, 7, 9), (128, 1, True, 64, 100, 3, 41, 43), (128, 2, True, 64, 72, 3, 49, 53),
     (128, 3, True, 32, 140, 3, 91, 99), (128, 4, True, 64, 130, 3, 145, 153),
+    (129, 5, True, 32, 140, 1, 251, 263), (129, 5, True, 32, 200, 3, 251, 263),
 ]
+
+# The instance of bfloat16 layers with large maps: a layer (input channels, output channels, filter size, height, width) and the sides of
+# square regions whose change lists the pixels for each of its tiles.
+LARGE_MAP_LAYER = (64, 130, 3, 251, 263)
+LARGE_MAP_REGIONS = [(10, 0), (27, 1), (43, 2), (80, 3), (118, 4), (215, 5)]

@@ -6,7 +6,7 @@ import subprocess
 
 import pytest
 
-from cl_tiles import TILE_CASES
+from cl_tiles import LARGE_MAP_LAYER, LARGE_MAP_REGIONS, TILE_CASES
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1808_05488_amd", "csrc")
 
@@ -14,20 +14,24 @@ SOURCE = r"""
 #include "cb_cl_rules.h"
 extern "C" int row(int q, int Wo, int Ho, int kw) { return cb::cl_row(cb::cl_div(Wo, Ho, kw), q, Wo); }
 extern "C" unsigned inv_kw(int kw) { return cb::cl_div(1, 1, kw).inv_kw; }
-template <bool F32> int tile(int N, int O, int Cs, int taps, int R)
+template <bool F32> int tile(int N, int O, int Po, int Cs, int taps, int R)
 {
     int t = -1;
     auto run = [&](auto tile) { t = decltype(tile)::value; };
-    switch (cb::cl_shape(O)) {
+    switch (cb::cl_shape(O, Po, F32)) {
         case 16: cb::cl_tile<F32, 16>(N, O, Cs, taps, R, run); break;
         case 32: cb::cl_tile<F32, 32>(N, O, Cs, taps, R, run); break;
         case 64: cb::cl_tile<F32, 64>(N, O, Cs, taps, R, run); break;
+        case 129: cb::cl_tile<F32, 129>(N, O, Cs, taps, R, run); break;
         default: cb::cl_tile<F32, 128>(N, O, Cs, taps, R, run);
     }
     return t;
 }
-extern "C" int tile(int bf16, int N, int O, int Cs, int taps, int R) { return bf16 ? tile<false>(N, O, Cs, taps, R) : tile<true>(N, O, Cs, taps, R); }
-extern "C" int shape(int O) { return cb::cl_shape(O); }
+extern "C" int tile(int bf16, int N, int O, int Po, int Cs, int taps, int R)
+{
+    return bf16 ? tile<false>(N, O, Po, Cs, taps, R) : tile<true>(N, O, Po, Cs, taps, R);
+}
+extern "C" int shape(int O, int Po, int bf16) { return cb::cl_shape(O, Po, !bf16); }
 extern "C" int tiles(int shape) { return cb::cl_tiles(shape); }
 """
 
@@ -67,7 +71,12 @@ def test_tile_cases_cover_every_tile(rules):
     for shape, tile, bf16, c, o, k, h, w in TILE_CASES:
         pixel = 16 // (2 if bf16 else 4)
         cs = pixel if c <= pixel else c
-        assert rules.shape(o) == shape
-        assert rules.tile(bf16, h * w, o, cs, k * k, c * k * k) == tile, (shape, tile, bf16, c, o, k, h, w)
-    every = {(s, t, b) for s in (16, 32, 64, 128) for t in range(rules.tiles(s)) for b in (False, True)}
-    assert {(s, t, b) for s, t, b, *_ in TILE_CASES} == every
+        assert rules.shape(o, h * w, bf16) == shape
+        assert rules.tile(bf16, h * w, o, h * w, cs, k * k, c * k * k) == tile, (shape, tile, bf16, c, o, k, h, w)
+    c, o, k, h, w = LARGE_MAP_LAYER
+    large = rules.shape(o, h * w, True)
+    for side, tile in LARGE_MAP_REGIONS:
+        assert rules.tile(True, (side + k - 1) ** 2, o, h * w, c, k * k, c * k * k) == tile, (side, tile)
+    every = {(s, t, b) for s in (16, 32, 64, 128) for b in (False, True) for t in range(rules.tiles(s))}
+    every |= {(129, t, True) for t in range(rules.tiles(129))}
+    assert {(s, t, b) for s, t, b, *_ in TILE_CASES} | {(large, t, True) for _, t in LARGE_MAP_REGIONS} == every

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import synth_inputs as syn
-from cl_tiles import TILE_CASES
+from cl_tiles import LARGE_MAP_LAYER, LARGE_MAP_REGIONS, TILE_CASES
 
 pytestmark = pytest.mark.gpu
 
@@ -369,6 +369,20 @@ def test_every_channel_last_tile(case):
     _, n = p.step(frames[0], 0.02, tag=f"tile {case} full update")
     assert n == H * W
     p.step(frames[1], 0.02, tag=f"tile {case} frame 1")
+
+
+def test_every_channel_last_tile_of_large_maps():
+    C, O, k, H, W = LARGE_MAP_LAYER
+    spec, frames = syn.random_layer_case(97, C, O, k, 1, k // 2, H, W, 1, relu=True)
+    p = Pair(spec, H, W, bf16=True, backend=2)
+    f = frames[0]
+    p.step(f, 0.02, tag="large map full update")
+    for i, (side, tile) in enumerate(LARGE_MAP_REGIONS):
+        _say(f"large map, tile {tile}")
+        f = f.copy()
+        f[:, 3 + i:3 + i + side, 5:5 + side] += np.float32(0.5)
+        _, n = p.step(f, 0.02, tag=f"large map tile {tile}")
+        assert n == (side + k - 1) ** 2
 
 
 # ... and, around the sizes where the rule changes from one tile to the next, other channel counts and filter sizes.
