@@ -67,7 +67,7 @@ template <bool F32, int SHAPE, typename FN> CB_HD void cl_tile(int N, int O, int
     const bool far = F32 && (unsigned long long)O * (unsigned)R > 700000ull;
     const unsigned k = CB_COST(16, 16, 100, 94, 1260, (far ? 80 : 49), 200, 30, 870, 16);
     if constexpr (SHAPE == 16) {
-        const unsigned a = CB_COST(16, 64, 0, 330, 1100, 222, 200, 110, 1000, 60), b = CB_COST(16, 128, 0, 700, 1300, 440, 300, 200, 1300, 110);
+        const unsigned a = CB_COST(16, 64, 1600, 330, 1100, 222, 200, 110, 1000, 60), b = CB_COST(16, 128, 2600, 700, 1300, 440, 300, 200, 1300, 110);
         if (k <= a && k <= b) run(std::integral_constant<int, 0>());
         else if (a <= b) run(std::integral_constant<int, 1>());
         else run(std::integral_constant<int, 2>());
@@ -87,7 +87,7 @@ template <bool F32, int SHAPE, typename FN> CB_HD void cl_tile(int N, int O, int
         else run(std::integral_constant<int, 3>());
     } else {
         const unsigned a = CB_COST(64, 16, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, 1000, 300, 1400, 203, 400, 80, 1100, 47),
-                       c = CB_COST(128, 32, 0, 400, 1000, 320, 0, 115, 100, 96), d = CB_COST(128, 64, 900, 745, 2900, 510, 700, 205, 1000, 140),
+                       c = CB_COST(128, 32, 1800, 380, 1000, 320, 1500, 95, 100, 96), d = CB_COST(128, 64, 900, 745, 2900, 510, 2000, 190, 1000, 140),
                        ab = a < b ? a : b, cd = c < d ? c : d;
         // 128 x 128 halves what a column costs in filter fragments and gathers; from two tiles per compute unit on, so that they
         // have others to run beside.  us, 128 x 64 / 128 x 128: 64 -> 128, 1x1, 101 376 pixels 33 / 20; 128 -> 256, 1x1, 41 216 in blocks 29 / 18;
