@@ -786,12 +786,12 @@ hipError_t launch_listed_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbi
 // of the pixels changed, 220 / 242 at 1, 341 / 377 at 6, 450 / 454 at 10, 641 / 598 at 20, 977 / 909 at 50; at 900x1600 (368 MB) 128 / 136
 // at 0.2 %, 298 / 332 at 10, 384 / 387 at 15, 543 / 506 at 30; 64 -> 128 at 1080p (265 MB) 97 / 89 at 0.2 %, 120 / 116 at 1, 154 / 157 at 3,
 // 251 / 302 at 10, 367 / 360 at 15, 504 / 475 at 30; 32 -> 64 at 1440x2560 (236 MB) 106 / 90 at 1 %, 140 / 130 at 3, 177 / 184 at 6, 214 / 256
-// at 10, 436 / 411 at 30; 128 -> 64 at 720x1280 (236 MB) 106 / 86 at 1 %, 172 / 156 at 10; 64 -> 64 at 900x1280 (147 MB) 69 / 61 at 1 %,
+// at 10, 436 / 411 at 30; 64 -> 96 at 1080p 173 / 189 at 5; 128 -> 64 at 720x1280 (236 MB) 106 / 86 at 1 %, 172 / 156 at 10, 200 / 186 at 15; 64 -> 64 at 900x1280 (147 MB) 69 / 61 at 1 %,
 // 120 / 100 at 10, 195 / 176 at 30.
 int2 state_read_once(const Geom& g, int esz, bool shadow)
 {
     const double state = (double)g.C * g.P * esz, out_px = (double)g.O * esz;
-    const double from = state >= 300e6 ? 0.0 : state >= 200e6 ? 25e6 / out_px : 2e9;
+    const double from = state >= 300e6 ? 0.0 : state >= 200e6 ? 23e6 / out_px : 2e9;
     const double below = 160e6 / (out_px + 0.8 * g.C * esz * (shadow ? 2 : 1));
     return make_int2((int)std::min(from, 2e9), (int)std::min(below, 2e9));
 }
