@@ -80,3 +80,9 @@ def test_tile_cases_cover_every_tile(rules):
     every = {(s, t, b) for s in (16, 32, 64, 128) for b in (False, True) for t in range(rules.tiles(s))}
     every |= {(129, t, True) for t in range(rules.tiles(129))}
     assert {(s, t, b) for s, t, b, *_ in TILE_CASES} | {(large, t, True) for _, t in LARGE_MAP_REGIONS} == every
+
+
+@pytest.mark.parametrize("c,o,n,tile", [(512, 512, 1425, 2), (512, 512, 1300, 2), (256, 512, 1425, 3)])
+def test_medium_counts_with_short_and_long_filters(rules, c, o, n, tile):
+    """bfloat16, 3x3, 46x82: between one round of 128 x 32 tiles and two of 64 x 32 ones."""
+    assert rules.tile(True, n, o, 46 * 82, c, 9, 9 * c) == tile
