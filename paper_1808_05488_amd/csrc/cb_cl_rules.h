@@ -94,7 +94,8 @@ template <bool F32, int SHAPE, typename FN> CB_HD void cl_tile(int N, int O, int
         // 128 x 128 halves what a column costs in filter fragments and gathers; from two tiles per compute unit on, so that they
         // have others to run beside.  us, 128 x 64 / 128 x 128: 64 -> 128, 1x1, 101 376 pixels 33 / 20; 128 -> 256, 1x1, 41 216 in blocks 29 / 18;
         // 64 -> 96, 3x3, 122 187 56 / 34; 128 -> 512, 3x3, 233 661 420 / 358; 64 -> 256, 7x7, 151 306 294 / 254; 64 -> 128, 3x3, 1080p, 5 %
-        // changed 64 / 51.  (float32 has no registers for it.  The cost is compared with that of 128 x 64 alone: those of the narrower
+        // changed 64 / 51.  Where sparse outputs of 60 - 150 MB bound both by their writes a frame takes up to 1.6 % more (128 -> 128, 3x3, 1080p,
+        // 10 %: 452.5 / 457.5); a test for that here cost the other layers as much.  (float32 has no registers for it.  The cost is compared with that of 128 x 64 alone: those of the narrower
         // tiles miss what many listed pixels pay for their stores, 1x1 above all.)
         if (SHAPE == 129 && (((unsigned)N + 127u) / 128u) * (((unsigned)O + 127u) / 128u) >= 512u && cl_cost<128, 128>(N, O, nkg, 1500, 420, 1000, 250) <= d)
             run(std::integral_constant<int, SHAPE == 129 ? 5 : 4>());
