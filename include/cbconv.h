@@ -80,7 +80,8 @@ typedef enum {
 
 /* How the last three processing steps are executed. */
 typedef enum {
-    CB_BACKEND_AUTO = 0,      /* fused where available, else explicit */
+    CB_BACKEND_AUTO = 0,      /* fused where available, closed-loop layers also beyond the limits of CB_BACKEND_FUSED,
+                                 else explicit */
     CB_BACKEND_EXPLICIT = 1,  /* three kernels; X' and Y' are materialised in the scratch buffer */
     CB_BACKEND_FUSED = 2      /* one kernel: receptive fields gathered into LDS, MFMA, bias/ReLU, scatter;
                                  X' and Y' never exist in memory (CB_EINVAL where it is not available:
@@ -133,11 +134,13 @@ typedef struct {
  *  state_bytes   : per-layer, lives as long as the layer (input state, cached
  *                  output, bit-packed change maps, index list, repacked filter
  *                  matrix -- the "variables to be stored per-layer" of Fig. 2;
- *                  closed-loop layers on the fused back end keep a second,
- *                  pixel-major copy of the input state for the gather if their
- *                  number of input channels is a power of two, float32 from 16
- *                  and bfloat16 from 32 on, or, padded to 16 bytes a pixel, up
- *                  to 4 / 8.  Such layers, and those that gather from a
+ *                  closed-loop layers keep a second, pixel-major copy of the
+ *                  input state for the gather, its pixels padded to whole
+ *                  16-byte pieces: with CB_BACKEND_AUTO whatever their number of
+ *                  input channels (while the copy stays below 2^32 - 256 bytes,
+ *                  up to 65 536 values a filter and 32 768 channels), with
+ *                  CB_BACKEND_FUSED if it is a power of two, float32 from 16 and
+ *                  bfloat16 from 32 on, or up to 4 / 8.  Such layers, and those that gather from a
  *                  producer's pixel-major output, multiply float32 values as six
  *                  bfloat16 products of exact three-term splits, accumulated in
  *                  float32; their repacked filters take 6 bytes a value.  Sums
@@ -221,7 +224,9 @@ int cb_layer_changes(cb_layer_t *layer, const uint8_t **m_in_dev, const uint8_t 
  * X' (R x ld) and Y' (c_out x ld) matrices of the last processed column chunk with
  * their leading dimension, column count and number of k-splits (device int32[3]: {ld, ncols,
  * nsplit}; Y' holds nsplit partial products of O x ld each, which the output update adds).
- * Only layers with the explicit back end have these matrices (CB_ESTATE otherwise). */
+ * Layers with the explicit back end have these matrices, and those of CB_BACKEND_AUTO that CB_BACKEND_FUSED would not
+ * take (CB_ESTATE otherwise); of the latter the closed-loop ones, which run fused, compute them in this call, from the state as
+ * the last frame left it. */
 int cb_layer_state(const cb_layer_t *layer, const void **state_dev);
 int cb_layer_matrices(const cb_layer_t *layer, const void **xprime_dev, const void **yprime_dev,
                       const int32_t **ld_ncols_dev);

@@ -15,14 +15,32 @@ namespace cb {
 // Divisions by layer constants.  tap / kw = tap * inv_kw >> 16 for the few taps there are.  q / Wo = q * inv_wo >> 42
 // with inv_wo = ceil(2^42 / Wo) (0: divide).  The quotient is exact while q * Wo < 2^42: q < 2^30 in every layer, so Wo < 2^12
 // is enough.  The product lies below (q / Wo + 1) * 2^42 and has to fit 64 bits, which takes Ho <= 2^22.
-struct ClDiv { unsigned long long inv_wo; unsigned inv_kw; };
+// k / Cs = k * inv_cs >> 32 with inv_cs = ceil(2^32 / Cs): exact while k * Cs < 2^32 (cl_fits keeps k below 2^16 + 2^12 and Cs up to 2^15).
+struct ClDiv { unsigned long long inv_wo; unsigned inv_kw, inv_cs; };
 
-inline ClDiv cl_div(int Wo, int Ho, int kw)
+// What the kernel's index arithmetic takes: the packed filter matrix of a row tile stays below 2^31 bytes, and the products above hold.
+CB_HD bool cl_fits(int Cs, int taps) { return Cs <= 32768 && (long long)Cs * taps <= 65536; }
+
+inline ClDiv cl_div(int Wo, int Ho, int kw, int Cs = 4)
 {
     ClDiv d;
     d.inv_wo = Wo < 4096 && Ho <= (1 << 22) ? ((1ull << 42) + (unsigned)Wo - 1ull) / (unsigned)Wo : 0ull;
     d.inv_kw = (65536u + (unsigned)kw - 1u) / (unsigned)kw;
+    d.inv_cs = (unsigned)(((1ull << 32) + (unsigned)Cs - 1ull) / (unsigned)Cs);
     return d;
+}
+
+// tap of value k of a filter (Cs > 1)
+CB_HD unsigned cl_tap(const ClDiv& d, unsigned k) { return (unsigned)(((unsigned long long)k * d.inv_cs) >> 32); }
+
+// The piece that lies dt taps and cl < Cs channels behind value kb of a filter: its tap, and its channel less cl (modulo 2^32).  kb is the
+// same for a whole workgroup, so its division is the scalar unit's.
+CB_HD void cl_piece(const ClDiv& d, unsigned Cs, unsigned kb, unsigned dt, unsigned cl, unsigned& tap, unsigned& coff)
+{
+    const unsigned tb = cl_tap(d, kb), s = kb - tb * Cs;
+    const bool next = s + cl >= Cs;
+    tap = tb + dt + (next ? 1u : 0u);
+    coff = s - (next ? Cs : 0u);
 }
 
 CB_HD int cl_row(const ClDiv& d, int q, int Wo) { return d.inv_wo ? (int)(((unsigned long long)(unsigned)q * d.inv_wo) >> 42) : q / Wo; }

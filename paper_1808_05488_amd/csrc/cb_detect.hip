@@ -110,7 +110,7 @@ __device__ __forceinline__ uint64_t spread4(uint64_t v)
 template <typename T, int VEC, int CS>
 __global__ __launch_bounds__(256) void detect_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2,
                                                      uint64_t* __restrict__ mbits0, int* __restrict__ ctl,
-                                                     int C, int P, int nwords, float tau, int flags)
+                                                     int C, int Cs, int P, int nwords, float tau, int flags)
 {
     typedef typename Pack<T, VEC>::type V;
     const int par = ctl[CTL_FRAME] & 1;          // which of the two map buffers and counters this frame fills
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256) void detect_kernel(const T* __restrict__ x, T*
             if (S2) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v)
-                    if (upd & (1u << v)) S2[(size_t)(p0 + v) * C + c] = x[off + v];
+                    if (upd & (1u << v)) S2[(size_t)(p0 + v) * Cs + c] = x[off + v];
             }
         }
     }
@@ -205,12 +205,13 @@ __global__ __launch_bounds__(256) void detect_kernel(const T* __restrict__ x, T*
 // PLX = 16 (one pixel per lane only): 16 instead of 64 pixel lanes per workgroup, for maps with so
 // few pixels that 64-pixel workgroups would leave most compute units idle; such a workgroup owns a
 // quarter of a 64-pixel word of the bit map and stores it as a half word.
-// SH: the layer keeps a channel-last shadow of its state (S2), C == CS*CPT, and channel q of group g is
-// g*CPT + q instead of g + q*CS, so that a lane's channels are neighbours in the shadow.
+// SH: the layer keeps a channel-last shadow of its state (S2), and channel q of group g is g*CPT + q instead of
+// g + q*CS, so that a lane's channels are neighbours in the shadow.  C <= CS*CPT; the shadow's pixels are the C channels rounded
+// up to whole 16-byte pieces, zero behind the last.  inv_per = ceil(2^20 / pieces of a pixel) divides a piece's number (below 1 024) by it.
 template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false>
 __global__ __launch_bounds__((PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS)
 void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2, uint64_t* __restrict__ mbits0,
-                       int* __restrict__ ctl, int C, int P, int nwords, float tau, int flags, int2 stream)
+                       int* __restrict__ ctl, int C, int Cs, unsigned inv_per, int P, int nwords, float tau, int flags, int2 stream)
 {
     typedef typename Pack<T, VEC>::type V;
     // which of the two map buffers and counters this frame fills: the frame count lives on the device
@@ -347,17 +348,24 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
         }
     }
 
-    // Shadow of a first layer: its few channels are in this lane's registers, a pixel is one 16-byte store.
-    if constexpr (CS == 1 && CPT * sizeof(T) <= 16) {
+    // Shadow of a first layer: its few channels are in this lane's registers, a pixel is one 16-byte store (5 - 8 float32 channels: two).
+    if constexpr (CS == 1) {
         if (S2 != nullptr && upd) {
-            constexpr int EPV = 16 / (int)sizeof(T);
+            constexpr int EPV = 16 / (int)sizeof(T), PIECES = (CPT + EPV - 1) / EPV;
 #pragma unroll
             for (int v = 0; v < VEC; ++v)
                 if (upd & (1u << v)) {
-                    __attribute__((aligned(16))) T e[EPV];
 #pragma unroll
-                    for (int j = 0; j < EPV; ++j) e[j] = j < CPT && j < C ? reinterpret_cast<const T*>(&xv[j < CPT ? j : 0])[v] : (T)0;
-                    *reinterpret_cast<uint4*>(S2 + (size_t)(p0 + v) * EPV) = *reinterpret_cast<const uint4*>(e);
+                    for (int h = 0; h < PIECES; ++h) {
+                        if (h * EPV >= Cs) break;
+                        __attribute__((aligned(16))) T e[EPV];
+#pragma unroll
+                        for (int j = 0; j < EPV; ++j) {
+                            const int c = h * EPV + j;
+                            e[j] = c < CPT && c < C ? reinterpret_cast<const T*>(&xv[c < CPT ? c : 0])[v] : (T)0;
+                        }
+                        *reinterpret_cast<uint4*>(S2 + (size_t)(p0 + v) * Cs + h * EPV) = *reinterpret_cast<const uint4*>(e);
+                    }
                 }
         }
     }
@@ -396,7 +404,15 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
                 for (int v = 0; v < VEC; ++v)
                     if (upd & (1u << v)) s_pix[before + __popc(upd & ((1u << v) - 1u))] = (int)(p0 + v);
             }
-            const int lp = 31 - __builtin_clz((unsigned)(CMAX / EPV));     // 16-byte pieces per pixel = 1 << lp
+            const int per = Cs / EPV;                 // 16-byte pieces per pixel
+            // bytes of a pixel's last piece that hold channels
+            unsigned keep[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int n = (C - (Cs - EPV)) * (int)sizeof(T) - 4 * j;
+                keep[j] = n >= 4 ? ~0u : n == 2 ? 0xFFFFu : 0u;
+            }
+            static_assert(KMAX * (CMAX / EPV) <= 1024, "pieces of a round, as inv_per takes them");
             // The 16-byte LDS stores want the same pixel of EPV channels in neighbouring registers,
             // the loads delivered the VEC pixels of one channel there.  Made opaque here, the
             // values are rearranged here -- and not right behind each load, where the compiler
@@ -424,11 +440,12 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
                     }
                 lds_barrier();                    // (also: s_pix is written; the buffer's readers of two rounds ago are done)
                 const int nrow = total - k0 < KMAX ? total - k0 : KMAX;
-                for (int i = tid; i < (nrow << lp); i += NT) {
-                    const int k = i >> lp, pc = i & ((1 << lp) - 1);
+                for (int i = tid; i < nrow * per; i += NT) {
+                    const int k = (int)(((unsigned)i * inv_per) >> 20), pc = i - k * per;
                     typedef unsigned uvec4 __attribute__((ext_vector_type(4)));
-                    __builtin_nontemporal_store(*reinterpret_cast<const uvec4*>(&stage[buf][k * PITCH + pc * EPV]),
-                                                reinterpret_cast<uvec4*>(S2 + (size_t)s_pix[k0 + k] * C + pc * EPV));
+                    uvec4 v4 = *reinterpret_cast<const uvec4*>(&stage[buf][k * PITCH + pc * EPV]);
+                    if (pc == per - 1) v4 &= uvec4{keep[0], keep[1], keep[2], keep[3]};
+                    __builtin_nontemporal_store(v4, reinterpret_cast<uvec4*>(S2 + (size_t)s_pix[k0 + k] * Cs + pc * EPV));
                 }
             }
         }
@@ -449,7 +466,7 @@ constexpr int APPLY_CC = 128;
 template <typename T>
 __global__ __launch_bounds__(256) void state_apply_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2,
                                                           const uint64_t* __restrict__ mbits0,
-                                                          const int* __restrict__ ctl, int C, int P, int nwords)
+                                                          const int* __restrict__ ctl, int C, int Cs, int P, int nwords)
 {
     typedef typename Pack<T, 4>::type V4;                  // four consecutive pixels of one channel
     constexpr int E16 = 16 / (int)sizeof(T);               // elements per 16 bytes
@@ -527,13 +544,15 @@ __global__ __launch_bounds__(256) void state_apply_kernel(const T* __restrict__ 
                 }
             }
             if (S2) {
+                const int cs = Cs - c0 < APPLY_CC ? Cs - c0 : APPLY_CC, zero = cs - cn;     // channels that pad a pixel of the shadow: up to 3 / 7
+                for (int i = tid; i < nchg * zero; i += 256) stage[(i / zero) * PITCH + cn + i % zero] = (T)0;
                 __syncthreads();
-                const int per = cn / E16;                  // 16-byte pieces per pixel (the shadow's C is a power of two >= 16 / 32)
+                const int per = cs / E16;                  // 16-byte pieces per pixel
                 for (int i = tid; i < nchg * per; i += 256) {
                     const int kk = i / per, pc = i - kk * per;
                     typedef unsigned uvec4 __attribute__((ext_vector_type(4)));
                     const uvec4 v4 = *reinterpret_cast<const uvec4*>(&stage[kk * PITCH + pc * E16]);
-                    __builtin_nontemporal_store(v4, reinterpret_cast<uvec4*>(S2 + (size_t)s_pix[kk] * C + c0 + pc * E16));
+                    __builtin_nontemporal_store(v4, reinterpret_cast<uvec4*>(S2 + (size_t)s_pix[kk] * Cs + c0 + pc * E16));
                 }
                 __syncthreads();                           // the tile and s_pix are rewritten by the next chunk / word
             }
@@ -564,45 +583,49 @@ __global__ __launch_bounds__(256) void shadow_rebuild_kernel(const T* __restrict
 }
 
 template <typename T, int VEC, int CS, int CPT, int PLX = 0>
-void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int P, float tau, int flags, int2 stream, hipStream_t st, Tm tm)
+void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int Cs, int P, float tau, int flags, int2 stream, hipStream_t st, Tm tm)
 {
     constexpr int PL = PLX ? PLX : (CS >= 4 ? 64 : 256 / CS);
     const long px_per_block = (long)PL * VEC;
     const unsigned grid = (unsigned)((P + px_per_block - 1) / px_per_block);
+    const unsigned per = (unsigned)Cs * (unsigned)sizeof(T) / 16u, inv_per = per ? ((1u << 20) + per - 1u) / per : 0u;
+#define CB_REG(sh, shadow)                                                                                                          \
+    CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX, sh>), dim3(grid), dim3(PL * CS), st, tm, x, S, shadow, mbits, ctl, C, Cs, \
+              inv_per, P, (P + 63) / 64, tau, flags, stream)
     if constexpr (CS >= 4 && (CPT * sizeof(T)) % 16 == 0) {
-        // (launch_t only passes a shadow on when the variant's registers hold exactly C channels)
-        if (S2 != nullptr && C == CS * CPT) {
-            CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX, true>), dim3(grid), dim3(PL * CS), st, tm, x, S, S2, mbits,
-                      ctl, C, P, (P + 63) / 64, tau, flags, stream);
+        // (launch_t only passes a shadow on when the variant's registers hold all C channels)
+        if (S2 != nullptr) {
+            CB_REG(true, S2);
             return;
         }
     }
-    CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX>), dim3(grid), dim3(PL * CS), st, tm, x, S, CS == 1 && CPT * sizeof(T) <= 16 ? S2 : (T*)nullptr, mbits,
-              ctl, C, P, (P + 63) / 64, tau, flags, stream);
+    CB_REG(false, CS == 1 ? S2 : (T*)nullptr);
+#undef CB_REG
 }
 
 template <typename T, int VEC>
-void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int P, float tau, int flags, int2 stream, hipStream_t st, Tm tm)
+void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int Cs, int P, float tau, int flags, int2 stream, hipStream_t st, Tm tm)
 {
     // channel groups CS and channels per lane CPT with CS*CPT >= C
-    if (C <= 4)        launch_reg<T, VEC, 1, 4>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
-    else if (C <= 8)   launch_reg<T, VEC, 1, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
-    else if (C <= 16)  launch_reg<T, VEC, 4, 4>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
-    else if (C <= 32)  launch_reg<T, VEC, 4, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
-    else if (C <= 64)  launch_reg<T, VEC, 8, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    if (C <= 4)        launch_reg<T, VEC, 1, 4>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    else if (C <= 8)   launch_reg<T, VEC, 1, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    // (bfloat16 with a shadow: eight channels per lane are one of its 16-byte pieces)
+    else if (C <= 16 && !(sizeof(T) == 2 && S2)) launch_reg<T, VEC, 4, 4>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    else if (C <= 32)  launch_reg<T, VEC, 4, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    else if (C <= 64)  launch_reg<T, VEC, 8, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
     // maps of fewer than 128 x 64 pixels with many channels: 16-pixel workgroups reach every compute unit
-    else if (VEC == 1 && P < 8192 && C <= 128) launch_reg<T, 1, 16, 8, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
-    else if (VEC == 1 && P < 8192 && C <= 256) launch_reg<T, 1, 16, 16, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
-    else if (VEC == 1 && P < 8192 && C <= 512) launch_reg<T, 1, 16, 32, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
-    else if (C <= 128) launch_reg<T, VEC, 16, 8>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    else if (VEC == 1 && P < 8192 && C <= 128) launch_reg<T, 1, 16, 8, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    else if (VEC == 1 && P < 8192 && C <= 256) launch_reg<T, 1, 16, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    else if (VEC == 1 && P < 8192 && C <= 512) launch_reg<T, 1, 16, 32, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    else if (C <= 128) launch_reg<T, VEC, 16, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
     // one pixel per lane leaves registers for more channels per lane (deep layers: many channels, few pixels)
-    else if (VEC == 1 && C <= 256) launch_reg<T, 1, 16, 16>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
-    else if (VEC == 1 && C <= 512) launch_reg<T, 1, 16, 32>(x, S, S2, mbits, ctl, C, P, tau, flags, stream, st, tm);
+    else if (VEC == 1 && C <= 256) launch_reg<T, 1, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    else if (VEC == 1 && C <= 512) launch_reg<T, 1, 16, 32>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
     else {
         // more channels than the register-resident variants hold: looped variant
         const long px_per_block = 64L * VEC;
         const unsigned grid = (unsigned)((P + px_per_block - 1) / px_per_block);
-        CB_LAUNCH((detect_kernel<T, VEC, 4>), dim3(grid), dim3(256), st, tm, x, S, S2, mbits, ctl, C, P,
+        CB_LAUNCH((detect_kernel<T, VEC, 4>), dim3(grid), dim3(256), st, tm, x, S, S2, mbits, ctl, C, Cs, P,
                   (P + 63) / 64, tau, flags);
     }
 }
@@ -617,7 +640,7 @@ void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int P, 
 // a word; the changed-pixel count adds the bits that were newly set, so a pixel reached through
 // several candidates (2x2 pooling maps up to four of them to one pixel) is counted once.  Duplicates race benignly: whoever copies the
 // pixel first makes the others compare equal, and the bit is set either way.
-// SH: the layer keeps a channel-last shadow S2 of its state (C a power of two).  The values of the candidates are
+// SH: the layer keeps a channel-last shadow S2 of its state and C is a power of two (other shadows are written from registers).  The values of the candidates are
 // staged in LDS ahead of the first barrier of a round and, once it is known which candidates fired, written to
 // S2 with consecutive lanes on consecutive channels; two alternating buffers, so the barriers the round has anyway
 // are enough.  (Written from the registers that hold them they are 4-byte stores to a different line per lane.)
@@ -759,7 +782,7 @@ hipError_t launch_listed_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbi
 #define CB_LISTED(cs, plc)                                                                                          \
     do {                                                                                                            \
         {                                                                                                           \
-            if (S2 != nullptr && g.Cs == g.C && g.C >= 16) {                                                        \
+            if (S2 != nullptr && g.C >= 16 && (g.C & (g.C - 1)) == 0) {                                                        \
                 CB_LAUNCH((detect_listed_kernel<T, cs, plc, true>), dim3(std::min(2048, (cand_cap + plc - 1) / plc)), \
                           dim3(cs * plc), st, tm, x, S, S2, mbits, ctl, cand, cand_count, cand_cap, g.C, g.Cs, g.P, g.W, tau, \
                           flags, pool_w, cand_W);                                                                   \
@@ -820,8 +843,8 @@ hipError_t launch_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int
     const bool aligned = P % 4 == 0 && (uintptr_t)x % valign == 0 && (uintptr_t)S % valign == 0;
     const bool vec4 = P >= (sizeof(T) == 4 ? 65536 : 32768) && !one_px &&
                       (aligned || (sizeof(T) == 2 && g.C <= 128)) && (g.C <= 128 || (P >= 65536 && !(S2 != nullptr && g.C <= 512)));
-    if (vec4) launch_v<T, 4>(x, S, S2, mbits, ctl, g.C, P, tau, flags, stream, st, tm);
-    else      launch_v<T, 1>(x, S, S2, mbits, ctl, g.C, P, tau, flags, stream, st, tm);
+    if (vec4) launch_v<T, 4>(x, S, S2, mbits, ctl, g.C, g.Cs, P, tau, flags, stream, st, tm);
+    else      launch_v<T, 1>(x, S, S2, mbits, ctl, g.C, g.Cs, P, tau, flags, stream, st, tm);
     return hipGetLastError();
 }
 
@@ -830,8 +853,8 @@ hipError_t launch_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int
 hipError_t launch_detect(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
                          float tau, int flags, hipStream_t st, Tm tm)
 {
-    // a shadow is kept for layers with a power-of-two channel count, and padded for first layers (fused_channel_last, fused_padded)
-    if (S2 && g.Cs == g.C && g.C > (g.bf16 ? 8 : 4) && (g.C < (g.bf16 ? 32 : 16) || (g.C & (g.C - 1)) != 0)) return hipErrorInvalidValue;
+    // the pixels of a shadow are whole 16-byte pieces
+    if (S2 && (g.Cs < g.C || g.Cs % (g.bf16 ? 8 : 4) != 0)) return hipErrorInvalidValue;
     if (g.bf16)
         return launch_t<uint16_t>(g, (const uint16_t*)x, (uint16_t*)S, (uint16_t*)S2, mbits, ctl, tau, flags,
                                   st, tm);
@@ -845,10 +868,10 @@ hipError_t launch_state_apply(const Geom& g, const void* x, void* S, void* S2, c
     const unsigned grid = (unsigned)std::min(nwords, 8192);
     if (g.bf16)
         CB_LAUNCH(state_apply_kernel<uint16_t>, dim3(grid), dim3(256), st, tm, (const uint16_t*)x, (uint16_t*)S, (uint16_t*)S2,
-                  mbits, ctl, g.C, g.P, nwords);
+                  mbits, ctl, g.C, g.Cs, g.P, nwords);
     else
         CB_LAUNCH(state_apply_kernel<float>, dim3(grid), dim3(256), st, tm, (const float*)x, (float*)S, (float*)S2, mbits, ctl,
-                  g.C, g.P, nwords);
+                  g.C, g.Cs, g.P, nwords);
     return hipGetLastError();
 }
 

@@ -21,9 +21,8 @@ constexpr int FUSED_GUARD = 128;        // bytes readable ahead of the gather so
 constexpr int FUSED_ZERO_TAP = 60;      // tap index of the zero rows that pad K (never inside the image)
 constexpr int FUSED_TAB_PAD = 64;       // entries of length 0 that close the chunk table: a group of gather rounds (up to 4 rounds of 16 fetchers) may read this far past the last chunk
 
-// Channel-last variant (C a power of two: >= 16 float32, >= 32 bfloat16; or up to 4 / 8, padded to 16 bytes a pixel): the
-// gather reads a pixel-major shadow of the state (or a producer's pixel-major output), K is walked tap-major, no chunk
-// table (cb_fused_cl.hip).
+// Channel-last variant (any channel count, the pixels padded to whole 16-byte pieces): the gather reads a pixel-major
+// shadow of the state (or a producer's pixel-major output), K is walked tap-major, no chunk table (cb_fused_cl.hip).
 
 // Chunk table.  The rows of X' that belong to one input channel c and one filter row j,
 // r = (c*kh + j)*kw + i for i = 0..kw-1 (construction of X below Eq. 2), are kw consecutive
@@ -118,11 +117,11 @@ __device__ __forceinline__ void st_out4(uint16_t* p, const float (&v)[4])
 // fragment order, the chunk table and the launch plan (synchronises the stream once when it uploads a chunk
 // table, i.e. for the channel-first kernels).
 bool fused_supported(const Geom& g);
-// whether a layer of this geometry that keeps an input state uses the channel-last variant
+// whether a layer of this geometry that keeps an input state can keep a pixel-major shadow of it and use the channel-last variant
+bool fused_shadow(const Geom& g);
+// whether a CB_PROPAGATE layer of this geometry can gather from its producer's pixel-major output
 bool fused_channel_last(const Geom& g);
-// ... or pads the pixels of its shadow to 16 bytes for it (up to 4 float32 / 8 bfloat16 channels: first layers)
-bool fused_padded(const Geom& g);
-size_t fused_pack_bytes(const Geom& g);
+size_t fused_pack_bytes(const Geom& g, bool channel_last);
 size_t fused_table_bytes(const Geom& g);
 hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, bool channel_last, hipStream_t st,
                          FusedPlan* plan);

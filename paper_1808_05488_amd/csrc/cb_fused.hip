@@ -4,6 +4,7 @@
 // column of X') and the plan of a launch (units per LDS stage).  The main kernels are in cb_fused_f32.hip and
 // cb_fused_bf16.hip.
 #include "cb_fused.h"
+#include "cb_cl_rules.h"
 
 #include <vector>
 
@@ -150,15 +151,15 @@ int stage_units(const Geom& g, int cw, int bn, unsigned tab_lds, const std::vect
 
 }  // namespace
 
-size_t fused_pack_bytes(const Geom& g)
+size_t fused_pack_bytes(const Geom& g, bool channel_last)
 {
     // (bfloat16: padded to 128 rows, the unit of the channel-last kernel)
-    const size_t Rs = fused_padded(g) ? (size_t)g.Cs * g.kh * g.kw : (size_t)g.R;
+    const size_t Rs = channel_last ? (size_t)g.Cs * g.kh * g.kw : (size_t)g.R;
     const size_t Rpad = g.bf16 ? (Rs + 127) / 128 * 128 : (Rs + KC - 1) / KC * KC;
     const size_t Mt16 = (size_t)(g.O + 127) / 128 * 8;     // 16-row tiles, padded to the largest row tile
     // 16 bytes per lane per k-group: 16 rows of float32, 32 rows of bfloat16
     // (float32, channel-last: three bfloat16 terms, 16 bytes each per lane and 32 rows)
-    if ((fused_channel_last(g) || fused_padded(g)) && !g.bf16) return Mt16 * (Rpad / 32) * 3 * 64 * 16;
+    if (channel_last && !g.bf16) return Mt16 * (Rpad / 32) * 3 * 64 * 16;
     return Mt16 * (Rpad / (g.bf16 ? 32 : 16)) * 64 * 16;
 }
 
@@ -186,19 +187,19 @@ bool fused_supported(const Geom& g)
 
 bool fused_channel_last(const Geom& g)
 {
-    // (bfloat16 from 32 channels on: change detection stages the shadow rows 16 bytes = 8 channels per lane)
     return g.C >= (g.bf16 ? 32 : 16) && (g.C & (g.C - 1)) == 0 && fused_supported(g);
 }
 
-bool fused_padded(const Geom& g)
+// (32-bit byte offsets into the shadow)
+bool fused_shadow(const Geom& g)
 {
-    return g.C <= (g.bf16 ? 8 : 4) && fused_supported(g) && (unsigned long long)g.P * 16 <= 0xFFFFFF00ull;
+    return cl_fits(g.Cs, g.kh * g.kw) && (unsigned long long)g.Cs * g.P * (g.bf16 ? 2 : 4) <= 0xFFFFFF00ull;
 }
 
 hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, bool channel_last, hipStream_t st,
                          FusedPlan* plan)
 {
-    plan->cl = channel_last && (fused_channel_last(g) || fused_padded(g));
+    plan->cl = channel_last;
     // 16-row (float32) / 32-row (bfloat16) groups of K; the channel-last bfloat16 kernel walks K in units of 128 rows
     const int KG = (plan->cl && g.bf16) ? (g.Cs * g.kh * g.kw + 127) / 128 * 4 : (g.R + KC - 1) / KC * KC / (g.bf16 ? 32 : 16);
     const int Mt16 = (g.O + 127) / 128 * 8;

@@ -3,9 +3,10 @@
 // side, so a filter tap of a listed pixel is C contiguous elements: fully coalesced 16-byte loads, no chunk table.
 //
 // Work item = BN listed columns x BM output channels x all of K; four wavefronts, WGM x WGN, each
-// (16*TM) x (16*TN).  K is walked tap-major, k' = (j*kw + i)*Cs + c (Cs a power of two: C, or the 16
-// bytes to which the pixels of a first layer's shadow are padded), in groups of 32 (one step of
-// v_mfma_f32_16x16x32_bf16), UKG groups = one stage.
+// (16*TM) x (16*TN).  K is walked tap-major, k' = (j*kw + i)*Cs + c (Cs: the channels of a pixel of the shadow, C rounded up to
+// whole 16-byte pieces), in groups of 32 (one step of v_mfma_f32_16x16x32_bf16), UKG groups = one stage.  Where Cs is a power of
+// two (P2) a piece finds its tap by shifts; elsewhere the stage's first tap comes from one multiplication on the scalar unit, and a piece is
+// in the tap of the stage's first value, dt taps on, or one further (cl_piece; two compares and adds a stage more).
 //   B operand: a thread fetches 16-byte pieces of a column (consecutive lanes: consecutive pieces) and stores them to
 //     LDS, [column][k], column pitch 4 mod 32 words (128 float32 columns: 20), so that the 16-byte fragment reads of eight
 //     neighbouring columns cover all 32 banks.  Two stage buffers alternate; stage u+1 is stored and a later one requested ahead of
@@ -77,19 +78,22 @@ __device__ __forceinline__ unsigned taps_within(int o, int k, int size)
 // Bound by the latency of its loads (few such sums) or the float32 matrix instruction (many).  Full updates, us, finite / one NaN /
 // every value infinite: 64 -> 64, 3x3, 480x640 227 / 258 / 669, 256 -> 256, 3x3, 92x164 120 / 173 / 410.  A lane that walks K by itself
 // for each of its sums took 547 / 28 100 and 2 606 / 16 960 for the latter two; a kernel on the float32 instruction throughout 330 and 180 for each.
-template <int TM>
+template <int TM, bool P2>
 __device__ __forceinline__ void exact_tiles(const Geom& g, const ClDiv& div, const __amdgpu_buffer_rsrc_t srsrc, const __amdgpu_buffer_rsrc_t krsrc,
                                             const float* __restrict__ KT, int nkg, int at, int lane, int q, int m, floatx4 (&sum)[TM])
 {
-    constexpr int U = 2;                         // k-groups in flight (nkg is even)
+    constexpr int U = P2 ? 2 : 1;                 // k-groups in flight (nkg is even; one without shifts: the second spilled registers of the whole kernel)
     const int lq = lane >> 4;
-    const int lc = 31 - __builtin_clz((unsigned)g.Cs);
+    const int lc = 31 - __builtin_clz((unsigned)g.Cs);       // (P2)
     const unsigned taps = (unsigned)(g.kh * g.kw);
+    auto tap_of = [&](unsigned k) { return P2 ? k >> lc : cl_tap(div, k); };
+    auto channel_of = [&](unsigned k, unsigned tap) { return P2 ? k & (unsigned)(g.Cs - 1) : k - tap * (unsigned)g.Cs; };
+    auto pixels = [&](unsigned n) { return P2 ? n << lc : n * (unsigned)g.Cs; };
     const int qq = q < 0 ? 0 : q;
     const int yo = cl_row(div, qq, g.Wo);
     const int y0 = yo * g.s - g.p, x0 = (qq - yo * g.Wo) * g.s - g.p;
     const unsigned okr = q < 0 ? 0u : taps_within(y0, g.kh, g.H), okc = taps_within(x0, g.kw, g.W);
-    const unsigned base = (unsigned)(y0 * g.W + x0) << lc;
+    const unsigned base = pixels((unsigned)(y0 * g.W + x0));
 #pragma unroll
     for (int a = 0; a < TM; ++a) sum[a] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
@@ -99,10 +103,10 @@ __device__ __forceinline__ void exact_tiles(const Geom& g, const ClDiv& div, con
         for (int u = 0; u < U; ++u) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const unsigned k = (unsigned)(32 * (kg + u) + 8 * lq + 4 * h), tap = k >> lc;
+                const unsigned k = (unsigned)(32 * (kg + u) + 8 * lq + 4 * h), tap = tap_of(k);
                 const unsigned j = (tap * div.inv_kw) >> 16, i = tap - j * (unsigned)g.kw;
                 const bool in = (((okr >> (j < 31u ? j : 31u)) & (okc >> i)) & 1u) != 0u;
-                const unsigned off = (base + ((j * (unsigned)g.W + i) << lc) + (k & (unsigned)(g.Cs - 1))) * 4u;
+                const unsigned off = (base + pixels(j * (unsigned)g.W + i) + channel_of(k, tap)) * 4u;
                 b[u][h] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(srsrc, (int)(in ? off : 0xFFFFFFF0u), 0, 0));
             }
 #pragma unroll
@@ -133,7 +137,7 @@ __device__ __forceinline__ void exact_tiles(const Geom& g, const ClDiv& div, con
                 if (__ballot(odd)) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
-                        const unsigned k = (unsigned)(32 * (kg + u) + 8 * lq + e), tap = k >> lc, c = k & (unsigned)(g.Cs - 1);
+                        const unsigned k = (unsigned)(32 * (kg + u) + 8 * lq + e), tap = tap_of(k), c = channel_of(k, tap);
                         if (!(fabsf(v[e]) < __builtin_inff())) v[e] = KT[((size_t)c * taps + tap) * g.Opad + m + 16 * a];
                     }
                 }
@@ -165,7 +169,7 @@ static_assert(3 * CL_LDS_F32 <= 163840 && cl_lds<float>(64) <= CL_LDS_F32 && cl_
               cl_lds<uint16_t>(16) <= CL_LDS_BF16 && cl_lds<float>(16, 4) <= CL_LDS_F32 && cl_lds<uint16_t>(16, 4) <= CL_LDS_BF16,
               "the widest tile takes the most LDS");
 
-template <typename T, int WGM, int WGN, int TM, int TN, int WGK = 1>
+template <typename T, bool P2, int WGM, int WGN, int TM, int TN, int WGK = 1>
 __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, const T* __restrict__ S2,
                                                  const int32_t* __restrict__ idx, const int N,
                                                  const uint4* __restrict__ KF, const float* __restrict__ KT,
@@ -204,7 +208,8 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 
     const int nkg = F32 ? (g.Cs * g.kh * g.kw + 63) / 64 * 2 : (g.Cs * g.kh * g.kw + 127) / 128 * 4;       // k-groups of the packed filter matrix
     const int nunits = (nkg + UKG - 1) / UKG;
-    const int lc = 31 - __builtin_clz((unsigned)g.Cs);
+    const int lc = 31 - __builtin_clz((unsigned)g.Cs);       // (P2)
+    auto pixels = [&](unsigned n) { return P2 ? n << lc : n * (unsigned)g.Cs; };
     const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<T*>(S2), 0, (int)((unsigned)g.Cs * (unsigned)g.P * ESZ), 0x00020000);
     constexpr unsigned NOWHERE = 0xFFFFFFF0u;
@@ -221,7 +226,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     const int wm_s = __builtin_amdgcn_readfirstlane(wm);
     const int l16 = lane & 15, lq = lane >> 4;
     const int gc = tid / PPC, ch = tid % PPC;    // first column of this thread, its piece of a stage
-    const int dt = (EPV * ch) >> lc, cl = (EPV * ch) & (g.Cs - 1);
+    const int dt = P2 ? (EPV * ch) >> lc : (int)cl_tap(div, (unsigned)(EPV * ch)), cl = P2 ? (EPV * ch) & (g.Cs - 1) : EPV * ch - dt * g.Cs;
 
     int qnext[NP];
     auto fetch_q = [&](unsigned u, int (&q)[NP]) {
@@ -274,15 +279,17 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             const int y0 = yo * g.s - g.p, x0 = xo * g.s - g.p;
             okr[p] = colv ? taps_within(y0, g.kh, g.H) : 0u;
             okc[p] = taps_within(x0, g.kw, g.W);
-            base[p] = (((unsigned)(y0 * g.W + x0) << lc) + (unsigned)cl) * ESZ;
+            base[p] = (pixels((unsigned)(y0 * g.W + x0)) + (unsigned)cl) * ESZ;
         }
 
         uint4 breg[GD][NP];
         auto gload = [&](int u, uint4 (&dst)[NP]) {
             const unsigned kb = (unsigned)u * (unsigned)UK;
-            const unsigned tap = (kb >> lc) + (unsigned)dt;
+            unsigned tap, coff;                  // the piece's tap, its channel less cl
+            if constexpr (P2) { tap = (kb >> lc) + (unsigned)dt; coff = kb & (unsigned)(g.Cs - 1); }
+            else cl_piece(div, (unsigned)g.Cs, kb, (unsigned)dt, (unsigned)cl, tap, coff);
             const unsigned j = (tap * div.inv_kw) >> 16, i = tap - j * (unsigned)g.kw;
-            const unsigned toff = (((j * (unsigned)g.W + i) << lc) + (kb & (unsigned)(g.Cs - 1))) * ESZ;
+            const unsigned toff = (pixels(j * (unsigned)g.W + i) + coff) * ESZ;
             // (rows that pad K have j >= kh, whose bit is clear, as bit 31 is for any j beyond it: kh, kw <= 31)
             const unsigned jj = j < 31u ? j : 31u;
 #pragma unroll
@@ -482,7 +489,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                     if (!__ballot(mine != 0u)) continue;
                     const int qn = qs[(wn * TN + b) * 16 + l16];
                     floatx4 sum[TM];
-                    exact_tiles<TM>(g, div, srsrc, krsrc, KT, nkg, wm_s * TM, lane, qn, mw + l16, sum);
+                    exact_tiles<TM, P2>(g, div, srsrc, krsrc, KT, nkg, wm_s * TM, lane, qn, mw + l16, sum);
 #pragma unroll
                     for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -529,7 +536,7 @@ __global__ __launch_bounds__(256) void pack_fused_split_kernel(Geom g, int Mt16,
     }
 }
 
-template <typename T, int SHAPE>
+template <typename T, int SHAPE, bool P2>
 // (wavefronts per SIMD: as many as the widest tile's registers allow.  They are worth more than wider tiles: bfloat16, O > 64
 // at 76 800 listed pixels 45 us with two, 40 us with four.)
 __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(Geom g, ClDiv div, const T* __restrict__ S2,
@@ -540,7 +547,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(G
 {
     const int N = *count;
     if (N <= 0) return;
-#define CB_BODY(...) fused_cl_body<T, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2)
+#define CB_BODY(...) fused_cl_body<T, P2, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2)
     // (the tiles of cb_cl_rules.h)
     cl_tile<sizeof(T) == 4, SHAPE>(N, g.O, g.Cs, g.kh * g.kw, g.R, [&](auto tile) __attribute__((always_inline)) {
         constexpr int t = decltype(tile)::value;
@@ -559,11 +566,13 @@ template <typename T>
 hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow, const int32_t* idx, const int* count,
                            const void* KF, const float* KT, const float* bias, int relu, T* OUT, T* OUT2, hipStream_t st, Tm tm)
 {
-    if (!plan.cl || (g.Cs & (g.Cs - 1)) != 0 || g.Cs < 16 / (int)sizeof(T) || g.bf16 != (sizeof(T) == 2)) return hipErrorInvalidValue;
-    const ClDiv div = cl_div(g.Wo, g.Ho, g.kw);
-#define CB_CL(shape)                                                                                                     \
-    CB_LAUNCH_LDS((fused_cl_kernel<T, shape>), dim3(1024), dim3(256), sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16, st, tm, g, \
-                          div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)
+    if (!plan.cl || g.Cs % (16 / (int)sizeof(T)) != 0 || g.Cs < g.C || !cl_fits(g.Cs, g.kh * g.kw) || g.bf16 != (sizeof(T) == 2)) return hipErrorInvalidValue;
+    const ClDiv div = cl_div(g.Wo, g.Ho, g.kw, g.Cs);
+    const bool p2 = (g.Cs & (g.Cs - 1)) == 0;
+#define CB_CL_LAUNCH(shape, p)                                                                                           \
+    CB_LAUNCH_LDS((fused_cl_kernel<T, shape, p>), dim3(1024), dim3(256), sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16, st, tm, g, \
+                  div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)
+#define CB_CL(shape) do { if (p2) CB_CL_LAUNCH(shape, true); else CB_CL_LAUNCH(shape, false); } while (0)
     switch (cl_shape(g.O, g.Po, sizeof(T) == 4)) {
         case 16: CB_CL(16); break;
         case 32: CB_CL(32); break;
@@ -572,6 +581,7 @@ hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow
         default: CB_CL(128);
     }
 #undef CB_CL
+#undef CB_CL_LAUNCH
     return hipGetLastError();
 }
 

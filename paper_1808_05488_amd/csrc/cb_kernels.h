@@ -30,7 +30,7 @@ struct Geom {
     int WWo;          // 64-bit words per output row of the bit-packed dilated map
     int Opad;         // O rounded up to 16: row pitch of the transposed filter matrix
     int bf16;         // element type: 0 float, 1 bfloat16 bit patterns
-    int Cs;           // channels of a pixel in the channel-last shadow: C, or the channels of 16 bytes where C is fewer
+    int Cs;           // channels of a pixel in the channel-last shadow: C rounded up to whole 16-byte pieces
 };
 
 // Small device-resident control block of a layer (int32 slots).
@@ -67,8 +67,8 @@ enum { DET_FORCE_ALL = 1,      // mark every pixel as changed (first frame)
                                // state_read_once in cb_detect.hip says so)
        DET_NO_UPDATE = 8 };    // compare and write the map only; launch_state_apply updates the state (and shadow)
 
-// S2: null, or the channel-last shadow of the state (pixel-major, Cs values per pixel: a power of two C >= 16, or the
-// 16 bytes that hold the few channels of a first layer, zero behind them), which receives the same updates as S.
+// S2: null, or the channel-last shadow of the state (pixel-major, Cs values per pixel, zero behind the C channels),
+// which receives the same updates as S.
 // mbits: the layer's two input maps, used by alternate frames and interleaved word by word (64-bit word w
 // of the map of frame parity p at index 2*w + p: the index extraction, which does not know p when it
 // starts, fetches both candidates with one 16-byte load); the frame count in ctl[CTL_FRAME] selects

@@ -69,9 +69,9 @@ int validate(const cb_layer_desc* d, cb::Geom* g)
     const int bm = cb::gemm_bm(d->c_out);
     g->Opad = (d->c_out + bm - 1) / bm * bm;
     g->bf16 = d->dtype == CB_BF16;
-    g->Cs = g->C <= (g->bf16 ? 8 : 4) ? (g->bf16 ? 8 : 4) : g->C;
+    g->Cs = g->bf16 ? (g->C + 7) & ~7 : (g->C + 3) & ~3;
     if (d->backend == CB_BACKEND_FUSED && !cb::fused_supported(*g)) return CB_EINVAL;
-    const bool fused = d->backend != CB_BACKEND_EXPLICIT && cb::fused_supported(*g);
+    const bool fused = d->backend != CB_BACKEND_EXPLICIT && cb::fused_supported(*g);     // (not the layers of use_shadow alone)
     // the pixel-major copy of the cached output is written by the fused kernel's epilogue, four channels at a time
     if (d->keep_output_channel_last &&
         (!fused || d->c_out < (g->bf16 ? 32 : 16) || (d->c_out & (d->c_out - 1)) != 0)) return CB_EINVAL;
@@ -80,19 +80,35 @@ int validate(const cb_layer_desc* d, cb::Geom* g)
     return CB_OK;
 }
 
-bool use_fused(const cb_layer_desc* d, const cb::Geom& g)
-{
-    return d->backend == CB_BACKEND_FUSED || (d->backend == CB_BACKEND_AUTO && cb::fused_supported(g));
-}
+// up to one 16-byte piece a pixel: first layers
+bool few_channels(const cb::Geom& g) { return g.C <= (g.bf16 ? 8 : 4); }
 
-// Closed-loop layers on the fused back end whose channel count allows it (16 and more: a power of two; first layers: as
-// many as 16 bytes hold, padded to that) keep a second,
-// pixel-major copy of the input state for the gather of the fused kernel.  Not feed-forward
-// layers, which rewrite the whole state every frame.
+// Closed-loop layers that do not ask for the explicit back end keep a second, pixel-major copy of the input state and run the
+// channel-last fused kernel on it: under CB_BACKEND_AUTO whatever their channel count and filter size, under
+// CB_BACKEND_FUSED, whose callers count on the memory that the header states, with the channel counts named there.  Not feed-forward
+// layers, which rewrite the whole state every frame.  What had no shadow ran the channel-first kernels or, beyond the limits of CB_BACKEND_FUSED,
+// X' and Y' in memory; frames, us, without / with: 48 -> 96 at 540x960, 3 % changed 83 / 58, 20 % 222 / 135, 5x5 stride 2 at 241x323 32 / 29;
+// 160 -> 128 at 270x480 131 / 60, bfloat16 100 / 61; 12 -> 16 at 720p 33 / 31; 5 -> 32 at 480x640 17.7 / 17.8; 9x9: 3 -> 16 at 480x640 36 / 22, 64 -> 64
+// there 352 / 118, bfloat16 165 / 49; 7x7 256 -> 256 at 60x80, bfloat16 103 / 50.
 bool use_shadow(const cb_layer_desc* d, const cb::Geom& g)
 {
-    return use_fused(d, g) && d->mode == CB_CLOSED_LOOP && (cb::fused_channel_last(g) || cb::fused_padded(g));
+    if (d->backend == CB_BACKEND_EXPLICIT || d->mode != CB_CLOSED_LOOP || !cb::fused_shadow(g)) return false;
+    return d->backend == CB_BACKEND_AUTO || few_channels(g) || cb::fused_channel_last(g);
 }
+
+bool use_fused(const cb_layer_desc* d, const cb::Geom& g)
+{
+    return d->backend == CB_BACKEND_FUSED || (d->backend == CB_BACKEND_AUTO && cb::fused_supported(g)) || use_shadow(d, g);
+}
+
+// Filters beyond what CB_BACKEND_FUSED takes, left to CB_BACKEND_AUTO: those layers run the channel-last kernel where they can keep a
+// shadow, with scratch and X' / Y' on request (cb_layer_matrices) as on the explicit back end.
+bool use_matrices(const cb_layer_desc* d, const cb::Geom& g)
+{
+    return d->backend == CB_BACKEND_EXPLICIT || !cb::fused_supported(g);
+}
+
+bool use_channel_last(const cb_layer_desc* d, const cb::Geom& g) { return use_shadow(d, g) || d->gather_channel_last; }
 
 StateLayout state_layout(const cb_layer_desc* d, const cb::Geom& g)
 {
@@ -115,8 +131,10 @@ StateLayout state_layout(const cb_layer_desc* d, const cb::Geom& g)
     L.m_u8 = o;   o += align256((size_t)g.P);
     L.mt_u8 = o;  o += align256((size_t)g.Po);
     const bool fused = use_fused(d, g);
-    L.KF = o;     o += fused ? align256(cb::fused_pack_bytes(g)) : 0;
-    L.rowtab = o; o += fused ? align256(cb::fused_table_bytes(g)) : 0;
+    // (what the header states as the price of a shadow is its own bytes: the other modes have room for the same filters and table)
+    const bool cl = use_channel_last(d, g) || few_channels(g) || cb::fused_channel_last(g);
+    L.KF = o;     o += fused ? align256(cb::fused_pack_bytes(g, cl)) : 0;
+    L.rowtab = o; o += fused && cb::fused_supported(g) ? align256(cb::fused_table_bytes(g)) : 0;
     L.total = o;
     return L;
 }
@@ -124,15 +142,15 @@ StateLayout state_layout(const cb_layer_desc* d, const cb::Geom& g)
 size_t col_bytes(const cb::Geom& g) { return (size_t)g.R * (g.bf16 ? 2 : 4) + (size_t)g.O * 4; }
 int po_pad(const cb::Geom& g) { return (g.Po + 255) & ~255; }
 
-// fused layers need the block counters only
-ScratchLayout scratch_layout(const cb::Geom& g, int cap, bool fused)
+// layers without X' and Y' need the block counters only
+ScratchLayout scratch_layout(const cb::Geom& g, int cap, bool matrices)
 {
     ScratchLayout L;
     L.cap = cap;
     size_t o = 0;
     L.blk = o; o += align256((size_t)cb::dilate_num_blocks(g) * 4);
-    L.X = o;   o += fused ? 0 : align256((size_t)g.R * cap * (g.bf16 ? 2 : 4));
-    L.Y = o;   o += fused ? 0 : align256((size_t)g.O * cap * 4);
+    L.X = o;   o += !matrices ? 0 : align256((size_t)g.R * cap * (g.bf16 ? 2 : 4));
+    L.Y = o;   o += !matrices ? 0 : align256((size_t)g.O * cap * 4);
     L.total = o;
     return L;
 }
@@ -308,7 +326,7 @@ int detect_and_update(cb_layer* L, const void* input_dev, float tau, const int32
         CB_HIP(cb::launch_detect_listed(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau,
                                         flags, cand, cand_count, cand_cap, pool_w, cand_W, L->st,
                                         next_tm(L, CB_STEP_DETECT)));
-    else if (L->shadow && L->g.C >= 16 && L->primed && !L->g.bf16 && (flags & cb::DET_STREAM_STATE)) {
+    else if (L->shadow && L->g.C > 8 && L->primed && !L->g.bf16 && (flags & cb::DET_STREAM_STATE)) {
         // a float32 state beyond the caches, with a shadow: detection as a pure stream, the update of the changed
         // pixels (state and shadow) in a kernel of its own (1080p x 128 channels: the detection variant that
         // updates the shadow itself costs 17 us more even when nothing changes, this one 0 - 10 us up to 1 % changed;
@@ -363,7 +381,7 @@ int cb_layer_workspace_bytes(const cb_layer_desc* desc, size_t* state_bytes, siz
     int rc = validate(desc, &g);
     if (rc) return rc;
     if (state_bytes) *state_bytes = state_layout(desc, g).total;
-    if (scratch_bytes) *scratch_bytes = scratch_layout(g, recommended_cap(g), use_fused(desc, g)).total;
+    if (scratch_bytes) *scratch_bytes = scratch_layout(g, recommended_cap(g), use_matrices(desc, g)).total;
     return CB_OK;
 }
 
@@ -372,7 +390,7 @@ int cb_layer_min_scratch_bytes(const cb_layer_desc* desc, size_t* scratch_bytes)
     cb::Geom g;
     int rc = validate(desc, &g);
     if (rc) return rc;
-    if (scratch_bytes) *scratch_bytes = scratch_layout(g, 256, use_fused(desc, g)).total;
+    if (scratch_bytes) *scratch_bytes = scratch_layout(g, 256, use_matrices(desc, g)).total;
     return CB_OK;
 }
 
@@ -391,13 +409,13 @@ int cb_layer_create(const cb_layer_desc* desc, const void* w_oihw_dev, const voi
     if (((uintptr_t)w_oihw_dev % esz) || (bias_dev && ((uintptr_t)bias_dev % esz))) return CB_EINVAL;
     StateLayout sl = state_layout(desc, g);
     if (state_bytes < sl.total) return CB_ENOMEM;
-    const bool fused = use_fused(desc, g);
-    if (scratch_bytes < scratch_layout(g, 256, fused).total) return CB_ENOMEM;
+    const bool fused = use_fused(desc, g), matrices = use_matrices(desc, g);
+    if (scratch_bytes < scratch_layout(g, 256, matrices).total) return CB_ENOMEM;
     // largest chunk capacity (multiple of 256 columns) that fits the given scratch
     size_t cols = (scratch_bytes / col_bytes(g) + 255) & ~(size_t)255;
     if (cols > (size_t)po_pad(g)) cols = po_pad(g);
     if (cols < 256) cols = 256;
-    while (cols > 256 && scratch_layout(g, (int)cols, fused).total > scratch_bytes) cols -= 256;
+    while (cols > 256 && scratch_layout(g, (int)cols, matrices).total > scratch_bytes) cols -= 256;
 
     cb_layer* L = new (std::nothrow) cb_layer();
     if (!L) return CB_ENOMEM;
@@ -407,7 +425,7 @@ int cb_layer_create(const cb_layer_desc* desc, const void* w_oihw_dev, const voi
     L->state = (char*)state_dev;
     L->sl = sl;
     L->scratch = (char*)scratch_dev;
-    L->sc = scratch_layout(g, (int)cols, fused);
+    L->sc = scratch_layout(g, (int)cols, matrices);
     L->fused = fused;
     L->shadow = use_shadow(desc, g);
     L->ext_cl = nullptr;
@@ -428,7 +446,7 @@ int cb_layer_create(const cb_layer_desc* desc, const void* w_oihw_dev, const voi
 
     hipError_t e = hipMemsetAsync(state_dev, 0, sl.total, L->st);
     if (e == hipSuccess) e = cb::launch_pack_weights(g, w_oihw_dev, bias_dev, L->KT(), L->bias(), L->st);
-    if (e == hipSuccess && fused) e = cb::fused_prepare(g, w_oihw_dev, L->KF(), L->rowtab(), L->shadow || desc->gather_channel_last, L->st, &L->plan);
+    if (e == hipSuccess && fused) e = cb::fused_prepare(g, w_oihw_dev, L->KF(), L->rowtab(), use_channel_last(desc, g), L->st, &L->plan);
     if (e != hipSuccess) { delete L; return hip_fail(e); }
     *out = L;
     return CB_OK;
@@ -639,7 +657,14 @@ int cb_layer_matrices(const cb_layer_t* L, const void** xprime_dev, const void**
                       const int32_t** ld_ncols_dev)
 {
     if (!L) return CB_EINVAL;
-    if (L->fused) return CB_ESTATE;
+    if (!use_matrices(&L->d, L->g)) return CB_ESTATE;
+    if (L->fused && L->primed)
+        // the fused kernel left no matrices: those of the last frame, from the state as that frame left it
+        for (int q = 0; q < L->nchunks; ++q) {
+            const int col0 = q * L->sc.cap;
+            CB_HIP(cb::launch_gather(L->g, L->S(), L->cur_idx, L->cur_count, col0, L->sc.cap, L->X(), L->ctl(), L->st));
+            CB_HIP(cb::launch_gemm(L->g, L->KT(), L->X(), L->Y(), L->cur_count, col0, L->sc.cap, L->ctl(), L->st));
+        }
     if (xprime_dev) *xprime_dev = L->X();
     if (yprime_dev) *yprime_dev = L->Y();
     if (ld_ncols_dev) *ld_ncols_dev = L->ctl() + cb::CTL_LD;
