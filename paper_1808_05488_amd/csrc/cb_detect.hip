@@ -618,6 +618,11 @@ void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int Cs,
     else if (VEC == 1 && P < 8192 && C <= 256) launch_reg<T, 1, 16, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
     else if (VEC == 1 && P < 8192 && C <= 512) launch_reg<T, 1, 16, 32, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
     else if (C <= 128) launch_reg<T, VEC, 16, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    // (129 - 256 bfloat16 channels: 82 registers.  They walked their channels one by one, or 2 bytes per lane and load: frames, us,
+    // 160 channels, 1x1, at 540x960 116 -> 77, 256 channels there 181 -> 105, at 180x200 36 -> 29.  float32 would need 140 registers.)
+    else if (VEC == 4 && sizeof(T) == 2 && C <= 256) {
+        if constexpr (VEC == 4 && sizeof(T) == 2) launch_reg<T, 4, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    }
     // one pixel per lane leaves registers for more channels per lane (deep layers: many channels, few pixels)
     else if (VEC == 1 && C <= 256) launch_reg<T, 1, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
     else if (VEC == 1 && C <= 512) launch_reg<T, 1, 16, 32>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
@@ -841,8 +846,9 @@ hipError_t launch_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int
     // 181x182, 12.7 against 8.7 at 200x201; 64 channels 6.3 / 6.7, 6.5 / 6.0, 6.7 / 6.1; up to 16 channels no difference.  float32 gains nothing from unaligned loads
     // (32 channels at 557x803: 25.1 us either way), and the looped variant for more than 128 channels wants aligned ones.
     const bool aligned = P % 4 == 0 && (uintptr_t)x % valign == 0 && (uintptr_t)S % valign == 0;
+    const int regs4 = sizeof(T) == 2 ? 256 : 128;         // channels that the variants with four pixels per lane hold in registers
     const bool vec4 = P >= (sizeof(T) == 4 ? 65536 : 32768) && !one_px &&
-                      (aligned || (sizeof(T) == 2 && g.C <= 128)) && (g.C <= 128 || (P >= 65536 && !(S2 != nullptr && g.C <= 512)));
+                      (aligned || (sizeof(T) == 2 && g.C <= regs4)) && (g.C <= regs4 || (P >= 65536 && !(S2 != nullptr && g.C <= 512)));
     if (vec4) launch_v<T, 4>(x, S, S2, mbits, ctl, g.C, g.Cs, P, tau, flags, stream, st, tm);
     else      launch_v<T, 1>(x, S, S2, mbits, ctl, g.C, g.Cs, P, tau, flags, stream, st, tm);
     return hipGetLastError();
