@@ -1,4 +1,4 @@
-// Rules of the channel-last fused kernel (cb_fused_cl.hip) that need no GPU: plain arithmetic on the geometry, usable
+// Rules of the channel-last fused kernel (cb_fused_cl.h) that need no GPU: plain arithmetic on the geometry, usable
 // from host code and kernels alike.
 #pragma once
 

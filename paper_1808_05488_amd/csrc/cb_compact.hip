@@ -15,255 +15,11 @@
 //                   (launch latency, not work, is what these steps cost there)
 //   dilate_compact_kernel: both in one launch of many workgroups (single-pass scan), for
 //                   maps of up to 262 144 words; the two-kernel form remains for larger ones
-#include "cb_kernels.h"
+#include "cb_extract.h"
 
 namespace cb {
 
 namespace {
-
-// 64-bit word wi of a bit map.  OWN: `w` holds the two input maps of a layer that detects its own
-// changes, interleaved word by word (word wi of the map of frame parity p at index 2*wi + p).  One
-// 16-byte load brings word wi of both; sel (the frame parity, which may still be on its way from
-// memory when the load is issued) picks.  Otherwise `w` is one plain map.
-template <bool OWN>
-__device__ __forceinline__ uint64_t map_word(const uint64_t* __restrict__ w, long wi, int sel)
-{
-    if (OWN) {
-        const ulonglong2 p = reinterpret_cast<const ulonglong2*>(w)[wi];
-        return (sel & 1) ? p.y : p.x;
-    }
-    return w[wi];
-}
-
-template <bool OWN>
-__device__ __forceinline__ bool test_bit(const uint64_t* __restrict__ bits, long bit, int sel)
-{
-    return (map_word<OWN>(bits, bit >> 6, sel) >> (bit & 63)) & 1ull;
-}
-
-// Where the words of the input map come from: memory ...
-template <bool OWN>
-struct MapInMemory {
-    const uint64_t* w;
-    int sel;
-    __device__ __forceinline__ uint64_t operator()(long wi) const { return map_word<OWN>(w, wi, sel); }
-};
-// ... or the part of it that a workgroup has staged in LDS (words first, first + 1, ...).
-struct MapInLds {
-    const uint64_t* w;
-    long first;
-    __device__ __forceinline__ uint64_t operator()(long wi) const { return w[wi - first]; }
-};
-
-// Bit q (q = 0..63) = OR over the filter footprint of an output whose receptive field's top-left
-// pixel is (y0, x0 + q); pixels outside the image read as zero.  -63 <= x0.  The filter's rows are
-// OR-ed first, as 128-column windows (their column limits are the same for every row), the columns
-// afterwards, once, by doubling: kw shifts become log2(kw).  The map has at least two words of
-// slack behind its last used word; the window is at most 64 + 30 columns wide.
-// KB: filter rows per batch of reads.
-template <int KB, typename WORDS>
-__device__ __forceinline__ uint64_t fires_rows(const Geom& g, const WORDS& words, long pitch, int y0, int x0)
-{
-    int a = x0 > 0 ? x0 : 0;
-    const int pre = a - x0;
-    const int len = (x0 + 128 < g.W ? x0 + 128 : g.W) - a;
-    if (a > g.W - 1) a = g.W - 1;                      // keep the address inside the row; len <= 0 masks it
-    uint64_t lo = 0, hi = 0;
-    // filter rows in batches: their reads are issued before the first use
-    for (int j0 = 0; j0 < g.kh; j0 += KB) {
-        uint64_t v[KB][3];
-        int sh[KB];
-#pragma unroll
-        for (int u = 0; u < KB; ++u) {
-            const int yi = y0 + j0 + u;
-            const bool valid = j0 + u < g.kh && yi >= 0 && yi < g.H;
-            const int yr = j0 + u < g.kh ? yi : y0 + j0;   // (a row beyond the filter's last repeats the batch's first)
-            const int yc = yr < 0 ? 0 : (yr >= g.H ? g.H - 1 : yr);
-            const long bit = (long)yc * pitch + a;
-            sh[u] = valid ? (int)(bit & 63) : -1;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) v[u][k] = words((bit >> 6) + k);
-        }
-#pragma unroll
-        for (int u = 0; u < KB; ++u) {
-            const int q = sh[u] & 63;
-            const uint64_t bl = q ? v[u][1] << (64 - q) : 0ull, cl = q ? v[u][2] << (64 - q) : 0ull;
-            lo |= sh[u] >= 0 ? (v[u][0] >> q) | bl : 0ull;
-            hi |= sh[u] >= 0 ? (v[u][1] >> q) | cl : 0ull;
-        }
-    }
-    lo &= len >= 64 ? ~0ull : (len > 0 ? (1ull << len) - 1ull : 0ull);
-    hi &= len >= 128 ? ~0ull : (len > 64 ? (1ull << (len - 64)) - 1ull : 0ull);
-    if (pre) { hi = (hi << pre) | (lo >> (64 - pre)); lo <<= pre; }
-    int n = 1;                                         // bit q holds columns q .. q + n - 1
-    while (2 * n <= g.kw) { lo |= (lo >> n) | (hi << (64 - n)); hi |= hi >> n; n *= 2; }
-    if (n < g.kw) { const int r = g.kw - n; lo |= (lo >> r) | (hi << (64 - r)); }
-    return lo;
-}
-
-template <typename WORDS>
-__device__ __forceinline__ uint64_t fires64(const Geom& g, const WORDS& words, long pitch, int y0, int x0)
-{
-    return g.kh == 1 ? fires_rows<1>(g, words, pitch, y0, x0) : fires_rows<4>(g, words, pitch, y0, x0);
-}
-
-// bits 0, 2, 4, ... of v squeezed into the lower half
-__device__ __forceinline__ uint64_t even_bits(uint64_t v)
-{
-    v &= 0x5555555555555555ull;
-    v = (v | (v >> 1)) & 0x3333333333333333ull;
-    v = (v | (v >> 2)) & 0x0F0F0F0F0F0F0F0Full;
-    v = (v | (v >> 4)) & 0x00FF00FF00FF00FFull;
-    v = (v | (v >> 8)) & 0x0000FFFF0000FFFFull;
-    return (v | (v >> 16)) & 0x00000000FFFFFFFFull;
-}
-
-// One word of the dilated map: output row yo, columns 64*wo .. 64*wo+63.  A strided layer takes every
-// s-th bit of the words a layer of stride 1 would have there: s window words per output word, all of
-// them words from the map.  (Testing the map bit by bit, kh*kw dependent loads per output, took 248 us
-// of a 273 us frame for 48 -> 96 channels, 5x5, stride 2 at 241x323.)  Beyond a stride of 64 the
-// outputs lie in different words anyway, one window each.
-template <typename WORDS>
-__device__ __forceinline__ uint64_t dilated_word_t(const Geom& g, const WORDS& words, long pitch, int yo, int wo)
-{
-    const int nvalid = g.Wo - 64 * wo < 64 ? g.Wo - 64 * wo : 64;
-    const uint64_t vmask = nvalid == 64 ? ~0ull : ((1ull << nvalid) - 1ull);
-    const int y0 = yo * g.s - g.p;
-    if (g.s == 1) return fires64(g, words, pitch, y0, 64 * wo - g.p) & vmask;
-    uint64_t word = 0;
-    if (g.s == 2) {
-        const int x0 = 128 * wo - g.p;
-        word = even_bits(fires64(g, words, pitch, y0, x0));
-        if (nvalid > 32) word |= even_bits(fires64(g, words, pitch, y0, x0 + 64)) << 32;
-    } else if (g.s <= 64) {
-        // output b is anchored at column b*s of the window; the anchors come in ascending order
-        int b = 0;
-        for (int t = 0; t < g.s && b < nvalid; ++t) {
-            const uint64_t f = fires64(g, words, pitch, y0, 64 * wo * g.s - g.p + 64 * t);
-            for (; b < nvalid && b * g.s < 64 * (t + 1); ++b) word |= ((f >> (b * g.s - 64 * t)) & 1ull) << b;
-        }
-    } else {
-        for (int b = 0; b < nvalid; ++b)
-            word |= (fires64(g, words, pitch, y0, (64 * wo + b) * g.s - g.p) & 1ull) << b;
-    }
-    return word & vmask;
-}
-
-// own_map: in_bits holds the layer's two interleaved input maps and sel is the frame parity
-__device__ __forceinline__ uint64_t dilated_word(const Geom& g, const uint64_t* __restrict__ in_bits, long pitch,
-                                                 int yo, int wo, int own_map, int sel)
-{
-    return own_map ? dilated_word_t(g, MapInMemory<true>{in_bits, sel}, pitch, yo, wo)
-                   : dilated_word_t(g, MapInMemory<false>{in_bits, 0}, pitch, yo, wo);
-}
-
-// Words it0 .. it0 + NT - 1 of the dilated map, one per thread of a workgroup of NT threads (0 beyond the
-// last).  The rows of the input map under them are one contiguous range of words: the workgroup stages it in
-// LDS with one round of loads, and the windows, which overlap kh times, are cut out there (7x7 at 240x320:
-// 8.4 -> 7.6 us for dilation and list, 9x9 10.7 -> 7.2).  Filters of up to four rows at stride 1 issue all their
-// loads in one batch anyway and go without the detour (1x1: 5.0 us, staged 5.8); ranges of
-// more than CAP words (large strides, very wide filters on narrow maps) are read from memory too.
-// Called by all threads of the workgroup.
-template <int NT, int CAP>
-__device__ __forceinline__ uint64_t dilated_block_word(const Geom& g, const uint64_t* __restrict__ in_bits, long pitch,
-                                                       int it0, int items, int own_map, int sel, uint64_t* s_map)
-{
-    const int tid = threadIdx.x, it = it0 + tid;
-    const int ilast = (it0 + NT < items ? it0 + NT : items) - 1;
-    const int y0 = it0 / g.WWo, y1 = ilast / g.WWo;
-    int r0 = y0 * g.s - g.p, r1 = y1 * g.s - g.p + g.kh - 1;
-    // (rows outside the image are read at its first / last row)
-    r0 = r0 < 0 ? 0 : (r0 > g.H - 1 ? g.H - 1 : r0);
-    r1 = r1 < 0 ? 0 : (r1 > g.H - 1 ? g.H - 1 : r1);
-    const long first = ((long)r0 * pitch) >> 6;
-    const long n = ((((long)r1 * pitch + g.W - 1) >> 6) + 3) - first;     // a window reads two words past its first
-    const int yo = it / g.WWo, wo = it - yo * g.WWo;
-    if ((g.s == 1 && g.kh <= 4) || n > CAP) return it < items ? dilated_word(g, in_bits, pitch, yo, wo, own_map, sel) : 0ull;
-    if (own_map) {
-        for (int i = tid; i < (int)n; i += NT) s_map[i] = map_word<true>(in_bits, first + i, sel);
-    } else {
-        for (int i = tid; i < (int)n; i += NT) s_map[i] = map_word<false>(in_bits, first + i, 0);
-    }
-    __syncthreads();
-    return it < items ? dilated_word_t(g, MapInLds{s_map, first}, pitch, yo, wo) : 0ull;
-}
-
-// Inclusive prefix sum over the 64 lanes of a wavefront with data-parallel-primitive moves: shifts by
-// 1, 2, 4, 8 inside each row of 16 lanes, then lane 15 of a row broadcast into the next row and lane 31
-// into the upper half (lanes without a source add 0).  Six register-to-register steps; the same scan
-// through general shuffles costs six LDS round trips.
-__device__ __forceinline__ int wave_inclusive_scan(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
-// ... and the sum over the wavefront, in every lane: the last lane of that scan
-__device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_inclusive_scan(v), 63); }
-
-// Index-list entries of the 64 words held by a wavefront (word, its exclusive offset, the
-// pixel index of its bit 0).  PER_LANE = false: the whole wavefront expands one non-empty word
-// at a time (coalesced stores, a handful of cross-lane reads per word) -- the faster form
-// when the words are spread over many compute units.  PER_LANE = true: every lane walks the
-// bits of its own word, no cross-lane traffic -- the faster form in the one-workgroup kernel,
-// where sixteen wavefronts share one compute unit's cross-lane hardware.
-template <bool PER_LANE>
-__device__ __forceinline__ void expand_words(uint64_t word, int off, int pixbase, int32_t* __restrict__ idx, int lane)
-{
-    if (PER_LANE) {
-        while (word) {
-            idx[off++] = pixbase + __builtin_ctzll(word);
-            word &= word - 1;
-        }
-        return;
-    }
-    uint64_t nz = __ballot(word != 0);
-    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    while (nz) {
-        // (nz comes from a ballot, so src is the same in every lane: plain lane reads into scalar registers,
-        // not the cross-lane permutes of a general shuffle, which cost an LDS round trip each)
-        const int src = __ffsll((long long)nz) - 1;
-        nz &= nz - 1;
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, src);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), src);
-        const uint64_t wsrc = ((uint64_t)hi << 32) | lo;
-        const int o = __builtin_amdgcn_readlane(off, src);
-        const int pb = __builtin_amdgcn_readlane(pixbase, src);
-        if ((wsrc >> lane) & 1ull) idx[o + __popcll(wsrc & below)] = pb + lane;
-    }
-}
-
-// A layer that detects its own changes keeps two input maps (interleaved word by word, see
-// map_word) and two changed-pixel counters, used by alternate frames: change detection fills the
-// pair that the frame count on the device (CTL_FRAME, advanced by the index extraction once per
-// frame) selects, and the index extraction clears the other pair for the next frame.  Nothing about
-// this lives on the host, so captured launches replay correctly whatever the number of frames in a
-// capture.  A layer that takes its map from its producer (own_map == 0) has one plain map and
-// nothing to clear.
-__device__ __forceinline__ int frame_parity(const int* ctl, int own_map) { return own_map ? (ctl[CTL_FRAME] & 1) : 0; }
-// the other map and the other counter start the next frame empty
-__device__ __forceinline__ void clear_other_map(uint64_t* maps, int* ctl, int par, int clear_words, int first, int step)
-{
-    if (first < NIN_SLOTS) *nin_counter(ctl, (unsigned)first, par ^ 1) = 0;
-    for (int i = first; i < clear_words; i += step) maps[2 * i + (par ^ 1)] = 0;
-}
-
-// word `it` of the dilated map of a full update: every output
-__device__ __forceinline__ uint64_t full_word(const Geom& g, int it)
-{
-    const int nvalid = g.Wo - 64 * (it % g.WWo);
-    return nvalid >= 64 ? ~0ull : ((1ull << nvalid) - 1ull);
-}
-
-// Words of the input map a workgroup can stage: 256 output words of a 1080p layer with stride 1 and a 31-row
-// filter need 1 200 words, of a VGA layer with stride 2 and 7 rows 1 092 (16 KB).  The one-workgroup kernel, up to 1024
-// output words, stages maps of up to 4 605 words whole (36 KB); that of a VGA layer with stride 3 or 4, 4 802 words, is
-// read from memory.
-constexpr int MAP_STAGE = 2048, MAP_STAGE_SMALL = 4608;
 
 __global__ __launch_bounds__(256) void dilate_kernel(Geom g, const uint64_t* __restrict__ in_bits,
                                                      long pitch, int full, uint64_t* __restrict__ mt_bits,
@@ -370,11 +126,9 @@ __global__ __launch_bounds__(256) void dilate_compact_kernel(Geom g, const uint6
 {
     // (needed only after the map words have been requested: both candidates come with one load)
     const int par = frame_parity(ctl, own_map);
-    __shared__ unsigned s_epoch;
-    __shared__ int wtot[4];
-    __shared__ int red[4];
+    __shared__ unsigned s_small[ONE_PASS_SMALL];
     __shared__ uint64_t s_map[MAP_STAGE];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x;
     const int items = g.Ho * g.WWo;
     const int nblk = (int)gridDim.x;
     // written by the previous launch's last workgroup; the load is in flight during the dilation
@@ -393,51 +147,8 @@ __global__ __launch_bounds__(256) void dilate_compact_kernel(Geom g, const uint6
     }
     // housekeeping for the next frame: the other input map starts out empty
     if (own_map) clear_other_map(const_cast<uint64_t*>(in_bits), ctl, par, clear_words, bid * 256 + tid, nblk * 256);
-    const int cnt = __popcll(word);
-    const int inc = wave_inclusive_scan(cnt);                  // inclusive scan inside the wavefront
-    if (lane == 63) wtot[wv] = inc;
-    if (tid == 0) s_epoch = epoch_ld + 1u ? epoch_ld + 1u : 1u;   // 0 is what never-written slots hold
-    __syncthreads();
-    const unsigned epoch = s_epoch;
-    if (tid == 0) {
-        const unsigned total = (unsigned)(wtot[0] + wtot[1] + wtot[2] + wtot[3]);
-        __hip_atomic_store(&look[bid], ((unsigned long long)epoch << 32) | total, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // counts of all earlier workgroups (count and epoch travel in one word: no ordering between words needed)
-    int part = 0;
-    for (int b = tid; b < bid; b += 256) {
-        unsigned long long v = 0;
-        int spins = 0;
-        for (;;) {
-            v = __hip_atomic_load(&look[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((unsigned)(v >> 32) == epoch) break;
-            if (++spins > spin_limit) {
-                v = (unsigned long long)(unsigned)recount_block(g, in_bits, pitch, full, b, own_map, par);
-                atomicAdd(&ctl[CTL_RECOUNTS], 1);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-        part += (int)(unsigned)v;
-    }
-    part = wave_sum(part);
-    if (lane == 0) red[wv] = part;
-    __syncthreads();
-    int off = red[0] + red[1] + red[2] + red[3];
-    for (int q = 0; q < wv; ++q) off += wtot[q];
-    off += inc - cnt;                                        // exclusive offset of this thread's word
-    if (bid == nblk - 1 && tid == 255) ctl[CTL_COUNT] = off + cnt;
-
-    expand_words<false>(word, off, pixbase, idx, lane);
-
-    if (tid == 0) {
-        if (atomicAdd(&ctl[CTL_DONE], 1) == nblk - 1) {      // everybody has read the epoch and the frame count
-            ctl[CTL_DONE] = 0;
-            ctl[CTL_EPOCH] = (int)epoch;
-            if (own_map) ctl[CTL_FRAME] = ctl[CTL_FRAME] + 1;
-        }
-    }
+    one_pass_tail(word, pixbase, epoch_ld, idx, ctl, look, own_map, bid, nblk, spin_limit, s_small,
+                  [&](int b) { return recount_block(g, in_bits, pitch, full, b, own_map, par); });
 }
 
 // Small maps: dilation, scan and index write in ONE workgroup of 1024 threads, so
@@ -532,26 +243,7 @@ __global__ __launch_bounds__(256) void pool_mask_kernel(int Ho, int Wo, int WWo,
     if (it >= items) return;
     const int yp = it / WWp, wp = it - yp * WWp;
     if (w == 2) {
-        // word-parallel: OR the two producer rows, OR neighbouring bit pairs, squeeze the even bits
-        // together (bits beyond Wo are 0 in the producer's words)
-        uint64_t v[2] = {0, 0};
-        for (int dy = 0; dy < 2; ++dy) {
-            const int y = 2 * yp + dy;
-            if (y >= Ho) break;
-            for (int h = 0; h < 2; ++h)
-                if (2 * wp + h < WWo) v[h] |= mt_bits[(long)y * WWo + 2 * wp + h];
-        }
-        uint64_t out = 0;
-        for (int h = 0; h < 2; ++h) {
-            uint64_t x = (v[h] | (v[h] >> 1)) & 0x5555555555555555ull;
-            x = (x | (x >> 1)) & 0x3333333333333333ull;
-            x = (x | (x >> 2)) & 0x0F0F0F0F0F0F0F0Full;
-            x = (x | (x >> 4)) & 0x00FF00FF00FF00FFull;
-            x = (x | (x >> 8)) & 0x0000FFFF0000FFFFull;
-            x = (x | (x >> 16)) & 0x00000000FFFFFFFFull;
-            out |= x << (32 * h);
-        }
-        pm_bits[it] = out;
+        pm_bits[it] = pooled_word(mt_bits, Ho, WWo, yp, wp);
         return;
     }
     uint64_t word = 0;
@@ -583,6 +275,13 @@ hipError_t launch_dilate_compact_small(const Geom& g, const uint64_t* in_bits, l
     CB_LAUNCH(dilate_compact_small_kernel, dim3(1), dim3(1024), st, tm, g, in_bits, in_pitch_bits, full,
               mt_bits, idx, ctl, own_map, clear_words);
     return hipGetLastError();
+}
+
+// (the input map of such a consumer has rows of whole words)
+bool extract_fits(const Geom& g)
+{
+    const long rows = (long)((255 + g.WWo - 1) / g.WWo) * g.s + g.kh, n = rows * ((g.W + 63) / 64) + 3;
+    return n <= MAP_STAGE && dilate_num_blocks(g) <= 256;
 }
 
 bool compact_one_pass(const Geom& g) { return dilate_num_blocks(g) <= ONE_PASS_MAX_BLOCKS; }

@@ -22,7 +22,7 @@ constexpr int FUSED_ZERO_TAP = 60;      // tap index of the zero rows that pad K
 constexpr int FUSED_TAB_PAD = 64;       // entries of length 0 that close the chunk table: a group of gather rounds (up to 4 rounds of 16 fetchers) may read this far past the last chunk
 
 // Channel-last variant (any channel count, the pixels padded to whole 16-byte pieces): the gather reads a pixel-major
-// shadow of the state (or a producer's pixel-major output), K is walked tap-major, no chunk table (cb_fused_cl.hip).
+// shadow of the state (or a producer's pixel-major output), K is walked tap-major, no chunk table (cb_fused_cl.h).
 
 // Chunk table.  The rows of X' that belong to one input channel c and one filter row j,
 // r = (c*kh + j)*kw + i for i = 0..kw-1 (construction of X below Eq. 2), are kw consecutive
@@ -127,12 +127,14 @@ hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, 
                          FusedPlan* plan);
 // src: the channel-first source of the gather (input state, or a producer's output); shadow: the
 // pixel-major copy of that source (used, and required, when plan.cl is set); KT: the transposed filter matrix (R x Opad); OUT2: null, or the
-// pixel-major copy of the cached output (Po x O; O a multiple of 16), which receives the same updates as OUT
+// pixel-major copy of the cached output (Po x O; O a multiple of 16), which receives the same updates as OUT; job: null, or the
+// index extraction of the layer behind, for the kernel's first workgroups (fused_takes_job)
 hipError_t launch_fused(const Geom& g, const FusedPlan& plan, const void* src, const void* shadow, const int32_t* idx,
                         const int* count, const void* KF, const void* KT, const void* tab, const float* bias, int relu, void* OUT,
-                        void* OUT2, hipStream_t st, Tm tm = Tm());
+                        void* OUT2, const ExtractJob* job, hipStream_t st, Tm tm = Tm());
+inline bool fused_takes_job(const Geom& g, const FusedPlan& plan) { return plan.cl && (g.Cs & (g.Cs - 1)) == 0; }
 
-// launches of the two element types (cb_fused_f32.hip, cb_fused_bf16.hip, cb_fused_cl.hip)
+// launches of the two element types (cb_fused_f32.hip, cb_fused_bf16.hip, cb_fused_cl_*.hip)
 hipError_t launch_fused_f32(const Geom& g, const FusedPlan& plan, const float* src, const int32_t* idx,
                             const int* count, const void* KF, const int2* tab, const float* bias, int relu,
                             float* OUT, float* OUT2, hipStream_t st, Tm tm);
@@ -144,6 +146,13 @@ hipError_t launch_pack_fused_split(const Geom& g, const float* w, void* KF, hipS
 hipError_t launch_fused_bf16_cl(const Geom& g, const FusedPlan& plan, const uint16_t* shadow, const int32_t* idx,
                                 const int* count, const void* KF, const float* bias, int relu, uint16_t* OUT, uint16_t* OUT2,
                                 hipStream_t st, Tm tm);
+// ... with the index extraction of the layer behind (cb_fused_cl_extract.h)
+hipError_t launch_fused_f32_cl_extract(const Geom& g, const FusedPlan& plan, const float* shadow, const int32_t* idx, const int* count,
+                                       const void* KF, const float* KT, const float* bias, int relu, float* OUT, float* OUT2,
+                                       const ExtractJob& job, hipStream_t st);
+hipError_t launch_fused_bf16_cl_extract(const Geom& g, const FusedPlan& plan, const uint16_t* shadow, const int32_t* idx, const int* count,
+                                        const void* KF, const float* bias, int relu, uint16_t* OUT, uint16_t* OUT2,
+                                        const ExtractJob& job, hipStream_t st);
 hipError_t launch_fused_bf16(const Geom& g, const FusedPlan& plan, const uint16_t* src, const int32_t* idx,
                              const int* count, const void* KF, const int2* tab, const float* bias, int relu,
                              uint16_t* OUT, uint16_t* OUT2, hipStream_t st, Tm tm);

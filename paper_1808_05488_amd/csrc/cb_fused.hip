@@ -222,7 +222,7 @@ hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (plan->cl) {
-        // no table, and the stages are the kernel's own (cb_fused_cl.hip)
+        // no table, and the stages are the kernel's own (cb_fused_cl.h)
         plan->cw = 4;
         plan->ntab = 0;
         plan->nunits = 0;
@@ -283,11 +283,18 @@ hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, 
 
 hipError_t launch_fused(const Geom& g, const FusedPlan& plan, const void* src, const void* shadow, const int32_t* idx,
                         const int* count, const void* KF, const void* KT, const void* tab, const float* bias, int relu, void* OUT,
-                        void* OUT2, hipStream_t st, Tm tm)
+                        void* OUT2, const ExtractJob* job, hipStream_t st, Tm tm)
 {
+    if (job && !fused_takes_job(g, plan)) return hipErrorInvalidValue;
     if (OUT2 && (g.O & 15) != 0) return hipErrorInvalidValue;
     if (plan.cl) {
         if (!shadow) return hipErrorInvalidValue;
+        if (job && g.bf16)
+            return launch_fused_bf16_cl_extract(g, plan, (const uint16_t*)shadow, idx, count, KF, bias, relu, (uint16_t*)OUT,
+                                                (uint16_t*)OUT2, *job, st);
+        if (job)
+            return launch_fused_f32_cl_extract(g, plan, (const float*)shadow, idx, count, KF, (const float*)KT, bias, relu, (float*)OUT,
+                                               (float*)OUT2, *job, st);
         if (g.bf16)
             return launch_fused_bf16_cl(g, plan, (const uint16_t*)shadow, idx, count, KF, bias, relu, (uint16_t*)OUT,
                                         (uint16_t*)OUT2, st, tm);

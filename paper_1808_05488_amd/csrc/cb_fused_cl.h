@@ -33,6 +33,7 @@
 // such makes the accumulated sum non-finite, and the epilogue recomputes every non-finite sum in plain
 // float32 from the state and the filter matrix (exact_tiles), so that infinities, NaNs and large numbers come out as they do
 // in float32 arithmetic.
+#pragma once
 #include "cb_fused.h"
 #include "cb_cl_rules.h"
 
@@ -174,7 +175,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                                                  const int32_t* __restrict__ idx, const int N,
                                                  const uint4* __restrict__ KF, const float* __restrict__ KT,
                                                  const float* __restrict__ bias, int relu, T* __restrict__ OUT,
-                                                 T* __restrict__ OUT2)
+                                                 T* __restrict__ OUT2, const unsigned bx, const unsigned gx)
 {
     constexpr bool F32 = sizeof(T) == 4;
     constexpr int TERMS = F32 ? 3 : 1;           // bfloat16 terms per value
@@ -218,7 +219,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     const unsigned NT = ((unsigned)N + BN - 1u) / BN;
     const unsigned MT = ((unsigned)g.O + BM - 1u) / BM;
     const unsigned per_xcd = (NT + 7u) / 8u, total = per_xcd * MT;
-    const unsigned xcd0 = (blockIdx.x & 7u) * per_xcd;
+    const unsigned xcd0 = (bx & 7u) * per_xcd;
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int wk = __builtin_amdgcn_readfirstlane(wv % WGK);
@@ -237,16 +238,16 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             q[p] = (u < total && n < (unsigned)N) ? idx[n] : -1;
         }
     };
-    if constexpr (!LEAN) fetch_q(blockIdx.x >> 3, qnext);
+    if constexpr (!LEAN) fetch_q(bx >> 3, qnext);
 
-    for (unsigned uq = blockIdx.x >> 3; uq < total; uq += gridDim.x >> 3) {
+    for (unsigned uq = bx >> 3; uq < total; uq += gx >> 3) {
         const int mt = (int)(uq % MT);
         const unsigned nt = xcd0 + uq / MT;
         int q[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) q[p] = LEAN ? 0 : qnext[p];
         if constexpr (LEAN) fetch_q(uq, q);
-        else fetch_q(uq + (gridDim.x >> 3), qnext);
+        else fetch_q(uq + (gx >> 3), qnext);
         if (nt >= NT) continue;
         const int m0 = mt * BM;
 
@@ -506,48 +507,16 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     }
 }
 
-// Filter matrix of the float32 kernel: for every 16-row tile and k-group of 32, three fragments (terms h, m, l of the scaled value) of 64 x 16
-// bytes: lane's 8 values are K(m = mtile*16 + lane%16, k' = kgroup*32 + 8*(lane/16) + 0..7), k' = (j*kw + i)*Cs + c; zero
-// outside the filter matrix and for the channels c >= C of a padded pixel.
-__global__ __launch_bounds__(256) void pack_fused_split_kernel(Geom g, int Mt16, int KG, const float* __restrict__ w,
-                                                               uint4* __restrict__ KF)
-{
-    const long n = (long)Mt16 * KG * 64;
-    const int taps = g.kh * g.kw;
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
-        const int lane = (int)(e & 63);
-        const long gk = e >> 6;
-        const int kgroup = (int)(gk % KG), mtile = (int)(gk / KG);
-        const int m = mtile * 16 + (lane & 15);
-        unsigned t[3][4];
-#pragma unroll
-        for (int q2 = 0; q2 < 4; ++q2) {
-            float v[2];
-#pragma unroll
-            for (int o = 0; o < 2; ++o) {
-                const int k = kgroup * 32 + 8 * (lane >> 4) + 2 * q2 + o;
-                const int tap = k / g.Cs, c = k - tap * g.Cs;
-                v[o] = (m < g.O && tap < taps && c < g.C) ? w[(size_t)m * g.R + (size_t)c * taps + tap] : 0.f;
-            }
-            split2(v[0], v[1], t[0][q2], t[1][q2], t[2][q2]);
-        }
-#pragma unroll
-        for (int s = 0; s < 3; ++s) KF[(gk * 3 + s) * 64 + lane] = make_uint4(t[s][0], t[s][1], t[s][2], t[s][3]);
-    }
-}
-
+// workgroup bx of gx
 template <typename T, int SHAPE, bool P2>
-// (wavefronts per SIMD: as many as the widest tile's registers allow.  They are worth more than wider tiles: bfloat16, O > 64
-// at 76 800 listed pixels 45 us with two, 40 us with four.)
-__global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(Geom g, ClDiv div, const T* __restrict__ S2,
-                                                          const int32_t* __restrict__ idx, const int* __restrict__ count,
-                                                          const uint4* __restrict__ KF, const float* __restrict__ KT,
-                                                          const float* __restrict__ bias, int relu,
-                                                          T* __restrict__ OUT, T* __restrict__ OUT2)
+__device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, const T* __restrict__ S2, const int32_t* __restrict__ idx,
+                                             const int* __restrict__ count, const uint4* __restrict__ KF, const float* __restrict__ KT,
+                                             const float* __restrict__ bias, int relu, T* __restrict__ OUT, T* __restrict__ OUT2,
+                                             const unsigned bx, const unsigned gx)
 {
     const int N = *count;
     if (N <= 0) return;
-#define CB_BODY(...) fused_cl_body<T, P2, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2)
+#define CB_BODY(...) fused_cl_body<T, P2, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx)
     // (the tiles of cb_cl_rules.h)
     cl_tile<sizeof(T) == 4, SHAPE>(N, g.O, g.Cs, g.kh * g.kw, g.R, [&](auto tile) __attribute__((always_inline)) {
         constexpr int t = decltype(tile)::value;
@@ -562,53 +531,51 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(G
 #undef CB_BODY
 }
 
+// (wavefronts per SIMD: as many as the widest tile's registers allow.  They are worth more than wider tiles: bfloat16, O > 64
+// at 76 800 listed pixels 45 us with two, 40 us with four.)
+template <typename T, int SHAPE, bool P2>
+__global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(Geom g, ClDiv div, const T* __restrict__ S2,
+                                                          const int32_t* __restrict__ idx, const int* __restrict__ count,
+                                                          const uint4* __restrict__ KF, const float* __restrict__ KT,
+                                                          const float* __restrict__ bias, int relu,
+                                                          T* __restrict__ OUT, T* __restrict__ OUT2)
+{
+    fused_cl_run<T, SHAPE, P2>(g, div, S2, idx, count, KF, KT, bias, relu, OUT, OUT2, blockIdx.x, gridDim.x);
+}
+
+// run(an integral constant: the kernel's instance) for a layer of this geometry; its arguments checked
+template <typename T, typename FN>
+hipError_t fused_cl_instance(const Geom& g, const FusedPlan& plan, FN&& run)
+{
+    if (!plan.cl || g.Cs % (16 / (int)sizeof(T)) != 0 || g.Cs < g.C || !cl_fits(g.Cs, g.kh * g.kw) || g.bf16 != (sizeof(T) == 2)) return hipErrorInvalidValue;
+    switch (cl_shape(g.O, g.Po, sizeof(T) == 4)) {
+        case 16: run(std::integral_constant<int, 16>()); break;
+        case 32: run(std::integral_constant<int, 32>()); break;
+        case 64: run(std::integral_constant<int, 64>()); break;
+        case 129: if constexpr (sizeof(T) == 2) run(std::integral_constant<int, 129>()); break;
+        default: run(std::integral_constant<int, 128>());
+    }
+    return hipGetLastError();
+}
+constexpr unsigned CL_GRID = 1024;
+template <typename T> constexpr unsigned cl_lds_bytes() { return sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16; }
+
 template <typename T>
 hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow, const int32_t* idx, const int* count,
                            const void* KF, const float* KT, const float* bias, int relu, T* OUT, T* OUT2, hipStream_t st, Tm tm)
 {
-    if (!plan.cl || g.Cs % (16 / (int)sizeof(T)) != 0 || g.Cs < g.C || !cl_fits(g.Cs, g.kh * g.kw) || g.bf16 != (sizeof(T) == 2)) return hipErrorInvalidValue;
     const ClDiv div = cl_div(g.Wo, g.Ho, g.kw, g.Cs);
     const bool p2 = (g.Cs & (g.Cs - 1)) == 0;
-#define CB_CL_LAUNCH(shape, p)                                                                                           \
-    CB_LAUNCH_LDS((fused_cl_kernel<T, shape, p>), dim3(1024), dim3(256), sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16, st, tm, g, \
-                  div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)
-#define CB_CL(shape) do { if (p2) CB_CL_LAUNCH(shape, true); else CB_CL_LAUNCH(shape, false); } while (0)
-    switch (cl_shape(g.O, g.Po, sizeof(T) == 4)) {
-        case 16: CB_CL(16); break;
-        case 32: CB_CL(32); break;
-        case 64: CB_CL(64); break;
-        case 129: if constexpr (sizeof(T) == 2) CB_CL(129); break;
-        default: CB_CL(128);
-    }
+    return fused_cl_instance<T>(g, plan, [&](auto shape) {
+#define CB_CL(p) \
+    CB_LAUNCH_LDS((fused_cl_kernel<T, decltype(shape)::value, p>), dim3(CL_GRID), dim3(256), cl_lds_bytes<T>(), st, tm, g, div, shadow, \
+                  idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)
+        if (p2) CB_CL(true);
+        else CB_CL(false);
 #undef CB_CL
-#undef CB_CL_LAUNCH
-    return hipGetLastError();
+    });
 }
 
 }  // namespace
-
-hipError_t launch_pack_fused_split(const Geom& g, const float* w, void* KF, hipStream_t st)
-{
-    const int KG = (g.Cs * g.kh * g.kw + 63) / 64 * 2, Mt16 = (g.O + 127) / 128 * 8;
-    const long n = (long)Mt16 * KG * 64;
-    unsigned grid = (unsigned)((n + 255) / 256);
-    if (grid > 2048) grid = 2048;
-    hipLaunchKernelGGL(pack_fused_split_kernel, dim3(grid), dim3(256), 0, st, g, Mt16, KG, w, (uint4*)KF);
-    return hipGetLastError();
-}
-
-hipError_t launch_fused_f32_cl(const Geom& g, const FusedPlan& plan, const float* shadow, const int32_t* idx,
-                               const int* count, const void* KF, const float* KT, const float* bias, int relu, float* OUT,
-                               float* OUT2, hipStream_t st, Tm tm)
-{
-    return launch_fused_cl<float>(g, plan, shadow, idx, count, KF, KT, bias, relu, OUT, OUT2, st, tm);
-}
-
-hipError_t launch_fused_bf16_cl(const Geom& g, const FusedPlan& plan, const uint16_t* shadow, const int32_t* idx,
-                                const int* count, const void* KF, const float* bias, int relu, uint16_t* OUT, uint16_t* OUT2,
-                                hipStream_t st, Tm tm)
-{
-    return launch_fused_cl<uint16_t>(g, plan, shadow, idx, count, KF, nullptr, bias, relu, OUT, OUT2, st, tm);
-}
 
 }  // namespace cb

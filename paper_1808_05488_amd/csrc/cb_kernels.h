@@ -59,6 +59,25 @@ __device__ __forceinline__ int* nin_counter(int* ctl, unsigned b, int par)
     return ctl + CTL_SLOTS + (b % NIN_SLOTS) * NIN_STRIDE + par;
 }
 
+// Index extraction of a layer that takes its change map from its producer (CB_PROPAGATE), run by the first nblk workgroups of
+// the producer's own product kernel: the list depends on the producer's map alone, which is complete before the
+// product starts.
+struct ExtractJob {
+    Geom g;                    // the consumer's
+    int nblk = 0;              // dilate_num_blocks(g); extract_fits(g)
+    int spin_limit = 0;
+    int src_Ho = 0, src_WWo = 0;
+    const uint64_t* in_bits = nullptr;     // the producer's dilated map (row-padded); pm_bits: its 2 x 2 pooled form is the input
+    long pitch = 0;                        // of the input map, in bits
+    uint64_t* pm_bits = nullptr;
+    uint64_t* mt_bits = nullptr;
+    int32_t* idx = nullptr;
+    int* ctl = nullptr;
+    unsigned long long* look = nullptr;
+};
+// ... for maps whose part under one workgroup's words fits its LDS, and of few enough workgroups to be resident at once beside the product's
+bool extract_fits(const Geom& consumer);
+
 // flags for detect
 enum { DET_FORCE_ALL = 1,      // mark every pixel as changed (first frame)
        DET_COPY_ALL = 2,       // copy every pixel into the state (feed-forward)

@@ -198,6 +198,11 @@ struct cb_layer {
     const void* chain_src;
     long chain_frames;
     float chain_tau;       // threshold of this layer's last frame
+    // within cb_network_forward: the stage behind, whose index list this layer's product kernel may extract on the side,
+    // with the pooling stage between them (or null), and whether this layer's list was extracted that way
+    cb_layer* next;
+    const cb_pool* next_pool;
+    bool list_ready;
 
     void* S() const { return state + sl.S; }
     void* S2() const { return shadow ? state + sl.S2 : nullptr; }
@@ -252,6 +257,9 @@ void pool_layout(cb_pool* p)
     p->total = o;
 }
 
+// 1 x 1, stride 1, no padding: outputs are input pixels
+bool pointwise(const cb::Geom& g) { return g.kh == 1 && g.kw == 1 && g.s == 1 && g.p == 0; }
+
 // Next pair of begin/end events for one kernel dispatch (null events when timing is off).
 cb::Tm next_tm(cb_layer* L, int step)
 {
@@ -262,6 +270,33 @@ cb::Tm next_tm(cb_layer* L, int step)
     L->ev_step[L->ev_used / 2] = step;
     L->ev_used += 2;
     return tm;
+}
+
+// The index extraction of the stage behind L as a job for L's product kernel: that stage takes over L's change map (itself, or 2 x 2
+// pooled) and is in step with it, so that its map and list follow from L->cur_mtbits, which is complete.  False: it extracts for
+// itself (cb_process_frame_propagated), as it does where per-step times are asked for.
+bool extract_job(const cb_layer* L, cb::ExtractJob* job)
+{
+    const cb_layer* n = L->next;
+    const cb_pool* p = L->next_pool;
+    if (!n || L->timing || n->timing || !cb::fused_takes_job(L->g, L->plan) || n == L || n->d.mode != CB_PROPAGATE || n->st != L->st) return false;
+    if (p && (p->w != 2 || p->prod != L)) return false;
+    const cb::Geom& g = n->g;
+    if (g.C != L->g.O || g.bf16 != L->g.bf16 || g.H != (p ? p->Hp : L->g.Ho) || g.W != (p ? p->Wp : L->g.Wo)) return false;
+    if (n->d.gather_channel_last && !L->OUT2()) return false;
+    if (!n->primed || n->chain_src != (p ? (const void*)p : (const void*)L) || n->chain_frames != L->frames) return false;
+    if (!p && pointwise(g)) return false;                   // takes over the list itself
+    if (!cb::extract_fits(g)) return false;
+    job->g = g;
+    job->nblk = cb::dilate_num_blocks(g);
+    job->spin_limit = g_scan_wait_limit.load(std::memory_order_relaxed);
+    job->src_Ho = L->g.Ho; job->src_WWo = L->g.WWo;
+    job->in_bits = L->cur_mtbits;
+    job->pitch = 64L * ((g.W + 63) / 64);
+    job->pm_bits = p ? p->pmbits() : nullptr;
+    job->mt_bits = n->mtbits(); job->idx = n->idx(); job->ctl = n->ctl();
+    job->look = reinterpret_cast<unsigned long long*>(n->look());
+    return true;
 }
 
 // dilate + compact into the layer's own buffers, then the chunked
@@ -292,9 +327,12 @@ int run_back_end(cb_layer* L, const void* src, bool have_list)
         L->cur_count = L->ctl() + cb::CTL_COUNT;
     }
     if (L->fused) {
+        cb::ExtractJob job;
+        const bool feeds = extract_job(L, &job);
         CB_HIP(cb::launch_fused(g, L->plan, src, L->d.gather_channel_last ? L->ext_cl : L->S2(), L->cur_idx, L->cur_count,
-                                L->KF(), L->KT(), L->rowtab(), L->bias(), L->d.relu, L->OUT(), L->OUT2(), L->st,
-                                next_tm(L, CB_STEP_FUSED)));
+                                L->KF(), L->KT(), L->rowtab(), L->bias(), L->d.relu, L->OUT(), L->OUT2(),
+                                feeds ? &job : nullptr, L->st, next_tm(L, CB_STEP_FUSED)));
+        if (feeds) L->next->list_ready = true;
         L->primed = true;
         L->frames++;
         return CB_OK;
@@ -443,6 +481,9 @@ int cb_layer_create(const cb_layer_desc* desc, const void* w_oihw_dev, const voi
     L->chain_src = nullptr;
     L->chain_frames = 0;
     L->chain_tau = 0.0f;
+    L->next = nullptr;
+    L->next_pool = nullptr;
+    L->list_ready = false;
 
     hipError_t e = hipMemsetAsync(state_dev, 0, sl.total, L->st);
     if (e == hipSuccess) e = cb::launch_pack_weights(g, w_oihw_dev, bias_dev, L->KT(), L->bias(), L->st);
@@ -538,7 +579,7 @@ int cb_process_frame_propagated(cb_layer_t* L, const void* input_dev, const cb_l
         if (L->d.gather_channel_last && !pp->POOL2()) return CB_EINVAL;
         L->ext_cl = pp->POOL2();
         if (pp->done_frames != pp->prod->frames) return CB_ESTATE;   // the pooling stage has not seen the producer's last frame
-        if ((rc = pool_mask(pp))) return rc;
+        if (!L->list_ready && (rc = pool_mask(pp))) return rc;
         L->cur_in_bits = pp->pmbits();
         L->cur_in_pitch = 64L * pp->WWp;
         L->cur_in_own = false;
@@ -551,9 +592,14 @@ int cb_process_frame_propagated(cb_layer_t* L, const void* input_dev, const cb_l
     L->chain_src = src;
     L->chain_frames = src_frames;
     L->ev_used = 0;
-    const bool pointwise = g.kh == 1 && g.kw == 1 && g.s == 1 && g.p == 0;
     bool have_list = false;
-    if (pl && pointwise && L->primed) {
+    if (L->list_ready) {
+        // extracted beside the producer's product
+        L->cur_mtbits = L->mtbits();
+        L->cur_idx = L->idx();
+        L->cur_count = L->ctl() + cb::CTL_COUNT;
+        have_list = true;
+    } else if (pl && pointwise(g) && L->primed) {
         // Sec. III-E case 2: the change map and the index list are the producer's
         L->cur_mtbits = pl->cur_mtbits;
         L->cur_idx = pl->cur_idx;
@@ -933,15 +979,23 @@ int cb_network_forward(const cb_stage* stages, int32_t n_stages, const void* inp
         const cb_layer* pl = (s > 0 && !stages[s - 1].pool) ? stages[s - 1].layer : nullptr;
         const cb_pool* pp = s > 0 ? stages[s - 1].pool : nullptr;
         const void* out = nullptr;
+        // (the stage's product kernel can extract the next one's index list beside its own work)
+        L->next = s + 1 < n_stages ? stages[s + 1].layer : nullptr;
+        L->next_pool = stages[s].pool;
         if (s == 0) rc = cb_process_frame(L, x, taus[0], &out);
         else if (L->d.mode == CB_PROPAGATE) rc = cb_process_frame_propagated(L, x, pl, pp, &out);
         else rc = cb_process_frame_chained(L, x, pl, pp, taus[s], &out);
-        if (rc) return rc;
-        x = out;
-        if (stages[s].pool) {
+        L->next = nullptr;
+        L->next_pool = nullptr;
+        L->list_ready = false;
+        if (!rc) x = out;
+        if (!rc && stages[s].pool) {
             rc = cb_pool_process(stages[s].pool, &out);
-            if (rc) return rc;
-            x = out;
+            if (!rc) x = out;
+        }
+        if (rc) {
+            if (s + 1 < n_stages) stages[s + 1].layer->list_ready = false;
+            return rc;
         }
     }
     if (output_dev) *output_dev = x;
