@@ -255,7 +255,11 @@ int cb_layer_out_shape(const cb_layer_t *layer, int32_t *c_out, int32_t *h_out, 
 int cb_layer_set_timing(cb_layer_t *layer, int32_t on);
 /* Waits for the layer's stream, then fills *stats for the last frame. */
 int cb_layer_stats(cb_layer_t *layer, cb_stats *stats);
-/* The one-launch index extraction (Sec. III-A, "Change Indexes Extraction") scans the per-workgroup
+/* The index extraction (Sec. III-A, "Change Indexes Extraction") runs inside the launch that detects the changes where it
+ * can, its workgroups waiting for those that detect.  It takes a launch of its own for very large maps, strides above 2 and
+ * very many channels, while per-step times are switched on (they are those of the separate launches), and with any other
+ * limit than the default here.
+ * The one-launch index extraction scans the per-workgroup
  * counts in a single pass: a workgroup polls for the counts of the workgroups before it.  After
  * `polls` unsuccessful polls of one count it recomputes that count from the change map instead, so
  * the index list and N never depend on how the GPU schedules workgroups (other streams or processes

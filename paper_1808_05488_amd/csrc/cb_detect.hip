@@ -10,7 +10,7 @@
 // group walks the channels g, g+CS, ...; the per-group flags are OR-ed through
 // LDS.  Splitting channels over groups multiplies the number of wavefronts in
 // flight for layers with many channels and few pixels.
-#include "cb_kernels.h"
+#include "cb_extract.h"
 #include <algorithm>
 
 namespace cb {
@@ -199,6 +199,18 @@ __global__ __launch_bounds__(256) void detect_kernel(const T* __restrict__ x, T*
     }
 }
 
+// The LDS of a workgroup of the register-resident variant: flags of the channel groups, and for a shadow the staged pixels' numbers and rows.
+template <typename T, int VEC, int CS, int CPT, int PLX, bool SH> struct DetectLds {
+    static constexpr int PL = PLX ? PLX : (CS >= 4 ? 64 : 256 / CS), NT = PL * CS;
+    static constexpr int EPV = 16 / (int)sizeof(T);  // elements per 16 bytes
+    static constexpr int CMAX = CS * CPT;
+    static constexpr int PITCH = CMAX + EPV;         // elements per staged pixel: 16-byte aligned rows, banks spread
+    static constexpr int KMAX = NT * 16 / (PITCH * (int)sizeof(T)) > 0 ? NT * 16 / (PITCH * (int)sizeof(T)) : 1;
+    static constexpr int flags = CS > 1 ? NT * 4 : 0, pix = SH ? PL * VEC * 4 : 0, rows = SH ? 2 * KMAX * PITCH * (int)sizeof(T) : 0;
+    static constexpr int bytes = flags + pix + rows;
+    static_assert(flags % 16 == 0 && pix % 16 == 0, "rows are 16-byte aligned");
+};
+
 // Register-resident variant: a lane keeps the CPT channel values it compared, so
 // the state update is stores only (no second, latency-bound read of the frame).
 // Workgroup = CS channel groups x PL pixel lanes.
@@ -208,16 +220,19 @@ __global__ __launch_bounds__(256) void detect_kernel(const T* __restrict__ x, T*
 // SH: the layer keeps a channel-last shadow of its state (S2), and channel q of group g is g*CPT + q instead of
 // g + q*CS, so that a lane's channels are neighbours in the shadow.  C <= CS*CPT; the shadow's pixels are the C channels rounded
 // up to whole 16-byte pieces, zero behind the last.  inv_per = ceil(2^20 / pieces of a pixel) divides a piece's number (below 1 024) by it.
-template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false>
-__global__ __launch_bounds__((PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS)
-void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2, uint64_t* __restrict__ mbits0,
-                       int* __restrict__ ctl, int C, int Cs, unsigned inv_per, int P, int nwords, float tau, int flags, int2 stream)
+// lds: detect_lds bytes (the extracting workgroups of the same launch put theirs to other uses).
+// MAIL: the map also goes, tagged, to the extracting workgroups of the same launch.
+template <typename T, int VEC, int CS, int CPT, int PLX, bool SH, bool MAIL>
+__device__ __forceinline__
+void detect_reg_block(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2, uint64_t* __restrict__ mbits0,
+                      int* __restrict__ ctl, int C, int Cs, unsigned inv_per, int P, int nwords, float tau, int flags, int2 stream, uint64_t* mail, char* lds)
 {
     typedef typename Pack<T, VEC>::type V;
     // which of the two map buffers and counters this frame fills: the frame count lives on the device
     // (the index extraction advances it), so that a captured launch replays correctly whatever the
     // number of frames captured
-    const int par = ctl[CTL_FRAME] & 1;
+    const int frame = ctl[CTL_FRAME], par = frame & 1;
+    const unsigned tag = (unsigned)frame + 1u;
     uint64_t* __restrict__ mbits = mbits0 + par;  // the two maps are interleaved: word w of this frame's map at [2 * w]
     int* __restrict__ nin = nin_counter(ctl, blockIdx.x, par);
     constexpr int PL = PLX ? PLX : (CS >= 4 ? 64 : 256 / CS);
@@ -286,7 +301,7 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
         }
     }
     if (CS > 1) {
-        __shared__ unsigned sflag[NT];
+        unsigned* const sflag = reinterpret_cast<unsigned*>(lds);
         sflag[tid] = bits;
         __syncthreads();
 #pragma unroll
@@ -306,6 +321,10 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
                 const int sh = 16 * lane;
                 uint64_t w = spread4((b0 >> sh) & 0xFFFF) | (spread4((b1 >> sh) & 0xFFFF) << 1) |
                              (spread4((b2 >> sh) & 0xFFFF) << 2) | (spread4((b3 >> sh) & 0xFFFF) << 3);
+                if constexpr (MAIL) {
+                    mail_put(mail, 2 * (w0 + lane), tag, (unsigned)w);
+                    mail_put(mail, 2 * (w0 + lane) + 1, tag, (unsigned)(w >> 32));
+                }
                 mbits[2 * (w0 + lane)] = w;
             }
             if (lane == 0) {
@@ -316,11 +335,18 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
             // the active lanes are lanes 0-15 of the first wavefront: 16 consecutive pixels
             const unsigned b0 = (unsigned)__ballot(bits & 1u) & 0xFFFFu;
             if (lane == 0) {
+                if constexpr (MAIL) {
+                    mail_put(mail, blockIdx.x, tag, b0);
+                    // (the last word's units behind the image have no workgroup of their own)
+                    if ((long)(blockIdx.x + 1) * 16 >= P)
+                        for (long u = (long)blockIdx.x + 1; u < 4L * nwords; ++u) mail_put(mail, u, tag, 0u);
+                }
                 reinterpret_cast<uint16_t*>(mbits + 2 * (blockIdx.x >> 2))[blockIdx.x & 3] = (uint16_t)b0;
                 if (b0) atomicAdd(nin, __popc(b0));
             }
         } else {
             uint64_t b0 = __ballot(bits & 1u);
+            if (MAIL && lane < 2 && w0 < nwords) mail_put(mail, 2 * w0 + lane, tag, (unsigned)(b0 >> (32 * lane)));
             if (lane == 0 && w0 < nwords) {
                 mbits[2 * w0] = b0;
                 int tot = __popcll(b0);
@@ -381,12 +407,10 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
     if constexpr (SH) {
         static_assert(CS >= 4 && (CPT * sizeof(T)) % 16 == 0, "shadow rows are staged 16 bytes at a time");
         if (S2 != nullptr) {
-            constexpr int EPV = 16 / (int)sizeof(T);  // elements per 16 bytes
-            constexpr int CMAX = CS * CPT;
-            constexpr int PITCH = CMAX + EPV;         // elements per staged pixel: 16-byte aligned rows, banks spread
-            constexpr int KMAX = NT * 16 / (PITCH * (int)sizeof(T)) > 0 ? NT * 16 / (PITCH * (int)sizeof(T)) : 1;
-            __shared__ int s_pix[PL * VEC];
-            __shared__ __align__(16) T stage[2][KMAX * PITCH];
+            typedef DetectLds<T, VEC, CS, CPT, PLX, SH> LDS;
+            constexpr int EPV = LDS::EPV, CMAX = LDS::CMAX, PITCH = LDS::PITCH, KMAX = LDS::KMAX;
+            int* const s_pix = reinterpret_cast<int*>(lds + LDS::flags);
+            T (* const stage)[KMAX * PITCH] = reinterpret_cast<T (*)[KMAX * PITCH]>(lds + LDS::flags + LDS::pix);
             // a channel group is a whole wavefront, or (16-lane groups) a quarter of one
             const int lane = tid & 63;
             const int seg_shift = PL >= 64 ? 0 : (lane & ~(PL - 1));
@@ -450,6 +474,39 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
             }
         }
     }
+}
+
+template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false>
+__global__ __launch_bounds__((PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS)
+void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2, uint64_t* __restrict__ mbits0,
+                       int* __restrict__ ctl, int C, int Cs, unsigned inv_per, int P, int nwords, float tau, int flags, int2 stream)
+{
+    typedef DetectLds<T, VEC, CS, CPT, PLX, SH> LDS;
+    __shared__ __align__(16) char lds[LDS::bytes ? LDS::bytes : 16];
+    detect_reg_block<T, VEC, CS, CPT, PLX, SH, false>(x, S, S2, mbits0, ctl, C, Cs, inv_per, P, nwords, tau, flags, stream, nullptr, lds);
+}
+
+// Detection with the index extraction in the same launch: the last job.nblk workgroups extract.  A launch of its own costs the extraction
+// 4 - 8 us, of which most is the end of one kernel, the start of the next and its first loads from memory.  Frames, us, before / now:
+// 3 -> 16 at 48x64 15.1 / 12.4, 64 -> 64 at 480x640 41.7 / 39.5, 64 -> 128 at 271x435 bfloat16 24.5 / 20.9, 48 -> 96 5x5 stride 2 at 241x323
+// 29.0 / 27.1, 3 -> 16 7x7 at 1080p 32.3 / 30.3, 32 -> 32 9x9 at 240x320 34.0 / 31.1, 128 -> 128 at 1080p bfloat16, 10 % 459 / 454.
+template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false>
+__global__ __launch_bounds__((PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS)
+void detect_extract_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2, uint64_t* __restrict__ mbits0,
+                           int* __restrict__ ctl, int C, int Cs, unsigned inv_per, int P, int nwords, float tau, int flags, int2 stream, DetectJob job)
+{
+    constexpr int NT = (PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS;
+    typedef DetectLds<T, VEC, CS, CPT, PLX, SH> LDS;
+    constexpr int EX = MAP_STAGE * 8 + one_pass_small<NT / 64>() * 4;
+    __shared__ __align__(16) char lds[LDS::bytes > EX ? LDS::bytes : EX];
+    const unsigned detecting = gridDim.x - (unsigned)job.nblk;
+    if (blockIdx.x >= detecting) {
+        const int frame = ctl[CTL_FRAME];
+        extract_own_block<NT, PLX ? 64 / (PLX ? PLX : 1) : 2>(job, ctl, mbits0, frame & 1, (unsigned)frame + 1u, (int)(blockIdx.x - detecting),
+                                                              reinterpret_cast<uint64_t*>(lds));
+        return;
+    }
+    detect_reg_block<T, VEC, CS, CPT, PLX, SH, true>(x, S, S2, mbits0, ctl, C, Cs, inv_per, P, nwords, tau, flags, stream, job.mail, lds);
 }
 
 // State update as a kernel of its own, for frames whose change detection ran with DET_NO_UPDATE: all
@@ -582,15 +639,37 @@ __global__ __launch_bounds__(256) void shadow_rebuild_kernel(const T* __restrict
     }
 }
 
+// The extraction inside the launch of detection, by workgroups of nt threads: words of the dilated map per wavefront (0: it takes a launch
+// of its own).  The workgroups that wait are at most a quarter of the chip's wavefronts, and the part of the map under one workgroup's words
+// fits its LDS.  Few words a wavefront spread the expansion of dense words and shorten the polls, many workgroups add up more
+// counts and poll for more of each other's rows.  Frames, us, 16 / 32 / 64 words: 3 -> 16, 7x7, 1080p (507, 254, 127 workgroups) 36.3 / 32.0 / 30.4;
+// 3 -> 16 at 720p (225, 113, 57) 18.2 / 16.8 / 16.9; 3 -> 16 at 240x320 (19, 10, 5) 13.1 / 13.4 / 14.1; 64 -> 32 at 120x160 14.8 / 15.0 / 15.9; 64 -> 64 at
+// 480x640, 20 % (38, 19, 10) 81.5 / 82.2 / 84.8; 128 -> 64 at 46x82, bfloat16 (2, 1, 1) 16.4 / 15.6 / 16.1.
+int extract_words(const Geom& g, int nt)
+{
+    if (g.s > 2) return 0;
+    const long items = (long)g.Ho * g.WWo;
+    auto blocks = [&](int per) { return (items - 1) / (nt / 64 * per) + 1; };
+    const int per = blocks(16) > 2 && blocks(16) <= 40 ? 16 : blocks(32) <= 80 ? 32 : 64;
+    const long ipb = nt / 64 * per;
+    const long rows = std::min<long>((ipb - 1 + g.WWo - 1) / g.WWo * g.s + std::max(g.kh, g.s) + 1 + g.p, g.H);
+    return blocks(per) * nt <= 131072 && rows * g.W / 64 + 5 <= MAP_STAGE ? per : 0;
+}
+
 template <typename T, int VEC, int CS, int CPT, int PLX = 0>
-void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int Cs, int P, float tau, int flags, int2 stream, hipStream_t st, Tm tm)
+void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int Cs, int P, float tau, int flags, int2 stream, DetectJob* job, hipStream_t st, Tm tm)
 {
     constexpr int PL = PLX ? PLX : (CS >= 4 ? 64 : 256 / CS);
     const long px_per_block = (long)PL * VEC;
     const unsigned grid = (unsigned)((P + px_per_block - 1) / px_per_block);
     const unsigned per = (unsigned)Cs * (unsigned)sizeof(T) / 16u, inv_per = per ? ((1u << 20) + per - 1u) / per : 0u;
+    // (job->nblk stays 0 where the extraction takes a launch of its own)
+    if (job && (job->per = extract_words(job->g, PL * CS)) > 0) job->nblk = (job->g.Ho * job->g.WWo - 1) / (PL * CS / 64 * job->per) + 1;
 #define CB_REG(sh, shadow)                                                                                                          \
-    CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX, sh>), dim3(grid), dim3(PL * CS), st, tm, x, S, shadow, mbits, ctl, C, Cs, \
+    if (job && job->nblk)                                                                                                           \
+        hipLaunchKernelGGL((detect_extract_kernel<T, VEC, CS, CPT, PLX, sh>), dim3(grid + (unsigned)job->nblk), dim3(PL * CS), 0, st, x, S, shadow, \
+                           mbits, ctl, C, Cs, inv_per, P, (P + 63) / 64, tau, flags, stream, *job);                                  \
+    else CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX, sh>), dim3(grid), dim3(PL * CS), st, tm, x, S, shadow, mbits, ctl, C, Cs, \
               inv_per, P, (P + 63) / 64, tau, flags, stream)
     if constexpr (CS >= 4 && (CPT * sizeof(T)) % 16 == 0) {
         // (launch_t only passes a shadow on when the variant's registers hold all C channels)
@@ -604,28 +683,28 @@ void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int C
 }
 
 template <typename T, int VEC>
-void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int Cs, int P, float tau, int flags, int2 stream, hipStream_t st, Tm tm)
+void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int Cs, int P, float tau, int flags, int2 stream, DetectJob* job, hipStream_t st, Tm tm)
 {
     // channel groups CS and channels per lane CPT with CS*CPT >= C
-    if (C <= 4)        launch_reg<T, VEC, 1, 4>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
-    else if (C <= 8)   launch_reg<T, VEC, 1, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    if (C <= 4)        launch_reg<T, VEC, 1, 4>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
+    else if (C <= 8)   launch_reg<T, VEC, 1, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
     // (bfloat16 with a shadow: eight channels per lane are one of its 16-byte pieces)
-    else if (C <= 16 && !(sizeof(T) == 2 && S2)) launch_reg<T, VEC, 4, 4>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
-    else if (C <= 32)  launch_reg<T, VEC, 4, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
-    else if (C <= 64)  launch_reg<T, VEC, 8, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    else if (C <= 16 && !(sizeof(T) == 2 && S2)) launch_reg<T, VEC, 4, 4>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
+    else if (C <= 32)  launch_reg<T, VEC, 4, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
+    else if (C <= 64)  launch_reg<T, VEC, 8, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
     // maps of fewer than 128 x 64 pixels with many channels: 16-pixel workgroups reach every compute unit
-    else if (VEC == 1 && P < 8192 && C <= 128) launch_reg<T, 1, 16, 8, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
-    else if (VEC == 1 && P < 8192 && C <= 256) launch_reg<T, 1, 16, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
-    else if (VEC == 1 && P < 8192 && C <= 512) launch_reg<T, 1, 16, 32, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
-    else if (C <= 128) launch_reg<T, VEC, 16, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    else if (VEC == 1 && P < 8192 && C <= 128) launch_reg<T, 1, 16, 8, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
+    else if (VEC == 1 && P < 8192 && C <= 256) launch_reg<T, 1, 16, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
+    else if (VEC == 1 && P < 8192 && C <= 512) launch_reg<T, 1, 16, 32, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
+    else if (C <= 128) launch_reg<T, VEC, 16, 8>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
     // (129 - 256 bfloat16 channels: 82 registers.  They walked their channels one by one, or 2 bytes per lane and load: frames, us,
     // 160 channels, 1x1, at 540x960 116 -> 77, 256 channels there 181 -> 105, at 180x200 36 -> 29.  float32 would need 140 registers.)
     else if (VEC == 4 && sizeof(T) == 2 && C <= 256) {
-        if constexpr (VEC == 4 && sizeof(T) == 2) launch_reg<T, 4, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+        if constexpr (VEC == 4 && sizeof(T) == 2) launch_reg<T, 4, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
     }
     // one pixel per lane leaves registers for more channels per lane (deep layers: many channels, few pixels)
-    else if (VEC == 1 && C <= 256) launch_reg<T, 1, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
-    else if (VEC == 1 && C <= 512) launch_reg<T, 1, 16, 32>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, st, tm);
+    else if (VEC == 1 && C <= 256) launch_reg<T, 1, 16, 16>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
+    else if (VEC == 1 && C <= 512) launch_reg<T, 1, 16, 32>(x, S, S2, mbits, ctl, C, Cs, P, tau, flags, stream, job, st, tm);
     else {
         // more channels than the register-resident variants hold: looped variant
         const long px_per_block = 64L * VEC;
@@ -826,7 +905,7 @@ int2 state_read_once(const Geom& g, int esz, bool shadow)
 
 template <typename T>
 hipError_t launch_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, float tau, int flags,
-                    hipStream_t st, Tm tm)
+                    DetectJob* job, hipStream_t st, Tm tm)
 {
     const int P = g.P;
     const int2 stream = state_read_once(g, sizeof(T), S2 != nullptr);
@@ -849,22 +928,41 @@ hipError_t launch_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int
     const int regs4 = sizeof(T) == 2 ? 256 : 128;         // channels that the variants with four pixels per lane hold in registers
     const bool vec4 = P >= (sizeof(T) == 4 ? 65536 : 32768) && !one_px &&
                       (aligned || (sizeof(T) == 2 && g.C <= regs4)) && (g.C <= regs4 || (P >= 65536 && !(S2 != nullptr && g.C <= 512)));
-    if (vec4) launch_v<T, 4>(x, S, S2, mbits, ctl, g.C, g.Cs, P, tau, flags, stream, st, tm);
-    else      launch_v<T, 1>(x, S, S2, mbits, ctl, g.C, g.Cs, P, tau, flags, stream, st, tm);
+    if (vec4) launch_v<T, 4>(x, S, S2, mbits, ctl, g.C, g.Cs, P, tau, flags, stream, job, st, tm);
+    else      launch_v<T, 1>(x, S, S2, mbits, ctl, g.C, g.Cs, P, tau, flags, stream, job, st, tm);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_detect(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
-                         float tau, int flags, hipStream_t st, Tm tm)
+static hipError_t launch_any(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl, float tau, int flags, DetectJob* job,
+                             hipStream_t st, Tm tm)
 {
     // the pixels of a shadow are whole 16-byte pieces
     if (S2 && (g.Cs < g.C || g.Cs % (g.bf16 ? 8 : 4) != 0)) return hipErrorInvalidValue;
     if (g.bf16)
-        return launch_t<uint16_t>(g, (const uint16_t*)x, (uint16_t*)S, (uint16_t*)S2, mbits, ctl, tau, flags,
-                                  st, tm);
-    return launch_t<float>(g, (const float*)x, (float*)S, (float*)S2, mbits, ctl, tau, flags, st, tm);
+        return launch_t<uint16_t>(g, (const uint16_t*)x, (uint16_t*)S, (uint16_t*)S2, mbits, ctl, tau, flags, job, st, tm);
+    return launch_t<float>(g, (const float*)x, (float*)S, (float*)S2, mbits, ctl, tau, flags, job, st, tm);
+}
+
+hipError_t launch_detect(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
+                         float tau, int flags, hipStream_t st, Tm tm)
+{
+    return launch_any(g, x, S, S2, mbits, ctl, tau, flags, nullptr, st, tm);
+}
+
+size_t detect_mail_bytes(const Geom& g) { return ((size_t)g.P + 63) / 64 * (g.P < 8192 ? 32 : 16); }
+
+// (at least 64 words a workgroup)
+size_t detect_look_bytes(const Geom& g) { return ((size_t)g.Ho * g.WWo / 64 + 1) * 8; }
+
+hipError_t launch_detect_extract(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl, float tau, int flags,
+                                 DetectJob job, hipStream_t st, bool* extracted)
+{
+    job.nblk = 0;
+    const hipError_t e = launch_any(g, x, S, S2, mbits, ctl, tau, flags, &job, st, Tm());
+    *extracted = job.nblk > 0;
+    return e;
 }
 
 hipError_t launch_state_apply(const Geom& g, const void* x, void* S, void* S2, const uint64_t* mbits, const int* ctl,

@@ -41,6 +41,25 @@ struct MapInLds {
     __device__ __forceinline__ uint64_t operator()(long wi) const { return w[wi - first]; }
 };
 
+// Bits q .. q + 127 (q < 64) of three consecutive words, with 32-bit shifts over two registers: four and five selections, where 64-bit shifts
+// take four, of several cycles each, and as many selections for q = 0.  (A 64-bit shift by an amount in the last register of a kernel's
+// allocation, v39 of 40, took that amount from register 0 now and then: gfx90a's compiler avoids the form, gfx950's does not.
+// tests/test_shift_amounts.py looks for it in every kernel.)
+__device__ __forceinline__ void window(const uint64_t (&v)[3], unsigned q, uint64_t& lo, uint64_t& hi)
+{
+    uint32_t w[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        const uint32_t a = (uint32_t)(v[i >> 1] >> (32 * (i & 1))), b = (uint32_t)(v[(i + 1) >> 1] >> (32 * ((i + 1) & 1)));
+        w[i] = q & 32u ? b : a;
+    }
+    uint32_t r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], q & 31u);
+    lo = (uint64_t)r[1] << 32 | r[0];
+    hi = (uint64_t)r[3] << 32 | r[2];
+}
+
 // Bit q (q = 0..63) = OR over the filter footprint of an output whose receptive field's top-left
 // pixel is (y0, x0 + q); pixels outside the image read as zero.  -63 <= x0.  The filter's rows are
 // OR-ed first, as 128-column windows (their column limits are the same for every row), the columns
@@ -72,10 +91,10 @@ __device__ __forceinline__ uint64_t fires_rows(const Geom& g, const WORDS& words
         }
 #pragma unroll
         for (int u = 0; u < KB; ++u) {
-            const int q = sh[u] & 63;
-            const uint64_t bl = q ? v[u][1] << (64 - q) : 0ull, cl = q ? v[u][2] << (64 - q) : 0ull;
-            lo |= sh[u] >= 0 ? (v[u][0] >> q) | bl : 0ull;
-            hi |= sh[u] >= 0 ? (v[u][1] >> q) | cl : 0ull;
+            uint64_t l, h;
+            window(v[u], (unsigned)sh[u] & 63u, l, h);
+            lo |= sh[u] >= 0 ? l : 0ull;
+            hi |= sh[u] >= 0 ? h : 0ull;
         }
     }
     lo &= len >= 64 ? ~0ull : (len > 0 ? (1ull << len) - 1ull : 0ull);
@@ -261,16 +280,18 @@ constexpr int MAP_STAGE = 2048, MAP_STAGE_SMALL = 4608;
 // The second half of the single-pass extraction, for workgroup bid of nblk: scan over the workgroups' words and index write.
 // word: this thread's word of the dilated map, pixbase the pixel of its bit 0; epoch_ld (thread 0): CTL_EPOCH as it was at launch;
 // recount(b): the set bits in workgroup b's 256 words, from the input map alone; small: LDS, ONE_PASS_SMALL words.
-constexpr int ONE_PASS_SMALL = 9;
-template <typename RECOUNT>
+// NW: wavefronts of a workgroup.
+template <int NW> __host__ __device__ constexpr int one_pass_small() { return 2 * NW + 1; }
+constexpr int ONE_PASS_SMALL = one_pass_small<4>();
+template <int NW = 4, typename RECOUNT>
 __device__ __forceinline__ void one_pass_tail(uint64_t word, int pixbase, unsigned epoch_ld, int32_t* __restrict__ idx, int* __restrict__ ctl,
                                               unsigned long long* __restrict__ look, int own_map, int bid, int nblk, int spin_limit,
                                               unsigned* small, RECOUNT&& recount)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     int* const wtot = reinterpret_cast<int*>(small);
-    int* const red = wtot + 4;
-    unsigned& s_epoch = small[8];
+    int* const red = wtot + NW;
+    unsigned& s_epoch = small[2 * NW];
     const int cnt = __popcll(word);
     const int inc = wave_inclusive_scan(cnt);                  // inclusive scan inside the wavefront
     if (lane == 63) wtot[wv] = inc;
@@ -278,13 +299,15 @@ __device__ __forceinline__ void one_pass_tail(uint64_t word, int pixbase, unsign
     __syncthreads();
     const unsigned epoch = s_epoch;
     if (tid == 0) {
-        const unsigned total = (unsigned)(wtot[0] + wtot[1] + wtot[2] + wtot[3]);
+        unsigned total = 0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) total += (unsigned)wtot[q];
         __hip_atomic_store(&look[bid], ((unsigned long long)epoch << 32) | total, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
     // counts of all earlier workgroups (count and epoch travel in one word: no ordering between words needed)
     int part = 0;
-    for (int b = tid; b < bid; b += 256) {
+    for (int b = tid; b < bid; b += 64 * NW) {
         unsigned long long v = 0;
         int spins = 0;
         for (;;) {
@@ -302,10 +325,12 @@ __device__ __forceinline__ void one_pass_tail(uint64_t word, int pixbase, unsign
     part = wave_sum(part);
     if (lane == 0) red[wv] = part;
     __syncthreads();
-    int off = red[0] + red[1] + red[2] + red[3];
+    int off = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) off += red[q];
     for (int q = 0; q < wv; ++q) off += wtot[q];
     off += inc - cnt;                                        // exclusive offset of this thread's word
-    if (bid == nblk - 1 && tid == 255) ctl[CTL_COUNT] = off + cnt;
+    if (bid == nblk - 1 && tid == 64 * NW - 1) ctl[CTL_COUNT] = off + cnt;
 
     expand_words<false>(word, off, pixbase, idx, lane);
 
@@ -365,13 +390,102 @@ __device__ __forceinline__ void extract_block(const ExtractJob& job, int bid, ui
         job.mt_bits[it] = word;
         pixbase = yo * g.Wo + 64 * wo;
     }
-    one_pass_tail(word, pixbase, epoch_ld, job.idx, job.ctl, job.look, 0, bid, job.nblk, job.spin_limit,
+    one_pass_tail<4>(word, pixbase, epoch_ld, job.idx, job.ctl, job.look, 0, bid, job.nblk, job.spin_limit,
                   reinterpret_cast<unsigned*>(lds + MAP_STAGE), [&](int b) {
                       int total = 0;
                       const int hi = b * 256 + 256 < items ? b * 256 + 256 : items;
                       for (int i = b * 256; i < hi; ++i) total += __popcll(dilated_word_t(g, src, job.pitch, i / g.WWo, i % g.WWo));
                       return total;
                   });
+}
+
+// The change map of a frame on its way to extracting workgroups of the same launch: units of up to 32 pixels (16 for workgroups of 16
+// pixels), each one 64-bit value with the frame's tag above the bits.  A unit travels whole, so its reader needs no other ordering than to see the
+// tag, and its writer waits for nothing.  (A count of finished workgroups instead means a wait for two round trips to memory in each
+// of them; a fence, needed for plain stores of the map, raised detection from 26 to 344 us on a VGA layer of 64 channels.)
+__device__ __forceinline__ void mail_put(uint64_t* mail, long unit, unsigned tag, unsigned bits)
+{
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(mail) + unit, ((unsigned long long)tag << 32) | bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// words i and i + step of the map (those from nwords on are 0), from UPW units each; waits for them
+template <int UPW> __device__ __forceinline__ void mail_words(const uint64_t* mail, long i, long step, long nwords, unsigned tag, uint64_t (&w)[2])
+{
+    unsigned long long v[2][UPW];
+    for (;;) {
+        bool all = true;
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int u = 0; u < UPW; ++u) {
+                const long wi = i + k * step < nwords ? i + k * step : i;        // (i itself is below nwords)
+                v[k][u] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(mail) + UPW * wi + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int u = 0; u < UPW; ++u) all = all && (unsigned)(v[k][u] >> 32) == tag;
+        if (all) break;
+        __builtin_amdgcn_s_sleep(1);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        w[k] = 0;
+#pragma unroll
+        for (int u = 0; u < UPW; ++u) w[k] |= (uint64_t)(unsigned)v[k][u] << (64 / UPW * u);
+        if (i + k * step >= nwords) w[k] = 0;
+    }
+}
+
+// Workgroup bid of job.nblk (NT threads) of an extraction inside the launch that detects the changes.  A wavefront has job.per words of
+// the dilated map, 16 where there are few: dense words are expanded one after the other, and a part of a map that is waited for should be small.  par, tag: of this frame; lds:
+// MAP_STAGE words and one_pass_small 32-bit words.  Strides 1 and 2 (extract_words in cb_detect.hip).  Every wait ends: a detecting workgroup waits for nothing, an
+// extracting one for detecting ones and extracting ones before it, and all extracting workgroups together fill at most a quarter of
+// the chip, so that none of the others can be kept from starting, whatever the order in which they are dispatched.
+template <int NT, int UPW>
+__device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __restrict__ ctl, uint64_t* maps, int par, unsigned tag, int bid, uint64_t* lds)
+{
+    const Geom& g = job.g;
+    const int tid = threadIdx.x, lane = tid & 63, items = g.Ho * g.WWo, nwords = (g.P + 63) / 64;
+    const int ipb = NT / 64 * job.per, it0 = bid * ipb;                  // words of a workgroup, its first
+    const int it = lane < job.per ? it0 + (tid >> 6) * job.per + lane : items;
+    const unsigned epoch_ld = tid == 0 ? (unsigned)ctl[CTL_EPOCH] : 0u;
+    clear_other_map(maps, ctl, par, job.clear_words, bid * NT + tid, job.nblk * NT);
+    // The input rows under this workgroup's words, and those between them and the next workgroup's, so that together the workgroups wait for
+    // every word: then all that detect have read the frame count and the last count of listed pixels, which the tail overwrites.
+    const int last = (it0 + ipb < items ? it0 + ipb : items) - 1;
+    int r0 = (it0 / g.WWo) * g.s - g.p, r1 = (last / g.WWo) * g.s - g.p + g.kh - 1;
+    const int next = last + 1 < items ? (last + 1) / g.WWo * g.s - g.p - 1 : g.H - 1;
+    r1 = r1 > next ? r1 : next;
+    r0 = r0 < 0 ? 0 : (r0 > g.H - 1 ? g.H - 1 : r0);
+    r1 = r1 < 0 ? 0 : (r1 > g.H - 1 ? g.H - 1 : r1);
+    const long first = ((long)r0 * g.W) >> 6;
+    const int n = (int)(((((long)r1 * g.W + g.W - 1) >> 6) + 3) - first);
+    for (int i = tid; i < n; i += 2 * NT) {
+        uint64_t w[2] = {0, 0};
+        if (first + i < nwords) mail_words<UPW>(job.mail, first + i, NT, nwords, tag, w);
+        lds[i] = w[0];
+        if (i + NT < n) lds[i + NT] = w[1];
+    }
+    __syncthreads();
+    const int yo = it / g.WWo, wo = it - yo * g.WWo;
+    uint64_t word = 0;
+    int pixbase = 0;
+    if (it < items) {
+        if (job.full) word = full_word(g, it);
+        else {
+            const int nvalid = g.Wo - 64 * wo < 64 ? g.Wo - 64 * wo : 64;
+#pragma unroll 1
+            for (int t = 0; t < g.s && 32 * t < nvalid; ++t) {
+                const uint64_t f = fires_rows<2>(g, MapInLds{lds, first}, g.W, yo * g.s - g.p, 64 * wo * g.s - g.p + 64 * t);
+                word |= g.s == 1 ? f : even_bits(f) << (32 * t);
+            }
+            word &= nvalid == 64 ? ~0ull : ((1ull << nvalid) - 1ull);
+        }
+        job.mt_bits[it] = word;
+        pixbase = yo * g.Wo + 64 * wo;
+    }
+    one_pass_tail<NT / 64>(word, pixbase, epoch_ld, job.idx, ctl, job.look, 1, bid, job.nblk, 0x7FFFFFFF,
+                           reinterpret_cast<unsigned*>(lds + MAP_STAGE), [](int) { return 0; });
 }
 
 }  // namespace

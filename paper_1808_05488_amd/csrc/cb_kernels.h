@@ -78,6 +78,18 @@ struct ExtractJob {
 // ... for maps whose part under one workgroup's words fits its LDS, and of few enough workgroups to be resident at once beside the product's
 bool extract_fits(const Geom& consumer);
 
+// Index extraction of a layer that detects its own changes, by the last workgroups of the launch that detects them.
+struct DetectJob {
+    Geom g;
+    int nblk = 0, per = 0, full = 0, clear_words = 0;
+    uint64_t* mail = nullptr;              // detect_mail_bytes(g), zero-initialised, of the layer's own
+    uint64_t* mt_bits = nullptr;
+    int32_t* idx = nullptr;
+    unsigned long long* look = nullptr;
+};
+size_t detect_mail_bytes(const Geom& g);
+size_t detect_look_bytes(const Geom& g);   // of the counts that its workgroups publish
+
 // flags for detect
 enum { DET_FORCE_ALL = 1,      // mark every pixel as changed (first frame)
        DET_COPY_ALL = 2,       // copy every pixel into the state (feed-forward)
@@ -94,6 +106,9 @@ enum { DET_FORCE_ALL = 1,      // mark every pixel as changed (first frame)
 // the map this frame fills and the changed-pixel counter it adds to.
 hipError_t launch_detect(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
                          float tau, int flags, hipStream_t st, Tm tm = Tm());
+// The same with the index extraction in the launch where that is possible (*extracted; else the caller launches it).
+hipError_t launch_detect_extract(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl, float tau, int flags,
+                                 DetectJob job, hipStream_t st, bool* extracted);
 
 // The state update of a frame whose detection ran with DET_NO_UPDATE (same stream, before the index
 // extraction of that frame): copies the marked pixels of x into S and, if not null, the shadow S2.

@@ -6,6 +6,7 @@
 // matrix kernels are launched with persistent grids that read it there.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
@@ -21,7 +22,8 @@ namespace {
 
 thread_local int g_last_hip = 0;
 // polls of a predecessor's count in the single-pass index extraction before the count is recomputed
-std::atomic<int> g_scan_wait_limit{1 << 20};
+constexpr int kScanWaitDefault = 1 << 20;
+std::atomic<int> g_scan_wait_limit{kScanWaitDefault};
 
 inline int hip_fail(hipError_t e) { g_last_hip = (int)e; return CB_EHIP; }
 #define CB_HIP(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return hip_fail(e_); } while (0)
@@ -29,7 +31,7 @@ inline int hip_fail(hipError_t e) { g_last_hip = (int)e; return CB_EHIP; }
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct StateLayout {
-    size_t S, S2, OUT, OUT2, mbits, mtbits, idx, ctl, look, KT, bias, m_u8, mt_u8, KF, rowtab, total;
+    size_t S, S2, OUT, OUT2, mbits, mail, mtbits, idx, ctl, look, KT, bias, m_u8, mt_u8, KF, rowtab, total;
 };
 
 struct ScratchLayout {
@@ -122,10 +124,11 @@ StateLayout state_layout(const cb_layer_desc* d, const cb::Geom& g)
     L.OUT = o;    o += align256((size_t)g.O * g.Po * b);
     L.OUT2 = o;   o += d->keep_output_channel_last ? align256((size_t)g.O * g.Po * b) : 0;
     L.mbits = o;  o += align256(((size_t)(g.P + 63) / 64 + 4) * 16);  // two maps, word-interleaved: frames alternate between them
+    L.mail = o;   o += d->mode == CB_PROPAGATE ? 0 : align256(cb::detect_mail_bytes(g));
     L.mtbits = o; o += align256(((size_t)g.Ho * g.WWo + 4) * 8);
     L.idx = o;    o += align256((size_t)g.Po * 4);
     L.ctl = o;    o += align256(cb::CTL_WORDS * 4);
-    L.look = o;   o += align256(cb::compact_one_pass_bytes(g));
+    L.look = o;   o += align256(std::max(cb::compact_one_pass_bytes(g), d->mode == CB_PROPAGATE ? 0 : cb::detect_look_bytes(g)));
     L.KT = o;     o += align256((size_t)g.R * g.Opad * b);
     L.bias = o;   o += align256((size_t)g.Opad * 4);
     L.m_u8 = o;   o += align256((size_t)g.P);
@@ -212,6 +215,7 @@ struct cb_layer {
     // the two input change maps, filled by alternate frames and interleaved word by word (the other
     // one is cleared for the next frame)
     uint64_t* mbits() const { return (uint64_t*)(state + sl.mbits); }
+    uint64_t* mail() const { return (uint64_t*)(state + sl.mail); }
     int mbits_words() const { return (g.P + 63) / 64; }
     uint64_t* mtbits() const { return (uint64_t*)(state + sl.mtbits); }
     int32_t* idx() const { return (int32_t*)(state + sl.idx); }
@@ -360,6 +364,7 @@ int detect_and_update(cb_layer* L, const void* input_dev, float tau, const int32
     if (!L->primed) flags = cb::DET_FORCE_ALL | cb::DET_COPY_ALL;
     else if (L->d.mode == CB_FEED_FORWARD) flags = cb::DET_COPY_ALL;
     if ((size_t)L->g.C * L->g.P * (L->g.bf16 ? 2 : 4) >= kStateBeyondCache) flags |= cb::DET_STREAM_STATE;
+    bool extracted = false;      // the index list comes with detection
     if (cand)
         CB_HIP(cb::launch_detect_listed(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau,
                                         flags, cand, cand_count, cand_cap, pool_w, cand_W, L->st,
@@ -373,13 +378,27 @@ int detect_and_update(cb_layer* L, const void* input_dev, float tau, const int32
                                  L->st, next_tm(L, CB_STEP_DETECT)));
         CB_HIP(cb::launch_state_apply(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), L->st,
                                       next_tm(L, CB_STEP_STATE)));
+    } else if (!L->timing && g_scan_wait_limit.load(std::memory_order_relaxed) == kScanWaitDefault) {
+        // (per-step times and a wait limit of the caller's are those of the launches one by one)
+        cb::DetectJob job;
+        job.g = L->g;
+        job.full = L->primed ? 0 : 1;
+        job.clear_words = L->mbits_words();
+        job.mail = L->mail(); job.mt_bits = L->mtbits(); job.idx = L->idx();
+        job.look = reinterpret_cast<unsigned long long*>(L->look());
+        CB_HIP(cb::launch_detect_extract(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau, flags, job, L->st, &extracted));
     } else
         CB_HIP(cb::launch_detect(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau, flags,
                                  L->st, next_tm(L, CB_STEP_DETECT)));
     L->cur_in_bits = L->mbits();
     L->cur_in_pitch = L->g.W;
     L->cur_in_own = true;
-    const int rc = run_back_end(L, L->S(), false);
+    if (extracted) {
+        L->cur_mtbits = L->mtbits();
+        L->cur_idx = L->idx();
+        L->cur_count = L->ctl() + cb::CTL_COUNT;
+    }
+    const int rc = run_back_end(L, L->S(), extracted);
     if (rc) return rc;
     if (output_dev) *output_dev = L->OUT();
     return CB_OK;
