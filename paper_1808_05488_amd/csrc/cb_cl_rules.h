@@ -125,4 +125,23 @@ template <bool F32, int SHAPE, typename FN> CB_HD void cl_tile(int N, int O, int
 #undef CB_COST
 }
 
+// Size of a packed filter matrix of nkg k-groups (bfloat16 64 bytes a group and row, float32 three such terms), and from which on its rows
+// are divided among the XCDs
+CB_HD unsigned cl_filter_kb(int O, unsigned nkg, bool f32) { return ((unsigned)O * nkg >> 4) * (f32 ? 3u : 1u); }
+constexpr unsigned CL_FAR_KB = 2048;
+
+// Logarithm of the groups of XCDs among which the row tiles (MT) are divided; the column tiles are divided among the XCDs of a group.
+// Each XCD brings its rows of the filter matrix (filter_kb in all) and the pixels of its columns (pixel_kb, about) into its own L2: 2^l groups
+// move filter_kb * 8 / 2^l + pixel_kb * 2^l.  Filters are fetched several groups ahead, pixels one stage, so that a miss of a pixel
+// costs more: they count fourfold (counted once: ten-layer trunk of 3 x 3 filters at 368x656, float32, 282 us, fourfold 279; 512 -> 512 at 46x82, bfloat16, 10 % 41.9 / 41.5).
+// Filters of up to 2 MB stay in every L2 beside the pixels and gain nothing.  Frames, us, undivided / divided: 512 -> 512, 3x3, 46x82, 2 % changed
+// 45.3 / 42.2, bfloat16 35.7 / 33.9, 30 % 46.5 / 46.8; 256 -> 512 there 28.9 / 26.9; 256 -> 256, 3x3, 92x164 31.3 / 30.0; 64 -> 256, 7x7, 120x160
+// 53.5 / 52.2; below the line 128 -> 256, 3x3, 184x328 (1.8 MB) 39.1 / 39.7.
+CB_HD unsigned cl_xcd_rows(unsigned MT, unsigned filter_kb, unsigned pixel_kb)
+{
+    unsigned l = filter_kb / 16u > pixel_kb ? 3u : filter_kb / 4u > pixel_kb ? 2u : filter_kb > pixel_kb ? 1u : 0u;
+    while ((1u << l) > MT) --l;
+    return l;
+}
+
 }  // namespace cb

@@ -170,7 +170,7 @@ static_assert(3 * CL_LDS_F32 <= 163840 && cl_lds<float>(64) <= CL_LDS_F32 && cl_
               cl_lds<uint16_t>(16) <= CL_LDS_BF16 && cl_lds<float>(16, 4) <= CL_LDS_F32 && cl_lds<uint16_t>(16, 4) <= CL_LDS_BF16,
               "the widest tile takes the most LDS");
 
-template <typename T, bool P2, int WGM, int WGN, int TM, int TN, int WGK = 1>
+template <typename T, bool P2, bool FAR, int WGM, int WGN, int TM, int TN, int WGK = 1>
 __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, const T* __restrict__ S2,
                                                  const int32_t* __restrict__ idx, const int N,
                                                  const uint4* __restrict__ KF, const float* __restrict__ KT,
@@ -215,11 +215,14 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
         const_cast<T*>(S2), 0, (int)((unsigned)g.Cs * (unsigned)g.P * ESZ), 0x00020000);
     constexpr unsigned NOWHERE = 0xFFFFFFF0u;
     // tiles: every XCD (workgroup number mod 8) walks its own range of column tiles, all row tiles of one column tile in
-    // turn.  (32 bits: the outputs of 2^31 such tiles would not fit any memory.)
+    // turn; with filters that half an XCD's L2 does not hold (FAR) the XCDs are 2, 4 or 8 groups with a range of the row tiles each
+    // (cl_xcd_rows).  (32 bits: the outputs of 2^31 such tiles would not fit any memory.)
     const unsigned NT = ((unsigned)N + BN - 1u) / BN;
     const unsigned MT = ((unsigned)g.O + BM - 1u) / BM;
-    const unsigned per_xcd = (NT + 7u) / 8u, total = per_xcd * MT;
-    const unsigned xcd0 = (bx & 7u) * per_xcd;
+    const unsigned lx = FAR ? cl_xcd_rows(MT, cl_filter_kb(g.O, (unsigned)nkg, F32), (unsigned)N * ((unsigned)g.Cs * ESZ / 16u) >> 6) : 0u;
+    const unsigned MTX = FAR ? (MT + (1u << lx) - 1u) >> lx : MT, mt0 = FAR ? (bx & ((1u << lx) - 1u)) * MTX : 0u;
+    const unsigned per_xcd = FAR ? (NT + (8u >> lx) - 1u) >> (3u - lx) : (NT + 7u) / 8u, total = per_xcd * MTX;
+    const unsigned xcd0 = (FAR ? (bx & 7u) >> lx : bx & 7u) * per_xcd;
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int wk = __builtin_amdgcn_readfirstlane(wv % WGK);
@@ -231,7 +234,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 
     int qnext[NP];
     auto fetch_q = [&](unsigned u, int (&q)[NP]) {
-        const unsigned ntt = xcd0 + u / MT;
+        const unsigned ntt = xcd0 + u / MTX;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const unsigned n = ntt * BN + gc + CPP * p;
@@ -241,14 +244,14 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     if constexpr (!LEAN) fetch_q(bx >> 3, qnext);
 
     for (unsigned uq = bx >> 3; uq < total; uq += gx >> 3) {
-        const int mt = (int)(uq % MT);
-        const unsigned nt = xcd0 + uq / MT;
+        const int mt = (int)(FAR ? mt0 + uq % MTX : uq % MTX);
+        const unsigned nt = xcd0 + uq / MTX;
         int q[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) q[p] = LEAN ? 0 : qnext[p];
         if constexpr (LEAN) fetch_q(uq, q);
         else fetch_q(uq + (gx >> 3), qnext);
-        if (nt >= NT) continue;
+        if (nt >= NT || (FAR && (unsigned)mt >= MT)) continue;
         const int m0 = mt * BM;
 
         // ring of filter fragments: [k-group mod D][row tile][term].  The resource covers this tile's rows.
@@ -508,7 +511,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 }
 
 // workgroup bx of gx
-template <typename T, int SHAPE, bool P2>
+template <typename T, int SHAPE, bool P2, bool FAR>
 __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, const T* __restrict__ S2, const int32_t* __restrict__ idx,
                                              const int* __restrict__ count, const uint4* __restrict__ KF, const float* __restrict__ KT,
                                              const float* __restrict__ bias, int relu, T* __restrict__ OUT, T* __restrict__ OUT2,
@@ -516,7 +519,7 @@ __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, co
 {
     const int N = *count;
     if (N <= 0) return;
-#define CB_BODY(...) fused_cl_body<T, P2, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx)
+#define CB_BODY(...) fused_cl_body<T, P2, FAR, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx)
     // (the tiles of cb_cl_rules.h)
     cl_tile<sizeof(T) == 4, SHAPE>(N, g.O, g.Cs, g.kh * g.kw, g.R, [&](auto tile) __attribute__((always_inline)) {
         constexpr int t = decltype(tile)::value;
@@ -533,14 +536,14 @@ __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, co
 
 // (wavefronts per SIMD: as many as the widest tile's registers allow.  They are worth more than wider tiles: bfloat16, O > 64
 // at 76 800 listed pixels 45 us with two, 40 us with four.)
-template <typename T, int SHAPE, bool P2>
+template <typename T, int SHAPE, bool P2, bool FAR>
 __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(Geom g, ClDiv div, const T* __restrict__ S2,
                                                           const int32_t* __restrict__ idx, const int* __restrict__ count,
                                                           const uint4* __restrict__ KF, const float* __restrict__ KT,
                                                           const float* __restrict__ bias, int relu,
                                                           T* __restrict__ OUT, T* __restrict__ OUT2)
 {
-    fused_cl_run<T, SHAPE, P2>(g, div, S2, idx, count, KF, KT, bias, relu, OUT, OUT2, blockIdx.x, gridDim.x);
+    fused_cl_run<T, SHAPE, P2, FAR>(g, div, S2, idx, count, KF, KT, bias, relu, OUT, OUT2, blockIdx.x, gridDim.x);
 }
 
 // run(an integral constant: the kernel's instance) for a layer of this geometry; its arguments checked
@@ -558,6 +561,13 @@ hipError_t fused_cl_instance(const Geom& g, const FusedPlan& plan, FN&& run)
     return hipGetLastError();
 }
 constexpr unsigned CL_GRID = 1024;
+// layers whose XCDs divide the row tiles among them: in instances of their own, since the few instructions more cost small layers
+// 0.2 us a launch (64 -> 128, 128 -> 128, bfloat16)
+constexpr bool cl_far_shape(int shape) { return shape >= 128; }
+inline bool fused_cl_far(const Geom& g)
+{
+    return cl_filter_kb(g.O, (unsigned)((long long)g.Cs * g.kh * g.kw + 31) / 32u, !g.bf16) >= CL_FAR_KB;
+}
 template <typename T> constexpr unsigned cl_lds_bytes() { return sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16; }
 
 template <typename T>
@@ -567,11 +577,17 @@ hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow
     const ClDiv div = cl_div(g.Wo, g.Ho, g.kw, g.Cs);
     const bool p2 = (g.Cs & (g.Cs - 1)) == 0;
     return fused_cl_instance<T>(g, plan, [&](auto shape) {
-#define CB_CL(p) \
-    CB_LAUNCH_LDS((fused_cl_kernel<T, decltype(shape)::value, p>), dim3(CL_GRID), dim3(256), cl_lds_bytes<T>(), st, tm, g, div, shadow, \
+        constexpr int SHAPE = decltype(shape)::value;
+#define CB_CL(p, far) \
+    CB_LAUNCH_LDS((fused_cl_kernel<T, SHAPE, p, far>), dim3(CL_GRID), dim3(256), cl_lds_bytes<T>(), st, tm, g, div, shadow, \
                   idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)
-        if (p2) CB_CL(true);
-        else CB_CL(false);
+        if constexpr (cl_far_shape(SHAPE))
+            if (p2 && fused_cl_far(g)) {
+                CB_CL(true, true);
+                return;
+            }
+        if (p2) CB_CL(true, false);
+        else CB_CL(false, false);
 #undef CB_CL
     });
 }
