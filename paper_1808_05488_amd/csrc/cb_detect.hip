@@ -12,6 +12,7 @@
 // flight for layers with many channels and few pixels.
 #include "cb_extract.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace cb {
 
@@ -502,8 +503,10 @@ void detect_extract_kernel(const T* __restrict__ x, T* __restrict__ S, T* __rest
     const unsigned detecting = gridDim.x - (unsigned)job.nblk;
     if (blockIdx.x >= detecting) {
         const int frame = ctl[CTL_FRAME];
-        extract_own_block<NT, PLX ? 64 / (PLX ? PLX : 1) : 2>(job, ctl, mbits0, frame & 1, (unsigned)frame + 1u, (int)(blockIdx.x - detecting),
-                                                              reinterpret_cast<uint64_t*>(lds));
+        extract_own_block<NT>(job, ctl, mbits0, frame & 1, (int)(blockIdx.x - detecting), reinterpret_cast<uint64_t*>(lds), false,
+                              [&](long i, long step, long nw, uint64_t (&w)[2]) {
+                                  mail_words<PLX ? 64 / (PLX ? PLX : 1) : 2>(job.mail, i, step, nw, (unsigned)frame + 1u, w);
+                              });
         return;
     }
     detect_reg_block<T, VEC, CS, CPT, PLX, SH, true>(x, S, S2, mbits0, ctl, C, Cs, inv_per, P, nwords, tau, flags, stream, job.mail, lds);
@@ -640,8 +643,8 @@ __global__ __launch_bounds__(256) void shadow_rebuild_kernel(const T* __restrict
 }
 
 // The extraction inside the launch of detection, by workgroups of nt threads: words of the dilated map per wavefront (0: it takes a launch
-// of its own).  The workgroups that wait are at most a quarter of the chip's wavefronts, and the part of the map under one workgroup's words
-// fits its LDS.  Few words a wavefront spread the expansion of dense words and shorten the polls, many workgroups add up more
+// of its own).  The workgroups that wait are at most a quarter of the chip's wavefronts (half of those that the registers of the widest
+// variant leave), and the part of the map under one workgroup's words fits its LDS.  Few words a wavefront spread the expansion of dense words and shorten the polls, many workgroups add up more
 // counts and poll for more of each other's rows.  Frames, us, 16 / 32 / 64 words: 3 -> 16, 7x7, 1080p (507, 254, 127 workgroups) 36.3 / 32.0 / 30.4;
 // 3 -> 16 at 720p (225, 113, 57) 18.2 / 16.8 / 16.9; 3 -> 16 at 240x320 (19, 10, 5) 13.1 / 13.4 / 14.1; 64 -> 32 at 120x160 14.8 / 15.0 / 15.9; 64 -> 64 at
 // 480x640, 20 % (38, 19, 10) 81.5 / 82.2 / 84.8; 128 -> 64 at 46x82, bfloat16 (2, 1, 1) 16.4 / 15.6 / 16.1.
@@ -728,36 +731,44 @@ void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int Cs,
 // staged in LDS ahead of the first barrier of a round and, once it is known which candidates fired, written to
 // S2 with consecutive lanes on consecutive channels; two alternating buffers, so the barriers the round has anyway
 // are enough.  (Written from the registers that hold them they are 4-byte stores to a different line per lane.)
-template <typename T, int CS, int PLC, bool SH = false>
-__global__ __launch_bounds__(CS * PLC) void detect_listed_kernel(const T* __restrict__ x, T* __restrict__ S,
-                                                                 T* __restrict__ S2, uint64_t* __restrict__ mbits0,
-                                                                 int* __restrict__ ctl,
-                                                                 const int32_t* __restrict__ cand,
-                                                                 const int* __restrict__ cand_count, int cand_cap,
-                                                                 int C, int Cpx, int P, int W, float tau, int flags, int pool_w,
-                                                                 int cand_W)
+constexpr int LISTED_U = 8;
+template <typename T, int CS, int PLC, bool SH> struct ListedLds {
+    static constexpr int PITCH = CS * LISTED_U + 1;   // staged values per candidate: candidates a lane apart fall into different banks
+    // (one buffer and a barrier at the end of the round where two would not fit)
+    static constexpr int NBUF = PLC * PITCH * (int)sizeof(T) * 2 <= 32768 ? 2 : 1;
+    static constexpr int flags = CS * PLC * 4, rows = SH ? (NBUF * PLC * PITCH * (int)sizeof(T) + 15) / 16 * 16 : 0, pix = SH ? NBUF * PLC * 4 : 0;
+    static constexpr int bytes = flags + rows + pix;
+};
+// Workgroup bx of `blocks`; lds: ListedLds bytes.  ARRIVE: it adds itself to the arrivals when its bits are set.
+template <typename T, int CS, int PLC, bool SH, bool ARRIVE>
+__device__ __forceinline__ void detect_listed_block(const T* __restrict__ x, T* __restrict__ S,
+                                                    T* __restrict__ S2, uint64_t* __restrict__ mbits0,
+                                                    int* __restrict__ ctl,
+                                                    const int32_t* __restrict__ cand,
+                                                    const int* __restrict__ cand_count, int cand_cap,
+                                                    int C, int Cpx, int P, int W, float tau, int flags, int pool_w,
+                                                    int cand_W, int bx, int blocks, char* lds)
 {
-    constexpr int U = 8;                          // channels per lane held in registers (all of them when C <= 8*CS)
+    constexpr int U = LISTED_U;                   // channels per lane held in registers (all of them when C <= 8*CS)
     const int par = ctl[CTL_FRAME] & 1;           // which of the two map buffers and counters this frame fills
     uint64_t* __restrict__ mbits = mbits0 + par;  // the two maps are interleaved: word w of this frame's map at [2 * w]
-    int* __restrict__ nin = nin_counter(ctl, blockIdx.x, par);
-    __shared__ unsigned sflag[CS * PLC];
-    constexpr int PITCH = CS * U + 1;             // staged values per candidate: candidates a lane apart fall into different banks
-    // (one buffer and a barrier at the end of the round where two would not fit)
-    constexpr int NBUF = PLC * PITCH * (int)sizeof(T) * 2 <= 32768 ? 2 : 1;
-    __shared__ T stage[SH ? NBUF : 1][SH ? PLC * PITCH : 1];
-    __shared__ int s_q[SH ? NBUF : 1][SH ? PLC : 1];
+    int* __restrict__ nin = nin_counter(ctl, (unsigned)bx, par);
+    typedef ListedLds<T, CS, PLC, SH> LDS;
+    unsigned* const sflag = reinterpret_cast<unsigned*>(lds);
+    constexpr int PITCH = LDS::PITCH, NBUF = LDS::NBUF;
+    T (* const stage)[SH ? PLC * PITCH : 1] = reinterpret_cast<T (*)[SH ? PLC * PITCH : 1]>(lds + LDS::flags);
+    int (* const s_q)[SH ? PLC : 1] = reinterpret_cast<int (*)[SH ? PLC : 1]>(lds + LDS::flags + LDS::rows);
     const int tid = threadIdx.x, g = tid / PLC, pl = tid - g * PLC;
     const int Cs = C < CS * U ? C : CS * U;       // channels held in registers (SH: a power of two)
     const int lcs = 31 - __builtin_clz((unsigned)Cs);
     int buf = 0;
     // the candidate of the first round is requested together with the count (the list has cand_cap
     // entries; those beyond the count are stale but readable), later ones a round ahead
-    const int step = (int)gridDim.x * PLC;
-    int nnext = (int)blockIdx.x * PLC + pl;
+    const int step = blocks * PLC;
+    int nnext = bx * PLC + pl;
     int qnext = cand[nnext < cand_cap ? nnext : cand_cap - 1];
     const int nc = *cand_count;
-    for (int t0 = blockIdx.x * PLC; t0 < nc; t0 += step) {
+    for (int t0 = bx * PLC; t0 < nc; t0 += step) {
         const int n = t0 + pl;
         const bool valid = n < nc;
         int q = valid ? qnext : 0;
@@ -802,7 +813,34 @@ __global__ __launch_bounds__(CS * PLC) void detect_listed_kernel(const T* __rest
         for (int k = 0; k < CS; ++k) fired |= sflag[k * PLC + pl];
         if (SH && g == 0) s_q[SH ? buf : 0][SH ? pl : 0] = (valid && (fired || (flags & DET_COPY_ALL))) ? q : -1;
         __syncthreads();                          // sflag is rewritten in the next round
-        // state update first: it does not depend on the bit map
+        auto set_bits = [&]() {
+            // lanes 0..PLC-1 of the first wavefront.  Neighbouring candidates mostly fall into the same
+            // 32-pixel word of the map: their bits are combined (segmented OR over runs of lanes with
+            // equal word index) and the last lane of each run issues ONE atomic for the run -- a
+            // few thousand atomics on a few hundred words otherwise queue up behind each other.
+            const bool set = valid && fired;
+            unsigned bits = set ? 1u << (q & 31) : 0u;
+            const int word = set ? q >> 5 : -1 - pl;          // lanes without a bit never match a neighbour
+#pragma unroll
+            for (int o = 1; o < PLC; o <<= 1) {
+                const unsigned b = __shfl_up(bits, o);
+                const int w = __shfl_up(word, o);
+                if (pl >= o && w == word) bits |= b;
+            }
+            const int wnext = __shfl_down(word, 1);
+            int fresh = 0;
+            if (set && (pl == PLC - 1 || wnext != word)) {
+                const unsigned old = atomicOr(reinterpret_cast<uint32_t*>(mbits + 2 * (word >> 1)) + (word & 1), bits);
+                fresh = __popc(bits & ~old);                  // a pixel reached through several candidates counts once
+            }
+#pragma unroll
+            for (int o = 1; o < PLC; o <<= 1) fresh += __shfl_xor(fresh, o);
+            if (ARRIVE && t0 + step >= nc && tid == 0) arrive(ctl, (unsigned)bx);
+            if (pl == 0 && fresh) atomicAdd(nin, fresh);
+        };
+        // State update first: it does not depend on the bit map.  Where extracting workgroups wait for the bits, these go first,
+        // and the workgroup arrives as soon as its last are set (behind the state update it would wait for those stores too).
+        if (ARRIVE && g == 0) set_bits();
         if (valid && (fired || (flags & DET_COPY_ALL))) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -829,59 +867,80 @@ __global__ __launch_bounds__(CS * PLC) void detect_listed_kernel(const T* __rest
             if (NBUF == 2) buf ^= 1;
             else lds_barrier();
         }
-        if (g == 0) {
-            // lanes 0..PLC-1 of the first wavefront.  Neighbouring candidates mostly fall into the same
-            // 32-pixel word of the map: their bits are combined (segmented OR over runs of lanes with
-            // equal word index) and the last lane of each run issues ONE atomic for the run -- a
-            // few thousand atomics on a few hundred words otherwise queue up behind each other.
-            const bool set = valid && fired;
-            unsigned bits = set ? 1u << (q & 31) : 0u;
-            const int word = set ? q >> 5 : -1 - pl;          // lanes without a bit never match a neighbour
-#pragma unroll
-            for (int o = 1; o < PLC; o <<= 1) {
-                const unsigned b = __shfl_up(bits, o);
-                const int w = __shfl_up(word, o);
-                if (pl >= o && w == word) bits |= b;
-            }
-            const int wnext = __shfl_down(word, 1);
-            int fresh = 0;
-            if (set && (pl == PLC - 1 || wnext != word)) {
-                const unsigned old = atomicOr(reinterpret_cast<uint32_t*>(mbits + 2 * (word >> 1)) + (word & 1), bits);
-                fresh = __popc(bits & ~old);                  // a pixel reached through several candidates counts once
-            }
-#pragma unroll
-            for (int o = 1; o < PLC; o <<= 1) fresh += __shfl_xor(fresh, o);
-            if (pl == 0 && fresh) atomicAdd(nin, fresh);
-        }
+        if (!ARRIVE && g == 0) set_bits();
     }
+}
+
+template <typename T, int CS, int PLC, bool SH = false>
+__global__ __launch_bounds__(CS * PLC) void detect_listed_kernel(const T* __restrict__ x, T* __restrict__ S,
+                                                                 T* __restrict__ S2, uint64_t* __restrict__ mbits0,
+                                                                 int* __restrict__ ctl,
+                                                                 const int32_t* __restrict__ cand,
+                                                                 const int* __restrict__ cand_count, int cand_cap,
+                                                                 int C, int Cpx, int P, int W, float tau, int flags, int pool_w,
+                                                                 int cand_W)
+{
+    __shared__ __align__(16) char lds[ListedLds<T, CS, PLC, SH>::bytes];
+    detect_listed_block<T, CS, PLC, SH, false>(x, S, S2, mbits0, ctl, cand, cand_count, cand_cap, C, Cpx, P, W, tau, flags, pool_w, cand_W, (int)blockIdx.x, (int)gridDim.x,
+                                              lds);
+}
+
+// Detection at listed pixels with the index extraction in the same launch, as detect_extract_kernel; here the first workgroups extract, since
+// those behind the last listed pixel, up to two thousand that only come and go, would delay them.  Frames, us, two launches a layer / one: five-layer 7 x 7 net
+// at 480x640 with detection in every layer 141.5 / 132.8, bfloat16 111 / 99.7, ten-layer 3 x 3 trunk at 368x656 388 / 367, bfloat16 269.5 / 248, at
+// 150x200 254 / 241.  (State update ahead of the bits, as in the launch by itself: 138, 113, 378, 262 and 257.)
+template <typename T, int CS, int PLC, bool SH = false>
+__global__ __launch_bounds__(CS * PLC) void detect_listed_extract_kernel(const T* __restrict__ x, T* __restrict__ S,
+                                                                         T* __restrict__ S2, uint64_t* __restrict__ mbits0,
+                                                                         int* __restrict__ ctl,
+                                                                         const int32_t* __restrict__ cand,
+                                                                         const int* __restrict__ cand_count, int cand_cap,
+                                                                         int C, int Cpx, int P, int W, float tau, int flags, int pool_w,
+                                                                         int cand_W, DetectJob job)
+{
+    constexpr int NT = CS * PLC, EX = MAP_STAGE * 8 + one_pass_small<NT / 64>() * 4, LI = ListedLds<T, CS, PLC, SH>::bytes;
+    __shared__ __align__(16) char lds[EX > LI ? EX : LI];
+    const int blocks = (int)gridDim.x - job.nblk;
+    if ((int)blockIdx.x < job.nblk) {
+        const int par = ctl[CTL_FRAME] & 1, nc = *cand_count, busy = (nc + PLC - 1) / PLC;
+        await_arrivals(ctl, busy < blocks ? busy : blocks);
+        extract_own_block<NT>(job, ctl, mbits0, par, (int)blockIdx.x, reinterpret_cast<uint64_t*>(lds), true,
+                              [&](long i, long step, long nw, uint64_t (&w)[2]) { map_words2(mbits0, par, i, step, nw, w); });
+        return;
+    }
+    detect_listed_block<T, CS, PLC, SH, true>(x, S, S2, mbits0, ctl, cand, cand_count, cand_cap, C, Cpx, P, W, tau, flags, pool_w, cand_W,
+                                              (int)blockIdx.x - job.nblk, blocks, lds);
 }
 
 template <typename T>
 hipError_t launch_listed_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, float tau, int flags,
                            const int32_t* cand, const int* cand_count, int cand_cap, int pool_w, int cand_W,
-                           hipStream_t st, Tm tm)
+                           DetectJob* job, hipStream_t st, Tm tm)
 {
     // channel groups so that a lane holds its (at most 8) channels in registers; few candidates per
     // workgroup, so that a few hundred candidates already spread over the chip
-#define CB_LISTED(cs, plc)                                                                                          \
-    do {                                                                                                            \
-        {                                                                                                           \
-            if (S2 != nullptr && g.C >= 16 && (g.C & (g.C - 1)) == 0) {                                                        \
-                CB_LAUNCH((detect_listed_kernel<T, cs, plc, true>), dim3(std::min(2048, (cand_cap + plc - 1) / plc)), \
-                          dim3(cs * plc), st, tm, x, S, S2, mbits, ctl, cand, cand_count, cand_cap, g.C, g.Cs, g.P, g.W, tau, \
-                          flags, pool_w, cand_W);                                                                   \
-                break;                                                                                              \
-            }                                                                                                       \
-        }                                                                                                           \
-        CB_LAUNCH((detect_listed_kernel<T, cs, plc>), dim3(std::min(2048, (cand_cap + plc - 1) / plc)), dim3(cs * plc), \
-                  st, tm, x, S, S2, mbits, ctl, cand, cand_count, cand_cap, g.C, g.Cs, g.P, g.W, tau, flags, pool_w, cand_W); \
-    } while (0)
-    if (g.C <= 32)       CB_LISTED(4, 64);
-    else if (g.C <= 64)  CB_LISTED(8, 32);
-    else if (g.C <= 128) CB_LISTED(16, 16);
-    else if (g.C <= 256) CB_LISTED(32, 16);
-    else                 CB_LISTED(64, 16);
+    auto run = [&](auto cs, auto plc) {
+        constexpr int CS = decltype(cs)::value, PLC = decltype(plc)::value;
+        const unsigned grid = (unsigned)std::min(2048, (cand_cap + PLC - 1) / PLC);
+        const bool sh = S2 != nullptr && g.C >= 16 && (g.C & (g.C - 1)) == 0;
+        if (job && (job->per = extract_words(job->g, CS * PLC)) > 0) job->nblk = (job->g.Ho * job->g.WWo - 1) / (CS * PLC / 64 * job->per) + 1;
+#define CB_LISTED(SH)                                                                                                            \
+    if (job && job->nblk)                                                                                                        \
+        hipLaunchKernelGGL((detect_listed_extract_kernel<T, CS, PLC, SH>), dim3(grid + (unsigned)job->nblk), dim3(CS * PLC), 0, st, x, S, S2, mbits, \
+                           ctl, cand, cand_count, cand_cap, g.C, g.Cs, g.P, g.W, tau, flags, pool_w, cand_W, *job);              \
+    else                                                                                                                         \
+        CB_LAUNCH((detect_listed_kernel<T, CS, PLC, SH>), dim3(grid), dim3(CS * PLC), st, tm, x, S, S2, mbits, ctl, cand, cand_count, \
+                  cand_cap, g.C, g.Cs, g.P, g.W, tau, flags, pool_w, cand_W)
+        if (sh) { CB_LISTED(true); }
+        else { CB_LISTED(false); }
 #undef CB_LISTED
+    };
+    typedef std::integral_constant<int, 16> I16;
+    if (g.C <= 32)       run(std::integral_constant<int, 4>(), std::integral_constant<int, 64>());
+    else if (g.C <= 64)  run(std::integral_constant<int, 8>(), std::integral_constant<int, 32>());
+    else if (g.C <= 128) run(I16(), I16());
+    else if (g.C <= 256) run(std::integral_constant<int, 32>(), I16());
+    else                 run(std::integral_constant<int, 64>(), I16());
     return hipGetLastError();
 }
 
@@ -991,16 +1050,32 @@ hipError_t launch_shadow_rebuild(const Geom& g, const void* S, void* S2, hipStre
     return hipGetLastError();
 }
 
-hipError_t launch_detect_listed(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
-                                float tau, int flags, const int32_t* cand, const int* cand_count, int cand_cap,
-                                int pool_w, int cand_W, hipStream_t st, Tm tm)
+static hipError_t launch_listed(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl, float tau, int flags,
+                                const int32_t* cand, const int* cand_count, int cand_cap, int pool_w, int cand_W, DetectJob* job, hipStream_t st, Tm tm)
 {
     if (cand_cap < 1) return hipErrorInvalidValue;
     if (g.bf16)
         return launch_listed_t<uint16_t>(g, (const uint16_t*)x, (uint16_t*)S, (uint16_t*)S2, mbits, ctl, tau,
-                                         flags, cand, cand_count, cand_cap, pool_w, cand_W, st, tm);
+                                         flags, cand, cand_count, cand_cap, pool_w, cand_W, job, st, tm);
     return launch_listed_t<float>(g, (const float*)x, (float*)S, (float*)S2, mbits, ctl, tau, flags, cand,
-                                  cand_count, cand_cap, pool_w, cand_W, st, tm);
+                                  cand_count, cand_cap, pool_w, cand_W, job, st, tm);
+}
+
+hipError_t launch_detect_listed(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
+                                float tau, int flags, const int32_t* cand, const int* cand_count, int cand_cap,
+                                int pool_w, int cand_W, hipStream_t st, Tm tm)
+{
+    return launch_listed(g, x, S, S2, mbits, ctl, tau, flags, cand, cand_count, cand_cap, pool_w, cand_W, nullptr, st, tm);
+}
+
+hipError_t launch_detect_listed_extract(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
+                                        float tau, int flags, const int32_t* cand, const int* cand_count, int cand_cap,
+                                        int pool_w, int cand_W, DetectJob job, hipStream_t st, bool* extracted)
+{
+    job.nblk = 0;
+    const hipError_t e = launch_listed(g, x, S, S2, mbits, ctl, tau, flags, cand, cand_count, cand_cap, pool_w, cand_W, &job, st, Tm());
+    *extracted = job.nblk > 0;
+    return e;
 }
 
 }  // namespace cb

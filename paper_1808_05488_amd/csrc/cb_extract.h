@@ -286,7 +286,7 @@ constexpr int ONE_PASS_SMALL = one_pass_small<4>();
 template <int NW = 4, typename RECOUNT>
 __device__ __forceinline__ void one_pass_tail(uint64_t word, int pixbase, unsigned epoch_ld, int32_t* __restrict__ idx, int* __restrict__ ctl,
                                               unsigned long long* __restrict__ look, int own_map, int bid, int nblk, int spin_limit,
-                                              unsigned* small, RECOUNT&& recount)
+                                              unsigned* small, RECOUNT&& recount, bool arrivals = false)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     int* const wtot = reinterpret_cast<int*>(small);
@@ -338,6 +338,8 @@ __device__ __forceinline__ void one_pass_tail(uint64_t word, int pixbase, unsign
         if (atomicAdd(&ctl[CTL_DONE], 1) == nblk - 1) {      // everybody has read the epoch and the frame count
             ctl[CTL_DONE] = 0;
             ctl[CTL_EPOCH] = (int)epoch;
+            if (arrivals)
+                for (int q = 0; q < ARRIVE_SLOTS; ++q) ctl[CTL_ARRIVE + q * NIN_STRIDE] = 0;
             if (own_map) ctl[CTL_FRAME] = ctl[CTL_FRAME] + 1;
         }
     }
@@ -437,12 +439,13 @@ template <int UPW> __device__ __forceinline__ void mail_words(const uint64_t* ma
 }
 
 // Workgroup bid of job.nblk (NT threads) of an extraction inside the launch that detects the changes.  A wavefront has job.per words of
-// the dilated map, 16 where there are few: dense words are expanded one after the other, and a part of a map that is waited for should be small.  par, tag: of this frame; lds:
+// the dilated map, 16 where there are few: dense words are expanded one after the other, and a part of a map that is waited for should be small.  par: of this frame; lds:
 // MAP_STAGE words and one_pass_small 32-bit words.  Strides 1 and 2 (extract_words in cb_detect.hip).  Every wait ends: a detecting workgroup waits for nothing, an
-// extracting one for detecting ones and extracting ones before it, and all extracting workgroups together fill at most a quarter of
+// extracting one for detecting ones and extracting ones before it, and all extracting workgroups together fill at most half of
 // the chip, so that none of the others can be kept from starting, whatever the order in which they are dispatched.
-template <int NT, int UPW>
-__device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __restrict__ ctl, uint64_t* maps, int par, unsigned tag, int bid, uint64_t* lds)
+// fetch2(i, step, nwords, w): words i < nwords and i + step of the map, once they are complete.
+template <int NT, typename FETCH>
+__device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __restrict__ ctl, uint64_t* maps, int par, int bid, uint64_t* lds, bool arrivals, FETCH&& fetch2)
 {
     const Geom& g = job.g;
     const int tid = threadIdx.x, lane = tid & 63, items = g.Ho * g.WWo, nwords = (g.P + 63) / 64;
@@ -462,7 +465,7 @@ __device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __r
     const int n = (int)(((((long)r1 * g.W + g.W - 1) >> 6) + 3) - first);
     for (int i = tid; i < n; i += 2 * NT) {
         uint64_t w[2] = {0, 0};
-        if (first + i < nwords) mail_words<UPW>(job.mail, first + i, NT, nwords, tag, w);
+        if (first + i < nwords) fetch2(first + i, (long)NT, (long)nwords, w);
         lds[i] = w[0];
         if (i + NT < n) lds[i + NT] = w[1];
     }
@@ -485,7 +488,39 @@ __device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __r
         pixbase = yo * g.Wo + 64 * wo;
     }
     one_pass_tail<NT / 64>(word, pixbase, epoch_ld, job.idx, ctl, job.look, 1, bid, job.nblk, 0x7FFFFFFF,
-                           reinterpret_cast<unsigned*>(lds + MAP_STAGE), [](int) { return 0; });
+                           reinterpret_cast<unsigned*>(lds + MAP_STAGE), [](int) { return 0; }, arrivals);
+}
+
+// Detection at listed pixels sets single bits of a cleared map with atomics, which are complete when their old value has come back; a workgroup
+// that had pixels then adds itself to one of the counters.  (A few hundred workgroups: one counter would queue them up for 3 us.)
+__device__ __forceinline__ void arrive(int* ctl, unsigned b)
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): every atomic of this wavefront has returned
+    asm volatile("" ::: "memory");
+    __hip_atomic_fetch_add(ctl + CTL_ARRIVE + (b % ARRIVE_SLOTS) * NIN_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// called by whole workgroups: waits for `expected` workgroups
+__device__ __forceinline__ void await_arrivals(const int* ctl, int expected)
+{
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x < 64)
+        for (;;) {
+            const int n = lane < ARRIVE_SLOTS ? __hip_atomic_load(ctl + CTL_ARRIVE + lane * NIN_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+            if (wave_sum(n) >= expected) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+    __syncthreads();
+}
+// words i and i + step of the map of parity par (interleaved with the other one), past the caches that do not see other XCDs' atomics
+__device__ __forceinline__ void map_words2(const uint64_t* maps, int par, long i, long step, long nwords, uint64_t (&w)[2])
+{
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const long wi = i + k * step < nwords ? i + k * step : i;
+        w[k] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(maps) + 2 * wi + par, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (i + step >= nwords) w[1] = 0;
 }
 
 }  // namespace

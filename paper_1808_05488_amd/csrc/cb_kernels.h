@@ -51,7 +51,10 @@ enum Ctl {
     // pixel changed: 98 us, 9 us without a change).
     NIN_SLOTS = 64,
     NIN_STRIDE = 32,
-    CTL_WORDS = CTL_SLOTS + NIN_SLOTS * NIN_STRIDE
+    // ... and behind them the workgroups of detection at listed pixels that have set their bits (extraction in the same launch; zero between launches)
+    ARRIVE_SLOTS = 16,
+    CTL_ARRIVE = CTL_SLOTS + NIN_SLOTS * NIN_STRIDE,
+    CTL_WORDS = CTL_ARRIVE + ARRIVE_SLOTS * NIN_STRIDE
 };
 // counter of the frame parity `par` for workgroup b
 __device__ __forceinline__ int* nin_counter(int* ctl, unsigned b, int par)
@@ -125,6 +128,10 @@ hipError_t launch_shadow_rebuild(const Geom& g, const void* S, void* S2, hipStre
 hipError_t launch_detect_listed(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
                                 float tau, int flags, const int32_t* cand, const int* cand_count, int cand_cap,
                                 int pool_w, int cand_W, hipStream_t st, Tm tm = Tm());
+// ... with the index extraction in the launch, as launch_detect_extract (job.mail is not used)
+hipError_t launch_detect_listed_extract(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
+                                        float tau, int flags, const int32_t* cand, const int* cand_count, int cand_cap,
+                                        int pool_w, int cand_W, DetectJob job, hipStream_t st, bool* extracted);
 
 // Dilation of a bit-packed map by the filter footprint + per-block popcounts.  own_map != 0: in_bits
 // holds the layer's two interleaved input maps (see launch_detect); the frame count on the device

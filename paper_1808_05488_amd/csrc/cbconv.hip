@@ -365,7 +365,18 @@ int detect_and_update(cb_layer* L, const void* input_dev, float tau, const int32
     else if (L->d.mode == CB_FEED_FORWARD) flags = cb::DET_COPY_ALL;
     if ((size_t)L->g.C * L->g.P * (L->g.bf16 ? 2 : 4) >= kStateBeyondCache) flags |= cb::DET_STREAM_STATE;
     bool extracted = false;      // the index list comes with detection
-    if (cand)
+    // (per-step times and a wait limit of the caller's are those of the launches one by one)
+    const bool together = !L->timing && g_scan_wait_limit.load(std::memory_order_relaxed) == kScanWaitDefault;
+    cb::DetectJob job;
+    job.g = L->g;
+    job.full = L->primed ? 0 : 1;
+    job.clear_words = L->mbits_words();
+    job.mail = L->mail(); job.mt_bits = L->mtbits(); job.idx = L->idx();
+    job.look = reinterpret_cast<unsigned long long*>(L->look());
+    if (cand && together)
+        CB_HIP(cb::launch_detect_listed_extract(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau, flags, cand, cand_count,
+                                                cand_cap, pool_w, cand_W, job, L->st, &extracted));
+    else if (cand)
         CB_HIP(cb::launch_detect_listed(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau,
                                         flags, cand, cand_count, cand_cap, pool_w, cand_W, L->st,
                                         next_tm(L, CB_STEP_DETECT)));
@@ -378,14 +389,7 @@ int detect_and_update(cb_layer* L, const void* input_dev, float tau, const int32
                                  L->st, next_tm(L, CB_STEP_DETECT)));
         CB_HIP(cb::launch_state_apply(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), L->st,
                                       next_tm(L, CB_STEP_STATE)));
-    } else if (!L->timing && g_scan_wait_limit.load(std::memory_order_relaxed) == kScanWaitDefault) {
-        // (per-step times and a wait limit of the caller's are those of the launches one by one)
-        cb::DetectJob job;
-        job.g = L->g;
-        job.full = L->primed ? 0 : 1;
-        job.clear_words = L->mbits_words();
-        job.mail = L->mail(); job.mt_bits = L->mtbits(); job.idx = L->idx();
-        job.look = reinterpret_cast<unsigned long long*>(L->look());
+    } else if (together) {
         CB_HIP(cb::launch_detect_extract(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau, flags, job, L->st, &extracted));
     } else
         CB_HIP(cb::launch_detect(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau, flags,

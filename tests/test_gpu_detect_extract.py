@@ -70,3 +70,43 @@ def test_many_frames_of_a_vga_layer():
         hit = torch.rand((H, W), generator=g, device="cuda") < 0.01
         hit[40 + t:90 + t, 100:160] = True
         x = torch.where(hit, torch.rand((C, H, W), generator=g, device="cuda") + 2.0 * (t + 1), x)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("widths", [(3, 5, 4), (16, 32, 20), (24, 64, 8), (8, 100, 6), (4, 128, 6), (6, 200, 5), (3, 256, 4), (5, 300, 3), (3, 512, 3)])
+def test_chained_layers(widths, bf16):
+    """Detection at the producer's listed pixels, directly and through a pooling stage, against detection of everything in layers of their own;
+    frames without a change, frames that take the launches one by one, and a frame in which everything changes."""
+    c, mid, o = widths
+    print("chained", widths, bf16, flush=True)
+    H, W = 61, 93
+    rng = np.random.default_rng(mid)
+    mk = lambda n, m, k: to_dev((rng.standard_normal((n, m, k, k)) * np.sqrt(2.0 / (m * k * k))).astype(np.float32), bf16)
+    w0, w1, w2 = mk(mid, c, 3), mk(o, mid, 3), mk(o, mid, 5)
+    first = cb.Layer(w0, None, 1, 1, H, W, True)
+    pool = cb.Pool(first, 2)
+    direct = [cb.Layer(w1, None, 2, 1, H, W, True) for _ in range(2)]
+    pooled = [cb.Layer(w2, None, 1, 2, pool.Hp, pool.Wp, False) for _ in range(2)]
+    _, frames = syn.random_layer_case(mid, c, 1, 1, 1, 0, H, W, 9, change_prob=0.02, noise_std=0.003)
+    frames[3] = frames[2]
+    frames[6] = frames[5] + 1.0
+    try:
+        for t, f in enumerate(frames):
+            x = first.process_frame(to_dev(f, bf16), 0.02)
+            y = pool.process()
+            one_by_one = t in (4, 7)
+            for L in (direct[0], pooled[0]):
+                cb.cb_layer_set_timing(L.handle, one_by_one)
+            direct[0].process_frame_chained(x, first, 0.02)
+            direct[1].process_frame(x, 0.02)
+            pooled[0].process_frame_chained(y, pool, 0.02)
+            pooled[1].process_frame(y, 0.02)
+            for a, b in (direct, pooled):
+                for u, v in zip(a.changes_host(), b.changes_host()):
+                    assert np.array_equal(u, v), (widths, t)
+                assert a.stats()["n_changed_in"] == b.stats()["n_changed_in"], (widths, t)
+                assert torch.equal(a.state(), b.state()), (widths, t)
+                (so, oo), (sr, orf) = a.export_state(), b.export_state()
+                assert torch.equal(oo, orf), (widths, t)
+    finally:
+        cb.cb_set_scan_wait_limit(1 << 20)
