@@ -147,11 +147,13 @@ typedef struct {
  *                  that are not finite or beyond 2^80 are computed again with
  *                  the float32 matrix instruction, which costs time where there
  *                  are many).
- *  scratch_bytes : X' and Y' matrices and block counters; may be shared by
+ *  scratch_bytes : X' and Y' matrices and block counters, 16 MB for partial sums
+ *                  of channel-last layers with very long filters; may be shared by
  *                  layers that run on the same stream (Sec. III-B).  This is the
  *                  recommended size; cb_layer_create accepts any size not below
  *                  cb_layer_min_scratch_bytes and processes the listed pixels in
- *                  column chunks that fit.
+ *                  column chunks that fit (without room for partial sums a
+ *                  long filter is summed in one piece).
  * Both buffers must be 256-byte aligned. */
 int cb_layer_workspace_bytes(const cb_layer_desc *desc, size_t *state_bytes, size_t *scratch_bytes);
 int cb_layer_min_scratch_bytes(const cb_layer_desc *desc, size_t *scratch_bytes);

@@ -144,4 +144,44 @@ CB_HD unsigned cl_xcd_rows(unsigned MT, unsigned filter_kb, unsigned pixel_kb)
     return l;
 }
 
+// Whether the K of a layer with such filters is divided, and into how many parts: 0, or parts + 16 * (128 x 64 instead of 128 x 32 tiles).
+// A few hundred tiles leave compute units idle in the last of one or two rounds, and tiles narrow enough to fill them fetch filters and pixels several times as
+// often; wide tiles in parts do neither.  The price is CL_SPLIT_NS: sums written through to memory, counted, read back.  Costs as in cl_tile.
+// Frames, us, whole / divided: float32 512 -> 512, 3x3, 46x82, 2 % changed 42.6 / 31.5, 10 % 51.7 / 43.9, 30 % 80 / 68; 64 -> 256, 7x7, 120x160, 10 %
+// 52.5 / 48.9; 128 -> 128, 9x9, 60x80 50.1 / 37.4; 256 -> 128 there 141 / 86; bfloat16 256 -> 256, 7x7, 60x80, 20 % 55.6 / 49.2.  Shorter filters
+// are not considered, for which the choice alone took 0.4 us: 256 -> 256, 3x3, 92x164 (72 groups) 29.7 / 30.6; bfloat16 512 -> 512, 3x3, 46x82 (144) 42.3 / 43.0.
+constexpr unsigned CL_SPLIT_NS = 8500, CL_SPLIT_MAX = 8;     // (tiles: at most 256)
+CB_HD bool cl_split_pays(unsigned nkg, bool f32) { return nkg >= (f32 ? 96u : 256u); }
+template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned ws_bytes)
+{
+#define CB_COST(bm, bn, n, a0, a1, a2, a3, b0, b1, b2, b3) \
+    (F32 ? cl_cost<bm, bn>(n, O, nkg, a0, a1, a2, a3) : cl_cost<bm, bn>(n, O, nkg, b0, b1, b2, b3))
+    const unsigned a = CB_COST(64, 16, N, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, N, 1000, 300, 1400, 203, 400, 80, 1100, 47),
+                   c = CB_COST(128, 32, N, 1800, 380, 1000, 320, 1500, 100, 100, 96), d = CB_COST(128, 64, N, 900, 745, 2900, 510, 2000, 190, 1000, 140),
+                   k = CB_COST(16, 16, N, 100, 94, 1260, 80, 200, 30, 870, 16);
+#undef CB_COST
+    unsigned best = a < b ? a : b, choice = 0;
+    best = best < c ? best : c;
+    best = best < d ? best : d;
+    best = best < k ? best : k;
+    if (best < CL_SPLIT_NS) return 0;
+    // as many parts as make one or two items per compute unit
+    const unsigned rows = ((unsigned)O + 127u) / 128u;
+    auto consider = [&](unsigned tiles, unsigned flag, unsigned bytes, unsigned l0, unsigned l1, unsigned c0, unsigned c1) {
+        if (tiles > 256u) return;
+        const unsigned one = 256u / tiles, two = 512u / tiles;
+        for (unsigned r = 0; r < 2; ++r) {
+            unsigned p = r ? two : one;
+            p = p > CL_SPLIT_MAX ? CL_SPLIT_MAX : p;
+            const unsigned g = (nkg + p - 1u) / p;
+            if (p < 2u || g < 8u || tiles * p * bytes > ws_bytes) continue;
+            const unsigned lat = l0 + l1 * g, busy = (tiles * p + 255u) / 256u * (c0 + c1 * g), v = (busy > lat ? busy : lat) + CL_SPLIT_NS;
+            if (v < best) { best = v; choice = p | flag; }
+        }
+    };
+    consider(((unsigned)N + 31u) / 32u * rows, 0u, 16384u, F32 ? 1800u : 1500u, F32 ? 380u : 100u, F32 ? 1000u : 100u, F32 ? 320u : 96u);
+    consider(((unsigned)N + 63u) / 64u * rows, 16u, 32768u, F32 ? 900u : 2000u, F32 ? 745u : 190u, F32 ? 2900u : 1000u, F32 ? 510u : 140u);
+    return choice;
+}
+
 }  // namespace cb

@@ -113,6 +113,13 @@ __device__ __forceinline__ void st_out4(uint16_t* p, const float (&v)[4])
 }
 #endif
 
+// Workspace of the channel-last kernel for layers that divide K (fused_cl_splits): partial sums (may be absent: bytes = 0) and a count per
+// tile, zero between launches.
+struct ClWork { float* ws = nullptr; unsigned bytes = 0; int* count = nullptr; };
+bool fused_cl_far(const Geom& g);
+bool fused_cl_splits(const Geom& g);        // ... of which those with very long ones divide K
+constexpr size_t CL_WORK_BYTES = (size_t)16 << 20, CL_COUNT_BYTES = 4096;
+
 // Layer-creation side: availability, buffer sizes, packing of the filter matrix into MFMA
 // fragment order, the chunk table and the launch plan (synchronises the stream once when it uploads a chunk
 // table, i.e. for the channel-first kernels).
@@ -131,7 +138,7 @@ hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, 
 // index extraction of the layer behind, for the kernel's first workgroups (fused_takes_job)
 hipError_t launch_fused(const Geom& g, const FusedPlan& plan, const void* src, const void* shadow, const int32_t* idx,
                         const int* count, const void* KF, const void* KT, const void* tab, const float* bias, int relu, void* OUT,
-                        void* OUT2, const ExtractJob* job, hipStream_t st, Tm tm = Tm());
+                        void* OUT2, const ClWork& work, const ExtractJob* job, hipStream_t st, Tm tm = Tm());
 inline bool fused_takes_job(const Geom& g, const FusedPlan& plan) { return plan.cl && (g.Cs & (g.Cs - 1)) == 0; }
 
 // launches of the two element types (cb_fused_f32.hip, cb_fused_bf16.hip, cb_fused_cl_*.hip)
@@ -140,19 +147,19 @@ hipError_t launch_fused_f32(const Geom& g, const FusedPlan& plan, const float* s
                             float* OUT, float* OUT2, hipStream_t st, Tm tm);
 hipError_t launch_fused_f32_cl(const Geom& g, const FusedPlan& plan, const float* shadow, const int32_t* idx,
                                const int* count, const void* KF, const float* KT, const float* bias, int relu, float* OUT,
-                               float* OUT2, hipStream_t st, Tm tm);
+                               float* OUT2, const ClWork& work, hipStream_t st, Tm tm);
 // its filter matrix: three bfloat16 terms per value, in fragment order (fused_pack_bytes)
 hipError_t launch_pack_fused_split(const Geom& g, const float* w, void* KF, hipStream_t st);
 hipError_t launch_fused_bf16_cl(const Geom& g, const FusedPlan& plan, const uint16_t* shadow, const int32_t* idx,
                                 const int* count, const void* KF, const float* bias, int relu, uint16_t* OUT, uint16_t* OUT2,
-                                hipStream_t st, Tm tm);
+                                const ClWork& work, hipStream_t st, Tm tm);
 // ... with the index extraction of the layer behind (cb_fused_cl_extract.h)
 hipError_t launch_fused_f32_cl_extract(const Geom& g, const FusedPlan& plan, const float* shadow, const int32_t* idx, const int* count,
                                        const void* KF, const float* KT, const float* bias, int relu, float* OUT, float* OUT2,
-                                       const ExtractJob& job, hipStream_t st);
+                                       const ClWork& work, const ExtractJob& job, hipStream_t st);
 hipError_t launch_fused_bf16_cl_extract(const Geom& g, const FusedPlan& plan, const uint16_t* shadow, const int32_t* idx, const int* count,
                                         const void* KF, const float* bias, int relu, uint16_t* OUT, uint16_t* OUT2,
-                                        const ExtractJob& job, hipStream_t st);
+                                        const ClWork& work, const ExtractJob& job, hipStream_t st);
 hipError_t launch_fused_bf16(const Geom& g, const FusedPlan& plan, const uint16_t* src, const int32_t* idx,
                              const int* count, const void* KF, const int2* tab, const float* bias, int relu,
                              uint16_t* OUT, uint16_t* OUT2, hipStream_t st, Tm tm);

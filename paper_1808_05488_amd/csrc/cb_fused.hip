@@ -185,6 +185,14 @@ bool fused_supported(const Geom& g)
     return table_lds_bytes((int)pieces, (int)nunits) <= (unsigned)FUSED_TAB_LDS_MAX;
 }
 
+bool fused_cl_far(const Geom& g)
+{
+    return (g.Cs & (g.Cs - 1)) == 0 && cl_shape(g.O, g.Po, !g.bf16) >= 128 &&
+           cl_filter_kb(g.O, ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u, !g.bf16) >= CL_FAR_KB;
+}
+
+bool fused_cl_splits(const Geom& g) { return fused_cl_far(g) && cl_split_pays(((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u, !g.bf16); }
+
 bool fused_channel_last(const Geom& g)
 {
     return g.C >= (g.bf16 ? 32 : 16) && (g.C & (g.C - 1)) == 0 && fused_supported(g);
@@ -283,7 +291,7 @@ hipError_t fused_prepare(const Geom& g, const void* w, void* KF, void* tab_dev, 
 
 hipError_t launch_fused(const Geom& g, const FusedPlan& plan, const void* src, const void* shadow, const int32_t* idx,
                         const int* count, const void* KF, const void* KT, const void* tab, const float* bias, int relu, void* OUT,
-                        void* OUT2, const ExtractJob* job, hipStream_t st, Tm tm)
+                        void* OUT2, const ClWork& work, const ExtractJob* job, hipStream_t st, Tm tm)
 {
     if (job && !fused_takes_job(g, plan)) return hipErrorInvalidValue;
     if (OUT2 && (g.O & 15) != 0) return hipErrorInvalidValue;
@@ -291,15 +299,15 @@ hipError_t launch_fused(const Geom& g, const FusedPlan& plan, const void* src, c
         if (!shadow) return hipErrorInvalidValue;
         if (job && g.bf16)
             return launch_fused_bf16_cl_extract(g, plan, (const uint16_t*)shadow, idx, count, KF, bias, relu, (uint16_t*)OUT,
-                                                (uint16_t*)OUT2, *job, st);
+                                                (uint16_t*)OUT2, work, *job, st);
         if (job)
             return launch_fused_f32_cl_extract(g, plan, (const float*)shadow, idx, count, KF, (const float*)KT, bias, relu, (float*)OUT,
-                                               (float*)OUT2, *job, st);
+                                               (float*)OUT2, work, *job, st);
         if (g.bf16)
             return launch_fused_bf16_cl(g, plan, (const uint16_t*)shadow, idx, count, KF, bias, relu, (uint16_t*)OUT,
-                                        (uint16_t*)OUT2, st, tm);
+                                        (uint16_t*)OUT2, work, st, tm);
         return launch_fused_f32_cl(g, plan, (const float*)shadow, idx, count, KF, (const float*)KT, bias, relu, (float*)OUT, (float*)OUT2,
-                                   st, tm);
+                                   work, st, tm);
     }
     if (g.bf16)
         return launch_fused_bf16(g, plan, (const uint16_t*)src, idx, count, KF, (const int2*)tab, bias, relu,

@@ -170,12 +170,15 @@ static_assert(3 * CL_LDS_F32 <= 163840 && cl_lds<float>(64) <= CL_LDS_F32 && cl_
               cl_lds<uint16_t>(16) <= CL_LDS_BF16 && cl_lds<float>(16, 4) <= CL_LDS_F32 && cl_lds<uint16_t>(16, 4) <= CL_LDS_BF16,
               "the widest tile takes the most LDS");
 
-template <typename T, bool P2, bool FAR, int WGM, int WGN, int TM, int TN, int WGK = 1>
+// SPLIT: a tile's K is divided into `parts` ranges of stages, an item each.  An item leaves its sums in the workspace and counts itself; the
+// tile's last one adds them up, in the order of K, and writes the outputs.
+struct ClSplit { float* ws; int* count; unsigned parts; };
+template <typename T, bool P2, int FAR, int WGM, int WGN, int TM, int TN, int WGK = 1, bool SPLIT = false>
 __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, const T* __restrict__ S2,
                                                  const int32_t* __restrict__ idx, const int N,
                                                  const uint4* __restrict__ KF, const float* __restrict__ KT,
                                                  const float* __restrict__ bias, int relu, T* __restrict__ OUT,
-                                                 T* __restrict__ OUT2, const unsigned bx, const unsigned gx)
+                                                 T* __restrict__ OUT2, const unsigned bx, const unsigned gx, const ClSplit& split = ClSplit())
 {
     constexpr bool F32 = sizeof(T) == 4;
     constexpr int TERMS = F32 ? 3 : 1;           // bfloat16 terms per value
@@ -208,7 +211,8 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     int* const qs = reinterpret_cast<int*>(Bs + 2 * BUF);
 
     const int nkg = F32 ? (g.Cs * g.kh * g.kw + 63) / 64 * 2 : (g.Cs * g.kh * g.kw + 127) / 128 * 4;       // k-groups of the packed filter matrix
-    const int nunits = (nkg + UKG - 1) / UKG;
+    const int stages = (nkg + UKG - 1) / UKG;
+    const unsigned parts = SPLIT ? split.parts : 1u;
     const int lc = 31 - __builtin_clz((unsigned)g.Cs);       // (P2)
     auto pixels = [&](unsigned n) { return P2 ? n << lc : n * (unsigned)g.Cs; };
     const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -221,7 +225,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     const unsigned MT = ((unsigned)g.O + BM - 1u) / BM;
     const unsigned lx = FAR ? cl_xcd_rows(MT, cl_filter_kb(g.O, (unsigned)nkg, F32), (unsigned)N * ((unsigned)g.Cs * ESZ / 16u) >> 6) : 0u;
     const unsigned MTX = FAR ? (MT + (1u << lx) - 1u) >> lx : MT, mt0 = FAR ? (bx & ((1u << lx) - 1u)) * MTX : 0u;
-    const unsigned per_xcd = FAR ? (NT + (8u >> lx) - 1u) >> (3u - lx) : (NT + 7u) / 8u, total = per_xcd * MTX;
+    const unsigned per_xcd = FAR ? (NT + (8u >> lx) - 1u) >> (3u - lx) : (NT + 7u) / 8u, total = per_xcd * MTX * parts;
     const unsigned xcd0 = (FAR ? (bx & 7u) >> lx : bx & 7u) * per_xcd;
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -234,7 +238,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 
     int qnext[NP];
     auto fetch_q = [&](unsigned u, int (&q)[NP]) {
-        const unsigned ntt = xcd0 + u / MTX;
+        const unsigned ntt = xcd0 + (SPLIT ? u / parts : u) / MTX;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const unsigned n = ntt * BN + gc + CPP * p;
@@ -244,8 +248,13 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     if constexpr (!LEAN) fetch_q(bx >> 3, qnext);
 
     for (unsigned uq = bx >> 3; uq < total; uq += gx >> 3) {
-        const int mt = (int)(FAR ? mt0 + uq % MTX : uq % MTX);
-        const unsigned nt = xcd0 + uq / MTX;
+        const unsigned ut = SPLIT ? uq / parts : uq;
+        const int mt = (int)(FAR ? mt0 + ut % MTX : ut % MTX);
+        const unsigned nt = xcd0 + ut / MTX;
+        // this item's stages: nunits from u0 on
+        const unsigned part = SPLIT ? uq % parts : 0u;
+        const int u0 = SPLIT ? (int)(part * (unsigned)stages / parts) : 0;
+        const int nunits = SPLIT ? (int)((part + 1u) * (unsigned)stages / parts) - u0 : stages;
         int q[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) q[p] = LEAN ? 0 : qnext[p];
@@ -288,7 +297,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 
         uint4 breg[GD][NP];
         auto gload = [&](int u, uint4 (&dst)[NP]) {
-            const unsigned kb = (unsigned)u * (unsigned)UK;
+            const unsigned kb = (unsigned)(SPLIT ? u0 + u : u) * (unsigned)UK;
             unsigned tap, coff;                  // the piece's tap, its channel less cl
             if constexpr (P2) { tap = (kb >> lc) + (unsigned)dt; coff = kb & (unsigned)(g.Cs - 1); }
             else cl_piece(div, (unsigned)g.Cs, kb, (unsigned)dt, (unsigned)cl, tap, coff);
@@ -334,7 +343,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
         if constexpr (GD == 2) {
             gload(1, breg[1]);
 #pragma unroll
-            for (int s = 0; s < D; ++s) aload(s * WGK + wk, areg[s]);
+            for (int s = 0; s < D; ++s) aload((SPLIT ? u0 * UKG : 0) + s * WGK + wk, areg[s]);
         }
         float bv[TM][4];                          // bias of this wavefront's rows
 #pragma unroll
@@ -353,7 +362,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
         gload(GD, breg[0]);
         if constexpr (GD == 1) {
 #pragma unroll
-            for (int s = 0; s < D; ++s) aload(s * WGK + wk, areg[s]);
+            for (int s = 0; s < D; ++s) aload((SPLIT ? u0 * UKG : 0) + s * WGK + wk, areg[s]);
         }
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
@@ -379,7 +388,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             bload(0, 0, bfr[0]);
 #pragma unroll
             for (int kgi = 0; kgi < UKW; ++kgi) {
-                const int kg = u * UKG + kgi * WGK + wk;
+                const int kg = (SPLIT ? u0 + u : u) * UKG + kgi * WGK + wk;
                 if ((WGK > 1 || kgi > 0) && kg >= nkg) break;        // the last stage may be short
                 uint4 (&af)[TM][TERMS] = areg[(S0 + kgi) % D];
 #pragma unroll
@@ -446,6 +455,61 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 #pragma unroll
                         for (int r = 0; r < 4; ++r) acc[a][b][r] += red[(wv + w) * PER + ((a * TN + b) * 4 + r) * 64];
         }
+        if constexpr (SPLIT) {
+            static_assert(WGK == 1, "parts are whole workgroups");
+            // Written through to where every XCD sees them; the count follows when all of the workgroup's are there.
+            const unsigned tile = nt * MT + (unsigned)mt;
+            typedef unsigned long long u64;
+            u64* const mine = reinterpret_cast<u64*>(split.ws) + (size_t)(tile * parts) * (BM * BN / 2) + tid;
+            auto word = [&](const floatx4& v, int h) { return (u64)__float_as_uint(v[2 * h]) | (u64)__float_as_uint(v[2 * h + 1]) << 32; };
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        __hip_atomic_store(mine + part * (BM * BN / 2) + ((a * TN + b) * 2 + h) * 256, word(acc[a][b], h), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+            asm volatile("" ::: "memory");
+            int* const s_last = qs + BN;
+            __syncthreads();
+            if (tid == 0) *s_last = (unsigned)__hip_atomic_fetch_add(split.count + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1u;
+            __syncthreads();
+            if (!*s_last) continue;
+            if (tid == 0) split.count[tile] = 0;  // for the next launch
+            floatx4 sum[TM][TN];
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b) sum[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+            // (a batch of parts in flight: one after the other they take a round trip to memory each)
+            constexpr int PB = TM * TN <= 4 ? 4 : 2;
+#pragma unroll 1
+            for (unsigned p0 = 0; p0 < parts; p0 += PB) {
+                u64 w[PB][TM * TN * 2];
+#pragma unroll
+                for (int q = 0; q < PB; ++q)
+#pragma unroll
+                    for (int i = 0; i < TM * TN * 2; ++i) {
+                        const unsigned p = p0 + q < parts ? p0 + q : part;
+                        w[q][i] = __hip_atomic_load(mine + p * (BM * BN / 2) + i * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+#pragma unroll
+                for (int q = 0; q < PB; ++q)
+                    if (p0 + q < parts)
+#pragma unroll
+                        for (int i = 0; i < TM * TN * 2; ++i) {
+                            floatx4& d = sum[i / 2 / TN][i / 2 % TN];
+                            d[2 * (i & 1)] += __uint_as_float((unsigned)w[q][i]);
+                            d[2 * (i & 1) + 1] += __uint_as_float((unsigned)(w[q][i] >> 32));
+                        }
+            }
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b) acc[a][b] = sum[a][b];
+        }
         if constexpr (LEAN) {
 #pragma unroll
             for (int a = 0; a < TM; ++a)
@@ -510,15 +574,28 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     }
 }
 
+// Workgroups of a launch.  (A constant: read from the launch's hidden arguments it lies beyond the kernel's own, on a line of its own, and was
+// up to 0.3 us of a launch: ten-layer trunk at 368x656, bfloat16, 155.1 us a frame, 152.3 without it.)
+constexpr unsigned CL_GRID = 1024;
+
 // workgroup bx of gx
-template <typename T, int SHAPE, bool P2, bool FAR>
+template <typename T, int SHAPE, bool P2, int FAR>
 __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, const T* __restrict__ S2, const int32_t* __restrict__ idx,
                                              const int* __restrict__ count, const uint4* __restrict__ KF, const float* __restrict__ KT,
                                              const float* __restrict__ bias, int relu, T* __restrict__ OUT, T* __restrict__ OUT2,
-                                             const unsigned bx, const unsigned gx)
+                                             const unsigned bx, const unsigned gx, float* ws, unsigned ws_bytes, int* kcount)
 {
     const int N = *count;
     if (N <= 0) return;
+    if constexpr (FAR == 2) {
+        const unsigned sp = cl_split<sizeof(T) == 4>(N, g.O, ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u, ws_bytes);
+        if (sp) {
+            const ClSplit split{ws, kcount, sp & 15u};
+            if (sp & 16u) fused_cl_body<T, P2, FAR, 4, 1, 2, 4, 1, true>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx, split);
+            else fused_cl_body<T, P2, FAR, 4, 1, 2, 2, 1, true>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx, split);
+            return;
+        }
+    }
 #define CB_BODY(...) fused_cl_body<T, P2, FAR, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx)
     // (the tiles of cb_cl_rules.h)
     cl_tile<sizeof(T) == 4, SHAPE>(N, g.O, g.Cs, g.kh * g.kw, g.R, [&](auto tile) __attribute__((always_inline)) {
@@ -536,14 +613,14 @@ __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, co
 
 // (wavefronts per SIMD: as many as the widest tile's registers allow.  They are worth more than wider tiles: bfloat16, O > 64
 // at 76 800 listed pixels 45 us with two, 40 us with four.)
-template <typename T, int SHAPE, bool P2, bool FAR>
+template <typename T, int SHAPE, bool P2, int FAR>
 __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(Geom g, ClDiv div, const T* __restrict__ S2,
                                                           const int32_t* __restrict__ idx, const int* __restrict__ count,
                                                           const uint4* __restrict__ KF, const float* __restrict__ KT,
                                                           const float* __restrict__ bias, int relu,
-                                                          T* __restrict__ OUT, T* __restrict__ OUT2)
+                                                          T* __restrict__ OUT, T* __restrict__ OUT2, float* ws, unsigned ws_bytes, int* kcount)
 {
-    fused_cl_run<T, SHAPE, P2, FAR>(g, div, S2, idx, count, KF, KT, bias, relu, OUT, OUT2, blockIdx.x, gridDim.x);
+    fused_cl_run<T, SHAPE, P2, FAR>(g, div, S2, idx, count, KF, KT, bias, relu, OUT, OUT2, blockIdx.x, CL_GRID, ws, ws_bytes, kcount);
 }
 
 // run(an integral constant: the kernel's instance) for a layer of this geometry; its arguments checked
@@ -560,19 +637,18 @@ hipError_t fused_cl_instance(const Geom& g, const FusedPlan& plan, FN&& run)
     }
     return hipGetLastError();
 }
-constexpr unsigned CL_GRID = 1024;
-// layers whose XCDs divide the row tiles among them: in instances of their own, since the few instructions more cost small layers
-// 0.2 us a launch (64 -> 128, 128 -> 128, bfloat16)
-constexpr bool cl_far_shape(int shape) { return shape >= 128; }
-inline bool fused_cl_far(const Geom& g)
+// FAR = 1: layers whose XCDs divide the row tiles among them; 2: which may divide K as well.  In instances of their own, since the few
+// instructions more, and what they do to the allocation of scalar registers, cost the layers that use neither 0.2 - 0.7 us a launch (64 -> 128,
+// 128 -> 128, bfloat16; 256 -> 256, 3x3, 92x164 23.6 / 24.4 us).
+inline int fused_cl_far_mode(const Geom& g, const ClWork& work)
 {
-    return cl_filter_kb(g.O, (unsigned)((long long)g.Cs * g.kh * g.kw + 31) / 32u, !g.bf16) >= CL_FAR_KB;
+    return !fused_cl_far(g) ? 0 : work.bytes && cl_shape(g.O, g.Po, !g.bf16) == 128 ? 2 : 1;
 }
 template <typename T> constexpr unsigned cl_lds_bytes() { return sizeof(T) == 4 ? CL_LDS_F32 : CL_LDS_BF16; }
 
 template <typename T>
 hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow, const int32_t* idx, const int* count,
-                           const void* KF, const float* KT, const float* bias, int relu, T* OUT, T* OUT2, hipStream_t st, Tm tm)
+                           const void* KF, const float* KT, const float* bias, int relu, T* OUT, T* OUT2, const ClWork& work, hipStream_t st, Tm tm)
 {
     const ClDiv div = cl_div(g.Wo, g.Ho, g.kw, g.Cs);
     const bool p2 = (g.Cs & (g.Cs - 1)) == 0;
@@ -580,14 +656,20 @@ hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow
         constexpr int SHAPE = decltype(shape)::value;
 #define CB_CL(p, far) \
     CB_LAUNCH_LDS((fused_cl_kernel<T, SHAPE, p, far>), dim3(CL_GRID), dim3(256), cl_lds_bytes<T>(), st, tm, g, div, shadow, \
-                  idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2)
-        if constexpr (cl_far_shape(SHAPE))
-            if (p2 && fused_cl_far(g)) {
-                CB_CL(true, true);
+                  idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2, work.ws, work.bytes, work.count)
+        const int far = fused_cl_far_mode(g, work);
+        if constexpr (SHAPE == 128)
+            if (far == 2) {
+                CB_CL(true, 2);
                 return;
             }
-        if (p2) CB_CL(true, false);
-        else CB_CL(false, false);
+        if constexpr (SHAPE >= 128)
+            if (far) {
+                CB_CL(true, 1);
+                return;
+            }
+        if (p2) CB_CL(true, 0);
+        else CB_CL(false, 0);
 #undef CB_CL
     });
 }

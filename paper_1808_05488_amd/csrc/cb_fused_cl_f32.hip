@@ -49,9 +49,9 @@ hipError_t launch_pack_fused_split(const Geom& g, const float* w, void* KF, hipS
 
 hipError_t launch_fused_f32_cl(const Geom& g, const FusedPlan& plan, const float* shadow, const int32_t* idx,
                                const int* count, const void* KF, const float* KT, const float* bias, int relu, float* OUT,
-                               float* OUT2, hipStream_t st, Tm tm)
+                               float* OUT2, const ClWork& work, hipStream_t st, Tm tm)
 {
-    return launch_fused_cl<float>(g, plan, shadow, idx, count, KF, KT, bias, relu, OUT, OUT2, st, tm);
+    return launch_fused_cl<float>(g, plan, shadow, idx, count, KF, KT, bias, relu, OUT, OUT2, work, st, tm);
 }
 
 }  // namespace cb

@@ -31,11 +31,11 @@ inline int hip_fail(hipError_t e) { g_last_hip = (int)e; return CB_EHIP; }
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct StateLayout {
-    size_t S, S2, OUT, OUT2, mbits, mail, mtbits, idx, ctl, look, KT, bias, m_u8, mt_u8, KF, rowtab, total;
+    size_t S, S2, OUT, OUT2, mbits, mail, mtbits, idx, ctl, look, kcount, KT, bias, m_u8, mt_u8, KF, rowtab, total;
 };
 
 struct ScratchLayout {
-    size_t blk, X, Y, total;
+    size_t blk, X, Y, total, ws;      // ws: partial sums of layers with long filters, where the caller's buffer has room for them
     int cap;       // columns per chunk, multiple of 256
 };
 
@@ -129,6 +129,7 @@ StateLayout state_layout(const cb_layer_desc* d, const cb::Geom& g)
     L.idx = o;    o += align256((size_t)g.Po * 4);
     L.ctl = o;    o += align256(cb::CTL_WORDS * 4);
     L.look = o;   o += align256(std::max(cb::compact_one_pass_bytes(g), d->mode == CB_PROPAGATE ? 0 : cb::detect_look_bytes(g)));
+    L.kcount = o; o += use_channel_last(d, g) && cb::fused_cl_splits(g) ? cb::CL_COUNT_BYTES : 0;
     L.KT = o;     o += align256((size_t)g.R * g.Opad * b);
     L.bias = o;   o += align256((size_t)g.Opad * 4);
     L.m_u8 = o;   o += align256((size_t)g.P);
@@ -155,6 +156,7 @@ ScratchLayout scratch_layout(const cb::Geom& g, int cap, bool matrices)
     L.X = o;   o += !matrices ? 0 : align256((size_t)g.R * cap * (g.bf16 ? 2 : 4));
     L.Y = o;   o += !matrices ? 0 : align256((size_t)g.O * cap * 4);
     L.total = o;
+    L.ws = o;
     return L;
 }
 
@@ -183,6 +185,7 @@ struct cb_layer {
     bool shadow;           // the layer keeps a pixel-major copy of its input state for the fused kernel
     const void* ext_cl;    // CB_PROPAGATE layer that gathers channel-last: the producer's pixel-major output (per call)
     cb::FusedPlan plan;
+    cb::ClWork work;       // long filters: room for partial sums in the scratch buffer
     bool primed;
     bool timing;
     std::vector<hipEvent_t> ev;      // begin/end event pairs, one pair per kernel dispatch
@@ -335,7 +338,7 @@ int run_back_end(cb_layer* L, const void* src, bool have_list)
         const bool feeds = extract_job(L, &job);
         CB_HIP(cb::launch_fused(g, L->plan, src, L->d.gather_channel_last ? L->ext_cl : L->S2(), L->cur_idx, L->cur_count,
                                 L->KF(), L->KT(), L->rowtab(), L->bias(), L->d.relu, L->OUT(), L->OUT2(),
-                                feeds ? &job : nullptr, L->st, next_tm(L, CB_STEP_FUSED)));
+                                L->work, feeds ? &job : nullptr, L->st, next_tm(L, CB_STEP_FUSED)));
         if (feeds) L->next->list_ready = true;
         L->primed = true;
         L->frames++;
@@ -442,7 +445,9 @@ int cb_layer_workspace_bytes(const cb_layer_desc* desc, size_t* state_bytes, siz
     int rc = validate(desc, &g);
     if (rc) return rc;
     if (state_bytes) *state_bytes = state_layout(desc, g).total;
-    if (scratch_bytes) *scratch_bytes = scratch_layout(g, recommended_cap(g), use_matrices(desc, g)).total;
+    if (scratch_bytes)
+        *scratch_bytes = scratch_layout(g, recommended_cap(g), use_matrices(desc, g)).total +
+                         (use_channel_last(desc, g) && cb::fused_cl_splits(g) ? cb::CL_WORK_BYTES : 0);
     return CB_OK;
 }
 
@@ -490,6 +495,11 @@ int cb_layer_create(const cb_layer_desc* desc, const void* w_oihw_dev, const voi
     L->fused = fused;
     L->shadow = use_shadow(desc, g);
     L->ext_cl = nullptr;
+    if (use_channel_last(desc, g) && cb::fused_cl_splits(g)) {
+        L->work.count = (int*)(L->state + sl.kcount);
+        L->work.ws = (float*)(L->scratch + L->sc.ws);
+        L->work.bytes = (unsigned)std::min(cb::CL_WORK_BYTES, scratch_bytes - L->sc.ws);
+    }
     L->nchunks = (po_pad(g) + L->sc.cap - 1) / L->sc.cap;
     L->primed = false;
     L->timing = false;

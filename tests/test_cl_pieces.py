@@ -25,6 +25,10 @@ extern "C" long pieces(int Cs, int kmax, int stage)
         }
     return -1;
 }
+extern "C" unsigned split(int f32, int N, int O, unsigned nkg, unsigned ws)
+{
+    return f32 ? cb::cl_split<true>(N, O, nkg, ws) : cb::cl_split<false>(N, O, nkg, ws);
+}
 extern "C" int fits(int Cs, int taps) { return cb::cl_fits(Cs, taps); }
 """
 
@@ -49,3 +53,23 @@ def test_tap_and_channel_of_every_piece(rules):
 def test_longest_filter(rules):
     assert rules.fits(32768, 2) and rules.fits(4, 961) and rules.fits(68, 961)
     assert not rules.fits(32772, 1) and not rules.fits(72, 961) and not rules.fits(32768, 3)
+
+
+def test_parts_of_k_fit_what_they_need(rules):
+    """Every choice leaves each part eight groups of K, its partial sums in the workspace and its tiles in the counters; none without a workspace."""
+    rules.split.restype = C.c_uint
+    chosen = set()
+    for f32 in (0, 1):
+        for o in (100, 128, 256, 300, 512, 2000):
+            for nkg in (96, 98, 144, 256, 392, 2048):
+                for n in (1, 31, 32, 33, 500, 1054, 2184, 5000, 8193, 40000, 1 << 22):
+                    assert rules.split(f32, n, o, nkg, 0) == 0
+                    for ws in (1 << 16, 1 << 20, 16 << 20):
+                        r = rules.split(f32, n, o, nkg, ws)
+                        if not r:
+                            continue
+                        parts, bn = r & 15, 64 if r & 16 else 32
+                        tiles = -(-n // bn) * -(-o // 128)
+                        chosen.add((parts, bn))
+                        assert 2 <= parts <= 8 and -(-nkg // parts) >= 8 and tiles <= 256 and tiles * parts * 128 * bn * 4 <= ws
+    assert {bn for _, bn in chosen} == {32, 64} and len(chosen) >= 8

@@ -1,5 +1,5 @@
 """Layers whose packed filter matrix is beyond 2 MB: the row tiles are divided among two, four or eight groups of XCDs, according to the listed
-pixels, with row and column tiles that do not come out even."""
+pixels, with row and column tiles that do not come out even; with very long filters K is divided too, if the scratch buffer has room."""
 import pytest
 import torch
 
@@ -8,6 +8,7 @@ import synth_inputs as syn
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
+    import paper_1808_05488_amd as cb
     from parity import Pair
 
 
@@ -22,3 +23,20 @@ def test_row_tiles_divided_among_the_xcds(geom, prob, bf16):
     p = Pair(spec, H, W, bf16=bf16)
     for t, f in enumerate(frames):
         p.step(f, 0.02, tag=f"{geom} frame {t}")
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("geom", [(256, 200, 7, 20, 30), (128, 130, 9, 30, 41), (512, 260, 3, 16, 19), (256, 128, 9, 34, 40)])
+def test_scratch_with_and_without_room_for_partial_sums(geom, bf16):
+    C, O, k, H, W = geom
+    print("partial sums", geom, bf16, flush=True)
+    spec, frames = syn.random_layer_case(C + O, C, O, k, 1, k // 2, H, W, 4, change_prob=0.01)
+    d = cb.make_desc(C, O, k, k, 1, k // 2, H, W, dtype=cb.CB_BF16 if bf16 else cb.CB_F32)
+    least = cb.cb_layer_min_scratch_bytes(d)
+    for size in (None, least, least + (1 << 20)):
+        p = Pair(spec, H, W, bf16=bf16, scratch_bytes=size)
+        for t, f in enumerate(frames):
+            p.step(f, 0.02, tag=f"{geom} scratch {size} frame {t}")
+    a, b = (Pair(spec, H, W, bf16=bf16) for _ in range(2))       # the sums do not depend on who comes last
+    for f in frames:
+        assert (a.step(f, 0.02)[0] == b.step(f, 0.02)[0]).all()
