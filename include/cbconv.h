@@ -125,8 +125,9 @@ typedef struct {
                                       (begin/end time stamps of the dispatches; TOTAL = first begin
                                       to last end); zeros unless cb_layer_set_timing switched it on */
     int32_t scan_recounts;   /* since create: how often a workgroup of the index extraction recomputed a
-                                predecessor's count itself because its bounded wait for it ran out (see
-                                cb_set_scan_wait_limit); 0 on an idle GPU; the results are the same */
+                                predecessor's count, or detected a block of pixels that no workgroup had begun,
+                                because its bounded wait ran out (see cb_set_scan_wait_limit); 0 on an idle
+                                GPU; the results are the same */
     int32_t reserved;
 } cb_stats;
 
@@ -258,15 +259,17 @@ int cb_layer_set_timing(cb_layer_t *layer, int32_t on);
 /* Waits for the layer's stream, then fills *stats for the last frame. */
 int cb_layer_stats(cb_layer_t *layer, cb_stats *stats);
 /* The index extraction (Sec. III-A, "Change Indexes Extraction") runs inside the launch that detects the changes where it
- * can, its workgroups waiting for those that detect.  It takes a launch of its own for very large maps, strides above 2 and
- * very many channels, while per-step times are switched on (they are those of the separate launches), and with any other
- * limit than the default here.
- * The one-launch index extraction scans the per-workgroup
+ * can; it takes a launch of its own for very large maps, strides above 2 and very many channels, while per-step times are
+ * switched on (they are those of the separate launches), and with a limit of 0 here.
+ * In the launch that detects, a workgroup that extracts polls for the part of the change map that it needs.  After `polls`
+ * unsuccessful polls (at most 4096) it detects itself whatever pixels no workgroup has begun to look at; a pixel is looked at by one
+ * workgroup, whichever begins first.  (With any other limit than the default these workgroups are numbered first.)
+ * In a launch of its own the index extraction scans the per-workgroup
  * counts in a single pass: a workgroup polls for the counts of the workgroups before it.  After
- * `polls` unsuccessful polls of one count it recomputes that count from the change map instead, so
- * the index list and N never depend on how the GPU schedules workgroups (other streams or processes
- * may hold compute units).  Process-wide; default 2^20 (tens of milliseconds); 0 = never wait.  Meant
- * for tests of that path; cb_stats.scan_recounts tells how often it was taken. */
+ * `polls` unsuccessful polls of one count it recomputes that count from the change map instead.
+ * So the index list and N never depend on how the GPU schedules workgroups (other streams or processes
+ * may hold compute units), and no launch waits for ever.  Process-wide; default 2^20 (tens of milliseconds); 0 = never wait.  Meant
+ * for tests of those paths; cb_stats.scan_recounts tells how often they were taken. */
 int cb_set_scan_wait_limit(int32_t polls);
 /* The next frame will be a full update (as after create). */
 int cb_layer_reset(cb_layer_t *layer);

@@ -212,6 +212,21 @@ template <typename T, int VEC, int CS, int CPT, int PLX, bool SH> struct DetectL
     static_assert(flags % 16 == 0 && pix % 16 == 0, "rows are 16-byte aligned");
 };
 
+// Arguments of detection with the extraction in the same launch
+template <typename T> struct DetectArgs {
+    const T* x;
+    T *S, *S2;
+    uint64_t* mbits0;
+    int* ctl;
+    int C, Cs;
+    unsigned inv_per;
+    int P, nwords;
+    float tau;
+    int flags;
+    int2 stream;
+    DetectJob job;
+};
+
 // Register-resident variant: a lane keeps the CPT channel values it compared, so
 // the state update is stores only (no second, latency-bound read of the frame).
 // Workgroup = CS channel groups x PL pixel lanes.
@@ -222,11 +237,12 @@ template <typename T, int VEC, int CS, int CPT, int PLX, bool SH> struct DetectL
 // g + q*CS, so that a lane's channels are neighbours in the shadow.  C <= CS*CPT; the shadow's pixels are the C channels rounded
 // up to whole 16-byte pieces, zero behind the last.  inv_per = ceil(2^20 / pieces of a pixel) divides a piece's number (below 1 024) by it.
 // lds: detect_lds bytes (the extracting workgroups of the same launch put theirs to other uses).
-// MAIL: the map also goes, tagged, to the extracting workgroups of the same launch.
+// MAIL: the map also goes, tagged, to the extracting workgroups of the same launch (job), of which one that waits may have taken this block.  A block
+// is what a workgroup, with one channel group a wavefront, detects.
 template <typename T, int VEC, int CS, int CPT, int PLX, bool SH, bool MAIL>
 __device__ __forceinline__
 void detect_reg_block(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2, uint64_t* __restrict__ mbits0,
-                      int* __restrict__ ctl, int C, int Cs, unsigned inv_per, int P, int nwords, float tau, int flags, int2 stream, uint64_t* mail, char* lds)
+                      int* __restrict__ ctl, int C, int Cs, unsigned inv_per, int P, int nwords, float tau, int flags, int2 stream, const DetectJob* job, unsigned bx, char* lds)
 {
     typedef typename Pack<T, VEC>::type V;
     // which of the two map buffers and counters this frame fills: the frame count lives on the device
@@ -235,7 +251,7 @@ void detect_reg_block(const T* __restrict__ x, T* __restrict__ S, T* __restrict_
     const int frame = ctl[CTL_FRAME], par = frame & 1;
     const unsigned tag = (unsigned)frame + 1u;
     uint64_t* __restrict__ mbits = mbits0 + par;  // the two maps are interleaved: word w of this frame's map at [2 * w]
-    int* __restrict__ nin = nin_counter(ctl, blockIdx.x, par);
+    int* __restrict__ nin = nin_counter(ctl, bx, par);
     constexpr int PL = PLX ? PLX : (CS >= 4 ? 64 : 256 / CS);
     static_assert(PLX == 0 || (PLX == 16 && VEC == 1 && CS > 1), "narrow workgroups: 16 lanes of one pixel each");
     constexpr int NT = PL * CS;
@@ -245,7 +261,7 @@ void detect_reg_block(const T* __restrict__ x, T* __restrict__ S, T* __restrict_
     const int pl = tid - g * PL;
     // The lane's pixels are pw .. pw + VEC - 1.  Where the image ends among them it loads the image's last VEC pixels
     // (p0 .. P - 1) instead, of which only those from pw on are its own.
-    const long pw = ((long)blockIdx.x * PL + pl) * VEC;
+    const long pw = ((long)bx * PL + pl) * VEC;
     const bool valid = pw < P;
     constexpr bool RAGGED = sizeof(T) == 2 && VEC > 1;      // (float32 takes several pixels per lane only where P is a multiple)
     const int over = RAGGED && valid && pw + VEC > P ? (int)(pw + VEC - P) : 0;
@@ -260,6 +276,16 @@ void detect_reg_block(const T* __restrict__ x, T* __restrict__ S, T* __restrict_
             once = before >= stream.x && before < stream.y;
         }
 
+    const bool claimer = CS > 1 ? tid == 0 : (tid & 63) == 0;
+    unsigned found = ~tag;                       // what the claim's word held
+    // (behind the loads of the pixels, whose data it delays by nothing: results come in order.  Ahead of them, 0.5 us more in a frame of 43)
+    auto claim = [&]() {
+        if constexpr (MAIL)
+            if (claimer) found = claim_block(DeviceMem(), job->claims + claim_index(CS > 1 ? bx : bx * (256 / 64) + (tid >> 6), (unsigned)job->nclaims), tag, &ctl[CTL_DONE], false);
+    };
+
+    uint64_t* const mail = MAIL ? job->mail : nullptr;
+
     V xv[CPT];
     unsigned bits = 0;
     if (valid) {
@@ -269,6 +295,7 @@ void detect_reg_block(const T* __restrict__ x, T* __restrict__ S, T* __restrict_
                 const int c = SH ? g * CPT + q : g + q * CS;
                 if (c < C) xv[q] = ld_px<T, VEC, false>(x + (size_t)c * P + p0);
             }
+            claim();
             // (first frame only.  Without this wait the compiler assumes these loads may still be in flight
             // in the other branch, and waits there between loads.)
             __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
@@ -283,6 +310,7 @@ void detect_reg_block(const T* __restrict__ x, T* __restrict__ S, T* __restrict_
                     sv[q] = once ? ld_px<T, VEC, true>(S + off) : ld_px<T, VEC, false>(S + off);
                 }
             }
+            claim();
             // every load is issued before the first compare waits for one: the kernel lives on loads in flight
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -303,16 +331,24 @@ void detect_reg_block(const T* __restrict__ x, T* __restrict__ S, T* __restrict_
     }
     if (CS > 1) {
         unsigned* const sflag = reinterpret_cast<unsigned*>(lds);
-        sflag[tid] = bits;
+        constexpr unsigned LOST = 1u << 31;
+        sflag[tid] = MAIL && tid == 0 && found == tag ? LOST : bits;
         __syncthreads();
+        if (MAIL && sflag[0] == LOST) {
+            if (tid == 0 && claim_lost(DeviceMem(), &ctl[CTL_DONE], job->nblk)) finish_frame(ctl, next_epoch((unsigned)ctl[CTL_EPOCH]), 1, false);
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < CS; ++q) bits |= sflag[q * PL + pl];
+    } else if (MAIL && __builtin_amdgcn_readfirstlane(found) == tag) {
+        if (claimer && claim_lost(DeviceMem(), &ctl[CTL_DONE], job->nblk)) finish_frame(ctl, next_epoch((unsigned)ctl[CTL_EPOCH]), 1, false);
+        return;
     }
     bits = (flags & DET_FORCE_ALL) ? own : bits & own;
 
     if (g == 0) {
         const int lane = tid & 63;
-        const long wave_p0 = ((long)blockIdx.x * PL + (pl & ~63)) * VEC;
+        const long wave_p0 = ((long)bx * PL + (pl & ~63)) * VEC;
         const long w0 = wave_p0 >> 6;
         const unsigned mapped = bits >> over;
         if (VEC == 4) {
@@ -337,12 +373,12 @@ void detect_reg_block(const T* __restrict__ x, T* __restrict__ S, T* __restrict_
             const unsigned b0 = (unsigned)__ballot(bits & 1u) & 0xFFFFu;
             if (lane == 0) {
                 if constexpr (MAIL) {
-                    mail_put(mail, blockIdx.x, tag, b0);
+                    mail_put(mail, bx, tag, b0);
                     // (the last word's units behind the image have no workgroup of their own)
-                    if ((long)(blockIdx.x + 1) * 16 >= P)
-                        for (long u = (long)blockIdx.x + 1; u < 4L * nwords; ++u) mail_put(mail, u, tag, 0u);
+                    if ((long)(bx + 1) * 16 >= P)
+                        for (long u = (long)bx + 1; u < 4L * nwords; ++u) mail_put(mail, u, tag, 0u);
                 }
-                reinterpret_cast<uint16_t*>(mbits + 2 * (blockIdx.x >> 2))[blockIdx.x & 3] = (uint16_t)b0;
+                reinterpret_cast<uint16_t*>(mbits + 2 * (bx >> 2))[bx & 3] = (uint16_t)b0;
                 if (b0) atomicAdd(nin, __popc(b0));
             }
         } else {
@@ -477,6 +513,45 @@ void detect_reg_block(const T* __restrict__ x, T* __restrict__ S, T* __restrict_
     }
 }
 
+// A block of PX pixels in place of its own workgroup, which has not begun: a lane a pixel, channel by channel.  For launches that do not get the chip, and
+// written to take no more registers than the rest.
+template <typename T, int PX, int NT>
+__device__ __forceinline__ void detect_taken(const T* __restrict__ x, T* S, T* S2, uint64_t* __restrict__ mbits0, int* __restrict__ ctl, int C, int Cs, int P, float tau,
+                                             int flags, int b, int par, unsigned tag, uint64_t* mail)
+{
+    const int lane = threadIdx.x & 63;
+    for (int o = threadIdx.x & ~63; o < PX; o += NT) {               // (whole wavefronts)
+        const long p = (long)b * PX + o + lane;
+        const bool valid = o + lane < PX && p < P;
+        bool fired = valid && (flags & DET_FORCE_ALL);
+#pragma unroll 1
+        for (int c = 0; c < C && valid && !fired; ++c)
+            fired = fabsf(widen(x[(size_t)c * P + p]) - widen(S[(size_t)c * P + p])) > tau;      // one float32 subtract, then |.| > tau (strict)
+        const uint64_t word = __ballot(fired);
+        if (valid && !(flags & DET_NO_UPDATE) && (fired || (flags & DET_COPY_ALL)))
+#pragma unroll 1
+            for (int c = 0; c < C; ++c) {
+                S[(size_t)c * P + p] = x[(size_t)c * P + p];
+                if (S2) S2[(size_t)p * Cs + c] = x[(size_t)c * P + p];
+            }
+        if (lane == 0) {
+            const int n = __popcll(word);
+            if (n) atomicAdd(nin_counter(ctl, (unsigned)b, par), n);
+            const long w = (p >> 6);
+            if (PX == 16) {
+                reinterpret_cast<uint16_t*>(mbits0 + par + 2 * w)[b & 3] = (uint16_t)word;
+                mail_put(mail, b, tag, (unsigned)word & 0xFFFFu);
+                if ((long)(b + 1) * 16 >= P)
+                    for (long u = (long)b + 1; u < 4L * ((P + 63) / 64); ++u) mail_put(mail, u, tag, 0u);
+            } else if (p < P) {
+                mbits0[2 * w + par] = word;
+                mail_put(mail, 2 * w, tag, (unsigned)word);
+                mail_put(mail, 2 * w + 1, tag, (unsigned)(word >> 32));
+            }
+        }
+    }
+}
+
 template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false>
 __global__ __launch_bounds__((PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS)
 void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2, uint64_t* __restrict__ mbits0,
@@ -484,32 +559,55 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
 {
     typedef DetectLds<T, VEC, CS, CPT, PLX, SH> LDS;
     __shared__ __align__(16) char lds[LDS::bytes ? LDS::bytes : 16];
-    detect_reg_block<T, VEC, CS, CPT, PLX, SH, false>(x, S, S2, mbits0, ctl, C, Cs, inv_per, P, nwords, tau, flags, stream, nullptr, lds);
+    detect_reg_block<T, VEC, CS, CPT, PLX, SH, false>(x, S, S2, mbits0, ctl, C, Cs, inv_per, P, nwords, tau, flags, stream, nullptr, blockIdx.x, lds);
 }
 
-// Detection with the index extraction in the same launch: the last job.nblk workgroups extract.  A launch of its own costs the extraction
+// Detection with the index extraction in the same launch: the last job.nblk workgroups extract (cb_claim.h).  A launch of its own costs the extraction
 // 4 - 8 us, of which most is the end of one kernel, the start of the next and its first loads from memory.  Frames, us, before / now:
 // 3 -> 16 at 48x64 15.1 / 12.4, 64 -> 64 at 480x640 41.7 / 39.5, 64 -> 128 at 271x435 bfloat16 24.5 / 20.9, 48 -> 96 5x5 stride 2 at 241x323
 // 29.0 / 27.1, 3 -> 16 7x7 at 1080p 32.3 / 30.3, 32 -> 32 9x9 at 240x320 34.0 / 31.1, 128 -> 128 at 1080p bfloat16, 10 % 459 / 454.
 template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false>
 __global__ __launch_bounds__((PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS)
-void detect_extract_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict__ S2, uint64_t* __restrict__ mbits0,
-                           int* __restrict__ ctl, int C, int Cs, unsigned inv_per, int P, int nwords, float tau, int flags, int2 stream, DetectJob job)
+void detect_extract_kernel(const DetectArgs<T> a)
 {
-    constexpr int NT = (PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS;
+    constexpr int NT = (PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS, PX = PLX ? PLX : 64 * VEC;      // (pixels of a block)
     typedef DetectLds<T, VEC, CS, CPT, PLX, SH> LDS;
-    constexpr int EX = MAP_STAGE * 8 + one_pass_small<NT / 64>() * 4;
-    __shared__ __align__(16) char lds[LDS::bytes > EX ? LDS::bytes : EX];
-    const unsigned detecting = gridDim.x - (unsigned)job.nblk;
-    if (blockIdx.x >= detecting) {
-        const int frame = ctl[CTL_FRAME];
-        extract_own_block<NT>(job, ctl, mbits0, frame & 1, (int)(blockIdx.x - detecting), reinterpret_cast<uint64_t*>(lds), false,
-                              [&](long i, long step, long nw, uint64_t (&w)[2]) {
-                                  mail_words<PLX ? 64 / (PLX ? PLX : 1) : 2>(job.mail, i, step, nw, (unsigned)frame + 1u, w);
-                              });
-        return;
-    }
-    detect_reg_block<T, VEC, CS, CPT, PLX, SH, true>(x, S, S2, mbits0, ctl, C, Cs, inv_per, P, nwords, tau, flags, stream, job.mail, lds);
+    constexpr int EX = (MAP_STAGE * 8 + one_pass_small<NT / 64>() * 4 + 15) / 16 * 16, USED = LDS::bytes > EX ? LDS::bytes : EX;
+    __shared__ __align__(16) char lds[USED + 16];
+    unsigned* const s_word = reinterpret_cast<unsigned*>(lds + USED);            // (behind both uses of the LDS)
+    const DetectJob& job = a.job;
+    const Role role = role_of(job);
+    const int bid = role.bid;
+    unsigned epoch = 0;
+    detect_or_extract(
+        bid >= 0,
+        [&]() {
+            detect_reg_block<T, VEC, CS, CPT, PLX, SH, true>(a.x, a.S, a.S2, a.mbits0, a.ctl, a.C, a.Cs, a.inv_per, a.P, a.nwords, a.tau, a.flags, a.stream, &job, (unsigned)role.own, lds);
+        },
+        [&](bool limited) {
+            const int frame = a.ctl[CTL_FRAME];
+            if (limited) {
+                if (threadIdx.x == 0) epoch = (unsigned)a.ctl[CTL_EPOCH];
+                clear_other_map(a.mbits0, a.ctl, frame & 1, job.clear_words, bid * NT + (int)threadIdx.x, job.nblk * NT);
+            }
+            int polls = job.patience;
+            return stage_own_block<NT>(job, bid, reinterpret_cast<uint64_t*>(lds), s_word, [&](long i, long step, long nw, uint64_t (&w)[2]) {
+                return mail_words<PLX ? 64 / (PLX ? PLX : 1) : 2>(job.mail, i, step, nw, (unsigned)frame + 1u, w, limited, polls);
+            });
+        },
+        [&]() {
+            const DetectArgs<T> r = launch_arguments<DetectArgs<T>>();
+            return unclaimed_block<NT>(r.job, r.job.nclaims, (unsigned)r.ctl[CTL_FRAME] + 1u, bid, reinterpret_cast<int*>(s_word));
+        },
+        [&](int b) {
+            const DetectArgs<T> r = launch_arguments<DetectArgs<T>>();
+            const int frame = r.ctl[CTL_FRAME];
+            if (take_block(r.job, r.ctl, b, (unsigned)frame + 1u, s_word))
+                detect_taken<T, PX, NT>(r.x, r.S, r.S2, r.mbits0, r.ctl, r.C, r.Cs, r.P, r.tau, r.flags, b, frame & 1, (unsigned)frame + 1u, r.job.mail);
+        },
+        [&]() {
+            extract_own_block<NT>(job, a.ctl, bid, reinterpret_cast<const uint64_t*>(lds), epoch, reinterpret_cast<unsigned*>(lds + MAP_STAGE * 8), false);
+        });
 }
 
 // State update as a kernel of its own, for frames whose change detection ran with DET_NO_UPDATE: all
@@ -643,8 +741,8 @@ __global__ __launch_bounds__(256) void shadow_rebuild_kernel(const T* __restrict
 }
 
 // The extraction inside the launch of detection, by workgroups of nt threads: words of the dilated map per wavefront (0: it takes a launch
-// of its own).  The workgroups that wait are at most a quarter of the chip's wavefronts (half of those that the registers of the widest
-// variant leave), and the part of the map under one workgroup's words fits its LDS.  Few words a wavefront spread the expansion of dense words and shorten the polls, many workgroups add up more
+// of its own).  The part of the map under one workgroup's words fits its LDS, and the workgroups that wait are at most a quarter of a whole chip's wavefronts: what
+// they wait for runs beside them (that it is ever done does not depend on that, cb_claim.h).  Few words a wavefront spread the expansion of dense words and shorten the polls, many workgroups add up more
 // counts and poll for more of each other's rows.  Frames, us, 16 / 32 / 64 words: 3 -> 16, 7x7, 1080p (507, 254, 127 workgroups) 36.3 / 32.0 / 30.4;
 // 3 -> 16 at 720p (225, 113, 57) 18.2 / 16.8 / 16.9; 3 -> 16 at 240x320 (19, 10, 5) 13.1 / 13.4 / 14.1; 64 -> 32 at 120x160 14.8 / 15.0 / 15.9; 64 -> 64 at
 // 480x640, 20 % (38, 19, 10) 81.5 / 82.2 / 84.8; 128 -> 64 at 46x82, bfloat16 (2, 1, 1) 16.4 / 15.6 / 16.1.
@@ -668,10 +766,12 @@ void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int C
     const unsigned per = (unsigned)Cs * (unsigned)sizeof(T) / 16u, inv_per = per ? ((1u << 20) + per - 1u) / per : 0u;
     // (job->nblk stays 0 where the extraction takes a launch of its own)
     if (job && (job->per = extract_words(job->g, PL * CS)) > 0) job->nblk = (job->g.Ho * job->g.WWo - 1) / (PL * CS / 64 * job->per) + 1;
+    if (job && job->ahead) job->ahead = job->nblk;
+    if (job) job->nclaims = CS > 1 ? (int)grid : (P + 64 * VEC - 1) / (64 * VEC);
 #define CB_REG(sh, shadow)                                                                                                          \
     if (job && job->nblk)                                                                                                           \
-        hipLaunchKernelGGL((detect_extract_kernel<T, VEC, CS, CPT, PLX, sh>), dim3(grid + (unsigned)job->nblk), dim3(PL * CS), 0, st, x, S, shadow, \
-                           mbits, ctl, C, Cs, inv_per, P, (P + 63) / 64, tau, flags, stream, *job);                                  \
+        hipLaunchKernelGGL((detect_extract_kernel<T, VEC, CS, CPT, PLX, sh>), dim3(grid + (unsigned)job->nblk), dim3(PL * CS), 0, st, \
+                           DetectArgs<T>{x, S, shadow, mbits, ctl, C, Cs, inv_per, P, (P + 63) / 64, tau, flags, stream, *job});      \
     else CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX, sh>), dim3(grid), dim3(PL * CS), st, tm, x, S, shadow, mbits, ctl, C, Cs, \
               inv_per, P, (P + 63) / 64, tau, flags, stream)
     if constexpr (CS >= 4 && (CPT * sizeof(T)) % 16 == 0) {
@@ -717,6 +817,19 @@ void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int Cs,
     }
 }
 
+template <typename T> struct ListedArgs {
+    const T* x;
+    T *S, *S2;
+    uint64_t* mbits0;
+    int* ctl;
+    const int32_t* cand;
+    const int* cand_count;
+    int cand_cap, C, Cpx, P, W;
+    float tau;
+    int flags, pool_w, cand_W, unused;
+    DetectJob job;
+};
+
 // Change detection restricted to candidate pixels (Eq. 3 where it can fire at all).  When a
 // layer's input is the cached output of a change-based producer, only the producer's listed
 // pixels were rewritten; every other input pixel holds the bits it held a frame ago, when it
@@ -731,7 +844,7 @@ void launch_v(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int Cs,
 // staged in LDS ahead of the first barrier of a round and, once it is known which candidates fired, written to
 // S2 with consecutive lanes on consecutive channels; two alternating buffers, so the barriers the round has anyway
 // are enough.  (Written from the registers that hold them they are 4-byte stores to a different line per lane.)
-constexpr int LISTED_U = 8;
+constexpr int LISTED_U = 8, LISTED_BLOCKS = 2048;
 template <typename T, int CS, int PLC, bool SH> struct ListedLds {
     static constexpr int PITCH = CS * LISTED_U + 1;   // staged values per candidate: candidates a lane apart fall into different banks
     // (one buffer and a barrier at the end of the round where two would not fit)
@@ -739,7 +852,8 @@ template <typename T, int CS, int PLC, bool SH> struct ListedLds {
     static constexpr int flags = CS * PLC * 4, rows = SH ? (NBUF * PLC * PITCH * (int)sizeof(T) + 15) / 16 * 16 : 0, pix = SH ? NBUF * PLC * 4 : 0;
     static constexpr int bytes = flags + rows + pix;
 };
-// Workgroup bx of `blocks`; lds: ListedLds bytes.  ARRIVE: it adds itself to the arrivals when its bits are set.
+// Workgroup bx of `blocks`; lds: ListedLds bytes.  ARRIVE: it adds itself to the arrivals when its bits are set, and claims its block of the job first if it
+// has pixels (a waiting workgroup may have taken it).
 template <typename T, int CS, int PLC, bool SH, bool ARRIVE>
 __device__ __forceinline__ void detect_listed_block(const T* __restrict__ x, T* __restrict__ S,
                                                     T* __restrict__ S2, uint64_t* __restrict__ mbits0,
@@ -747,12 +861,14 @@ __device__ __forceinline__ void detect_listed_block(const T* __restrict__ x, T* 
                                                     const int32_t* __restrict__ cand,
                                                     const int* __restrict__ cand_count, int cand_cap,
                                                     int C, int Cpx, int P, int W, float tau, int flags, int pool_w,
-                                                    int cand_W, int bx, int blocks, char* lds)
+                                                    int cand_W, int bx, int blocks, const DetectJob* job, char* lds)
 {
     constexpr int U = LISTED_U;                   // channels per lane held in registers (all of them when C <= 8*CS)
-    const int par = ctl[CTL_FRAME] & 1;           // which of the two map buffers and counters this frame fills
+    const int frame = ctl[CTL_FRAME], par = frame & 1;          // which of the two map buffers and counters this frame fills
     uint64_t* __restrict__ mbits = mbits0 + par;  // the two maps are interleaved: word w of this frame's map at [2 * w]
     int* __restrict__ nin = nin_counter(ctl, (unsigned)bx, par);
+    const unsigned tag = (unsigned)frame + 1u;
+    unsigned found = ~tag;                        // (thread 0) what the claim's word held
     typedef ListedLds<T, CS, PLC, SH> LDS;
     unsigned* const sflag = reinterpret_cast<unsigned*>(lds);
     constexpr int PITCH = LDS::PITCH, NBUF = LDS::NBUF;
@@ -780,6 +896,7 @@ __device__ __forceinline__ void detect_listed_block(const T* __restrict__ x, T* 
         }
         unsigned fired = 0;
         T xr[U];
+        if (ARRIVE && tid == 0 && t0 == bx * PLC) found = claim_block(DeviceMem(), job->claims + claim_index((unsigned)bx, (unsigned)job->nclaims), tag, &ctl[CTL_DONE], false);
         if (valid) {
             T sr[U];
 #pragma unroll
@@ -807,8 +924,13 @@ __device__ __forceinline__ void detect_listed_block(const T* __restrict__ x, T* 
                 if (c < C) stage[SH ? buf : 0][SH ? pl * PITCH + c : 0] = xr[u];
             }
         }
-        sflag[tid] = fired;
+        constexpr unsigned LOST = 1u << 31;
+        sflag[tid] = ARRIVE && tid == 0 && found == tag ? LOST : fired;
         __syncthreads();
+        if (ARRIVE && sflag[0] == LOST) {
+            if (tid == 0 && claim_lost(DeviceMem(), &ctl[CTL_DONE], job->nblk)) finish_frame(ctl, next_epoch((unsigned)ctl[CTL_EPOCH]), 1, true);
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < CS; ++k) fired |= sflag[k * PLC + pl];
         if (SH && g == 0) s_q[SH ? buf : 0][SH ? pl : 0] = (valid && (fired || (flags & DET_COPY_ALL))) ? q : -1;
@@ -871,6 +993,42 @@ __device__ __forceinline__ void detect_listed_block(const T* __restrict__ x, T* 
     }
 }
 
+// The candidates of workgroup bx in its place, as detect_taken: a wavefront a candidate, a lane a channel.
+template <typename T, int PLC, int NT>
+__device__ __forceinline__ void detect_listed_taken(const T* __restrict__ x, T* S, T* S2, uint64_t* __restrict__ mbits0, int* __restrict__ ctl, const int32_t* __restrict__ cand,
+                                                    int nc, int C, int Cpx, int P, int W, float tau, int flags, int pool_w, int cand_W, int bx, int blocks, int par)
+{
+    const int lane = threadIdx.x & 63;
+    int fresh = 0;
+    for (int i = threadIdx.x >> 6;; i += NT / 64) {
+        const long n = (long)(i / PLC * blocks + bx) * PLC + i % PLC;
+        if (n - i % PLC >= nc) break;
+        if (n >= nc) continue;
+        int q = cand[n];
+        if (pool_w > 1) {
+            const int yo = q / cand_W, xo = q - yo * cand_W;
+            q = (yo / pool_w) * W + xo / pool_w;
+        }
+        bool fired = false;
+#pragma unroll 1
+        for (int c = lane; c < C; c += 64) fired |= fabsf(to_f(x[(size_t)c * P + q]) - to_f(S[(size_t)c * P + q])) > tau;     // one float32 subtract, then |.| > tau (strict)
+        fired = __ballot(fired) != 0;
+        if (fired && lane == 0) {
+            const unsigned bit = 1u << (q & 31);
+            if (!(atomicOr(reinterpret_cast<uint32_t*>(mbits0 + par + 2 * (q >> 6)) + (q >> 5 & 1), bit) & bit)) ++fresh;
+        }
+        if (fired || (flags & DET_COPY_ALL))
+#pragma unroll 1
+            for (int c = lane; c < C; c += 64) {
+                S[(size_t)c * P + q] = x[(size_t)c * P + q];
+                if (S2) S2[(size_t)q * Cpx + c] = x[(size_t)c * P + q];
+            }
+    }
+    if (fresh) atomicAdd(nin_counter(ctl, (unsigned)bx, par), fresh);
+    __syncthreads();                              // (every bit's atomic has returned its old value)
+    if (threadIdx.x == 0) arrive(ctl, (unsigned)bx);
+}
+
 template <typename T, int CS, int PLC, bool SH = false>
 __global__ __launch_bounds__(CS * PLC) void detect_listed_kernel(const T* __restrict__ x, T* __restrict__ S,
                                                                  T* __restrict__ S2, uint64_t* __restrict__ mbits0,
@@ -882,34 +1040,58 @@ __global__ __launch_bounds__(CS * PLC) void detect_listed_kernel(const T* __rest
 {
     __shared__ __align__(16) char lds[ListedLds<T, CS, PLC, SH>::bytes];
     detect_listed_block<T, CS, PLC, SH, false>(x, S, S2, mbits0, ctl, cand, cand_count, cand_cap, C, Cpx, P, W, tau, flags, pool_w, cand_W, (int)blockIdx.x, (int)gridDim.x,
-                                              lds);
+                                              nullptr, lds);
 }
 
-// Detection at listed pixels with the index extraction in the same launch, as detect_extract_kernel; here the first workgroups extract, since
-// those behind the last listed pixel, up to two thousand that only come and go, would delay them.  Frames, us, two launches a layer / one: five-layer 7 x 7 net
-// at 480x640 with detection in every layer 141.5 / 132.8, bfloat16 111 / 99.7, ten-layer 3 x 3 trunk at 368x656 388 / 367, bfloat16 269.5 / 248, at
-// 150x200 254 / 241.  (State update ahead of the bits, as in the launch by itself: 138, 113, 378, 262 and 257.)
+// Detection at listed pixels with the index extraction in the same launch, as detect_extract_kernel.  Frames, us, two launches a layer / one: five-layer 7 x 7 net
+// at 480x640 with detection in every layer 144 / 130, bfloat16 117 / 104, ten-layer 3 x 3 trunk at 368x656 394 / 375, bfloat16 269 / 257, at
+// 150x200 204.5 / 200.5.  (State update ahead of the bits, as in the launch by itself, gains half of that.  Extracting workgroups in front: the same within 0.5 %, but
+// 355 instead of 346 on the bfloat16 trunk with 20 % of its pixels changed; 512 detecting workgroups at most 356 there.)
 template <typename T, int CS, int PLC, bool SH = false>
-__global__ __launch_bounds__(CS * PLC) void detect_listed_extract_kernel(const T* __restrict__ x, T* __restrict__ S,
-                                                                         T* __restrict__ S2, uint64_t* __restrict__ mbits0,
-                                                                         int* __restrict__ ctl,
-                                                                         const int32_t* __restrict__ cand,
-                                                                         const int* __restrict__ cand_count, int cand_cap,
-                                                                         int C, int Cpx, int P, int W, float tau, int flags, int pool_w,
-                                                                         int cand_W, DetectJob job)
+__global__ __launch_bounds__(CS * PLC) void detect_listed_extract_kernel(const ListedArgs<T> a)
 {
-    constexpr int NT = CS * PLC, EX = MAP_STAGE * 8 + one_pass_small<NT / 64>() * 4, LI = ListedLds<T, CS, PLC, SH>::bytes;
-    __shared__ __align__(16) char lds[EX > LI ? EX : LI];
-    const int blocks = (int)gridDim.x - job.nblk;
-    if ((int)blockIdx.x < job.nblk) {
-        const int par = ctl[CTL_FRAME] & 1, nc = *cand_count, busy = (nc + PLC - 1) / PLC;
-        await_arrivals(ctl, busy < blocks ? busy : blocks);
-        extract_own_block<NT>(job, ctl, mbits0, par, (int)blockIdx.x, reinterpret_cast<uint64_t*>(lds), true,
-                              [&](long i, long step, long nw, uint64_t (&w)[2]) { map_words2(mbits0, par, i, step, nw, w); });
-        return;
-    }
-    detect_listed_block<T, CS, PLC, SH, true>(x, S, S2, mbits0, ctl, cand, cand_count, cand_cap, C, Cpx, P, W, tau, flags, pool_w, cand_W,
-                                              (int)blockIdx.x - job.nblk, blocks, lds);
+    constexpr int NT = CS * PLC, EX = (MAP_STAGE * 8 + one_pass_small<NT / 64>() * 4 + 15) / 16 * 16, LI = (ListedLds<T, CS, PLC, SH>::bytes + 15) / 16 * 16,
+                  USED = EX > LI ? EX : LI;
+    __shared__ __align__(16) char lds[USED + 16];
+    unsigned* const s_word = reinterpret_cast<unsigned*>(lds + USED);
+    const Role role = role_of(a.job);
+    const int blocks = role.n, bid = role.bid;
+    auto busy = [&](const int* count) {
+        const int want = (*count + PLC - 1) / PLC;
+        return want < blocks ? want : blocks;
+    };
+    unsigned epoch = 0;
+    detect_or_extract(
+        bid >= 0,
+        [&]() {
+            detect_listed_block<T, CS, PLC, SH, true>(a.x, a.S, a.S2, a.mbits0, a.ctl, a.cand, a.cand_count, a.cand_cap, a.C, a.Cpx, a.P, a.W, a.tau, a.flags, a.pool_w, a.cand_W,
+                                                     role.own, blocks, &a.job, lds);
+        },
+        [&](bool limited) {
+            const ListedArgs<T> r = launch_arguments<ListedArgs<T>>();
+            const int par = r.ctl[CTL_FRAME] & 1;
+            if (limited) {
+                if (threadIdx.x == 0) epoch = (unsigned)r.ctl[CTL_EPOCH];
+                clear_other_map(r.mbits0, r.ctl, par, r.job.clear_words, bid * NT + (int)threadIdx.x, r.job.nblk * NT);
+            }
+            return await_arrivals(r.ctl, busy(r.cand_count), limited, r.job.patience, s_word) &&
+                   stage_own_block<NT>(r.job, bid, reinterpret_cast<uint64_t*>(lds), s_word,
+                                       [&](long i, long step, long nw, uint64_t (&w)[2]) { return map_words2(r.mbits0, par, i, step, nw, w); });
+        },
+        [&]() {
+            const ListedArgs<T> r = launch_arguments<ListedArgs<T>>();
+            return unclaimed_block<NT>(r.job, busy(r.cand_count), (unsigned)r.ctl[CTL_FRAME] + 1u, bid, reinterpret_cast<int*>(s_word));
+        },
+        [&](int b) {
+            const ListedArgs<T> r = launch_arguments<ListedArgs<T>>();
+            const int frame = r.ctl[CTL_FRAME];
+            if (take_block(r.job, r.ctl, b, (unsigned)frame + 1u, s_word))
+                detect_listed_taken<T, PLC, NT>(r.x, r.S, r.S2, r.mbits0, r.ctl, r.cand, *r.cand_count, r.C, r.Cpx, r.P, r.W, r.tau, r.flags, r.pool_w, r.cand_W, b, blocks, frame & 1);
+        },
+        [&]() {
+            const ListedArgs<T> r = launch_arguments<ListedArgs<T>>();
+            extract_own_block<NT>(r.job, r.ctl, bid, reinterpret_cast<const uint64_t*>(lds), epoch, reinterpret_cast<unsigned*>(lds + MAP_STAGE * 8), true);
+        });
 }
 
 template <typename T>
@@ -921,13 +1103,15 @@ hipError_t launch_listed_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbi
     // workgroup, so that a few hundred candidates already spread over the chip
     auto run = [&](auto cs, auto plc) {
         constexpr int CS = decltype(cs)::value, PLC = decltype(plc)::value;
-        const unsigned grid = (unsigned)std::min(2048, (cand_cap + PLC - 1) / PLC);
+        const unsigned grid = (unsigned)std::min(LISTED_BLOCKS, (cand_cap + PLC - 1) / PLC);
         const bool sh = S2 != nullptr && g.C >= 16 && (g.C & (g.C - 1)) == 0;
         if (job && (job->per = extract_words(job->g, CS * PLC)) > 0) job->nblk = (job->g.Ho * job->g.WWo - 1) / (CS * PLC / 64 * job->per) + 1;
+        if (job && job->ahead) job->ahead = job->nblk;
+        if (job) job->nclaims = (int)grid;
 #define CB_LISTED(SH)                                                                                                            \
     if (job && job->nblk)                                                                                                        \
-        hipLaunchKernelGGL((detect_listed_extract_kernel<T, CS, PLC, SH>), dim3(grid + (unsigned)job->nblk), dim3(CS * PLC), 0, st, x, S, S2, mbits, \
-                           ctl, cand, cand_count, cand_cap, g.C, g.Cs, g.P, g.W, tau, flags, pool_w, cand_W, *job);              \
+        hipLaunchKernelGGL((detect_listed_extract_kernel<T, CS, PLC, SH>), dim3(grid + (unsigned)job->nblk), dim3(CS * PLC), 0, st, \
+                           ListedArgs<T>{x, S, S2, mbits, ctl, cand, cand_count, cand_cap, g.C, g.Cs, g.P, g.W, tau, flags, pool_w, cand_W, 0, *job}); \
     else                                                                                                                         \
         CB_LAUNCH((detect_listed_kernel<T, CS, PLC, SH>), dim3(grid), dim3(CS * PLC), st, tm, x, S, S2, mbits, ctl, cand, cand_count, \
                   cand_cap, g.C, g.Cs, g.P, g.W, tau, flags, pool_w, cand_W)
@@ -1011,6 +1195,10 @@ hipError_t launch_detect(const Geom& g, const void* x, void* S, void* S2, uint64
 }
 
 size_t detect_mail_bytes(const Geom& g) { return ((size_t)g.P + 63) / 64 * (g.P < 8192 ? 32 : 16); }
+
+// a word for each of: 64 pixels (a workgroup of one pixel a lane, or a wavefront of one that has one channel group), 16 of small maps, 2 048 workgroups of
+// detection at listed pixels
+size_t detect_claim_bytes(const Geom& g) { return 4 * (size_t)claim_words(std::max(((unsigned)g.P + 63u) / 64u, (unsigned)LISTED_BLOCKS)); }
 
 // (at least 64 words a workgroup)
 size_t detect_look_bytes(const Geom& g) { return ((size_t)g.Ho * g.WWo / 64 + 1) * 8; }

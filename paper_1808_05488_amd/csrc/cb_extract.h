@@ -1,6 +1,7 @@
 // Device functions of the dilation (Sec. III-A Eq. 4) and of the index extraction ("Change Indexes Extraction") that more than one
 // kernel runs: the kernels of cb_compact.hip, and the fused kernel, whose first workgroups can extract the next layer's list.
 #pragma once
+#include "cb_claim.h"
 #include "cb_kernels.h"
 
 namespace cb {
@@ -277,6 +278,30 @@ __device__ __forceinline__ uint64_t full_word(const Geom& g, int it)
 // read from memory.
 constexpr int MAP_STAGE = 2048, MAP_STAGE_SMALL = 4608;
 
+// The end of a frame's extraction, by one thread, when nobody of the launch reads the epoch, the frame count or the arrivals any more.
+__device__ __forceinline__ void finish_frame(int* ctl, unsigned epoch, int own_map, bool arrivals)
+{
+    ctl[CTL_DONE] = 0;
+    ctl[CTL_EPOCH] = (int)epoch;
+    if (arrivals)
+#pragma unroll 1
+        for (int q = 0; q < ARRIVE_SLOTS; ++q) ctl[CTL_ARRIVE + q * NIN_STRIDE] = 0;
+    if (own_map) ctl[CTL_FRAME] = ctl[CTL_FRAME] + 1;
+}
+// epoch of the launch that follows the one of epoch `last` (0 is what never-written slots hold)
+__device__ __forceinline__ unsigned next_epoch(unsigned last) { return last + 1u ? last + 1u : 1u; }
+
+// atomics of cb_claim.h, past the caches of an XCD
+struct DeviceMem {
+    __device__ __forceinline__ unsigned exchange(unsigned* p, unsigned v) const { return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ int add(int* p, int v) const
+    {
+        int old = __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("" : "+v"(old) :: "memory");            // it has returned
+        return old;
+    }
+};
+
 // The second half of the single-pass extraction, for workgroup bid of nblk: scan over the workgroups' words and index write.
 // word: this thread's word of the dilated map, pixbase the pixel of its bit 0; epoch_ld (thread 0): CTL_EPOCH as it was at launch;
 // recount(b): the set bits in workgroup b's 256 words, from the input map alone; small: LDS, ONE_PASS_SMALL words.
@@ -295,7 +320,7 @@ __device__ __forceinline__ void one_pass_tail(uint64_t word, int pixbase, unsign
     const int cnt = __popcll(word);
     const int inc = wave_inclusive_scan(cnt);                  // inclusive scan inside the wavefront
     if (lane == 63) wtot[wv] = inc;
-    if (tid == 0) s_epoch = epoch_ld + 1u ? epoch_ld + 1u : 1u;   // 0 is what never-written slots hold
+    if (tid == 0) s_epoch = next_epoch(epoch_ld);
     __syncthreads();
     const unsigned epoch = s_epoch;
     if (tid == 0) {
@@ -334,15 +359,7 @@ __device__ __forceinline__ void one_pass_tail(uint64_t word, int pixbase, unsign
 
     expand_words<false>(word, off, pixbase, idx, lane);
 
-    if (tid == 0) {
-        if (atomicAdd(&ctl[CTL_DONE], 1) == nblk - 1) {      // everybody has read the epoch and the frame count
-            ctl[CTL_DONE] = 0;
-            ctl[CTL_EPOCH] = (int)epoch;
-            if (arrivals)
-                for (int q = 0; q < ARRIVE_SLOTS; ++q) ctl[CTL_ARRIVE + q * NIN_STRIDE] = 0;
-            if (own_map) ctl[CTL_FRAME] = ctl[CTL_FRAME] + 1;
-        }
-    }
+    if (tid == 0 && extraction_done(DeviceMem(), &ctl[CTL_DONE], nblk)) finish_frame(ctl, epoch, own_map, arrivals);
 }
 
 // Word wi (row-padded) of the 2 x 2 pooled map of a producer's row-padded dilated map: OR over the windows, border windows clipped.
@@ -409,8 +426,8 @@ __device__ __forceinline__ void mail_put(uint64_t* mail, long unit, unsigned tag
 {
     __hip_atomic_store(reinterpret_cast<unsigned long long*>(mail) + unit, ((unsigned long long)tag << 32) | bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// words i and i + step of the map (those from nwords on are 0), from UPW units each; waits for them
-template <int UPW> __device__ __forceinline__ void mail_words(const uint64_t* mail, long i, long step, long nwords, unsigned tag, uint64_t (&w)[2])
+// words i and i + step of the map (those from nwords on are 0), from UPW units each; waits for them (limited: for as many polls as are left)
+template <int UPW> __device__ __forceinline__ bool mail_words(const uint64_t* mail, long i, long step, long nwords, unsigned tag, uint64_t (&w)[2], bool limited, int& polls)
 {
     unsigned long long v[2][UPW];
     for (;;) {
@@ -427,6 +444,7 @@ template <int UPW> __device__ __forceinline__ void mail_words(const uint64_t* ma
 #pragma unroll
             for (int u = 0; u < UPW; ++u) all = all && (unsigned)(v[k][u] >> 32) == tag;
         if (all) break;
+        if (limited && --polls < 0) return false;
         __builtin_amdgcn_s_sleep(1);
     }
 #pragma unroll
@@ -436,23 +454,20 @@ template <int UPW> __device__ __forceinline__ void mail_words(const uint64_t* ma
         for (int u = 0; u < UPW; ++u) w[k] |= (uint64_t)(unsigned)v[k][u] << (64 / UPW * u);
         if (i + k * step >= nwords) w[k] = 0;
     }
+    return true;
 }
 
-// Workgroup bid of job.nblk (NT threads) of an extraction inside the launch that detects the changes.  A wavefront has job.per words of
-// the dilated map, 16 where there are few: dense words are expanded one after the other, and a part of a map that is waited for should be small.  par: of this frame; lds:
-// MAP_STAGE words and one_pass_small 32-bit words.  Strides 1 and 2 (extract_words in cb_detect.hip).  Every wait ends: a detecting workgroup waits for nothing, an
-// extracting one for detecting ones and extracting ones before it, and all extracting workgroups together fill at most half of
-// the chip, so that none of the others can be kept from starting, whatever the order in which they are dispatched.
-// fetch2(i, step, nwords, w): words i < nwords and i + step of the map, once they are complete.
+// The extraction inside the launch of detection, workgroup bid of job.nblk (NT threads).  A wavefront has job.per words of
+// the dilated map, 16 where there are few: dense words are expanded one after the other, and a part of a map that is waited for should be
+// small.  Strides 1 and 2 (extract_words in cb_detect.hip).
+// First: the part of the input map that its words are made from, into lds (MAP_STAGE words), complete.  fetch2(i, step, nwords, w): words i < nwords and
+// i + step of the map, or false if they did not come in time; then so is the result, in all threads.  s_short: a word of LDS of its own.
 template <int NT, typename FETCH>
-__device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __restrict__ ctl, uint64_t* maps, int par, int bid, uint64_t* lds, bool arrivals, FETCH&& fetch2)
+__device__ __forceinline__ bool stage_own_block(const DetectJob& job, int bid, uint64_t* lds, unsigned* s_short, FETCH&& fetch2)
 {
     const Geom& g = job.g;
-    const int tid = threadIdx.x, lane = tid & 63, items = g.Ho * g.WWo, nwords = (g.P + 63) / 64;
+    const int tid = threadIdx.x, items = g.Ho * g.WWo, nwords = (g.P + 63) / 64;
     const int ipb = NT / 64 * job.per, it0 = bid * ipb;                  // words of a workgroup, its first
-    const int it = lane < job.per ? it0 + (tid >> 6) * job.per + lane : items;
-    const unsigned epoch_ld = tid == 0 ? (unsigned)ctl[CTL_EPOCH] : 0u;
-    clear_other_map(maps, ctl, par, job.clear_words, bid * NT + tid, job.nblk * NT);
     // The input rows under this workgroup's words, and those between them and the next workgroup's, so that together the workgroups wait for
     // every word: then all that detect have read the frame count and the last count of listed pixels, which the tail overwrites.
     const int last = (it0 + ipb < items ? it0 + ipb : items) - 1;
@@ -463,13 +478,30 @@ __device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __r
     r1 = r1 < 0 ? 0 : (r1 > g.H - 1 ? g.H - 1 : r1);
     const long first = ((long)r0 * g.W) >> 6;
     const int n = (int)(((((long)r1 * g.W + g.W - 1) >> 6) + 3) - first);
-    for (int i = tid; i < n; i += 2 * NT) {
+    if (tid == 0) *s_short = 0;
+    __syncthreads();
+    bool all = true;
+    for (int i = tid; i < n && all; i += 2 * NT) {
         uint64_t w[2] = {0, 0};
-        if (first + i < nwords) fetch2(first + i, (long)NT, (long)nwords, w);
+        if (first + i < nwords) all = fetch2(first + i, (long)NT, (long)nwords, w);
         lds[i] = w[0];
         if (i + NT < n) lds[i + NT] = w[1];
     }
+    if (!all) *s_short = 1;
     __syncthreads();
+    return *s_short == 0;
+}
+// Then: its words, and its part of the list.  epoch_ld (thread 0): CTL_EPOCH; small: one_pass_small 32-bit words of LDS.
+template <int NT>
+__device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __restrict__ ctl, int bid, const uint64_t* lds, unsigned epoch_ld, unsigned* small, bool arrivals)
+{
+    const Geom& g = job.g;
+    const int tid = threadIdx.x, lane = tid & 63, items = g.Ho * g.WWo;
+    const int ipb = NT / 64 * job.per, it0 = bid * ipb;
+    const int it = lane < job.per ? it0 + (tid >> 6) * job.per + lane : items;
+    int r0 = (it0 / g.WWo) * g.s - g.p;                                  // (as in stage_own_block)
+    r0 = r0 < 0 ? 0 : (r0 > g.H - 1 ? g.H - 1 : r0);
+    const long first = ((long)r0 * g.W) >> 6;
     const int yo = it / g.WWo, wo = it - yo * g.WWo;
     uint64_t word = 0;
     int pixbase = 0;
@@ -487,8 +519,64 @@ __device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __r
         job.mt_bits[it] = word;
         pixbase = yo * g.Wo + 64 * wo;
     }
-    one_pass_tail<NT / 64>(word, pixbase, epoch_ld, job.idx, ctl, job.look, 1, bid, job.nblk, 0x7FFFFFFF,
-                           reinterpret_cast<unsigned*>(lds + MAP_STAGE), [](int) { return 0; }, arrivals);
+    one_pass_tail<NT / 64>(word, pixbase, epoch_ld, job.idx, ctl, job.look, 1, bid, job.nblk, 0x7FFFFFFF, small, [](int) { return 0; }, arrivals);
+}
+
+// Some block among the first n that nobody has claimed in this frame, in all threads of the workgroup, or -1; each workgroup looks from a place of its own on.
+// s_found: a word of LDS of its own.
+template <int NT> __device__ __forceinline__ int unclaimed_block(const DetectJob& job, int n, unsigned tag, int bid, int* s_found)
+{
+    const int from = (int)((long)n * bid / job.nblk);
+    for (int i = 0; i < n; i += NT) {
+        if (threadIdx.x == 0) *s_found = n;
+        __syncthreads();
+        const int o = i + (int)threadIdx.x, c = from + o < n ? from + o : from + o - n;
+        if (o < n && __hip_atomic_load(job.claims + claim_index((unsigned)c, (unsigned)job.nclaims), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != tag) atomicMin(s_found, o);
+        __syncthreads();
+        const int found = *s_found;
+        __syncthreads();
+        if (found < n) return __builtin_amdgcn_readfirstlane(from + found < n ? from + found : from + found - n);
+    }
+    return -1;
+}
+
+// The arguments of a kernel whose only parameter is an A, loaded once more where this is called: what only a rare path needs need not be held in registers on
+// the way there.
+template <typename A> __device__ __forceinline__ A launch_arguments()
+{
+    typedef const __attribute__((address_space(4))) unsigned* words;
+    words p = (words)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    static_assert(sizeof(A) % 4 == 0, "whole words");
+    unsigned w[sizeof(A) / 4];
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(A) / 4; ++i) w[i] = p[i];
+    A a;
+    __builtin_memcpy(&a, w, sizeof(A));
+    return a;
+}
+
+// What workgroup number blockIdx.x does: extracts, as number bid, or (bid < 0) detects, as number own of n.
+struct Role { int bid, own, n; };
+__device__ __forceinline__ Role role_of(const DetectJob& job)
+{
+    const int n = (int)gridDim.x - job.nblk, own = (int)blockIdx.x - job.ahead;
+    return Role{own < 0 ? (int)blockIdx.x : own >= n ? own - n : -1, own, n};
+}
+
+// Claims a block for a workgroup other than its own: whether it has it now, in all threads.  s_word: a word of LDS of its own.
+__device__ __forceinline__ bool take_block(const DetectJob& job, int* ctl, int b, unsigned tag, unsigned* s_word)
+{
+    if (threadIdx.x == 0) {
+        const bool lost = claim_block(DeviceMem(), job.claims + claim_index((unsigned)b, (unsigned)job.nclaims), tag, &ctl[CTL_DONE], true) == tag;
+        if (lost) claim_lost(DeviceMem(), &ctl[CTL_DONE], job.nblk);         // (never the end of the frame: this workgroup is not through)
+        else atomicAdd(&ctl[CTL_RECOUNTS], 1);
+        *s_word = lost ? 1u : 0u;
+    }
+    __syncthreads();
+    const bool mine = *s_word == 0;
+    __syncthreads();
+    return mine;
 }
 
 // Detection at listed pixels sets single bits of a cleared map with atomics, which are complete when their old value has come back; a workgroup
@@ -500,20 +588,25 @@ __device__ __forceinline__ void arrive(int* ctl, unsigned b)
     asm volatile("" ::: "memory");
     __hip_atomic_fetch_add(ctl + CTL_ARRIVE + (b % ARRIVE_SLOTS) * NIN_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// called by whole workgroups: waits for `expected` workgroups
-__device__ __forceinline__ void await_arrivals(const int* ctl, int expected)
+// called by whole workgroups: waits for `expected` workgroups (limited: so many polls, then false); s_short: a word of LDS of its own
+__device__ __forceinline__ bool await_arrivals(const int* ctl, int expected, bool limited, int polls, unsigned* s_short)
 {
     const int lane = threadIdx.x & 63;
     if (threadIdx.x < 64)
         for (;;) {
             const int n = lane < ARRIVE_SLOTS ? __hip_atomic_load(ctl + CTL_ARRIVE + lane * NIN_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-            if (wave_sum(n) >= expected) break;
+            const bool all = wave_sum(n) >= expected, stop = all || (limited && --polls < 0);
+            if (stop && lane == 0) *s_short = all ? 0u : 1u;
+            if (stop) break;
             __builtin_amdgcn_s_sleep(1);
         }
     __syncthreads();
+    const bool all = *s_short == 0;
+    __syncthreads();
+    return all;
 }
 // words i and i + step of the map of parity par (interleaved with the other one), past the caches that do not see other XCDs' atomics
-__device__ __forceinline__ void map_words2(const uint64_t* maps, int par, long i, long step, long nwords, uint64_t (&w)[2])
+__device__ __forceinline__ bool map_words2(const uint64_t* maps, int par, long i, long step, long nwords, uint64_t (&w)[2])
 {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -521,6 +614,7 @@ __device__ __forceinline__ void map_words2(const uint64_t* maps, int par, long i
         w[k] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(maps) + 2 * wi + par, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (i + step >= nwords) w[1] = 0;
+    return true;
 }
 
 }  // namespace

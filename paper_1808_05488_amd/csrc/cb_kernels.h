@@ -39,11 +39,11 @@ enum Ctl {
     CTL_LD = 3,        // leading dimension of X'/Y' of the last chunk
     CTL_NCOLS = 4,     // columns of the last chunk
     CTL_NSPLIT = 5,    // k-splits (partial products stacked in Y') of the last chunk
-    CTL_DONE = 7,      // single-pass dilate + compact: workgroups that have finished
+    CTL_DONE = 7,      // single-pass dilate + compact: workgroups that have finished (inside the launch of detection: `done` of cb_claim.h)
     CTL_EPOCH = 8,     //   epoch of the last completed launch
     CTL_FRAME = 10,    // frames processed by a layer that detects its own changes: its parity selects the input-map
                        //   buffer and the changed-pixel counter of the frame (advanced by the index extraction)
-    CTL_RECOUNTS = 9,  //   predecessor counts a workgroup recomputed itself after its bounded wait ran out
+    CTL_RECOUNTS = 9,  //   predecessor counts a workgroup recomputed itself after its bounded wait ran out, blocks of detection it took
     CTL_SLOTS = 64,
     // Behind the slots: the changed-input counters, NIN_SLOTS pairs (even / odd frames) on lines of their own; their sum is the
     // count.  Every wavefront of change detection that found something adds to one of them: to a single counter these
@@ -81,16 +81,21 @@ struct ExtractJob {
 // ... for maps whose part under one workgroup's words fits its LDS, and of few enough workgroups to be resident at once beside the product's
 bool extract_fits(const Geom& consumer);
 
-// Index extraction of a layer that detects its own changes, by the last workgroups of the launch that detects them.
+// Index extraction of a layer that detects its own changes, by the last workgroups of the launch that detects them (cb_claim.h).
 struct DetectJob {
     Geom g;
     int nblk = 0, per = 0, full = 0, clear_words = 0;
-    uint64_t* mail = nullptr;              // detect_mail_bytes(g), zero-initialised, of the layer's own
+    int patience = 0;                      // polls of a workgroup that waits before it detects what no workgroup has begun
+    int ahead = 0;                         // for tests: extracting workgroups numbered before those that detect, of which those of large maps have not all begun then
+    int nclaims = 0;                       // blocks of detection that are claimed (cb_claim.h)
+    unsigned* claims = nullptr;            // detect_claim_bytes(g), zero-initialised, of the layer's own
+    uint64_t* mail = nullptr;              // detect_mail_bytes(g), likewise
     uint64_t* mt_bits = nullptr;
     int32_t* idx = nullptr;
     unsigned long long* look = nullptr;
 };
 size_t detect_mail_bytes(const Geom& g);
+size_t detect_claim_bytes(const Geom& g);
 size_t detect_look_bytes(const Geom& g);   // of the counts that its workgroups publish
 
 // flags for detect

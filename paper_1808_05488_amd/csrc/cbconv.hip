@@ -24,6 +24,8 @@ thread_local int g_last_hip = 0;
 // polls of a predecessor's count in the single-pass index extraction before the count is recomputed
 constexpr int kScanWaitDefault = 1 << 20;
 std::atomic<int> g_scan_wait_limit{kScanWaitDefault};
+// polls (about a microsecond each) of a workgroup that waits for detection in its own launch before it detects what no workgroup has begun
+constexpr int kPatience = 4096;
 
 inline int hip_fail(hipError_t e) { g_last_hip = (int)e; return CB_EHIP; }
 #define CB_HIP(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return hip_fail(e_); } while (0)
@@ -31,7 +33,7 @@ inline int hip_fail(hipError_t e) { g_last_hip = (int)e; return CB_EHIP; }
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct StateLayout {
-    size_t S, S2, OUT, OUT2, mbits, mail, mtbits, idx, ctl, look, kcount, KT, bias, m_u8, mt_u8, KF, rowtab, total;
+    size_t S, S2, OUT, OUT2, mbits, mail, claims, mtbits, idx, ctl, look, kcount, KT, bias, m_u8, mt_u8, KF, rowtab, total;
 };
 
 struct ScratchLayout {
@@ -125,6 +127,7 @@ StateLayout state_layout(const cb_layer_desc* d, const cb::Geom& g)
     L.OUT2 = o;   o += d->keep_output_channel_last ? align256((size_t)g.O * g.Po * b) : 0;
     L.mbits = o;  o += align256(((size_t)(g.P + 63) / 64 + 4) * 16);  // two maps, word-interleaved: frames alternate between them
     L.mail = o;   o += d->mode == CB_PROPAGATE ? 0 : align256(cb::detect_mail_bytes(g));
+    L.claims = o; o += d->mode == CB_PROPAGATE ? 0 : align256(cb::detect_claim_bytes(g));
     L.mtbits = o; o += align256(((size_t)g.Ho * g.WWo + 4) * 8);
     L.idx = o;    o += align256((size_t)g.Po * 4);
     L.ctl = o;    o += align256(cb::CTL_WORDS * 4);
@@ -219,6 +222,7 @@ struct cb_layer {
     // one is cleared for the next frame)
     uint64_t* mbits() const { return (uint64_t*)(state + sl.mbits); }
     uint64_t* mail() const { return (uint64_t*)(state + sl.mail); }
+    unsigned* claims() const { return (unsigned*)(state + sl.claims); }
     int mbits_words() const { return (g.P + 63) / 64; }
     uint64_t* mtbits() const { return (uint64_t*)(state + sl.mtbits); }
     int32_t* idx() const { return (int32_t*)(state + sl.idx); }
@@ -368,13 +372,16 @@ int detect_and_update(cb_layer* L, const void* input_dev, float tau, const int32
     else if (L->d.mode == CB_FEED_FORWARD) flags = cb::DET_COPY_ALL;
     if ((size_t)L->g.C * L->g.P * (L->g.bf16 ? 2 : 4) >= kStateBeyondCache) flags |= cb::DET_STREAM_STATE;
     bool extracted = false;      // the index list comes with detection
-    // (per-step times and a wait limit of the caller's are those of the launches one by one)
-    const bool together = !L->timing && g_scan_wait_limit.load(std::memory_order_relaxed) == kScanWaitDefault;
+    // (per-step times are those of the launches one by one, and a wait limit of 0 is none that one workgroup would wait for another in)
+    const int wait_limit = g_scan_wait_limit.load(std::memory_order_relaxed);
+    const bool together = !L->timing && wait_limit > 0;
     cb::DetectJob job;
     job.g = L->g;
     job.full = L->primed ? 0 : 1;
     job.clear_words = L->mbits_words();
-    job.mail = L->mail(); job.mt_bits = L->mtbits(); job.idx = L->idx();
+    job.patience = std::min(wait_limit, kPatience);
+    job.ahead = wait_limit != kScanWaitDefault;
+    job.mail = L->mail(); job.claims = L->claims(); job.mt_bits = L->mtbits(); job.idx = L->idx();
     job.look = reinterpret_cast<unsigned long long*>(L->look());
     if (cand && together)
         CB_HIP(cb::launch_detect_listed_extract(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau, flags, cand, cand_count,

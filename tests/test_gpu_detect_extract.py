@@ -110,3 +110,102 @@ def test_chained_layers(widths, bf16):
                 assert torch.equal(oo, orf), (widths, t)
     finally:
         cb.cb_set_scan_wait_limit(1 << 20)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("geom", GEOMS)
+def test_blocks_taken_by_workgroups_that_wait(geom, bf16):
+    """With a wait limit of one poll the workgroups that extract are numbered first and detect themselves what no other has begun: the same maps, lists,
+    states and outputs."""
+    C, O, k, s, pad, H, W = geom
+    print("taken blocks", geom, bf16, flush=True)
+    spec, frames = syn.random_layer_case(C + H, C, O, k, s, pad, H, W, 5, change_prob=0.03)
+    p = Pair(spec, H, W, bf16=bf16)
+    q = Pair(spec, H, W, bf16=bf16, feed_forward=True)
+    try:
+        for t, f in enumerate(frames):
+            cb.cb_set_scan_wait_limit(1 if t != 3 else 1 << 20)
+            p.step(f, 0.02, tag=f"{geom} frame {t}")
+            q.step(f, 0.02, tag=f"feed-forward {geom} frame {t}")
+    finally:
+        cb.cb_set_scan_wait_limit(1 << 20)
+    if (C, H) in ((2, 1300), (33, 400)) and not (bf16 and C == 33):      # (more workgroups than begin at once)
+        assert p.g.stats()["scan_recounts"] > 0
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("widths", [(3, 5, 4), (16, 32, 20), (8, 100, 6), (4, 128, 6), (6, 200, 5), (3, 256, 4), (5, 300, 3)])
+def test_listed_blocks_taken_by_workgroups_that_wait(widths, bf16):
+    """Detection at listed pixels likewise, directly and through a pooling stage, against detection of everything."""
+    c, mid, o = widths
+    print("taken listed blocks", widths, bf16, flush=True)
+    H, W = 301, 403
+    rng = np.random.default_rng(mid)
+    mk = lambda n, m, k: to_dev((rng.standard_normal((n, m, k, k)) * np.sqrt(2.0 / (m * k * k))).astype(np.float32), bf16)
+    w0, w1, w2 = mk(mid, c, 3), mk(o, mid, 3), mk(o, mid, 5)
+    first = cb.Layer(w0, None, 1, 1, H, W, True)
+    pool = cb.Pool(first, 2)
+    direct = [cb.Layer(w1, None, 2, 1, H, W, True) for _ in range(2)]
+    pooled = [cb.Layer(w2, None, 1, 2, pool.Hp, pool.Wp, False) for _ in range(2)]
+    _, frames = syn.random_layer_case(mid, c, 1, 1, 1, 0, H, W, 7, change_prob=0.02, noise_std=0.003)
+    frames[2] = frames[1]
+    frames[4] = frames[3] + 1.0
+    try:
+        for t, f in enumerate(frames):
+            cb.cb_set_scan_wait_limit(1 << 20)
+            x = first.process_frame(to_dev(f, bf16), 0.02)
+            y = pool.process()
+            direct[1].process_frame(x, 0.02)
+            pooled[1].process_frame(y, 0.02)
+            cb.cb_set_scan_wait_limit(1 if t != 5 else 1 << 20)
+            direct[0].process_frame_chained(x, first, 0.02)
+            pooled[0].process_frame_chained(y, pool, 0.02)
+            for a, b in (direct, pooled):
+                for u, v in zip(a.changes_host(), b.changes_host()):
+                    assert np.array_equal(u, v), (widths, t)
+                assert a.stats()["n_changed_in"] == b.stats()["n_changed_in"], (widths, t)
+                assert torch.equal(a.state(), b.state()), (widths, t)
+                assert torch.equal(a.export_state()[1], b.export_state()[1]), (widths, t)
+    finally:
+        cb.cb_set_scan_wait_limit(1 << 20)
+    if mid >= 200:                                              # (more workgroups than begin at once)
+        assert direct[0].stats()["scan_recounts"] > 0
+
+
+@pytest.mark.parametrize("limit", [1, 1 << 20])
+def test_layers_on_several_streams_at_once(limit):
+    """Frames of four layers on streams of their own, nothing waiting between them, against the same layers one after the other."""
+    C, H, W = 33, 300, 400
+    rng = np.random.default_rng(8)
+    w = to_dev((rng.standard_normal((4, C, 3, 3)) / 17).astype(np.float32), False)
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    cases = [[to_dev(f, False) for f in syn.random_layer_case(20 + i, C, 4, 3, 1, 1, H, W, 6, change_prob=0.02)[1]] for i in range(4)]
+    torch.cuda.synchronize()
+
+    def build():
+        layers = []
+        for s in streams:
+            with torch.cuda.stream(s):
+                layers.append(cb.Layer(w, None, 1, 1, H, W, True))
+        return layers
+
+    a, b = build(), build()
+    cb.cb_set_scan_wait_limit(limit)
+    try:
+        for t in range(6):
+            for i in range(4):
+                with torch.cuda.stream(streams[i]):
+                    a[i].process_frame(cases[i][t], 0.02)
+        torch.cuda.synchronize()
+    finally:
+        cb.cb_set_scan_wait_limit(1 << 20)
+    for i in range(4):
+        with torch.cuda.stream(streams[i]):
+            for f in cases[i]:
+                out = b[i].process_frame(f, 0.02)
+            torch.cuda.synchronize()
+            for u, v in zip(a[i].changes_host(), b[i].changes_host()):
+                assert np.array_equal(u, v)
+            (sa, oa), (sb, ob) = a[i].export_state(), b[i].export_state()
+            torch.cuda.synchronize()
+            assert torch.equal(sa, sb) and torch.equal(oa, ob)
