@@ -42,6 +42,10 @@ template <typename MEM, typename D> CB_HD bool claim_lost(MEM&& mem, D* done, in
 // an extracting workgroup is through: true if the frame is over
 template <typename MEM, typename D> CB_HD bool extraction_done(MEM&& mem, D* done, int extracting) { return mem.add(done, 1) == extracting - 1; }
 
+// The number of an extracting workgroup, in the order in which they begin: it waits, without a limit, for what those with lower numbers publish, and each publishes
+// before it waits for any of them.
+template <typename MEM, typename D> CB_HD int extraction_number(MEM&& mem, D* begun) { return mem.add(begun, 1); }
+
 // One workgroup, all of its threads together.  extracts: its role, by number; detect(): claims its block of detection and does it; unclaimed(): some block
 // that nobody has claimed, -1: none; take(block): claims it and does it; await(limited): until what this workgroup extracts from is there, or (limited) until
 // its patience runs out: false.

@@ -577,16 +577,17 @@ void detect_extract_kernel(const DetectArgs<T> a)
     unsigned* const s_word = reinterpret_cast<unsigned*>(lds + USED);            // (behind both uses of the LDS)
     const DetectJob& job = a.job;
     const Role role = role_of(job);
-    const int bid = role.bid;
+    int bid = 0;
     unsigned epoch = 0;
     detect_or_extract(
-        bid >= 0,
+        role.extracts,
         [&]() {
             detect_reg_block<T, VEC, CS, CPT, PLX, SH, true>(a.x, a.S, a.S2, a.mbits0, a.ctl, a.C, a.Cs, a.inv_per, a.P, a.nwords, a.tau, a.flags, a.stream, &job, (unsigned)role.own, lds);
         },
         [&](bool limited) {
             const int frame = a.ctl[CTL_FRAME];
             if (limited) {
+                bid = begin_extraction(a.ctl, s_word);
                 if (threadIdx.x == 0) epoch = (unsigned)a.ctl[CTL_EPOCH];
                 clear_other_map(a.mbits0, a.ctl, frame & 1, job.clear_words, bid * NT + (int)threadIdx.x, job.nblk * NT);
             }
@@ -1055,14 +1056,15 @@ __global__ __launch_bounds__(CS * PLC) void detect_listed_extract_kernel(const L
     __shared__ __align__(16) char lds[USED + 16];
     unsigned* const s_word = reinterpret_cast<unsigned*>(lds + USED);
     const Role role = role_of(a.job);
-    const int blocks = role.n, bid = role.bid;
+    const int blocks = role.n;
+    int bid = 0;
     auto busy = [&](const int* count) {
         const int want = (*count + PLC - 1) / PLC;
         return want < blocks ? want : blocks;
     };
     unsigned epoch = 0;
     detect_or_extract(
-        bid >= 0,
+        role.extracts,
         [&]() {
             detect_listed_block<T, CS, PLC, SH, true>(a.x, a.S, a.S2, a.mbits0, a.ctl, a.cand, a.cand_count, a.cand_cap, a.C, a.Cpx, a.P, a.W, a.tau, a.flags, a.pool_w, a.cand_W,
                                                      role.own, blocks, &a.job, lds);
@@ -1071,6 +1073,7 @@ __global__ __launch_bounds__(CS * PLC) void detect_listed_extract_kernel(const L
             const ListedArgs<T> r = launch_arguments<ListedArgs<T>>();
             const int par = r.ctl[CTL_FRAME] & 1;
             if (limited) {
+                bid = begin_extraction(r.ctl, s_word);
                 if (threadIdx.x == 0) epoch = (unsigned)r.ctl[CTL_EPOCH];
                 clear_other_map(r.mbits0, r.ctl, par, r.job.clear_words, bid * NT + (int)threadIdx.x, r.job.nblk * NT);
             }

@@ -282,6 +282,7 @@ constexpr int MAP_STAGE = 2048, MAP_STAGE_SMALL = 4608;
 __device__ __forceinline__ void finish_frame(int* ctl, unsigned epoch, int own_map, bool arrivals)
 {
     ctl[CTL_DONE] = 0;
+    ctl[CTL_BEGUN] = 0;
     ctl[CTL_EPOCH] = (int)epoch;
     if (arrivals)
 #pragma unroll 1
@@ -305,10 +306,11 @@ struct DeviceMem {
 // The second half of the single-pass extraction, for workgroup bid of nblk: scan over the workgroups' words and index write.
 // word: this thread's word of the dilated map, pixbase the pixel of its bit 0; epoch_ld (thread 0): CTL_EPOCH as it was at launch;
 // recount(b): the set bits in workgroup b's 256 words, from the input map alone; small: LDS, ONE_PASS_SMALL words.
-// NW: wavefronts of a workgroup.
+// NW: wavefronts of a workgroup.  LIMITED: the wait for another workgroup's count ends after spin_limit polls and the count is
+// recomputed; otherwise workgroups of lower numbers have begun (extraction_number in cb_claim.h), and the wait ends with the count.
 template <int NW> __host__ __device__ constexpr int one_pass_small() { return 2 * NW + 1; }
 constexpr int ONE_PASS_SMALL = one_pass_small<4>();
-template <int NW = 4, typename RECOUNT>
+template <int NW = 4, bool LIMITED = true, typename RECOUNT>
 __device__ __forceinline__ void one_pass_tail(uint64_t word, int pixbase, unsigned epoch_ld, int32_t* __restrict__ idx, int* __restrict__ ctl,
                                               unsigned long long* __restrict__ look, int own_map, int bid, int nblk, int spin_limit,
                                               unsigned* small, RECOUNT&& recount, bool arrivals = false)
@@ -338,11 +340,12 @@ __device__ __forceinline__ void one_pass_tail(uint64_t word, int pixbase, unsign
         for (;;) {
             v = __hip_atomic_load(&look[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if ((unsigned)(v >> 32) == epoch) break;
-            if (++spins > spin_limit) {
-                v = (unsigned long long)(unsigned)recount(b);
-                atomicAdd(&ctl[CTL_RECOUNTS], 1);
-                break;
-            }
+            if constexpr (LIMITED)
+                if (++spins > spin_limit) {
+                    v = (unsigned long long)(unsigned)recount(b);
+                    atomicAdd(&ctl[CTL_RECOUNTS], 1);
+                    break;
+                }
             __builtin_amdgcn_s_sleep(1);
         }
         part += (int)(unsigned)v;
@@ -519,7 +522,7 @@ __device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __r
         job.mt_bits[it] = word;
         pixbase = yo * g.Wo + 64 * wo;
     }
-    one_pass_tail<NT / 64>(word, pixbase, epoch_ld, job.idx, ctl, job.look, 1, bid, job.nblk, 0x7FFFFFFF, small, [](int) { return 0; }, arrivals);
+    one_pass_tail<NT / 64, false>(word, pixbase, epoch_ld, job.idx, ctl, job.look, 1, bid, job.nblk, 0, small, [](int) {}, arrivals);
 }
 
 // Some block among the first n that nobody has claimed in this frame, in all threads of the workgroup, or -1; each workgroup looks from a place of its own on.
@@ -556,12 +559,21 @@ template <typename A> __device__ __forceinline__ A launch_arguments()
     return a;
 }
 
-// What workgroup number blockIdx.x does: extracts, as number bid, or (bid < 0) detects, as number own of n.
-struct Role { int bid, own, n; };
+// What workgroup number blockIdx.x does: extracts, or detects, as number own of n.
+struct Role { bool extracts; int own, n; };
 __device__ __forceinline__ Role role_of(const DetectJob& job)
 {
     const int n = (int)gridDim.x - job.nblk, own = (int)blockIdx.x - job.ahead;
-    return Role{own < 0 ? (int)blockIdx.x : own >= n ? own - n : -1, own, n};
+    return Role{own < 0 || own >= n, own, n};
+}
+// An extracting workgroup begins: its number.  s_word: a word of LDS of its own.
+__device__ __forceinline__ int begin_extraction(int* ctl, unsigned* s_word)
+{
+    if (threadIdx.x == 0) *s_word = (unsigned)extraction_number(DeviceMem(), &ctl[CTL_BEGUN]);
+    __syncthreads();
+    const int bid = (int)__builtin_amdgcn_readfirstlane(*s_word);
+    __syncthreads();
+    return bid;
 }
 
 // Claims a block for a workgroup other than its own: whether it has it now, in all threads.  s_word: a word of LDS of its own.

@@ -43,6 +43,7 @@ enum Ctl {
     CTL_EPOCH = 8,     //   epoch of the last completed launch
     CTL_FRAME = 10,    // frames processed by a layer that detects its own changes: its parity selects the input-map
                        //   buffer and the changed-pixel counter of the frame (advanced by the index extraction)
+    CTL_BEGUN = 32,    // extraction inside the launch of detection: workgroups that have begun it (on a line of its own: every workgroup reads the one above)
     CTL_RECOUNTS = 9,  //   predecessor counts a workgroup recomputed itself after its bounded wait ran out, blocks of detection it took
     CTL_SLOTS = 64,
     // Behind the slots: the changed-input counters, NIN_SLOTS pairs (even / odd frames) on lines of their own; their sum is the

@@ -27,10 +27,10 @@ struct Mem {
 struct Stuck {};
 // a layer's device memory
 struct Layer {
-    std::vector<std::atomic<unsigned>> claims, mail;
+    std::vector<std::atomic<unsigned>> claims, mail, counts;
     std::vector<std::atomic<int>> detected;
-    std::atomic<int> done{0}, frame{0}, ended{0}, early{0};
-    explicit Layer(int n) : claims(cb::claim_words(n)), mail(n), detected(n) {}
+    std::atomic<int> begun{0}, done{0}, frame{0}, ended{0}, early{0};
+    Layer(int n, int e) : claims(cb::claim_words(n)), mail(n), counts(e), detected(n) {}
 };
 struct Chip {
     std::mutex m;
@@ -40,16 +40,18 @@ struct Chip {
     void enter() { std::unique_lock<std::mutex> l(m); cv.wait(l, [&] { return places > 0 || stop; }); if (stop) throw Stuck(); --places; }
     void leave() { { std::lock_guard<std::mutex> l(m); ++places; } cv.notify_all(); }
 };
-void workgroup(Layer& L, Chip& chip, int number, int blocks, int extracting, int patience)
+// in_order: extracting workgroups have the numbers in which they begin
+void workgroup(Layer& L, Chip& chip, int number, int blocks, int extracting, int patience, bool in_order)
 {
     Mem mem;
     std::this_thread::yield();
     const unsigned tag = (unsigned)L.frame.load() + 1u;
     auto claim = [&](int b) { return &L.claims[cb::claim_index(b, blocks)]; };
-    auto end = [&]() { L.done = 0; ++L.ended; ++L.frame; };
+    auto end = [&]() { L.done = 0; L.begun = 0; ++L.ended; ++L.frame; };
     auto work = [&](int b) { std::this_thread::yield(); ++L.detected[b]; L.mail[b] = tag; };
+    const int bid = number < blocks ? -1 : in_order ? cb::extraction_number(mem, &L.begun) : number - blocks;
     cb::detect_or_extract(
-        number >= blocks,
+        bid >= 0,
         [&]() {
             if (cb::claim_block(mem, claim(number), tag, &L.done, false) != tag) work(number);
             else if (cb::claim_lost(mem, &L.done, extracting)) end();
@@ -69,18 +71,26 @@ void workgroup(Layer& L, Chip& chip, int number, int blocks, int extracting, int
             if (cb::claim_block(mem, claim(b), tag, &L.done, true) != tag) work(b);
             else if (cb::claim_lost(mem, &L.done, extracting)) ++L.early;       // an extracting workgroup that is not through cannot end the frame
         },
-        [&]() { if (cb::extraction_done(mem, &L.done, extracting)) end(); });
+        [&]() {
+            L.counts[bid] = tag;
+            for (int b = 0; b < bid; ++b)
+                while (L.counts[b] != tag) {
+                    if (chip.stop) throw Stuck();
+                    std::this_thread::yield();
+                }
+            if (cb::extraction_done(mem, &L.done, extracting)) end();
+        });
 }
 }  // namespace
 
 // order: 0 as numbered, 1 extracting workgroups first, 2 any.  Launches (one a layer) of all streams share the places.  0, or what went wrong
-extern "C" int play(int places, int streams, int blocks, int extracting, int frames, int patience, int order, int seed, int seconds)
+extern "C" int play(int places, int streams, int blocks, int extracting, int frames, int patience, int order, int in_order, int seed, int seconds)
 {
     std::mt19937 rng(seed);
     Chip chip;
     chip.places = places;
     std::vector<Layer*> layers;
-    for (int s = 0; s < streams; ++s) layers.push_back(new Layer(blocks));
+    for (int s = 0; s < streams; ++s) layers.push_back(new Layer(blocks, extracting));
     int wrong = 0;
     for (int f = 0; f < frames && !wrong; ++f) {
         std::vector<std::pair<int, int>> wg;
@@ -93,8 +103,8 @@ extern "C" int play(int places, int streams, int blocks, int extracting, int fra
             try {
                 for (auto& w : wg) {
                     chip.enter();
-                    t.emplace_back([&chip, &left, &stuck, &layers, w, blocks, extracting, patience] {
-                        try { workgroup(*layers[w.first], chip, w.second, blocks, extracting, patience); } catch (Stuck&) { ++stuck; }
+                    t.emplace_back([&chip, &left, &stuck, &layers, w, blocks, extracting, patience, in_order] {
+                        try { workgroup(*layers[w.first], chip, w.second, blocks, extracting, patience, in_order); } catch (Stuck&) { ++stuck; }
                         chip.leave();
                         --left;
                     });
@@ -145,13 +155,18 @@ def claims(tmp_path_factory):
 def test_no_launch_gets_stuck(claims, places, streams, blocks, extracting, order):
     for seed in range(4):
         for patience in (0, 1, 50):
-            assert claims.play(places, streams, blocks, extracting, 4, patience, order, seed, 60) == 0, (seed, patience)
+            assert claims.play(places, streams, blocks, extracting, 4, patience, order, 1, seed, 60) == 0, (seed, patience)
 
 
 @pytest.mark.parametrize("places,streams,blocks,extracting", [(4, 1, 9, 4), (8, 2, 20, 6)])
 def test_the_play_sees_workgroups_that_only_wait(claims, places, streams, blocks, extracting):
     """Without an end to its patience a workgroup waits for others that never get a place."""
-    assert claims.play(places, streams, blocks, extracting, 1, -1, 1, 0, 1) & 1
+    assert claims.play(places, streams, blocks, extracting, 1, -1, 1, 1, 0, 1) & 1
+
+
+def test_the_play_sees_workgroups_that_wait_for_later_ones(claims):
+    """Numbered otherwise than they begin, extracting workgroups wait for counts that nobody publishes."""
+    assert claims.play(1, 1, 9, 3, 1, 0, 1, 0, 0, 1) & 1
 
 
 def test_every_block_has_a_word_of_its_own(claims):
