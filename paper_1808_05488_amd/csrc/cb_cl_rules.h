@@ -150,7 +150,13 @@ CB_HD unsigned cl_xcd_rows(unsigned MT, unsigned filter_kb, unsigned pixel_kb)
 // Frames, us, whole / divided: float32 512 -> 512, 3x3, 46x82, 2 % changed 42.6 / 31.5, 10 % 51.7 / 43.9, 30 % 80 / 68; 64 -> 256, 7x7, 120x160, 10 %
 // 52.5 / 48.9; 128 -> 128, 9x9, 60x80 50.1 / 37.4; 256 -> 128 there 141 / 86; bfloat16 256 -> 256, 7x7, 60x80, 20 % 55.6 / 49.2.  Shorter filters
 // are not considered, for which the choice alone took 0.4 us: 256 -> 256, 3x3, 92x164 (72 groups) 29.7 / 30.6; bfloat16 512 -> 512, 3x3, 46x82 (144) 42.3 / 43.0.
+// float32: K is only divided where that rounds the sums no worse than the whole tile.  Relative errors of sums over a K of 4 608 against float64: one
+// chain of products 1.06e-6, two (the small terms in one of their own: up to two tiles a wavefront, and four in parts) 4.1e-7, two in each of four wavefronts
+// that share K 1.9e-7; in p parts they fall with the square root of p.  Without the rule 512 -> 260, 3x3, 46x82, every output: 4.1e-7 whole, 7.4e-7 in
+// two parts of one chain.
 constexpr unsigned CL_SPLIT_NS = 8500, CL_SPLIT_MAX = 8;     // (tiles: at most 256)
+// the fewest parts of one chain (or of two) that are as exact as a whole tile: 0: 64 x 16 and 64 x 32, 1: 16 x 16, 2: 128 x 32 and 128 x 64
+CB_HD unsigned cl_least_parts(int whole, bool two) { return whole == 2 ? 2u : whole == 0 ? (two ? 2u : 7u) : two ? 5u : CL_SPLIT_MAX + 1u; }
 CB_HD bool cl_split_pays(unsigned nkg, bool f32) { return nkg >= (f32 ? 96u : 256u); }
 template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned ws_bytes)
 {
@@ -158,13 +164,14 @@ template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned
     (F32 ? cl_cost<bm, bn>(n, O, nkg, a0, a1, a2, a3) : cl_cost<bm, bn>(n, O, nkg, b0, b1, b2, b3))
     const unsigned a = CB_COST(64, 16, N, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, N, 1000, 300, 1400, 203, 400, 80, 1100, 47),
                    c = CB_COST(128, 32, N, 1800, 380, 1000, 320, 1500, 100, 100, 96), d = CB_COST(128, 64, N, 900, 745, 2900, 510, 2000, 190, 1000, 140),
-                   k = CB_COST(16, 16, N, 100, 94, 1260, 80, 200, 30, 870, 16);
+                   k = CB_COST(16, 16, N, 100, 94, 1260, (O * (unsigned long long)nkg > 700000ull / 32u ? 80 : 49), 200, 30, 870, 16);
 #undef CB_COST
     unsigned best = a < b ? a : b, choice = 0;
     best = best < c ? best : c;
     best = best < d ? best : d;
     best = best < k ? best : k;
     if (best < CL_SPLIT_NS) return 0;
+    const int whole = best == k ? 1 : best == a || best == b ? 0 : 2;        // (of equal ones the most exact)
     // as many parts as make one or two items per compute unit
     const unsigned rows = ((unsigned)O + 127u) / 128u;
     auto consider = [&](unsigned tiles, unsigned flag, unsigned bytes, unsigned l0, unsigned l1, unsigned c0, unsigned c1) {
@@ -174,7 +181,7 @@ template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned
             unsigned p = r ? two : one;
             p = p > CL_SPLIT_MAX ? CL_SPLIT_MAX : p;
             const unsigned g = (nkg + p - 1u) / p;
-            if (p < 2u || g < 8u || tiles * p * bytes > ws_bytes) continue;
+            if (p < (F32 ? cl_least_parts(whole, !flag) : 2u) || g < 8u || tiles * p * bytes > ws_bytes) continue;
             const unsigned lat = l0 + l1 * g, busy = (tiles * p + 255u) / 256u * (c0 + c1 * g), v = (busy > lat ? busy : lat) + CL_SPLIT_NS;
             if (v < best) { best = v; choice = p | flag; }
         }

@@ -205,7 +205,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     constexpr unsigned PLANE = UKG * 64u;        // bytes of one term of a column
     // the largest tile has no registers for what can be fetched when it is used: the next tile's pixels, the bias, a longer ring
     constexpr bool LEAN = TM * TN > 8;
-    constexpr bool TWO = TM * TN < 4;            // second accumulator chain where a wavefront has few tiles
+    constexpr bool TWO = TM * TN < 4 || (SPLIT && F32 && TM * TN == 4);     // second accumulator chain where a wavefront has few tiles (errors: cl_least_parts)
     extern __shared__ uint4 dyn_lds4[];          // two stage buffers, then the listed pixel of every column
     char* const Bs = reinterpret_cast<char*>(dyn_lds4);
     int* const qs = reinterpret_cast<int*>(Bs + 2 * BUF);
