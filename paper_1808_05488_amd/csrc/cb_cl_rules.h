@@ -129,6 +129,7 @@ template <bool F32, int SHAPE, typename FN> CB_HD void cl_tile(int N, int O, int
 // are divided among the XCDs
 CB_HD unsigned cl_filter_kb(int O, unsigned nkg, bool f32) { return ((unsigned)O * nkg >> 4) * (f32 ? 3u : 1u); }
 constexpr unsigned CL_FAR_KB = 2048;
+CB_HD unsigned cl_pixel_kb(unsigned N, unsigned Cs, unsigned esz) { return N * (Cs * esz / 16u) >> 6; }
 
 // Logarithm of the groups of XCDs among which the row tiles (MT) are divided; the column tiles are divided among the XCDs of a group.
 // Each XCD brings its rows of the filter matrix (filter_kb in all) and the pixels of its columns (pixel_kb, about) into its own L2: 2^l groups
@@ -137,10 +138,22 @@ constexpr unsigned CL_FAR_KB = 2048;
 // Filters of up to 2 MB stay in every L2 beside the pixels and gain nothing.  Frames, us, undivided / divided: 512 -> 512, 3x3, 46x82, 2 % changed
 // 45.3 / 42.2, bfloat16 35.7 / 33.9, 30 % 46.5 / 46.8; 256 -> 512 there 28.9 / 26.9; 256 -> 256, 3x3, 92x164 31.3 / 30.0; 64 -> 256, 7x7, 120x160
 // 53.5 / 52.2; below the line 128 -> 256, 3x3, 184x328 (1.8 MB) 39.1 / 39.7.
-CB_HD unsigned cl_xcd_rows(unsigned MT, unsigned filter_kb, unsigned pixel_kb)
+// Groups among which the tiles (NT column tiles, an item each or `parts`) do not come out even keep some XCDs waiting for others: at most an eighth
+// more items on one than undivided, or one for each of its 32 compute units.  Without that limit, frames, us, undivided / divided: 128 -> 330, 5x5, 60x80, 30 % 57.4 / 68.2,
+// every output 79.1 / 90.1, bfloat16 35.2 / 40.8; 512 -> 520, 3x3, 46x82, 30 % 89.5 / 96.7.
+CB_HD unsigned cl_xcd_tiles(unsigned MT, unsigned NT, unsigned l) { return ((NT + (8u >> l) - 1u) >> (3u - l)) * ((MT + (1u << l) - 1u) >> l); }
+CB_HD unsigned cl_xcd_rows(unsigned MT, unsigned NT, unsigned parts, unsigned filter_kb, unsigned pixel_kb)
 {
     unsigned l = filter_kb / 16u > pixel_kb ? 3u : filter_kb / 4u > pixel_kb ? 2u : filter_kb > pixel_kb ? 1u : 0u;
-    while ((1u << l) > MT) --l;
+    const unsigned most = cl_xcd_tiles(MT, NT, 0u) * 9u / 8u;
+    // (a loop: every workgroup fetches this code before its first load)
+#ifdef __HIPCC__
+#pragma unroll 1
+#endif
+    for (; l > 0u; --l) {
+        const unsigned tiles = cl_xcd_tiles(MT, NT, l);
+        if ((1u << l) <= MT && (tiles <= most || tiles * parts <= 32u)) break;
+    }
     return l;
 }
 
@@ -158,7 +171,7 @@ constexpr unsigned CL_SPLIT_NS = 8500, CL_SPLIT_MAX = 8;     // (tiles: at most 
 // the fewest parts of one chain (or of two) that are as exact as a whole tile: 0: 64 x 16 and 64 x 32, 1: 16 x 16, 2: 128 x 32 and 128 x 64
 CB_HD unsigned cl_least_parts(int whole, bool two) { return whole == 2 ? 2u : whole == 0 ? (two ? 2u : 7u) : two ? 5u : CL_SPLIT_MAX + 1u; }
 CB_HD bool cl_split_pays(unsigned nkg, bool f32) { return nkg >= (f32 ? 96u : 256u); }
-template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned ws_bytes)
+template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned ws_bytes, unsigned pixel_kb = ~0u)
 {
 #define CB_COST(bm, bn, n, a0, a1, a2, a3, b0, b1, b2, b3) \
     (F32 ? cl_cost<bm, bn>(n, O, nkg, a0, a1, a2, a3) : cl_cost<bm, bn>(n, O, nkg, b0, b1, b2, b3))
@@ -174,20 +187,23 @@ template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned
     const int whole = best == k ? 1 : best == a || best == b ? 0 : 2;        // (of equal ones the most exact)
     // as many parts as make one or two items per compute unit
     const unsigned rows = ((unsigned)O + 127u) / 128u;
-    auto consider = [&](unsigned tiles, unsigned flag, unsigned bytes, unsigned l0, unsigned l1, unsigned c0, unsigned c1) {
+    // (an XCD's compute units take what falls to that XCD: 512 -> 260, 3x3, 46x82, 30 %, 432 items of which one XCD had 80, not 54, whole 58.7, divided 64.5)
+    auto consider = [&](unsigned cols, unsigned flag, unsigned bytes, unsigned l0, unsigned l1, unsigned c0, unsigned c1) {
+        const unsigned tiles = cols * rows;
         if (tiles > 256u) return;
+        const unsigned on_one = cl_xcd_tiles(rows, cols, cl_xcd_rows(rows, cols, CL_SPLIT_MAX, cl_filter_kb(O, nkg, F32), pixel_kb));
         const unsigned one = 256u / tiles, two = 512u / tiles;
         for (unsigned r = 0; r < 2; ++r) {
             unsigned p = r ? two : one;
             p = p > CL_SPLIT_MAX ? CL_SPLIT_MAX : p;
             const unsigned g = (nkg + p - 1u) / p;
             if (p < (F32 ? cl_least_parts(whole, !flag) : 2u) || g < 8u || tiles * p * bytes > ws_bytes) continue;
-            const unsigned lat = l0 + l1 * g, busy = (tiles * p + 255u) / 256u * (c0 + c1 * g), v = (busy > lat ? busy : lat) + CL_SPLIT_NS;
+            const unsigned lat = l0 + l1 * g, busy = (on_one * p + 31u) / 32u * (c0 + c1 * g), v = (busy > lat ? busy : lat) + CL_SPLIT_NS;
             if (v < best) { best = v; choice = p | flag; }
         }
     };
-    consider(((unsigned)N + 31u) / 32u * rows, 0u, 16384u, F32 ? 1800u : 1500u, F32 ? 380u : 100u, F32 ? 1000u : 100u, F32 ? 320u : 96u);
-    consider(((unsigned)N + 63u) / 64u * rows, 16u, 32768u, F32 ? 900u : 2000u, F32 ? 745u : 190u, F32 ? 2900u : 1000u, F32 ? 510u : 140u);
+    consider(((unsigned)N + 31u) / 32u, 0u, 16384u, F32 ? 1800u : 1500u, F32 ? 380u : 100u, F32 ? 1000u : 100u, F32 ? 320u : 96u);
+    consider(((unsigned)N + 63u) / 64u, 16u, 32768u, F32 ? 900u : 2000u, F32 ? 745u : 190u, F32 ? 2900u : 1000u, F32 ? 510u : 140u);
     return choice;
 }
 

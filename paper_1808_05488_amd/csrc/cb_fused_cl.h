@@ -223,7 +223,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     // (cl_xcd_rows).  (32 bits: the outputs of 2^31 such tiles would not fit any memory.)
     const unsigned NT = ((unsigned)N + BN - 1u) / BN;
     const unsigned MT = ((unsigned)g.O + BM - 1u) / BM;
-    const unsigned lx = FAR ? cl_xcd_rows(MT, cl_filter_kb(g.O, (unsigned)nkg, F32), (unsigned)N * ((unsigned)g.Cs * ESZ / 16u) >> 6) : 0u;
+    const unsigned lx = FAR ? cl_xcd_rows(MT, NT, parts, cl_filter_kb(g.O, (unsigned)nkg, F32), cl_pixel_kb((unsigned)N, (unsigned)g.Cs, ESZ)) : 0u;
     const unsigned MTX = FAR ? (MT + (1u << lx) - 1u) >> lx : MT, mt0 = FAR ? (bx & ((1u << lx) - 1u)) * MTX : 0u;
     const unsigned per_xcd = FAR ? (NT + (8u >> lx) - 1u) >> (3u - lx) : (NT + 7u) / 8u, total = per_xcd * MTX * parts;
     const unsigned xcd0 = (FAR ? (bx & 7u) >> lx : bx & 7u) * per_xcd;
@@ -588,7 +588,8 @@ __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, co
     const int N = *count;
     if (N <= 0) return;
     if constexpr (FAR == 2) {
-        const unsigned sp = cl_split<sizeof(T) == 4>(N, g.O, ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u, ws_bytes);
+        const unsigned sp = cl_split<sizeof(T) == 4>(N, g.O, ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u, ws_bytes,
+                                                           cl_pixel_kb((unsigned)N, (unsigned)g.Cs, (unsigned)sizeof(T)));
         if (sp) {
             const ClSplit split{ws, kcount, sp & 15u};
             if (sp & 16u) fused_cl_body<T, P2, FAR, 4, 1, 2, 4, 1, true>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx, split);

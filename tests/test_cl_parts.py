@@ -1,5 +1,5 @@
-"""float32 layers whose K is divided among workgroups (csrc/cb_cl_rules.h), compiled for the host: K is divided only where the sums round no
-worse than those of the tile that would take all of K."""
+"""Layers whose filters are divided (csrc/cb_cl_rules.h), compiled for the host: float32 K is divided only where the sums round no
+worse than those of the tile that would take all of K, and the items of a layer come out even enough among the XCDs."""
 import ctypes as C
 import os
 import subprocess
@@ -12,6 +12,7 @@ SOURCE = r"""
 #include "cb_cl_rules.h"
 extern "C" unsigned split(int N, int O, unsigned nkg, unsigned ws) { return cb::cl_split<true>(N, O, nkg, ws); }
 extern "C" int far(int O, unsigned nkg) { return cb::cl_filter_kb(O, nkg, true) >= cb::CL_FAR_KB; }
+extern "C" unsigned rows(unsigned MT, unsigned NT, unsigned parts, unsigned filter_kb, unsigned pixel_kb) { return cb::cl_xcd_rows(MT, NT, parts, filter_kb, pixel_kb); }
 extern "C" int tile(int N, int O, int C, int taps)
 {
     int t = -1;
@@ -53,3 +54,28 @@ def test_divided_sums_round_no_worse(rules):
                 divided.add((t, bool(r & 16)))
                 assert err <= whole[t] * 1.001, (n, o, c, taps, t, r)
     assert len(divided) >= 4
+
+
+def test_no_xcd_has_much_more_than_its_share(rules):
+    """Items of every XCD counted one by one as the kernel walks them: all of them once, and the most on one XCD at most an eighth above what undivided
+    rows give it, or no more than its 32 compute units."""
+    def items(mt, nt, l):
+        per, cols = (mt + (1 << l) - 1) >> l, (nt + (8 >> l) - 1) >> (3 - l)
+        on = []
+        for x in range(8):
+            m0, c0 = (x & ((1 << l) - 1)) * per, (x >> l) * cols
+            on.append({(m, c) for m in range(m0, min(m0 + per, mt)) for c in range(c0, min(c0 + cols, nt))})
+        return on
+
+    seen = set()
+    for mt in (1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 17, 20, 33):
+        for nt in (1, 2, 3, 7, 8, 9, 15, 16, 18, 23, 36, 59, 62, 118, 150, 236):
+            for parts in (1, 2, 5, 8):
+                for filter_kb, pixel_kb in ((4096, 100), (4096, 700), (4096, 2000), (4096, 9000)):
+                    l = rules.rows(mt, nt, parts, filter_kb, pixel_kb)
+                    on = items(mt, nt, l)
+                    assert sum(len(s) for s in on) == mt * nt and len(set().union(*on)) == mt * nt
+                    most, whole = (max(len(s) for s in o) for o in (on, items(mt, nt, 0)))
+                    assert most * 8 <= whole * 9 or most * parts <= 32, (mt, nt, parts, l)
+                    seen.add(l)
+    assert seen == {0, 1, 2, 3}
