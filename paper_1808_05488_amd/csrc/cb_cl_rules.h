@@ -62,6 +62,12 @@ CB_HD constexpr int cl_tiles(int shape) { return shape == 16 ? 3 : shape == 128 
 // on it take about max(latency of one, n * its share of a busy unit) beyond the launch; both grow with the k-groups of the
 // layer.  Fitted to every tile forced in turn (K = 288 to 12 544, 24 to 307 200 listed pixels, O = 8 to 512, both types):
 // the choice is within a few percent of the best tile.
+// N up to which the costs of O output channels fit 32 bits, whatever the filter (2 048 k-groups); with more listed pixels the tiles compare as they do with so many
+CB_HD int cl_cost_pixels(int N, int O)
+{
+    const int most = (1 << 30) >> (32 - __builtin_clz((unsigned)O));
+    return N < most ? N : most;
+}
 template <int BM, int BN> CB_HD unsigned cl_cost(int N, int O, unsigned nkg, unsigned l0, unsigned l1, unsigned c0, unsigned c1)
 {
     const unsigned tiles = (((unsigned)N + BN - 1u) / BN) * (((unsigned)O + BM - 1u) / BM);
@@ -74,6 +80,7 @@ template <int BM, int BN> CB_HD unsigned cl_cost(int N, int O, unsigned nkg, uns
 // bfloat16 at 1080p 453 -> 458 us.)
 template <bool F32, int SHAPE, typename FN> CB_HD void cl_tile(int N, int O, int Cs, int taps, int R, FN&& run)
 {
+    N = cl_cost_pixels(N, O);
     // (literal arguments, not a table: a table would be fetched from memory ahead of everything else)
     const unsigned nkg = ((unsigned)(Cs * taps) + 31u) / 32u;
 #define CB_COST(bm, bn, a0, a1, a2, a3, b0, b1, b2, b3) \
@@ -173,6 +180,7 @@ CB_HD unsigned cl_least_parts(int whole, bool two) { return whole == 2 ? 2u : wh
 CB_HD bool cl_split_pays(unsigned nkg, bool f32) { return nkg >= (f32 ? 96u : 256u); }
 template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned ws_bytes, unsigned pixel_kb = ~0u)
 {
+    if (N > cl_cost_pixels(N, O)) return 0;       // (far more tiles than parts are considered for)
 #define CB_COST(bm, bn, n, a0, a1, a2, a3, b0, b1, b2, b3) \
     (F32 ? cl_cost<bm, bn>(n, O, nkg, a0, a1, a2, a3) : cl_cost<bm, bn>(n, O, nkg, b0, b1, b2, b3))
     const unsigned a = CB_COST(64, 16, N, 0, 176, 1250, 120, 100, 58, 650, 41), b = CB_COST(64, 32, N, 1000, 300, 1400, 203, 400, 80, 1100, 47),

@@ -13,6 +13,28 @@ SOURCE = r"""
 extern "C" unsigned split(int N, int O, unsigned nkg, unsigned ws) { return cb::cl_split<true>(N, O, nkg, ws); }
 extern "C" int far(int O, unsigned nkg) { return cb::cl_filter_kb(O, nkg, true) >= cb::CL_FAR_KB; }
 extern "C" unsigned rows(unsigned MT, unsigned NT, unsigned parts, unsigned filter_kb, unsigned pixel_kb) { return cb::cl_xcd_rows(MT, NT, parts, filter_kb, pixel_kb); }
+// the tile of 128-row layers from costs in 64 bits
+extern "C" int tile64(int f32, int N, int O, unsigned nkg)
+{
+    auto cost = [&](int bm, int bn, long long a0, long long a1, long long a2, long long a3, long long b0, long long b1, long long b2, long long b3) {
+        const long long tiles = ((N + bn - 1LL) / bn) * ((O + bm - 1LL) / bm), l0 = f32 ? a0 : b0, l1 = f32 ? a1 : b1, c0 = f32 ? a2 : b2, c1 = f32 ? a3 : b3;
+        const long long lat = l0 + l1 * nkg, busy = (tiles + 255) / 256 * (c0 + c1 * nkg);
+        return busy > lat ? busy : lat;
+    };
+    const bool far = f32 && (long long)O * nkg * 32 > 700000;
+    const long long v[5] = {cost(16, 16, 100, 94, 1260, far ? 80 : 49, 200, 30, 870, 16), cost(64, 16, 0, 176, 1250, 120, 100, 58, 650, 41),
+                            cost(64, 32, 1000, 300, 1400, 203, 400, 80, 1100, 47), cost(128, 32, 1800, 380, 1000, 320, 1500, 100, 100, 96),
+                            cost(128, 64, 900, 745, 2900, 510, 2000, 190, 1000, 140)};
+    int best = 0;
+    for (int i = 1; i < 5; ++i) if (v[i] < v[best]) best = i;
+    return best;
+}
+extern "C" int tile_bf16(int N, int O, int C, int taps)
+{
+    int t = -1;
+    cb::cl_tile<false, 128>(N, O, C, taps, C * taps, [&](auto x) { t = decltype(x)::value; });
+    return t;
+}
 extern "C" int tile(int N, int O, int C, int taps)
 {
     int t = -1;
@@ -79,3 +101,12 @@ def test_no_xcd_has_much_more_than_its_share(rules):
                     assert most * 8 <= whole * 9 or most * parts <= 32, (mt, nt, parts, l)
                     seen.add(l)
     assert seen == {0, 1, 2, 3}
+
+
+def test_costs_of_the_largest_layers(rules):
+    """The tile picked with costs in 32 bits is the one of 64 bits, up to the longest filters and the most listed pixels."""
+    for o in (65, 100, 128, 256, 500, 1024, 2048, 30000, (1 << 20) - 1):
+        for c, taps in ((32, 9), (512, 9), (1024, 49), (8192, 8), (32768, 2), (65536 // 25 // 4 * 4, 25)):
+            for n in (1000, 307200, 2073600, 8294400, 100000000, (1 << 30) - 1):
+                for f32, pick in ((1, rules.tile), (0, rules.tile_bf16)):
+                    assert pick(n, o, c, taps) == rules.tile64(f32, n, o, (c * taps + 31) // 32), (n, o, c, taps, f32)
