@@ -484,11 +484,14 @@ int cb_layer_create(const cb_layer_desc* desc, const void* w_oihw_dev, const voi
     if (state_bytes < sl.total) return CB_ENOMEM;
     const bool fused = use_fused(desc, g), matrices = use_matrices(desc, g);
     if (scratch_bytes < scratch_layout(g, 256, matrices).total) return CB_ENOMEM;
-    // largest chunk capacity (multiple of 256 columns) that fits the given scratch
-    size_t cols = (scratch_bytes / col_bytes(g) + 255) & ~(size_t)255;
+    // largest chunk capacity (multiple of 256 columns) that fits the given scratch; from the recommended size on, less the room for partial sums
+    const bool splits = use_channel_last(desc, g) && cb::fused_cl_splits(g);
+    size_t for_chunks = scratch_bytes;
+    if (splits && scratch_bytes >= scratch_layout(g, recommended_cap(g), matrices).total + cb::CL_WORK_BYTES) for_chunks -= cb::CL_WORK_BYTES;
+    size_t cols = (for_chunks / col_bytes(g) + 255) & ~(size_t)255;
     if (cols > (size_t)po_pad(g)) cols = po_pad(g);
     if (cols < 256) cols = 256;
-    while (cols > 256 && scratch_layout(g, (int)cols, matrices).total > scratch_bytes) cols -= 256;
+    while (cols > 256 && scratch_layout(g, (int)cols, matrices).total > for_chunks) cols -= 256;
 
     cb_layer* L = new (std::nothrow) cb_layer();
     if (!L) return CB_ENOMEM;
@@ -502,7 +505,7 @@ int cb_layer_create(const cb_layer_desc* desc, const void* w_oihw_dev, const voi
     L->fused = fused;
     L->shadow = use_shadow(desc, g);
     L->ext_cl = nullptr;
-    if (use_channel_last(desc, g) && cb::fused_cl_splits(g)) {
+    if (splits) {
         L->work.count = (int*)(L->state + sl.kcount);
         L->work.ws = (float*)(L->scratch + L->sc.ws);
         L->work.bytes = (unsigned)std::min(cb::CL_WORK_BYTES, scratch_bytes - L->sc.ws);

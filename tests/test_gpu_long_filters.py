@@ -68,3 +68,27 @@ def test_divided_sums_are_as_exact(geom):
             idx = torch.from_numpy(L.changes_host()[2]).long().cuda()
             err.append(((out - ref)[:, idx].norm() / ref[:, idx].norm()).item())
         assert err[0] <= 1.02 * err[1], err
+
+
+def test_recommended_scratch_has_room_for_partial_sums():
+    """X' of this layer is processed in chunks, and the chunks leave the recommended size's room for partial sums alone: the same sums, bit for bit, as with
+    room for X' whole, and others than without room for partial sums."""
+    C, O, k, H, W = 64, 128, 9, 480, 640
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    w = torch.randn((O, C, k, k), generator=g, device="cuda") / (C * k * k) ** 0.5
+    x = torch.rand((C, H, W), generator=g, device="cuda")
+    y = x.clone()
+    y[:, 100:130, 200:230] += 1.0
+    d = cb.make_desc(C, O, k, k, 1, k // 2, H, W)
+    size = cb.cb_layer_workspace_bytes(d)[1]
+    whole = (C * k * k * 4 + O * 4) * (-(-H * W // 256) * 256) + (32 << 20)
+    assert size < whole                              # (the recommended size is that of a chunk)
+    outs = []
+    for s in (size, whole, cb.cb_layer_min_scratch_bytes(d)):
+        L = cb.Layer(w, None, 1, k // 2, H, W, False, scratch_bytes=s)
+        L.process_frame(x, 0.0)
+        outs.append(L.process_frame(y, 0.0).clone())
+        del L
+        torch.cuda.empty_cache()
+    assert torch.equal(outs[0], outs[1]) and not torch.equal(outs[0], outs[2])
