@@ -229,7 +229,7 @@ int cb_layer_changes(cb_layer_t *layer, const uint8_t **m_in_dev, const uint8_t 
  * nsplit}; Y' holds nsplit partial products of O x ld each, which the output update adds).
  * Layers with the explicit back end have these matrices, and those of CB_BACKEND_AUTO that CB_BACKEND_FUSED would not
  * take (CB_ESTATE otherwise); of the latter the closed-loop ones, which run fused, compute them in this call, from the state as
- * the last frame left it. */
+ * the last frame left it.  They hold nothing before the first frame, and no column (ncols = 0) behind an import. */
 int cb_layer_state(const cb_layer_t *layer, const void **state_dev);
 int cb_layer_matrices(const cb_layer_t *layer, const void **xprime_dev, const void **yprime_dev,
                       const int32_t **ld_ncols_dev);

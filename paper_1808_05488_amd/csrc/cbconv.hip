@@ -747,8 +747,9 @@ int cb_layer_matrices(const cb_layer_t* L, const void** xprime_dev, const void**
 {
     if (!L) return CB_EINVAL;
     if (!use_matrices(&L->d, L->g)) return CB_ESTATE;
-    if (L->fused && L->primed)
-        // the fused kernel left no matrices: those of the last frame, from the state as that frame left it
+    if (L->fused && L->frames > 0)
+        // the fused kernel left no matrices: those of the last frame, from the state and the list as that frame left them (also behind a
+        // reset, which changes neither; behind an import the list is empty)
         for (int q = 0; q < L->nchunks; ++q) {
             const int col0 = q * L->sc.cap;
             CB_HIP(cb::launch_gather(L->g, L->S(), L->cur_idx, L->cur_count, col0, L->sc.cap, L->X(), L->ctl(), L->st));

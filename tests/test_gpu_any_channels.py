@@ -115,6 +115,28 @@ def test_matrices_on_request():
             assert np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][2], got[1][2])
 
 
+def test_matrices_behind_a_reset_and_an_import():
+    """Behind a reset the matrices of the last frame, as the explicit back end still has them; behind an import, whose change set is empty, none."""
+    spec, frames = syn.random_layer_case(3, 8, 12, 9, 1, 4, 40, 50, 3, change_prob=0.02)
+    auto, expl = Pair(spec, 40, 50), Pair(spec, 40, 50, backend=1)
+
+    def matrices(p):
+        xp, yp, ldn = cb.cb_layer_matrices(p.g.handle)
+        ld, ncols, nsplit = [int(v) for v in _raw_to_host(ldn, 3, p.g.device)]
+        return (ld, ncols, nsplit), _raw_to_host(xp, 648 * ld, p.g.device), _raw_to_host(yp, 12 * ld * nsplit, p.g.device)
+
+    for t, f in enumerate(frames):
+        for p in (auto, expl):
+            p.step(f, 0.02, tag=f"frame {t}")
+            p.g.reset()
+        a, b = matrices(auto), matrices(expl)
+        assert a[0] == b[0] and a[0][1] > 0 and np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
+        for p in (auto, expl):
+            p.o.reset()
+    auto.g.import_state(auto.g.state().clone(), auto.g_out.clone())
+    assert int(_raw_to_host(cb.cb_layer_matrices(auto.g.handle)[2], 3, auto.g.device)[1]) == 0
+
+
 def test_what_the_fused_back_end_refused_it_refuses():
     for kw in ({"backend": 2}, {"keep_output_channel_last": True}, {"gather_channel_last": True, "mode": cb.CB_PROPAGATE}):
         with pytest.raises(Exception):
