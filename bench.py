@@ -561,20 +561,20 @@ def main() -> int:
         print(f"[bench] explicit back end: {explicit}", file=sys.stderr, flush=True)
         del layer_e
 
-    # dominant kernel: change detection.  Algorithmic bytes per launch: the frame and
-    # the state read once over all channels, the bit-packed map written, and the changed
-    # pixels' channels written into the state.
-    det_bytes = 2 * C * P * 4 + P / 8 + C * M_mean * 4
+    # dominant kernel: change detection, with the index extraction in its launch.  Algorithmic bytes per
+    # launch: the frame and the state read once over all channels, the bit-packed map written, the changed
+    # pixels' channels written into the state, the dilated map and the index list written.
+    det_bytes = 2 * C * P * 4 + P / 8 + C * M_mean * 4 + P / 8 + 4 * N_mean
     det_gbs = det_bytes / (us["detect"] * 1e-6) / 1e9
     copy_GBs = measured_copy_GBs(dev)
     print(f"[bench] plain device copy of 1 GiB: {copy_GBs:.0f} GB/s (read + write)", file=sys.stderr, flush=True)
-    roofline = {"kernel": "detect_reg_kernel", "bound": "hbm", "achieved": round(det_gbs, 1), "peak": HBM_PEAK_GBS,
+    roofline = {"kernel": "detect_extract_kernel", "bound": "hbm", "achieved": round(det_gbs, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(det_gbs / HBM_PEAK_GBS, 4), "traffic": None,
                 "bytes_per_launch": int(det_bytes), "us_per_launch": round(us["detect"], 2),
                 "peak_measured_copy": round(copy_GBs, 1), "frac_of_measured_copy": round(det_gbs / copy_GBs, 4),
-                "note": "cache-assisted: this workload's 78.6 MB input state stays in the 256 MB last-level cache "
-                        "from frame to frame, so `achieved` is not all HBM traffic; the clean HBM measurement is "
-                        "c5.rows[*].roofline_detect (1.06 GB state)"}
+                "note": "detection and index extraction, one launch; cache-assisted: this workload's 78.6 MB input "
+                        "state stays in the 256 MB last-level cache from frame to frame, so `achieved` is not all "
+                        "HBM traffic; the clean HBM measurement is c5.rows[*].roofline_detect (1.06 GB state)"}
     # HBM bytes per launch from the committed rocprofv3 FETCH_SIZE / WRITE_SIZE summary of this workload
     prof = os.path.join(ROOT, "profiles", "cbconv_c2_480x640_hbm_traffic.txt")
     if os.path.exists(prof):

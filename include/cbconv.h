@@ -123,7 +123,10 @@ typedef struct {
     int64_t ops;             /* 2 * c_out * (c_in*kh*kw) * N multiply-adds counted as 2 */
     float us_step[CB_NUM_STEPS];   /* GPU time of each step's kernel dispatches in microseconds
                                       (begin/end time stamps of the dispatches; TOTAL = first begin
-                                      to last end); zeros unless cb_layer_set_timing switched it on */
+                                      to last end), of the dispatches that a frame has without
+                                      timing too: DETECT has the index extraction in it where that
+                                      runs in its launch, FUSED that of the next stage of a chain;
+                                      zeros unless cb_layer_set_timing switched it on */
     int32_t scan_recounts;   /* since create: how often a workgroup of the index extraction recomputed a
                                 predecessor's count, or detected a block of pixels that no workgroup had begun,
                                 because its bounded wait ran out (see cb_set_scan_wait_limit); 0 on an idle
@@ -259,8 +262,7 @@ int cb_layer_set_timing(cb_layer_t *layer, int32_t on);
 /* Waits for the layer's stream, then fills *stats for the last frame. */
 int cb_layer_stats(cb_layer_t *layer, cb_stats *stats);
 /* The index extraction (Sec. III-A, "Change Indexes Extraction") runs inside the launch that detects the changes where it
- * can; it takes a launch of its own for very large maps, strides above 2 and very many channels, while per-step times are
- * switched on (they are those of the separate launches), and with a limit of 0 here.
+ * can; it takes a launch of its own for very large maps, strides above 2 and very many channels, and with a limit of 0 here.
  * In the launch that detects, a workgroup that extracts polls for the part of the change map that it needs.  After `polls`
  * unsuccessful polls (at most 4096) it detects itself whatever pixels no workgroup has begun to look at; a pixel is looked at by one
  * workgroup, whichever begins first.  (With any other limit than the default these workgroups are numbered first.)

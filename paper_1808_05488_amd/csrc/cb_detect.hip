@@ -771,8 +771,8 @@ void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int C
     if (job) job->nclaims = CS > 1 ? (int)grid : (P + 64 * VEC - 1) / (64 * VEC);
 #define CB_REG(sh, shadow)                                                                                                          \
     if (job && job->nblk)                                                                                                           \
-        hipLaunchKernelGGL((detect_extract_kernel<T, VEC, CS, CPT, PLX, sh>), dim3(grid + (unsigned)job->nblk), dim3(PL * CS), 0, st, \
-                           DetectArgs<T>{x, S, shadow, mbits, ctl, C, Cs, inv_per, P, (P + 63) / 64, tau, flags, stream, *job});      \
+        CB_LAUNCH((detect_extract_kernel<T, VEC, CS, CPT, PLX, sh>), dim3(grid + (unsigned)job->nblk), dim3(PL * CS), st, tm,       \
+                  (DetectArgs<T>{x, S, shadow, mbits, ctl, C, Cs, inv_per, P, (P + 63) / 64, tau, flags, stream, *job}));             \
     else CB_LAUNCH((detect_reg_kernel<T, VEC, CS, CPT, PLX, sh>), dim3(grid), dim3(PL * CS), st, tm, x, S, shadow, mbits, ctl, C, Cs, \
               inv_per, P, (P + 63) / 64, tau, flags, stream)
     if constexpr (CS >= 4 && (CPT * sizeof(T)) % 16 == 0) {
@@ -1113,8 +1113,8 @@ hipError_t launch_listed_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbi
         if (job) job->nclaims = (int)grid;
 #define CB_LISTED(SH)                                                                                                            \
     if (job && job->nblk)                                                                                                        \
-        hipLaunchKernelGGL((detect_listed_extract_kernel<T, CS, PLC, SH>), dim3(grid + (unsigned)job->nblk), dim3(CS * PLC), 0, st, \
-                           ListedArgs<T>{x, S, S2, mbits, ctl, cand, cand_count, cand_cap, g.C, g.Cs, g.P, g.W, tau, flags, pool_w, cand_W, 0, *job}); \
+        CB_LAUNCH((detect_listed_extract_kernel<T, CS, PLC, SH>), dim3(grid + (unsigned)job->nblk), dim3(CS * PLC), st, tm,      \
+                  (ListedArgs<T>{x, S, S2, mbits, ctl, cand, cand_count, cand_cap, g.C, g.Cs, g.P, g.W, tau, flags, pool_w, cand_W, 0, *job}));  \
     else                                                                                                                         \
         CB_LAUNCH((detect_listed_kernel<T, CS, PLC, SH>), dim3(grid), dim3(CS * PLC), st, tm, x, S, S2, mbits, ctl, cand, cand_count, \
                   cand_cap, g.C, g.Cs, g.P, g.W, tau, flags, pool_w, cand_W)
@@ -1207,10 +1207,10 @@ size_t detect_claim_bytes(const Geom& g) { return 4 * (size_t)claim_words(std::m
 size_t detect_look_bytes(const Geom& g) { return ((size_t)g.Ho * g.WWo / 64 + 1) * 8; }
 
 hipError_t launch_detect_extract(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl, float tau, int flags,
-                                 DetectJob job, hipStream_t st, bool* extracted)
+                                 DetectJob job, hipStream_t st, Tm tm, bool* extracted)
 {
     job.nblk = 0;
-    const hipError_t e = launch_any(g, x, S, S2, mbits, ctl, tau, flags, &job, st, Tm());
+    const hipError_t e = launch_any(g, x, S, S2, mbits, ctl, tau, flags, &job, st, tm);
     *extracted = job.nblk > 0;
     return e;
 }
@@ -1261,10 +1261,10 @@ hipError_t launch_detect_listed(const Geom& g, const void* x, void* S, void* S2,
 
 hipError_t launch_detect_listed_extract(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
                                         float tau, int flags, const int32_t* cand, const int* cand_count, int cand_cap,
-                                        int pool_w, int cand_W, DetectJob job, hipStream_t st, bool* extracted)
+                                        int pool_w, int cand_W, DetectJob job, hipStream_t st, Tm tm, bool* extracted)
 {
     job.nblk = 0;
-    const hipError_t e = launch_listed(g, x, S, S2, mbits, ctl, tau, flags, cand, cand_count, cand_cap, pool_w, cand_W, &job, st, Tm());
+    const hipError_t e = launch_listed(g, x, S, S2, mbits, ctl, tau, flags, cand, cand_count, cand_cap, pool_w, cand_W, &job, st, tm);
     *extracted = job.nblk > 0;
     return e;
 }

@@ -156,10 +156,10 @@ hipError_t launch_fused_bf16_cl(const Geom& g, const FusedPlan& plan, const uint
 // ... with the index extraction of the layer behind (cb_fused_cl_extract.h)
 hipError_t launch_fused_f32_cl_extract(const Geom& g, const FusedPlan& plan, const float* shadow, const int32_t* idx, const int* count,
                                        const void* KF, const float* KT, const float* bias, int relu, float* OUT, float* OUT2,
-                                       const ClWork& work, const ExtractJob& job, hipStream_t st);
+                                       const ClWork& work, const ExtractJob& job, hipStream_t st, Tm tm);
 hipError_t launch_fused_bf16_cl_extract(const Geom& g, const FusedPlan& plan, const uint16_t* shadow, const int32_t* idx, const int* count,
                                         const void* KF, const float* bias, int relu, uint16_t* OUT, uint16_t* OUT2,
-                                        const ClWork& work, const ExtractJob& job, hipStream_t st);
+                                        const ClWork& work, const ExtractJob& job, hipStream_t st, Tm tm);
 hipError_t launch_fused_bf16(const Geom& g, const FusedPlan& plan, const uint16_t* src, const int32_t* idx,
                              const int* count, const void* KF, const int2* tab, const float* bias, int relu,
                              uint16_t* OUT, uint16_t* OUT2, hipStream_t st, Tm tm);

@@ -299,10 +299,10 @@ hipError_t launch_fused(const Geom& g, const FusedPlan& plan, const void* src, c
         if (!shadow) return hipErrorInvalidValue;
         if (job && g.bf16)
             return launch_fused_bf16_cl_extract(g, plan, (const uint16_t*)shadow, idx, count, KF, bias, relu, (uint16_t*)OUT,
-                                                (uint16_t*)OUT2, work, *job, st);
+                                                (uint16_t*)OUT2, work, *job, st, tm);
         if (job)
             return launch_fused_f32_cl_extract(g, plan, (const float*)shadow, idx, count, KF, (const float*)KT, bias, relu, (float*)OUT,
-                                               (float*)OUT2, work, *job, st);
+                                               (float*)OUT2, work, *job, st, tm);
         if (g.bf16)
             return launch_fused_bf16_cl(g, plan, (const uint16_t*)shadow, idx, count, KF, bias, relu, (uint16_t*)OUT,
                                         (uint16_t*)OUT2, work, st, tm);

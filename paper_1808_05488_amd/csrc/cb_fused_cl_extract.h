@@ -31,15 +31,15 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_extract_
 
 template <typename T>
 hipError_t launch_fused_cl_extract(const Geom& g, const FusedPlan& plan, const T* shadow, const int32_t* idx, const int* count, const void* KF,
-                                   const float* KT, const float* bias, int relu, T* OUT, T* OUT2, const ClWork& work, const ExtractJob& job, hipStream_t st)
+                                   const float* KT, const float* bias, int relu, T* OUT, T* OUT2, const ClWork& work, const ExtractJob& job, hipStream_t st, Tm tm)
 {
     if (!fused_takes_job(g, plan) || !extract_fits(job.g) || job.nblk != dilate_num_blocks(job.g)) return hipErrorInvalidValue;
     const ClDiv div = cl_div(g.Wo, g.Ho, g.kw, g.Cs);
     return fused_cl_instance<T>(g, plan, [&](auto shape) {
         constexpr int SHAPE = decltype(shape)::value;
 #define CB_CLX(far) \
-    hipLaunchKernelGGL((fused_cl_extract_kernel<T, SHAPE, far>), dim3(CL_GRID + (((unsigned)job.nblk + 7u) & ~7u)), dim3(256), \
-                       cl_lds_bytes<T>(), st, g, div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2, job, work.ws, work.bytes, work.count)
+    CB_LAUNCH_LDS((fused_cl_extract_kernel<T, SHAPE, far>), dim3(CL_GRID + (((unsigned)job.nblk + 7u) & ~7u)), dim3(256), \
+                  cl_lds_bytes<T>(), st, tm, g, div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2, job, work.ws, work.bytes, work.count)
         const int far = fused_cl_far_mode(g, work);
         if constexpr (SHAPE == 128)
             if (far == 2) {

@@ -117,7 +117,7 @@ hipError_t launch_detect(const Geom& g, const void* x, void* S, void* S2, uint64
                          float tau, int flags, hipStream_t st, Tm tm = Tm());
 // The same with the index extraction in the launch where that is possible (*extracted; else the caller launches it).
 hipError_t launch_detect_extract(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl, float tau, int flags,
-                                 DetectJob job, hipStream_t st, bool* extracted);
+                                 DetectJob job, hipStream_t st, Tm tm, bool* extracted);
 
 // The state update of a frame whose detection ran with DET_NO_UPDATE (same stream, before the index
 // extraction of that frame): copies the marked pixels of x into S and, if not null, the shadow S2.
@@ -137,7 +137,7 @@ hipError_t launch_detect_listed(const Geom& g, const void* x, void* S, void* S2,
 // ... with the index extraction in the launch, as launch_detect_extract (job.mail is not used)
 hipError_t launch_detect_listed_extract(const Geom& g, const void* x, void* S, void* S2, uint64_t* mbits, int* ctl,
                                         float tau, int flags, const int32_t* cand, const int* cand_count, int cand_cap,
-                                        int pool_w, int cand_W, DetectJob job, hipStream_t st, bool* extracted);
+                                        int pool_w, int cand_W, DetectJob job, hipStream_t st, Tm tm, bool* extracted);
 
 // Dilation of a bit-packed map by the filter footprint + per-block popcounts.  own_map != 0: in_bits
 // holds the layer's two interleaved input maps (see launch_detect); the frame count on the device

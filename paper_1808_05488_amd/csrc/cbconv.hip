@@ -285,12 +285,12 @@ cb::Tm next_tm(cb_layer* L, int step)
 
 // The index extraction of the stage behind L as a job for L's product kernel: that stage takes over L's change map (itself, or 2 x 2
 // pooled) and is in step with it, so that its map and list follow from L->cur_mtbits, which is complete.  False: it extracts for
-// itself (cb_process_frame_propagated), as it does where per-step times are asked for.
+// itself (cb_process_frame_propagated).
 bool extract_job(const cb_layer* L, cb::ExtractJob* job)
 {
     const cb_layer* n = L->next;
     const cb_pool* p = L->next_pool;
-    if (!n || L->timing || n->timing || !cb::fused_takes_job(L->g, L->plan) || n == L || n->d.mode != CB_PROPAGATE || n->st != L->st) return false;
+    if (!n || !cb::fused_takes_job(L->g, L->plan) || n == L || n->d.mode != CB_PROPAGATE || n->st != L->st) return false;
     if (p && (p->w != 2 || p->prod != L)) return false;
     const cb::Geom& g = n->g;
     if (g.C != L->g.O || g.bf16 != L->g.bf16 || g.H != (p ? p->Hp : L->g.Ho) || g.W != (p ? p->Wp : L->g.Wo)) return false;
@@ -372,9 +372,9 @@ int detect_and_update(cb_layer* L, const void* input_dev, float tau, const int32
     else if (L->d.mode == CB_FEED_FORWARD) flags = cb::DET_COPY_ALL;
     if ((size_t)L->g.C * L->g.P * (L->g.bf16 ? 2 : 4) >= kStateBeyondCache) flags |= cb::DET_STREAM_STATE;
     bool extracted = false;      // the index list comes with detection
-    // (per-step times are those of the launches one by one, and a wait limit of 0 is none that one workgroup would wait for another in)
+    // (a wait limit of 0 is none that one workgroup would wait for another in)
     const int wait_limit = g_scan_wait_limit.load(std::memory_order_relaxed);
-    const bool together = !L->timing && wait_limit > 0;
+    const bool together = wait_limit > 0;
     cb::DetectJob job;
     job.g = L->g;
     job.full = L->primed ? 0 : 1;
@@ -385,7 +385,7 @@ int detect_and_update(cb_layer* L, const void* input_dev, float tau, const int32
     job.look = reinterpret_cast<unsigned long long*>(L->look());
     if (cand && together)
         CB_HIP(cb::launch_detect_listed_extract(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau, flags, cand, cand_count,
-                                                cand_cap, pool_w, cand_W, job, L->st, &extracted));
+                                                cand_cap, pool_w, cand_W, job, L->st, next_tm(L, CB_STEP_DETECT), &extracted));
     else if (cand)
         CB_HIP(cb::launch_detect_listed(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau,
                                         flags, cand, cand_count, cand_cap, pool_w, cand_W, L->st,
@@ -400,7 +400,8 @@ int detect_and_update(cb_layer* L, const void* input_dev, float tau, const int32
         CB_HIP(cb::launch_state_apply(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), L->st,
                                       next_tm(L, CB_STEP_STATE)));
     } else if (together) {
-        CB_HIP(cb::launch_detect_extract(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau, flags, job, L->st, &extracted));
+        CB_HIP(cb::launch_detect_extract(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau, flags, job, L->st,
+                                         next_tm(L, CB_STEP_DETECT), &extracted));
     } else
         CB_HIP(cb::launch_detect(L->g, input_dev, L->S(), L->S2(), L->mbits(), L->ctl(), tau, flags,
                                  L->st, next_tm(L, CB_STEP_DETECT)));

@@ -1,6 +1,6 @@
 """The index list extracted inside the launch of change detection, against the oracle: maps whose last word and last group of 16
 pixels are partly filled, rows that no output reads, paddings beyond the filter, one workgroup and many; and frames of which some take the launches
-one by one (per-step times on, another wait limit), some detect at listed pixels, some are full updates."""
+one by one (a wait limit of 0), some are timed, some detect at listed pixels, some are full updates."""
 import numpy as np
 import pytest
 import torch
@@ -94,12 +94,13 @@ def test_chained_layers(widths, bf16):
         for t, f in enumerate(frames):
             x = first.process_frame(to_dev(f, bf16), 0.02)
             y = pool.process()
-            one_by_one = t in (4, 7)
+            cb.cb_set_scan_wait_limit(0 if t in (4, 7) else 1 << 20)      # one by one
             for L in (direct[0], pooled[0]):
-                cb.cb_layer_set_timing(L.handle, one_by_one)
+                cb.cb_layer_set_timing(L.handle, t in (5, 7))
             direct[0].process_frame_chained(x, first, 0.02)
-            direct[1].process_frame(x, 0.02)
             pooled[0].process_frame_chained(y, pool, 0.02)
+            cb.cb_set_scan_wait_limit(1 << 20)
+            direct[1].process_frame(x, 0.02)
             pooled[1].process_frame(y, 0.02)
             for a, b in (direct, pooled):
                 for u, v in zip(a.changes_host(), b.changes_host()):
@@ -209,3 +210,27 @@ def test_layers_on_several_streams_at_once(limit):
             (sa, oa), (sb, ob) = a[i].export_state(), b[i].export_state()
             torch.cuda.synchronize()
             assert torch.equal(sa, sb) and torch.equal(oa, ob)
+
+
+def test_timed_frames_have_the_launches_of_others():
+    """Per-step times are those of the launches that a frame has without them: the list is part of detection, or of the product of the stage before."""
+    rng = np.random.default_rng(2)
+    w = [to_dev((rng.standard_normal((32, c, 3, 3)) / 12).astype(np.float32), False) for c in (16, 32, 32)]
+    layers = [cb.Layer(w[0], None, 1, 1, 120, 160, True, keep_output_channel_last=True), cb.Layer(w[1], None, 1, 1, 120, 160, True),
+              cb.Layer(w[2], None, 1, 1, 120, 160, True, mode=cb.CB_PROPAGATE)]
+    net = cb.Network(layers, [None] * 3)
+    _, frames = syn.random_layer_case(4, 16, 1, 1, 1, 0, 120, 160, 4, change_prob=0.02)
+    for L in layers:
+        L.set_timing(True)
+    for t, f in enumerate(frames):
+        net.forward(to_dev(f, False), [0.02] * 3)
+        us = [L.stats()["us_step"] for L in layers]
+        assert all(u["fused"] > 0 for u in us) and us[0]["detect"] > 0 and us[1]["detect"] > 0
+        assert us[0]["dilate"] == us[1]["dilate"] == us[0]["compact"] == us[1]["compact"] == 0, t
+        assert (us[2]["dilate"] == 0) == (t > 0), t                # (the first frame is a full update)
+    cb.cb_set_scan_wait_limit(0)
+    try:
+        net.forward(to_dev(frames[0], False), [0.02] * 3)
+        assert layers[0].stats()["us_step"]["dilate"] > 0
+    finally:
+        cb.cb_set_scan_wait_limit(1 << 20)
