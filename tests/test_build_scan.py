@@ -1,0 +1,18 @@
+"""The build refuses kernels that take the amount of a 64-bit shift from the last vector register of their allocation."""
+from paper_1808_05488_amd import build
+
+ASM = """
+_Z1kPf:
+\tv_lshlrev_b64 v[2:3], v%d, v[4:5]
+\ts_endpgm
+\t.amdhsa_kernel _Z1kPf
+\t\t.amdhsa_next_free_vgpr %d
+\t.end_amdhsa_kernel
+"""
+
+
+def test_the_form_is_found_and_no_other():
+    for used, last in ((33, 39), (40, 39), (41, 47), (8, 7)):
+        assert build.shifts_by_last_register(ASM % (last, used)) == [("_Z1kPf", f"v_lshlrev_b64 v[2:3], v{last}, v[4:5]")]
+        assert build.shifts_by_last_register(ASM % (last - 1, used)) == []
+    assert build.shifts_by_last_register(ASM.replace("v%d, v[4:5]", "s%d, v[4:5]") % (39, 40)) == []
