@@ -167,8 +167,8 @@ CB_HD unsigned cl_xcd_rows(unsigned MT, unsigned NT, unsigned parts, unsigned fi
 // Whether the K of a layer with such filters is divided, and into how many parts: 0, or parts + 16 * (128 x 64 instead of 128 x 32 tiles).
 // A few hundred tiles leave compute units idle in the last of one or two rounds, and tiles narrow enough to fill them fetch filters and pixels several times as
 // often; wide tiles in parts do neither.  The price is CL_SPLIT_NS: sums written through to memory, counted, read back.  Costs as in cl_tile.
-// Frames, us, whole / divided: float32 512 -> 512, 3x3, 46x82, 2 % changed 42.6 / 31.5, 10 % 51.7 / 43.9, 30 % 80 / 68; 64 -> 256, 7x7, 120x160, 10 %
-// 52.5 / 48.9; 128 -> 128, 9x9, 60x80 50.1 / 37.4; 256 -> 128 there 141 / 86; bfloat16 256 -> 256, 7x7, 60x80, 20 % 55.6 / 49.2.  Shorter filters
+// Frames, us, whole / divided: float32 512 -> 512, 3x3, 46x82, 2 and 10 % changed 45.5 / 35.8, 30 % 74.7 / 60.3, every output 113.5 / 109.2; 64 -> 256, 7x7, 30x40
+// 30.3 / 24.2, but 120x160, 10 % 55.1 / 56.1; 128 -> 128, 9x9, 60x80 44.8 / 37.8; 256 -> 128 there 77.5 / 56.7; bfloat16 256 -> 256, 7x7, 60x80, 20 % 55.0 / 44.8.  Shorter filters
 // are not considered, for which the choice alone took 0.4 us: 256 -> 256, 3x3, 92x164 (72 groups) 29.7 / 30.6; bfloat16 512 -> 512, 3x3, 46x82 (144) 42.3 / 43.0.
 // float32: K is only divided where that rounds the sums no worse than the whole tile.  Relative errors of sums over a K of 4 608 against float64: one
 // chain of products 1.06e-6, two (the small terms in one of their own: up to two tiles a wavefront, and four in parts) 4.1e-7, two in each of four wavefronts
@@ -178,7 +178,7 @@ constexpr unsigned CL_SPLIT_NS = 8500, CL_SPLIT_MAX = 8;     // (tiles: at most 
 // the fewest parts of one chain (or of two) that are as exact as a whole tile: 0: 64 x 16 and 64 x 32, 1: 16 x 16, 2: 128 x 32 and 128 x 64
 CB_HD unsigned cl_least_parts(int whole, bool two) { return whole == 2 ? 2u : whole == 0 ? (two ? 2u : 7u) : two ? 5u : CL_SPLIT_MAX + 1u; }
 CB_HD bool cl_split_pays(unsigned nkg, bool f32) { return nkg >= (f32 ? 96u : 256u); }
-template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned ws_bytes, unsigned pixel_kb = ~0u)
+template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned ws_bytes)
 {
     if (N > cl_cost_pixels(N, O)) return 0;       // (far more tiles than parts are considered for)
 #define CB_COST(bm, bn, n, a0, a1, a2, a3, b0, b1, b2, b3) \
@@ -194,12 +194,13 @@ template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned
     if (best < CL_SPLIT_NS) return 0;
     const int whole = best == k ? 1 : best == a || best == b ? 0 : 2;        // (of equal ones the most exact)
     // as many parts as make one or two items per compute unit
-    const unsigned rows = ((unsigned)O + 127u) / 128u;
+    // (of the tiles of the busiest XCD, with as many groups as the row tiles come out even in: the rule of cl_xcd_rows here took 0.5 us of a launch)
+    const unsigned rows = ((unsigned)O + 127u) / 128u, even = rows & 1u ? 0u : rows & 2u ? 1u : rows & 4u ? 2u : 3u;
     // (an XCD's compute units take what falls to that XCD: 512 -> 260, 3x3, 46x82, 30 %, 432 items of which one XCD had 80, not 54, whole 58.7, divided 64.5)
     auto consider = [&](unsigned cols, unsigned flag, unsigned bytes, unsigned l0, unsigned l1, unsigned c0, unsigned c1) {
         const unsigned tiles = cols * rows;
         if (tiles > 256u) return;
-        const unsigned on_one = cl_xcd_tiles(rows, cols, cl_xcd_rows(rows, cols, CL_SPLIT_MAX, cl_filter_kb(O, nkg, F32), pixel_kb));
+        const unsigned on_one = cl_xcd_tiles(rows, cols, even);
         const unsigned one = 256u / tiles, two = 512u / tiles;
         for (unsigned r = 0; r < 2; ++r) {
             unsigned p = r ? two : one;

@@ -588,8 +588,7 @@ __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, co
     const int N = *count;
     if (N <= 0) return;
     if constexpr (FAR == 2) {
-        const unsigned sp = cl_split<sizeof(T) == 4>(N, g.O, ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u, ws_bytes,
-                                                           cl_pixel_kb((unsigned)N, (unsigned)g.Cs, (unsigned)sizeof(T)));
+        const unsigned sp = cl_split<sizeof(T) == 4>(N, g.O, ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u, ws_bytes);
         if (sp) {
             const ClSplit split{ws, kcount, sp & 15u};
             if (sp & 16u) fused_cl_body<T, P2, FAR, 4, 1, 2, 4, 1, true>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx, split);
