@@ -563,9 +563,9 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
 }
 
 // Detection with the index extraction in the same launch: the last job.nblk workgroups extract (cb_claim.h).  A launch of its own costs the extraction
-// 4 - 8 us, of which most is the end of one kernel, the start of the next and its first loads from memory.  Frames, us, before / now:
-// 3 -> 16 at 48x64 15.1 / 12.4, 64 -> 64 at 480x640 41.7 / 39.5, 64 -> 128 at 271x435 bfloat16 24.5 / 20.9, 48 -> 96 5x5 stride 2 at 241x323
-// 29.0 / 27.1, 3 -> 16 7x7 at 1080p 32.3 / 30.3, 32 -> 32 9x9 at 240x320 34.0 / 31.1, 128 -> 128 at 1080p bfloat16, 10 % 459 / 454.
+// 4 - 8 us, of which most is the end of one kernel, the start of the next and its first loads from memory.  Frames, us, two launches / one:
+// 3 -> 16 at 48x64 14.4 / 11.1, 64 -> 64 at 480x640 43.0 / 42.0, 64 -> 128 at 271x435 bfloat16 25.8 / 22.0, 3 -> 16 7x7 at 1080p 33.7 / 30.8, feed-forward
+// 64 -> 64 at 240x320 29.0 / 26.6, 128 -> 128 at 1080p bfloat16, 10 % 457 / 455.  (Without claims, whose answer a workgroup waits for: 11.0, 41.1, 21.5, 30.6, 26.4, 451.5.)
 template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false>
 __global__ __launch_bounds__((PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS)
 void detect_extract_kernel(const DetectArgs<T> a)
@@ -744,7 +744,7 @@ __global__ __launch_bounds__(256) void shadow_rebuild_kernel(const T* __restrict
 // The extraction inside the launch of detection, by workgroups of nt threads: words of the dilated map per wavefront (0: it takes a launch
 // of its own).  The part of the map under one workgroup's words fits its LDS, and the workgroups that wait are at most a quarter of a whole chip's wavefronts: what
 // they wait for runs beside them (that it is ever done does not depend on that, cb_claim.h).  Few words a wavefront spread the expansion of dense words and shorten the polls, many workgroups add up more
-// counts and poll for more of each other's rows.  Frames, us, 16 / 32 / 64 words: 3 -> 16, 7x7, 1080p (507, 254, 127 workgroups) 36.3 / 32.0 / 30.4;
+// counts and poll for more of each other's rows.  Frames, us (without claims), 16 / 32 / 64 words: 3 -> 16, 7x7, 1080p (507, 254, 127 workgroups) 36.3 / 32.0 / 30.4;
 // 3 -> 16 at 720p (225, 113, 57) 18.2 / 16.8 / 16.9; 3 -> 16 at 240x320 (19, 10, 5) 13.1 / 13.4 / 14.1; 64 -> 32 at 120x160 14.8 / 15.0 / 15.9; 64 -> 64 at
 // 480x640, 20 % (38, 19, 10) 81.5 / 82.2 / 84.8; 128 -> 64 at 46x82, bfloat16 (2, 1, 1) 16.4 / 15.6 / 16.1.
 int extract_words(const Geom& g, int nt)

@@ -116,6 +116,8 @@ __device__ __forceinline__ void st_out4(uint16_t* p, const float (&v)[4])
 // Workspace of the channel-last kernel for layers that divide K (fused_cl_splits): partial sums (may be absent: bytes = 0) and a count per
 // tile, zero between launches.
 struct ClWork { float* ws = nullptr; unsigned bytes = 0; int* count = nullptr; };
+// Layers with long filters, whose rows are divided among the XCDs.  As with the list beside the product (fused_takes_job) only where the shadow's channels are a
+// power of two: for other counts each of these forms would be another row of instances, whose scalar registers spill without them already.
 bool fused_cl_far(const Geom& g);
 bool fused_cl_splits(const Geom& g);        // ... of which those with very long ones divide K
 constexpr size_t CL_WORK_BYTES = (size_t)16 << 20, CL_COUNT_BYTES = 4096;
