@@ -9,8 +9,8 @@
 // in the tap of the stage's first value, dt taps on, or one further (cl_piece; two compares and adds a stage more).
 //   B operand: a thread fetches 16-byte pieces of a column (consecutive lanes: consecutive pieces) and stores them to
 //     LDS, [column][k], column pitch 4 mod 32 words (128 float32 columns: 20), so that the 16-byte fragment reads of eight
-//     neighbouring columns cover all 32 banks.  Two stage buffers alternate; stage u+1 is stored and a later one requested ahead of
-//     the MFMAs of stage u, one barrier per stage.  Narrow tiles, whose MFMAs are short, take long stages (the same
+//     neighbouring columns cover all 32 banks.  Two stage buffers alternate; stage u+1 is stored and a later one requested between
+//     the MFMAs of stage u (SPREAD) or ahead of them, one barrier per stage.  Narrow tiles, whose MFMAs are short, take long stages (the same
 //     number of loads in flight whatever the tile width) and keep two of them in flight (GD).
 //   A operand: packed in MFMA fragment order at layer creation, read from L2 into a ring of D groups of registers,
 //     refilled as soon as a group's MFMAs are issued.
@@ -205,6 +205,13 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     constexpr unsigned PLANE = UKG * 64u;        // bytes of one term of a column
     // the largest tile has no registers for what can be fetched when it is used: the next tile's pixels, the bias, a longer ring
     constexpr bool LEAN = TM * TN > 8;
+    // Column fragments of a wavefront and stage, and how many of them are in registers.  SPREAD: the next stages' pieces are passed on between the products of
+    // this one.  A narrow tile has one or two wavefronts on a SIMD, and what one does not overlap itself is not overlapped: with one fragment ahead and
+    // everything else in front of the products a k-group of 64 x 32 bfloat16 tiles took 210 cycles, for 32 of matrix instructions and 96 of L1, whether its loads
+    // hit or missed.  Frames, us, before / now: 512 -> 512 3x3 46x82 10 % bfloat16 42.4 / 39.5, 256 -> 256 3x3 92x164 30.2 / 29.2, bfloat16 10 % 28.1 / 26.9, 32 -> 32 9x9 at
+    // 240x320 29.9 / 28.6, a full update of 256 -> 256 92x164 107.0 / 102.5.  Wider bfloat16 tiles have the wavefronts and not the registers (128 x 128 spread: 458 / 544).
+    constexpr bool SPREAD = F32 ? TM * TN <= (P2 ? 8 : 4) : TM * TN <= 2 && WGK == 1;
+    constexpr int NF = UKW * TN, BR = !F32 && SPREAD ? 4 : 2;
     constexpr bool TWO = TM * TN < 4 || (SPLIT && F32 && TM * TN == 4);     // second accumulator chain where a wavefront has few tiles (errors: cl_least_parts)
     extern __shared__ uint4 dyn_lds4[];          // two stage buffers, then the listed pixel of every column
     char* const Bs = reinterpret_cast<char*>(dyn_lds4);
@@ -282,7 +289,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
         // per column: which filter rows and columns lie inside the image (all clear for a column without a pixel), and the
         // byte offset of the top-left tap's channel cl in the shadow (it may wrap below zero at the border: only
         // taps inside are fetched, and for those the sum is a valid offset again)
-        unsigned okr[NP], okc[NP], base[NP];
+        unsigned outr[NP], outc[NP], base[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const bool colv = q[p] >= 0;
@@ -290,42 +297,39 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             const int yo = cl_row(div, qq, g.Wo);
             const int xo = qq - yo * g.Wo;
             const int y0 = yo * g.s - g.p, x0 = xo * g.s - g.p;
-            okr[p] = colv ? taps_within(y0, g.kh, g.H) : 0u;
-            okc[p] = taps_within(x0, g.kw, g.W);
+            outr[p] = ~(colv ? taps_within(y0, g.kh, g.H) : 0u);
+            outc[p] = ~taps_within(x0, g.kw, g.W);
             base[p] = (pixels((unsigned)(y0 * g.W + x0)) + (unsigned)cl) * ESZ;
         }
 
         uint4 breg[GD][NP];
-        auto gload = [&](int u, uint4 (&dst)[NP]) {
+        // stage u's piece of every column: its filter row and column, its offset
+        struct Piece { unsigned j, i, off; };
+        auto piece_of = [&](int u) {
             const unsigned kb = (unsigned)(SPLIT ? u0 + u : u) * (unsigned)UK;
             unsigned tap, coff;                  // the piece's tap, its channel less cl
             if constexpr (P2) { tap = (kb >> lc) + (unsigned)dt; coff = kb & (unsigned)(g.Cs - 1); }
             else cl_piece(div, (unsigned)g.Cs, kb, (unsigned)dt, (unsigned)cl, tap, coff);
             const unsigned j = (tap * div.inv_kw) >> 16, i = tap - j * (unsigned)g.kw;
-            const unsigned toff = (pixels(j * (unsigned)g.W + i) + coff) * ESZ;
-            // (rows that pad K have j >= kh, whose bit is clear, as bit 31 is for any j beyond it: kh, kw <= 31)
-            const unsigned jj = j < 31u ? j : 31u;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const bool in = (((okr[p] >> jj) & (okc[p] >> i)) & 1u) != 0u;
-                dst[p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                    srsrc, (int)(in ? base[p] + toff : NOWHERE), 0, 0));
-            }
+            // (rows that pad K have j >= kh, whose bit is set, as bit 31 is for any j beyond it: kh, kw <= 31)
+            return Piece{j < 31u ? j : 31u, i, (pixels(j * (unsigned)g.W + i) + coff) * ESZ};
         };
-        auto lds_store = [&](int buf, const uint4 (&v)[NP]) {
+        // (all ones for a tap outside the image: the offset is NOWHERE then, base and off are multiples of 16)
+        auto gload = [&](const Piece& w, int p) {
+            const unsigned out = (unsigned)(__builtin_amdgcn_sbfe((int)outr[p], w.j, 1u) | __builtin_amdgcn_sbfe((int)outc[p], w.i, 1u));
+            return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(srsrc, (int)((out & NOWHERE) | (base[p] + w.off)), 0, 0));
+        };
+        auto lds_store = [&](int buf, int p, const uint4& v) {
             char* dst = Bs + buf * BUF + gc * PITCH + (F32 ? 8 : 16) * ch;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                if constexpr (F32) {
-                    uint2 h, m, l;
-                    split2(__uint_as_float(v[p].x), __uint_as_float(v[p].y), h.x, m.x, l.x);
-                    split2(__uint_as_float(v[p].z), __uint_as_float(v[p].w), h.y, m.y, l.y);
-                    *reinterpret_cast<uint2*>(dst + CPP * p * PITCH) = h;
-                    *reinterpret_cast<uint2*>(dst + CPP * p * PITCH + PLANE) = m;
-                    *reinterpret_cast<uint2*>(dst + CPP * p * PITCH + 2 * PLANE) = l;
-                } else
-                    *reinterpret_cast<uint4*>(dst + CPP * p * PITCH) = v[p];
-            }
+            if constexpr (F32) {
+                uint2 h, m, l;
+                split2(__uint_as_float(v.x), __uint_as_float(v.y), h.x, m.x, l.x);
+                split2(__uint_as_float(v.z), __uint_as_float(v.w), h.y, m.y, l.y);
+                *reinterpret_cast<uint2*>(dst + CPP * p * PITCH) = h;
+                *reinterpret_cast<uint2*>(dst + CPP * p * PITCH + PLANE) = m;
+                *reinterpret_cast<uint2*>(dst + CPP * p * PITCH + 2 * PLANE) = l;
+            } else
+                *reinterpret_cast<uint4*>(dst + CPP * p * PITCH) = v;
         };
 
         floatx4 acc[TM][TN], acc1[TM][TN];         // (acc1: unused unless TWO)
@@ -339,9 +343,14 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 
         // (the loads in flight at the stage loop's entry are in the order of those in flight at its back edge: where
         // the two differ the compiler waits for the longer of the two queues)
-        gload(0, breg[0]);
+        auto gather = [&](int u, uint4 (&dst)[NP]) {
+            const Piece w = piece_of(u);
+#pragma unroll
+            for (int p = 0; p < NP; ++p) dst[p] = gload(w, p);
+        };
+        gather(0, breg[0]);
         if constexpr (GD == 2) {
-            gload(1, breg[1]);
+            gather(1, breg[1]);
 #pragma unroll
             for (int s = 0; s < D; ++s) aload((SPLIT ? u0 * UKG : 0) + s * WGK + wk, areg[s]);
         }
@@ -358,8 +367,9 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 #pragma unroll
             for (int p = 0; p < NP; ++p) qs[gc + CPP * p] = q[p];
         }
-        lds_store(0, breg[0]);
-        gload(GD, breg[0]);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) lds_store(0, p, breg[0][p]);
+        gather(GD, breg[0]);
         if constexpr (GD == 1) {
 #pragma unroll
             for (int s = 0; s < D; ++s) aload((SPLIT ? u0 * UKG : 0) + s * WGK + wk, areg[s]);
@@ -373,34 +383,46 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             constexpr int SI = decltype(si)::value;
             constexpr int S0 = SI * UKW % D;      // ring slot of the stage's first k-group
             const int cur = u & 1;
-            // stage u+1 goes into the buffer that stage u-1 was read from; stage u+1+GD is requested
-            if (u + 1 < nunits) lds_store(cur ^ 1, breg[(SI + 1) % GD]);
-            gload(u + 1 + GD, breg[(SI + 1) % GD]);
-            // (left to itself the compiler sinks these loads to the end of the stage)
-            __builtin_amdgcn_sched_barrier(0);
             const char* const Bu = Bw + cur * BUF;
-            // the fragment of the next column tile is requested ahead of the MFMAs of this one
-            uint4 bfr[2][TERMS];
-            auto bload = [&](int kgi, int b, uint4 (&dst)[TERMS]) {
+            // ring of column fragments, f = kgi * TN + b (those of k-groups behind the last are read, and not used)
+            uint4 bfr[BR][TERMS];
+            auto bload = [&](int f) {
 #pragma unroll
-                for (int e = 0; e < TERMS; ++e) dst[e] = *reinterpret_cast<const uint4*>(Bu + b * 16 * PITCH + e * PLANE + (kgi * WGK + wk) * 64);
+                for (int e = 0; e < TERMS; ++e)
+                    bfr[f % BR][e] = *reinterpret_cast<const uint4*>(Bu + (f % TN) * 16 * PITCH + e * PLANE + (f / TN * WGK + wk) * 64);
             };
-            bload(0, 0, bfr[0]);
+#pragma unroll
+            for (int f = 0; f + 1 < BR && f < NF; ++f) bload(f);
+            // stage u+1 goes into the buffer that stage u-1 was read from; stage u+1+GD is requested: piece by piece between the products
+            const Piece w = piece_of(u + 1 + GD);
+            auto pass_on = [&](int p) {
+                if (u + 1 < nunits) lds_store(cur ^ 1, p, breg[(SI + 1) % GD][p]);
+                breg[(SI + 1) % GD][p] = gload(w, p);
+            };
+            if constexpr (!SPREAD) {
+                if (u + 1 < nunits) {
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) lds_store(cur ^ 1, p, breg[(SI + 1) % GD][p]);
+                }
+#pragma unroll
+                for (int p = 0; p < NP; ++p) breg[(SI + 1) % GD][p] = gload(w, p);
+            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int kgi = 0; kgi < UKW; ++kgi) {
                 const int kg = (SPLIT ? u0 + u : u) * UKG + kgi * WGK + wk;
-                if ((WGK > 1 || kgi > 0) && kg >= nkg) break;        // the last stage may be short
+                // the last stage may be short (whole pairs / fours of k-groups)
+                if ((WGK > 1 || (kgi > 0 && kgi % (F32 ? 2 : 4) == 0)) && kg >= nkg) break;
                 uint4 (&af)[TM][TERMS] = areg[(S0 + kgi) % D];
 #pragma unroll
                 for (int b = 0; b < TN; ++b) {
-                    const int cb_ = (kgi * TN + b) & 1;
-                    if (b + 1 < TN) bload(kgi, b + 1, bfr[cb_ ^ 1]);
-                    else if (kgi + 1 < UKW) bload(kgi + 1, 0, bfr[cb_ ^ 1]);
+                    const int f = kgi * TN + b;
+                    if (f + BR - 1 < NF) bload(f + BR - 1);
                     auto mul = [&](int ea, int eb, floatx4 (&d)[TM][TN]) {
 #pragma unroll
                         for (int a = 0; a < TM; ++a)
                             d[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[a][ea]),
-                                                                              __builtin_bit_cast(bf16x8, bfr[cb_][eb]), d[a][b], 0, 0, 0);
+                                                                              __builtin_bit_cast(bf16x8, bfr[f % BR][eb]), d[a][b], 0, 0, 0);
                     };
                     if constexpr (F32) {
                         // smallest terms first; a chain of their own where a wavefront has few tiles
@@ -409,6 +431,11 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                         mul(0, 0, acc);
                     } else
                         mul(0, 0, TWO && (kgi & 1) ? acc1 : acc);
+                    if constexpr (SPREAD) {
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+                            if (p * NF / NP == f) pass_on(p);
+                    }
                 }
                 aload(kg + D * WGK, af);
                 __builtin_amdgcn_sched_barrier(0);
