@@ -40,7 +40,13 @@ template <typename MEM, typename W, typename D> CB_HD unsigned claim_block(MEM&&
 // ... if somebody has it: true if the frame is over
 template <typename MEM, typename D> CB_HD bool claim_lost(MEM&& mem, D* done, int extracting) { return mem.add(done, -CLAIM_TAKEN) == extracting + CLAIM_TAKEN; }
 // an extracting workgroup is through: true if the frame is over
-template <typename MEM, typename D> CB_HD bool extraction_done(MEM&& mem, D* done, int extracting) { return mem.add(done, 1) == extracting - 1; }
+CB_HD constexpr bool extraction_last(int before, int extracting) { return before == extracting - 1; }
+template <typename MEM, typename D> CB_HD bool extraction_done(MEM&& mem, D* done, int extracting) { return extraction_last(mem.add(done, 1), extracting); }
+
+// Row of word `it` of a map of w words a row, with inv = map_row_inv(w): exact while it * w < 2^31.  (Maps that are extracted in the launch of detection have at most 2^17
+// words, and rows of at most 2^11.)
+inline unsigned map_row_inv(unsigned w) { return (0x80000000u + w - 1u) / w; }
+CB_HD unsigned map_row(unsigned it, unsigned inv) { return (unsigned)(((unsigned long long)it * inv) >> 31); }
 
 // The number of an extracting workgroup, in the order in which they begin: it waits, without a limit, for what those with lower numbers publish, and each publishes
 // before it waits for any of them.

@@ -587,7 +587,7 @@ void detect_extract_kernel(const DetectArgs<T> a)
         [&](bool limited) {
             const int frame = a.ctl[CTL_FRAME];
             if (limited) {
-                bid = begin_extraction(a.ctl, s_word);
+                bid = begin_extraction(a.ctl, job.nblk, s_word);
                 if (threadIdx.x == 0) epoch = (unsigned)a.ctl[CTL_EPOCH];
                 clear_other_map(a.mbits0, a.ctl, frame & 1, job.clear_words, bid * NT + (int)threadIdx.x, job.nblk * NT);
             }
@@ -767,6 +767,7 @@ void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int C
     const unsigned per = (unsigned)Cs * (unsigned)sizeof(T) / 16u, inv_per = per ? ((1u << 20) + per - 1u) / per : 0u;
     // (job->nblk stays 0 where the extraction takes a launch of its own)
     if (job && (job->per = extract_words(job->g, PL * CS)) > 0) job->nblk = (job->g.Ho * job->g.WWo - 1) / (PL * CS / 64 * job->per) + 1;
+    if (job) job->inv_wwo = map_row_inv((unsigned)job->g.WWo);
     if (job && job->ahead) job->ahead = job->nblk;
     if (job) job->nclaims = CS > 1 ? (int)grid : (P + 64 * VEC - 1) / (64 * VEC);
 #define CB_REG(sh, shadow)                                                                                                          \
@@ -1073,7 +1074,7 @@ __global__ __launch_bounds__(CS * PLC) void detect_listed_extract_kernel(const L
             const ListedArgs<T> r = launch_arguments<ListedArgs<T>>();
             const int par = r.ctl[CTL_FRAME] & 1;
             if (limited) {
-                bid = begin_extraction(r.ctl, s_word);
+                bid = begin_extraction(r.ctl, r.job.nblk, s_word);
                 if (threadIdx.x == 0) epoch = (unsigned)r.ctl[CTL_EPOCH];
                 clear_other_map(r.mbits0, r.ctl, par, r.job.clear_words, bid * NT + (int)threadIdx.x, r.job.nblk * NT);
             }
@@ -1109,6 +1110,7 @@ hipError_t launch_listed_t(const Geom& g, const T* x, T* S, T* S2, uint64_t* mbi
         const unsigned grid = (unsigned)std::min(LISTED_BLOCKS, (cand_cap + PLC - 1) / PLC);
         const bool sh = S2 != nullptr && g.C >= 16 && (g.C & (g.C - 1)) == 0;
         if (job && (job->per = extract_words(job->g, CS * PLC)) > 0) job->nblk = (job->g.Ho * job->g.WWo - 1) / (CS * PLC / 64 * job->per) + 1;
+        if (job) job->inv_wwo = map_row_inv((unsigned)job->g.WWo);
         if (job && job->ahead) job->ahead = job->nblk;
         if (job) job->nclaims = (int)grid;
 #define CB_LISTED(SH)                                                                                                            \

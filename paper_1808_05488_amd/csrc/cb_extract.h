@@ -107,6 +107,69 @@ __device__ __forceinline__ uint64_t fires_rows(const Geom& g, const WORDS& words
     return lo;
 }
 
+// The same from the part of a map that is staged in LDS (its first bit: first_bit), for whole wavefronts: 2^share groups of 64 >> share lanes hold the same outputs,
+// each takes every 2^share-th filter row from `group` on, and all have the result.  32-bit windows over single words of the map; a window is at most
+// 64 + 30 columns.  (fires_rows there: 1.0 us with 3 rows, 1.6 with 9, of which most is the arithmetic of a lone wavefront.)
+__device__ __forceinline__ uint64_t fires_shared(const Geom& g, const uint64_t* lds, unsigned first_bit, int y0, int x0, int share, int group)
+{
+    const uint32_t* const map = reinterpret_cast<const uint32_t*>(lds);
+    int a = x0 > 0 ? x0 : 0;
+    const int pre = a - x0, len = g.W - a;
+    if (a > g.W - 1) a = g.W - 1;                      // keep the address inside the row; len <= 0 masks it
+    uint32_t r0 = 0, r1 = 0, r2 = 0;
+    for (int j0 = 0; j0 < g.kh; j0 += 2 << share) {
+        uint32_t v[2][4];
+        unsigned sh[2];
+        bool in[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int j = j0 + group + (u << share), yi = y0 + j;
+            in[u] = j < g.kh && yi >= 0 && yi < g.H;
+            const int yr = y0 + (j < g.kh ? j : g.kh - 1), yc = yr < 0 ? 0 : (yr >= g.H ? g.H - 1 : yr);
+            const unsigned bit = (unsigned)yc * (unsigned)g.W + (unsigned)a - first_bit;
+            sh[u] = bit & 31u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[u][k] = map[(bit >> 5) + k];
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t on = in[u] ? ~0u : 0u;
+            r0 |= __builtin_amdgcn_alignbit(v[u][1], v[u][0], sh[u]) & on;
+            r1 |= __builtin_amdgcn_alignbit(v[u][2], v[u][1], sh[u]) & on;
+            r2 |= __builtin_amdgcn_alignbit(v[u][3], v[u][2], sh[u]) & on;
+        }
+    }
+    auto both = [](auto p) { return p[0] | p[1]; };
+    if (share >= 1) {
+        r0 = both(__builtin_amdgcn_permlane32_swap(r0, r0, false, false));
+        r1 = both(__builtin_amdgcn_permlane32_swap(r1, r1, false, false));
+        r2 = both(__builtin_amdgcn_permlane32_swap(r2, r2, false, false));
+    }
+    if (share >= 2) {
+        r0 = both(__builtin_amdgcn_permlane16_swap(r0, r0, false, false));
+        r1 = both(__builtin_amdgcn_permlane16_swap(r1, r1, false, false));
+        r2 = both(__builtin_amdgcn_permlane16_swap(r2, r2, false, false));
+    }
+    auto first_bits = [](int n) { return n >= 32 ? ~0u : n > 0 ? (1u << n) - 1u : 0u; };
+    r0 &= first_bits(len);
+    r1 &= first_bits(len - 32);
+    r2 &= first_bits(len - 64);
+    if (pre) {                                         // at most pad <= 31 columns
+        r2 = __builtin_amdgcn_alignbit(r2, r1, 32 - pre);
+        r1 = __builtin_amdgcn_alignbit(r1, r0, 32 - pre);
+        r0 <<= pre;
+    }
+    auto or_shifted = [&](int n) {
+        r0 |= __builtin_amdgcn_alignbit(r1, r0, n);
+        r1 |= __builtin_amdgcn_alignbit(r2, r1, n);
+        r2 |= r2 >> n;
+    };
+    int n = 1;                                         // bit q holds columns q .. q + n - 1
+    while (2 * n <= g.kw) { or_shifted(n); n *= 2; }
+    if (n < g.kw) or_shifted(g.kw - n);
+    return (uint64_t)r1 << 32 | r0;
+}
+
 template <typename WORDS>
 __device__ __forceinline__ uint64_t fires64(const Geom& g, const WORDS& words, long pitch, int y0, int x0)
 {
@@ -235,18 +298,18 @@ __device__ __forceinline__ void expand_words(uint64_t word, int off, int pixbase
         return;
     }
     uint64_t nz = __ballot(word != 0);
-    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     while (nz) {
         // (nz comes from a ballot, so src is the same in every lane: plain lane reads into scalar registers,
-        // not the cross-lane permutes of a general shuffle, which cost an LDS round trip each)
+        // not the cross-lane permutes of a general shuffle, which cost an LDS round trip each; the word is the mask of the
+        // lanes that store, and what precedes a lane's bit two instructions)
         const int src = __ffsll((long long)nz) - 1;
         nz &= nz - 1;
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, src);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), src);
-        const uint64_t wsrc = ((uint64_t)hi << 32) | lo;
         const int o = __builtin_amdgcn_readlane(off, src);
         const int pb = __builtin_amdgcn_readlane(pixbase, src);
-        if ((wsrc >> lane) & 1ull) idx[o + __popcll(wsrc & below)] = pb + lane;
+        const int at = (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, (unsigned)o));
+        if (__builtin_amdgcn_inverse_ballot_w64(((uint64_t)hi << 32) | lo)) idx[at] = pb + lane;
     }
 }
 
@@ -301,6 +364,11 @@ struct DeviceMem {
         asm volatile("" : "+v"(old) :: "memory");            // it has returned
         return old;
     }
+};
+
+// ... whose answer is waited for where it is used
+struct DeviceMemLater {
+    __device__ __forceinline__ int add(int* p, int v) const { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 };
 
 // The second half of the single-pass extraction, for workgroup bid of nblk: scan over the workgroups' words and index write.
@@ -360,9 +428,11 @@ __device__ __forceinline__ void one_pass_tail(uint64_t word, int pixbase, unsign
     off += inc - cnt;                                        // exclusive offset of this thread's word
     if (bid == nblk - 1 && tid == 64 * NW - 1) ctl[CTL_COUNT] = off + cnt;
 
+    // (what ends the frame reads nothing of the list: the answer, a round trip of 0.8 us, is on its way beside the list's stores)
+    int through = 0;
+    if (tid == 0) through = DeviceMemLater().add(&ctl[CTL_DONE], 1);
     expand_words<false>(word, off, pixbase, idx, lane);
-
-    if (tid == 0 && extraction_done(DeviceMem(), &ctl[CTL_DONE], nblk)) finish_frame(ctl, epoch, own_map, arrivals);
+    if (tid == 0 && extraction_last(through, nblk)) finish_frame(ctl, epoch, own_map, arrivals);
 }
 
 // Word wi (row-padded) of the 2 x 2 pooled map of a producer's row-padded dilated map: OR over the windows, border windows clipped.
@@ -474,8 +544,8 @@ __device__ __forceinline__ bool stage_own_block(const DetectJob& job, int bid, u
     // The input rows under this workgroup's words, and those between them and the next workgroup's, so that together the workgroups wait for
     // every word: then all that detect have read the frame count and the last count of listed pixels, which the tail overwrites.
     const int last = (it0 + ipb < items ? it0 + ipb : items) - 1;
-    int r0 = (it0 / g.WWo) * g.s - g.p, r1 = (last / g.WWo) * g.s - g.p + g.kh - 1;
-    const int next = last + 1 < items ? (last + 1) / g.WWo * g.s - g.p - 1 : g.H - 1;
+    int r0 = (int)map_row((unsigned)it0, job.inv_wwo) * g.s - g.p, r1 = (int)map_row((unsigned)last, job.inv_wwo) * g.s - g.p + g.kh - 1;
+    const int next = last + 1 < items ? (int)map_row((unsigned)last + 1u, job.inv_wwo) * g.s - g.p - 1 : g.H - 1;
     r1 = r1 > next ? r1 : next;
     r0 = r0 < 0 ? 0 : (r0 > g.H - 1 ? g.H - 1 : r0);
     r1 = r1 < 0 ? 0 : (r1 > g.H - 1 ? g.H - 1 : r1);
@@ -501,27 +571,28 @@ __device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __r
     const Geom& g = job.g;
     const int tid = threadIdx.x, lane = tid & 63, items = g.Ho * g.WWo;
     const int ipb = NT / 64 * job.per, it0 = bid * ipb;
-    const int it = lane < job.per ? it0 + (tid >> 6) * job.per + lane : items;
-    int r0 = (it0 / g.WWo) * g.s - g.p;                                  // (as in stage_own_block)
+    // lanes of one word: 64 / per, with a part of the filter's rows each; the first of them holds it
+    const int lper = 31 - __builtin_clz((unsigned)job.per), last = (it0 + ipb < items ? it0 + ipb : items) - 1;
+    const int it = it0 + (tid >> 6) * job.per + (lane & (job.per - 1)), at = it < last ? it : last;
+    const bool mine = lane < job.per && it < items;
+    int r0 = (int)map_row((unsigned)it0, job.inv_wwo) * g.s - g.p;       // (as in stage_own_block)
     r0 = r0 < 0 ? 0 : (r0 > g.H - 1 ? g.H - 1 : r0);
-    const long first = ((long)r0 * g.W) >> 6;
-    const int yo = it / g.WWo, wo = it - yo * g.WWo;
+    const unsigned first_bit = (unsigned)r0 * (unsigned)g.W & ~63u;
+    const int yo = (int)map_row((unsigned)at, job.inv_wwo), wo = at - yo * g.WWo;
     uint64_t word = 0;
-    int pixbase = 0;
-    if (it < items) {
-        if (job.full) word = full_word(g, it);
-        else {
-            const int nvalid = g.Wo - 64 * wo < 64 ? g.Wo - 64 * wo : 64;
+    if (job.full) word = full_word(g, at);
+    else {
+        const int nvalid = g.Wo - 64 * wo < 64 ? g.Wo - 64 * wo : 64;
 #pragma unroll 1
-            for (int t = 0; t < g.s && 32 * t < nvalid; ++t) {
-                const uint64_t f = fires_rows<2>(g, MapInLds{lds, first}, g.W, yo * g.s - g.p, 64 * wo * g.s - g.p + 64 * t);
-                word |= g.s == 1 ? f : even_bits(f) << (32 * t);
-            }
-            word &= nvalid == 64 ? ~0ull : ((1ull << nvalid) - 1ull);
+        for (int t = 0; t < g.s; ++t) {                                  // (the second half of a word beyond the map is masked)
+            const uint64_t f = fires_shared(g, lds, first_bit, yo * g.s - g.p, 64 * wo * g.s - g.p + 64 * t, 6 - lper, lane >> lper);
+            word |= g.s == 1 ? f : even_bits(f) << (32 * t);
         }
-        job.mt_bits[it] = word;
-        pixbase = yo * g.Wo + 64 * wo;
+        word &= nvalid == 64 ? ~0ull : ((1ull << nvalid) - 1ull);
     }
+    if (!mine) word = 0;
+    else job.mt_bits[it] = word;
+    const int pixbase = yo * g.Wo + 64 * wo;
     one_pass_tail<NT / 64, false>(word, pixbase, epoch_ld, job.idx, ctl, job.look, 1, bid, job.nblk, 0, small, [](int) {}, arrivals);
 }
 
@@ -567,8 +638,9 @@ __device__ __forceinline__ Role role_of(const DetectJob& job)
     return Role{own < 0 || own >= n, own, n};
 }
 // An extracting workgroup begins: its number.  s_word: a word of LDS of its own.
-__device__ __forceinline__ int begin_extraction(int* ctl, unsigned* s_word)
+__device__ __forceinline__ int begin_extraction(int* ctl, int nblk, unsigned* s_word)
 {
+    if (nblk == 1) return 0;                     // (without the round trip)
     if (threadIdx.x == 0) *s_word = (unsigned)extraction_number(DeviceMem(), &ctl[CTL_BEGUN]);
     __syncthreads();
     const int bid = (int)__builtin_amdgcn_readfirstlane(*s_word);

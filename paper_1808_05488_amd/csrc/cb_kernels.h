@@ -86,6 +86,7 @@ bool extract_fits(const Geom& consumer);
 struct DetectJob {
     Geom g;
     int nblk = 0, per = 0, full = 0, clear_words = 0;
+    unsigned inv_wwo = 0;                  // map_row_inv(g.WWo)
     int patience = 0;                      // polls of a workgroup that waits before it detects what no workgroup has begun
     int ahead = 0;                         // for tests: extracting workgroups numbered before those that detect, of which those of large maps have not all begun then
     int nclaims = 0;                       // blocks of detection that are claimed (cb_claim.h)
