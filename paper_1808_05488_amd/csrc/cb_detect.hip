@@ -938,33 +938,37 @@ __device__ __forceinline__ void detect_listed_block(const T* __restrict__ x, T* 
         if (SH && g == 0) s_q[SH ? buf : 0][SH ? pl : 0] = (valid && (fired || (flags & DET_COPY_ALL))) ? q : -1;
         __syncthreads();                          // sflag is rewritten in the next round
         auto set_bits = [&]() {
-            // lanes 0..PLC-1 of the first wavefront.  Neighbouring candidates mostly fall into the same
-            // 32-pixel word of the map: their bits are combined (segmented OR over runs of lanes with
-            // equal word index) and the last lane of each run issues ONE atomic for the run -- a
-            // few thousand atomics on a few hundred words otherwise queue up behind each other.
-            const bool set = valid && fired;
-            unsigned bits = set ? 1u << (q & 31) : 0u;
-            const int word = set ? q >> 5 : -1 - pl;          // lanes without a bit never match a neighbour
-#pragma unroll
-            for (int o = 1; o < PLC; o <<= 1) {
-                const unsigned b = __shfl_up(bits, o);
-                const int w = __shfl_up(word, o);
-                if (pl >= o && w == word) bits |= b;
+            // The first wavefront (PLC lanes of it have a candidate).  Neighbouring candidates mostly fall into the same
+            // 32-pixel word of the map: the bits of a word are combined and set with ONE atomic -- a
+            // few thousand atomics on a few hundred words otherwise queue up behind each other.  (A word at a time with lane reads and data-parallel-primitive moves; a
+            // segmented OR over all lanes takes a dozen shuffles, an LDS round trip each.)
+            const int lane = tid & 63;
+            const bool set = lane < PLC && valid && fired;
+            const unsigned bit = set ? 1u << (q & 31) : 0u;
+            const int word = q >> 5;
+            uint64_t left = __ballot(set);
+            unsigned bits = 0;                                // of the lane-th word
+            int at = 0, words = 0;
+            for (; left && words < 8; ++words) {
+                const int w = __builtin_amdgcn_readlane(word, __builtin_ctzll(left));
+                const bool here = set && word == w;
+                left &= ~__ballot(here);
+                const unsigned all = (unsigned)wave_or(here ? (int)bit : 0);
+                if (lane == words) { bits = all; at = w; }
             }
-            const int wnext = __shfl_down(word, 1);
-            int fresh = 0;
-            if (set && (pl == PLC - 1 || wnext != word)) {
-                const unsigned old = atomicOr(reinterpret_cast<uint32_t*>(mbits + 2 * (word >> 1)) + (word & 1), bits);
-                fresh = __popc(bits & ~old);                  // a pixel reached through several candidates counts once
-            }
-#pragma unroll
-            for (int o = 1; o < PLC; o <<= 1) fresh += __shfl_xor(fresh, o);
+            uint32_t* const map = reinterpret_cast<uint32_t*>(mbits);
+            unsigned old = 0, alone = 0;
+            if (lane < words) old = atomicOr(map + 4 * (at >> 1) + (at & 1), bits);
+            const bool more = (left >> lane) & 1ull;          // (scattered over more words: a pixel each)
+            if (more) alone = atomicOr(map + 4 * (word >> 1) + (word & 1), bit);
             if (ARRIVE && t0 + step >= nc && tid == 0) arrive(ctl, (unsigned)bx);
-            if (pl == 0 && fresh) atomicAdd(nin, fresh);
+            // a pixel reached through several candidates counts once
+            const int fresh = wave_sum(__popc(bits & ~old) + (more && !(alone & bit) ? 1 : 0));
+            if (lane == 0 && fresh) atomicAdd(nin, fresh);
         };
         // State update first: it does not depend on the bit map.  Where extracting workgroups wait for the bits, these go first,
         // and the workgroup arrives as soon as its last are set (behind the state update it would wait for those stores too).
-        if (ARRIVE && g == 0) set_bits();
+        if (ARRIVE && tid < 64) set_bits();
         if (valid && (fired || (flags & DET_COPY_ALL))) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -991,7 +995,7 @@ __device__ __forceinline__ void detect_listed_block(const T* __restrict__ x, T* 
             if (NBUF == 2) buf ^= 1;
             else lds_barrier();
         }
-        if (!ARRIVE && g == 0) set_bits();
+        if (!ARRIVE && tid < 64) set_bits();
     }
 }
 

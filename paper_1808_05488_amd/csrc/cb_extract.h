@@ -281,6 +281,18 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
 // ... and the sum over the wavefront, in every lane: the last lane of that scan
 __device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_inclusive_scan(v), 63); }
 
+// OR over the wavefront, in every lane
+__device__ __forceinline__ int wave_or(int v)
+{
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
 // Index-list entries of the 64 words held by a wavefront (word, its exclusive offset, the
 // pixel index of its bit 0).  PER_LANE = false: the whole wavefront expands one non-empty word
 // at a time (coalesced stores, a handful of cross-lane reads per word) -- the faster form

@@ -1,5 +1,6 @@
 """The words of the dilated map that the extraction beside detection makes, each by one, two or four lanes (csrc/cb_extract.h, fires_shared): filters of 1 to
-31 rows and columns, paddings up to 31, widths around whole and half words, both strides, few and many words a workgroup."""
+31 rows and columns, paddings up to 31, widths around whole and half words, both strides, few and many words a workgroup; and the bits that detection at
+listed pixels sets, for candidates in one word, in as many as are combined, and in more."""
 import numpy as np
 import pytest
 import torch
@@ -36,3 +37,29 @@ def test_dilated_words_and_list(geom):
         ref = torch.nn.functional.max_pool2d(p, (kh, kw), s)[0].numpy() > 0
         assert np.array_equal(mt > 0, ref)
         assert n == ref.sum() and np.array_equal(idx, np.flatnonzero(ref))
+
+
+@pytest.mark.parametrize("channels", [16, 64, 128, 256, 512, 24, 300])
+@pytest.mark.parametrize("apart", [1, 3, 5, 33, 97])
+def test_bits_of_listed_pixels(channels, apart):
+    """Candidates `apart` pixels from each other: all of a wavefront's in one word of 32 pixels, in some, in one each; every second of them fires."""
+    H, W = 43, 97
+    print("listed bits", channels, apart, flush=True)
+    first = cb.Layer(torch.ones((channels, 1, 1, 1), device="cuda"), None, 1, 0, H, W, False)
+    eye = torch.zeros((1, channels, 1, 1), device="cuda")
+    eye[0, 0] = 1
+    layers = [cb.Layer(eye, None, 1, 0, H, W, False) for _ in range(2)]
+    x = torch.zeros((1, H, W), device="cuda")
+    for t in range(4):
+        if t:
+            d = torch.zeros(H * W, device="cuda")
+            d[t::apart] = 0.2
+            d[t::2 * apart] = 1.0
+            x = x + d.view(1, H, W)
+        y = first.process_frame(x, 0.1)
+        layers[0].process_frame_chained(y, first, 0.5)
+        layers[1].process_frame(y, 0.5)
+        for u, v in zip(layers[0].changes_host(), layers[1].changes_host()):
+            assert np.array_equal(u, v), (channels, apart, t)
+        assert layers[0].stats()["n_changed_in"] == layers[1].stats()["n_changed_in"]
+        assert torch.equal(layers[0].state(), layers[1].state())
