@@ -192,7 +192,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     constexpr int PPC = UK / EPV;                // 16-byte pieces of a column in a stage
     constexpr int CPP = 256 / PPC;               // columns one round of loads covers
     constexpr int NP = BN / CPP;                 // loads per thread and stage
-    static_assert(PPC <= 256 && NP * CPP == BN, "pieces come out even");
+    static_assert(PPC <= 64 && NP * CPP == BN, "pieces come out even");
     // k-groups of filter fragments in flight: an L2 latency's worth of MFMAs, as far as the registers go
     constexpr int DMAX = F32 ? (TM == 1 ? 4 : 2)
                           : (TM * TN <= 2 ? 8 : TM * TN <= 8 ? 4 : 2);
@@ -243,16 +243,17 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     const int gc = tid / PPC, ch = tid % PPC;    // first column of this thread, its piece of a stage
     const int dt = P2 ? (EPV * ch) >> lc : (int)cl_tap(div, (unsigned)(EPV * ch)), cl = P2 ? (EPV * ch) & (g.Cs - 1) : EPV * ch - dt * g.Cs;
 
-    int qnext[NP];
-    auto fetch_q = [&](unsigned u, int (&q)[NP]) {
-        const unsigned ntt = xcd0 + (SPLIT ? u / parts : u) / MTX;
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const unsigned n = ntt * BN + gc + CPP * p;
-            q[p] = (u < total && n < (unsigned)N) ? idx[n] : -1;
-        }
+    // Of the NP columns that a column group of lanes fetches, lane ch has the pixel of column ch % NP, and works out what the others need of it (one column after
+    // the other in every lane took 0.3 us a tile)
+    static_assert(PPC >= NP && (NP & (NP - 1)) == 0, "a lane for each column");
+    const int mycol = gc + CPP * (ch & (NP - 1));
+    auto fetch_q = [&](unsigned u) {
+        const unsigned n = (xcd0 + (SPLIT ? u / parts : u) / MTX) * BN + mycol;
+        const int q = idx[n < (unsigned)N ? n : (unsigned)N - 1u];
+        return u < total && n < (unsigned)N ? q : -1;
     };
-    if constexpr (!LEAN) fetch_q(bx >> 3, qnext);
+    int qnext = -1;
+    if constexpr (!LEAN) qnext = fetch_q(bx >> 3);
 
     for (unsigned uq = bx >> 3; uq < total; uq += gx >> 3) {
         const unsigned ut = SPLIT ? uq / parts : uq;
@@ -262,11 +263,9 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
         const unsigned part = SPLIT ? uq % parts : 0u;
         const int u0 = SPLIT ? (int)(part * (unsigned)stages / parts) : 0;
         const int nunits = SPLIT ? (int)((part + 1u) * (unsigned)stages / parts) - u0 : stages;
-        int q[NP];
-#pragma unroll
-        for (int p = 0; p < NP; ++p) q[p] = LEAN ? 0 : qnext[p];
-        if constexpr (LEAN) fetch_q(uq, q);
-        else fetch_q(uq + (gx >> 3), qnext);
+        int q = qnext;
+        if constexpr (LEAN) q = fetch_q(uq);
+        else qnext = fetch_q(uq + (gx >> 3));
         if (nt >= NT || (FAR && (unsigned)mt >= MT)) continue;
         const int m0 = mt * BM;
 
@@ -290,16 +289,20 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
         // byte offset of the top-left tap's channel cl in the shadow (it may wrap below zero at the border: only
         // taps inside are fetched, and for those the sum is a valid offset again)
         unsigned outr[NP], outc[NP], base[NP];
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const bool colv = q[p] >= 0;
-            const int qq = colv ? q[p] : 0;
+        {
+            const bool colv = q >= 0;
+            const int qq = colv ? q : 0;
             const int yo = cl_row(div, qq, g.Wo);
             const int xo = qq - yo * g.Wo;
             const int y0 = yo * g.s - g.p, x0 = xo * g.s - g.p;
-            outr[p] = ~(colv ? taps_within(y0, g.kh, g.H) : 0u);
-            outc[p] = ~taps_within(x0, g.kw, g.W);
-            base[p] = (pixels((unsigned)(y0 * g.W + x0)) + (unsigned)cl) * ESZ;
+            const unsigned r = ~(colv ? taps_within(y0, g.kh, g.H) : 0u), c = ~taps_within(x0, g.kw, g.W), b = pixels((unsigned)(y0 * g.W + x0)) * ESZ;
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const int from = (lane & ~(PPC - 1)) + p;      // (PPC: up to a wavefront)
+                outr[p] = (unsigned)__shfl((int)r, from);
+                outc[p] = (unsigned)__shfl((int)c, from);
+                base[p] = (unsigned)__shfl((int)b, from) + (unsigned)cl * ESZ;
+            }
         }
 
         uint4 breg[GD][NP];
@@ -363,10 +366,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                 bv[a][r] = LEAN ? 0.f : bias[m < g.O ? m : g.O - 1];
             }
         __syncthreads();                          // the previous tile has read its last stage and its qs
-        if (ch == 0) {
-#pragma unroll
-            for (int p = 0; p < NP; ++p) qs[gc + CPP * p] = q[p];
-        }
+        if (ch < NP) qs[mycol] = q;
 #pragma unroll
         for (int p = 0; p < NP; ++p) lds_store(0, p, breg[0][p]);
         gather(GD, breg[0]);
@@ -601,6 +601,18 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     }
 }
 
+// The arguments of a launch, requested at once: left to itself the compiler asks for the count's address, the count, and, once that is known not to be zero, in two
+// or three rounds for the rest.  With this and the pixels worked out by a lane each, frames, us: ten-layer trunk bfloat16 146.8 / 139.5, 64 -> 128 271x435 bfloat16
+// 20.1 / 19.7, 48 -> 96 5x5 stride 2 241x323 26.3 / 25.7, 64 -> 32 240x320 21.1 / 20.2, 16 -> 16 1x1 368x656 15.3 / 14.8.
+template <typename T>
+__device__ __forceinline__ void hold_arguments(const Geom& g, const ClDiv& div, const T* S2, const int32_t* idx, const int* count, const uint4* KF, const float* KT, const float* bias, int relu,
+                                               const T* OUT, const T* OUT2)
+{
+    asm volatile("" :: "s"(count), "s"(idx), "s"(S2), "s"(KF), "s"(bias), "s"(OUT), "s"(OUT2), "s"(relu), "s"(g.O), "s"(g.Cs), "s"(g.kh), "s"(g.kw), "s"(g.s), "s"(g.p), "s"(g.H),
+                 "s"(g.W));
+    asm volatile("" :: "s"(KT), "s"(g.Opad), "s"(g.Wo), "s"(g.P), "s"(g.Po), "s"(g.R), "s"(div.inv_wo), "s"(div.inv_kw), "s"(div.inv_cs));
+}
+
 // Workgroups of a launch.  (A constant: read from the launch's hidden arguments it lies beyond the kernel's own, on a line of its own, and was
 // up to 0.3 us of a launch: ten-layer trunk at 368x656, bfloat16, 155.1 us a frame, 152.3 without it.)
 constexpr unsigned CL_GRID = 1024;
@@ -612,7 +624,8 @@ __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, co
                                              const float* __restrict__ bias, int relu, T* __restrict__ OUT, T* __restrict__ OUT2,
                                              const unsigned bx, const unsigned gx, float* ws, unsigned ws_bytes, int* kcount)
 {
-    const int N = *count;
+    hold_arguments(g, div, S2, idx, count, KF, KT, bias, relu, OUT, OUT2);
+    const int N = *(const __attribute__((address_space(4))) int*)count;       // (a scalar load: nothing of this launch writes it)
     if (N <= 0) return;
     if constexpr (FAR == 2) {
         const unsigned sp = cl_split<sizeof(T) == 4>(N, g.O, ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u, ws_bytes);
