@@ -7,6 +7,7 @@
 // many columns, so the listed pixel is looked up once); the cached output is written
 // only at the listed pixels, all other values keep their bits.
 #include "cb_kernels.h"
+#include "cb_cl_rules.h"
 
 namespace cb {
 
@@ -107,6 +108,72 @@ __global__ __launch_bounds__(256) void update_kernel(int O, int Opad, int R, int
     }
 }
 
+// The common window, 2 x 2: items of 256 listed pixels and OCH channels, the channels of a pixel in a row (which pixels an item has does not depend on their count then).
+// Bound by its chain of loads (count and pixel together, then sixteen values a lane) and, with a pixel-major copy, by the number of its stores: a pixel's OCH
+// channels are one.  32-bit items, rows by reciprocal.  With 64-bit divisions, the pixel asked for behind the count and a store a channel, frames, us, before / now: ten-layer trunk
+// of 3 x 3 filters (three stages) bfloat16 141.2 / 137.6, float32 225 / 222, five-layer net (two) 71.4 / 70.6.  1 024 workgroups: 512 140.0, 4 096 of which most find nothing 143.8.
+template <typename T>
+__global__ __launch_bounds__(256) void pool2_kernel(int O, int Ho, int Wo, int Hp, int Wp, ClDiv div, const T* __restrict__ OUT,
+                                                    const int32_t* __restrict__ idx, const int* __restrict__ count,
+                                                    T* __restrict__ POOL, T* __restrict__ POOL2)
+{
+    const unsigned Po = (unsigned)Ho * (unsigned)Wo, Pp = (unsigned)Hp * (unsigned)Wp;
+    const unsigned och = (unsigned)(O + OCH - 1) / OCH;
+    // (the list has Po entries; those from the count on are stale but readable)
+    auto entry = [&](unsigned t) {
+        const unsigned n = t / och * 256u + threadIdx.x;
+        return idx ? idx[n < Po ? n : Po - 1u] : (int)n;
+    };
+    int q = entry(blockIdx.x);
+    const unsigned N = idx ? (unsigned)*count : Po;
+    for (unsigned t = blockIdx.x; t / och * 256u < N; t += gridDim.x) {
+        const int here = q;
+        q = entry(t + gridDim.x);
+        const unsigned tile = t / och;
+        const int o0 = (int)(t - tile * och) * OCH, on = O - o0 < OCH ? O - o0 : OCH;
+        if (tile * 256u + threadIdx.x >= N) continue;
+        const T* const src = OUT + (size_t)o0 * Po;
+        const int yo = cl_row(div, here, Wo), xo = here - yo * Wo;
+        const int yp = yo >> 1, xp = xo >> 1;
+        // clamped at the border: a clamped tap repeats a value of the window
+        const int ya = yp * 2, yb = ya + 1 < Ho ? ya + 1 : ya, xa = xp * 2, xb = xa + 1 < Wo ? xa + 1 : xa;
+        const unsigned at[4] = {(unsigned)ya * (unsigned)Wo + (unsigned)xa, (unsigned)ya * (unsigned)Wo + (unsigned)xb,
+                                (unsigned)yb * (unsigned)Wo + (unsigned)xa, (unsigned)yb * (unsigned)Wo + (unsigned)xb};
+        T v[OCH][4];
+#pragma unroll
+        for (int j = 0; j < OCH; ++j) {
+            const T* const s = src + (size_t)(j < on ? j : on - 1) * Po;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[j][e] = s[at[e]];
+        }
+        const unsigned cell = (unsigned)yp * (unsigned)Wp + (unsigned)xp;
+        __attribute__((aligned(OCH * sizeof(T)))) T best[OCH];
+#pragma unroll
+        for (int j = 0; j < OCH; ++j) {
+            // same scan order as the general form: the first of equal maxima wins
+            best[j] = v[j][0];
+            float bv = ld_elem(&best[j]);
+#pragma unroll
+            for (int e = 1; e < 4; ++e) {
+                const float cv = ld_elem(&v[j][e]);
+                if (cv > bv) { bv = cv; best[j] = v[j][e]; }
+            }
+            if (j < on) POOL[(size_t)(o0 + j) * Pp + cell] = best[j];
+        }
+        if (POOL2) {
+            T* const d = POOL2 + (size_t)cell * O + o0;
+            if ((O & (OCH - 1)) == 0) {
+                typedef unsigned vec __attribute__((ext_vector_type(OCH * sizeof(T) / 4)));
+                *reinterpret_cast<vec*>(d) = *reinterpret_cast<const vec*>(best);
+            } else {
+#pragma unroll
+                for (int j = 0; j < OCH; ++j)
+                    if (j < on) d[j] = best[j];
+            }
+        }
+    }
+}
+
 // One lane per listed producer pixel: recompute the pooled cell that holds it.
 // Up to w*w listed pixels share a cell and write the same value.
 // idx == null: every producer pixel counts as listed (the whole pooled map is recomputed).
@@ -132,38 +199,6 @@ __global__ __launch_bounds__(256) void pool_kernel(int O, int Ho, int Wo, int w,
         const int y1 = (yp + 1) * w < Ho ? (yp + 1) * w : Ho;
         const int x1 = (xp + 1) * w < Wo ? (xp + 1) * w : Wo;
         const int o1 = (oc + 1) * OCH < O ? (oc + 1) * OCH : O;
-        if (w == 2) {
-            // the common window: all sixteen loads of the item (four channels x 2 x 2, clamped at the
-            // border: a clamped tap repeats a value of the window) are issued before the first compare
-            const int ya = yp * 2, yb = ya + 1 < Ho ? ya + 1 : ya;
-            const int xa = xp * 2, xb = xa + 1 < Wo ? xa + 1 : xa;
-            T v[OCH][4];
-#pragma unroll
-            for (int j = 0; j < OCH; ++j) {
-                const int o = oc * OCH + j < o1 ? oc * OCH + j : o1 - 1;
-                const T* src = OUT + (size_t)o * Ho * Wo;
-                v[j][0] = src[(size_t)ya * Wo + xa];
-                v[j][1] = src[(size_t)ya * Wo + xb];
-                v[j][2] = src[(size_t)yb * Wo + xa];
-                v[j][3] = src[(size_t)yb * Wo + xb];
-            }
-#pragma unroll
-            for (int j = 0; j < OCH; ++j) {
-                const int o = oc * OCH + j;
-                if (o >= o1) break;
-                // same scan order as the general form: the first of equal maxima wins
-                T best = v[j][0];
-                float bv = ld_elem(&best);
-#pragma unroll
-                for (int e = 1; e < 4; ++e) {
-                    const float cv = ld_elem(&v[j][e]);
-                    if (cv > bv) { bv = cv; best = v[j][e]; }
-                }
-                POOL[((size_t)o * Hp + yp) * Wp + xp] = best;
-                if (POOL2) POOL2[((size_t)yp * Wp + xp) * O + o] = best;
-            }
-            continue;
-        }
         for (int o = oc * OCH; o < o1; ++o) {
             const T* src = OUT + (size_t)o * Ho * Wo;
             // maximum taken on the stored bit patterns' values; the winner's bits are copied
@@ -220,6 +255,16 @@ hipError_t launch_pool(int O, int Ho, int Wo, int w, int bf16, const void* OUT, 
                        const int* count, void* POOL, void* POOL2, hipStream_t st)
 {
     const int Hp = (Ho + w - 1) / w, Wp = (Wo + w - 1) / w;
+    if (w == 2) {
+        const long items = (((long)Ho * Wo + 255) / 256) * ((O + OCH - 1) / OCH);
+        const dim3 grid((unsigned)(items < 1024 ? items : 1024));
+        const ClDiv div = cl_div(Wo, Ho, 1);
+        if (bf16)
+            hipLaunchKernelGGL(pool2_kernel<uint16_t>, grid, dim3(256), 0, st, O, Ho, Wo, Hp, Wp, div, (const uint16_t*)OUT, idx, count, (uint16_t*)POOL, (uint16_t*)POOL2);
+        else
+            hipLaunchKernelGGL(pool2_kernel<float>, grid, dim3(256), 0, st, O, Ho, Wo, Hp, Wp, div, (const float*)OUT, idx, count, (float*)POOL, (float*)POOL2);
+        return hipGetLastError();
+    }
     long max_items = (long)(((long)Ho * Wo + 255) / 256) * ((O + OCH - 1) / OCH);
     unsigned grid = (unsigned)(max_items < 2048 ? max_items : 2048);
     if (grid == 0) grid = 1;
