@@ -747,12 +747,14 @@ __global__ __launch_bounds__(256) void shadow_rebuild_kernel(const T* __restrict
 // counts and poll for more of each other's rows.  Frames, us (without claims), 16 / 32 / 64 words: 3 -> 16, 7x7, 1080p (507, 254, 127 workgroups) 36.3 / 32.0 / 30.4;
 // 3 -> 16 at 720p (225, 113, 57) 18.2 / 16.8 / 16.9; 3 -> 16 at 240x320 (19, 10, 5) 13.1 / 13.4 / 14.1; 64 -> 32 at 120x160 14.8 / 15.0 / 15.9; 64 -> 64 at
 // 480x640, 20 % (38, 19, 10) 81.5 / 82.2 / 84.8; 128 -> 64 at 46x82, bfloat16 (2, 1, 1) 16.4 / 15.6 / 16.1.
+// Where one workgroup has them all in any case, 16 a wavefront occupy more of its wavefronts (16 / 32 words): 3 -> 16 at 48x64, 30 % changed, 11.1 / 11.9, 64 -> 64 at 40x60
+// 12.5 / 13.1, 16 -> 16 5x5 at 60x60 11.5 / 12.2, five-layer net at 100x128 87.0 / 89.4.
 int extract_words(const Geom& g, int nt)
 {
     if (g.s > 2) return 0;
     const long items = (long)g.Ho * g.WWo;
     auto blocks = [&](int per) { return (items - 1) / (nt / 64 * per) + 1; };
-    const int per = blocks(16) > 2 && blocks(16) <= 40 ? 16 : blocks(32) <= 80 ? 32 : 64;
+    const int per = blocks(16) == 1 || (blocks(16) > 2 && blocks(16) <= 40) ? 16 : blocks(32) <= 80 ? 32 : 64;
     const long ipb = nt / 64 * per;
     const long rows = std::min<long>((ipb - 1 + g.WWo - 1) / g.WWo * g.s + std::max(g.kh, g.s) + 1 + g.p, g.H);
     return blocks(per) * nt <= 131072 && rows * g.W / 64 + 5 <= MAP_STAGE ? per : 0;
