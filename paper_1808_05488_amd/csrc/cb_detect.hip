@@ -565,7 +565,7 @@ void detect_reg_kernel(const T* __restrict__ x, T* __restrict__ S, T* __restrict
 // Detection with the index extraction in the same launch: the last job.nblk workgroups extract (cb_claim.h).  A launch of its own costs the extraction
 // 4 - 8 us, of which most is the end of one kernel, the start of the next and its first loads from memory.  Frames, us, two launches / one:
 // 3 -> 16 at 48x64 14.4 / 11.1, 64 -> 64 at 480x640 43.0 / 42.0, 64 -> 128 at 271x435 bfloat16 25.8 / 22.0, 3 -> 16 7x7 at 1080p 33.7 / 30.8, feed-forward
-// 64 -> 64 at 240x320 29.0 / 26.6, 128 -> 128 at 1080p bfloat16, 10 % 457 / 455.  (Without claims, whose answer a workgroup waits for: 11.0, 41.1, 21.5, 30.6, 26.4, 451.5.)
+// 64 -> 64 at 240x320 29.0 / 26.6.  (Without claims, whose answer a workgroup waits for: 11.0, 41.1, 21.5, 30.6, 26.4.)
 template <typename T, int VEC, int CS, int CPT, int PLX = 0, bool SH = false>
 __global__ __launch_bounds__((PLX ? PLX : (CS >= 4 ? 64 : 256 / CS)) * CS)
 void detect_extract_kernel(const DetectArgs<T> a)
@@ -768,7 +768,12 @@ void launch_reg(const T* x, T* S, T* S2, uint64_t* mbits, int* ctl, int C, int C
     const unsigned grid = (unsigned)((P + px_per_block - 1) / px_per_block);
     const unsigned per = (unsigned)Cs * (unsigned)sizeof(T) / 16u, inv_per = per ? ((1u << 20) + per - 1u) / per : 0u;
     // (job->nblk stays 0 where the extraction takes a launch of its own)
-    if (job && (job->per = extract_words(job->g, PL * CS)) > 0) job->nblk = (job->g.Ho * job->g.WWo - 1) / (PL * CS / 64 * job->per) + 1;
+    // A workgroup of 16 wavefronts with eight bfloat16 channels a lane has little to load and one other beside it on its compute unit, so that the answer of a claim, waited for by
+    // all of it, is not hidden: from more workgroups on than run at once (512) every round of them pays it.  Frames, us, in one launch / a launch of its own, 0.3 and 10 % changed: 128 -> 64 at
+    // 1080p 208.7 / 183.7 and 381.4 / 358.2, at 720x1280 91.9 / 78.2 and 165.8 / 152.4, at 480x640 40.8 / 37.2 and 60.5 / 56.9; 80 -> 128 at 600x800 44.8 / 37.1 and 72.2 / 65.3; 96 -> 64 at
+    // 360x640 (900 workgroups) 29.3 / 27.3 and 42.5 / 40.8; 128 -> 128 at 1080p 213.3 / 185.8 and 458.3 / 460.2 (as a first frame 442 / 421); one round: 128 -> 64 at 270x480 (507) 22.7 / 22.5 and 31.4 / 32.9.
+    const bool alone = sizeof(T) == 2 && VEC == 4 && CS == 16 && CPT == 8 && grid > 512u;
+    if (job && (job->per = alone ? 0 : extract_words(job->g, PL * CS)) > 0) job->nblk = (job->g.Ho * job->g.WWo - 1) / (PL * CS / 64 * job->per) + 1;
     if (job) job->inv_wwo = map_row_inv((unsigned)job->g.WWo);
     if (job && job->ahead) job->ahead = job->nblk;
     if (job) job->nclaims = CS > 1 ? (int)grid : (P + 64 * VEC - 1) / (64 * VEC);
