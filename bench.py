@@ -33,7 +33,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, published
-SPLIT_MFMA_PEAK_TFLOPS = 2500.0 / 3   # MI355X dense float16 matrix, published; wide tiles of the fused float32 kernel take three float16 products each (narrow ones six bfloat16)
+SPLIT_MFMA_PEAK_TFLOPS = 2500.0 / 6   # MI355X dense bf16 matrix, published; the fused float32 kernel takes six bf16 products each
 
 
 def frame_order(n_frames: int, n_steps: int):

@@ -146,15 +146,11 @@ typedef struct {
  *                  CB_BACKEND_FUSED if it is a power of two, float32 from 16 and
  *                  bfloat16 from 32 on, or up to 4 / 8.  Such layers, and those that gather from a
  *                  producer's pixel-major output, multiply float32 values as six
- *                  bfloat16 products of exact three-term splits or, many listed
- *                  pixels of layers with more than 16 output channels and sums of
- *                  more than 96 products, as three float16 products of two-term
- *                  splits of 22 - 23 bits, accumulated in float32 (relative errors of
- *                  whole layers up to 3.6e-7); their repacked filters take 6 or 10
- *                  bytes a value.  Sums that are not finite, beyond 2^80, or of
- *                  values whose range float16 does not hold where that may matter,
- *                  are computed again with the float32 matrix instruction, which
- *                  costs time where there are many).
+ *                  bfloat16 products of exact three-term splits, accumulated in
+ *                  float32; their repacked filters take 6 bytes a value.  Sums
+ *                  that are not finite or beyond 2^80 are computed again with
+ *                  the float32 matrix instruction, which costs time where there
+ *                  are many).
  *  scratch_bytes : X' and Y' matrices and block counters, 16 MB for partial sums
  *                  of channel-last layers with very long filters; may be shared by
  *                  layers that run on the same stream (Sec. III-B).  This is the

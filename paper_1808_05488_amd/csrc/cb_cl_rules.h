@@ -132,24 +132,6 @@ template <bool F32, int SHAPE, typename FN> CB_HD void cl_tile(int N, int O, int
 #undef CB_COST
 }
 
-// float32 in two float16 terms (cb_fused_cl.h).  Layers whose wide tiles use them: of more than 16 output channels (narrower ones have no such tile) and with
-// sums of more than 96 products.  The two terms hold 22 - 23 bits: relative error of a sum 7.5e-8 whatever its length, where the six bfloat16 products in one chain have
-// 4e-8 - 7e-8 for up to 64 products, 1.0e-7 for 72, 1.6e-7 for 144 and 5e-7 for 1 152.
-CB_HD bool cl_halves(int O, unsigned nkg) { return O > 16 && nkg >= 4u; }
-// The power of two (its biased exponent) in front of a column, from the largest magnitude (float32 bits, without the sign) among the first values of it.  2^8 takes magnitudes from
-// 2^-22 to 2^8 without loss, which is what columns that begin with 2^-14 .. 2^0 or with zeros get; others are moved to 2^8.  (2^112 at most: 2^-14 through it is a normal number.)
-CB_HD unsigned cl_half_scale(unsigned most)
-{
-    const unsigned e = most >> 23;
-    if (most == 0u || (e >= 113u && e < 127u)) return 135u;
-    return e < 23u ? 239u : 262u - e;
-}
-// What a scaled sum has to exceed to be trusted that has n products of which a factor is, scaled, below 2^-14: of such a factor the first term keeps what is above 2^-25,
-// the second what is above 2^-36, and what the first leaves is no longer small beside it.  Lost are, of a pixel, at most 2^-36 times weights up to 2^15 and 2^-25 times their rests up to 2^3;
-// of a weight the same, times pixels up to 2^16 (beyond which they overflow) and rests up to 2^4: 4.5 * 2^-21 in all.  Sixteen times n: less than 2^-22 of the sum, as much as the
-// terms' own rounding.  (n and not the length of the sum: a recomputation keeps its workgroup for tens of us, and one value in 10^7 is that small by chance.)
-CB_HD float cl_half_doubt(unsigned n) { return 16.f * (float)n; }
-
 // Size of a packed filter matrix of nkg k-groups (bfloat16 64 bytes a group and row, float32 three such terms), and from which on its rows
 // are divided among the XCDs
 CB_HD unsigned cl_filter_kb(int O, unsigned nkg, bool f32) { return ((unsigned)O * nkg >> 4) * (f32 ? 3u : 1u); }

@@ -158,9 +158,8 @@ size_t fused_pack_bytes(const Geom& g, bool channel_last)
     const size_t Rpad = g.bf16 ? (Rs + 127) / 128 * 128 : (Rs + KC - 1) / KC * KC;
     const size_t Mt16 = (size_t)(g.O + 127) / 128 * 8;     // 16-row tiles, padded to the largest row tile
     // 16 bytes per lane per k-group: 16 rows of float32, 32 rows of bfloat16
-    // (float32, channel-last: three bfloat16 terms, 16 bytes each per lane and 32 rows, and where wide tiles use them two float16 terms and two ints a row)
-    if (channel_last && !g.bf16)
-        return cl_halves(g.O, (unsigned)((Rs + 31) / 32)) ? Mt16 * (Rpad / 32) * 5 * 64 * 16 + Mt16 * 16 * 8 : Mt16 * (Rpad / 32) * 3 * 64 * 16;
+    // (float32, channel-last: three bfloat16 terms, 16 bytes each per lane and 32 rows)
+    if (channel_last && !g.bf16) return Mt16 * (Rpad / 32) * 3 * 64 * 16;
     return Mt16 * (Rpad / (g.bf16 ? 32 : 16)) * 64 * 16;
 }
 

@@ -33,18 +33,6 @@
 // such makes the accumulated sum non-finite, and the epilogue recomputes every non-finite sum in plain
 // float32 from the state and the filter matrix (exact_tiles), so that infinities, NaNs and large numbers come out as they do
 // in float32 arithmetic.
-//
-// Wide tiles (H2: four and more 16 x 16 tiles a wavefront, which are bound by the matrix cores and have no registers for a second chain of six products) take
-// two float16 terms instead, x * s = h + l / 2^11 with h and l the nearest float16, and three products in two chains,
-//     h*h   and   l*h + h*l, times 2^-11 in the end:
-// half the matrix-core time, two thirds of the filter bytes, LDS and split.  The terms hold 22 - 23 bits and l*l is left out, 7.5e-8 of a sum in all; but a sum is rounded
-// once per 32 products and chain instead of six times, which is more: errors against float64 over whole layers, six products / three, 16 -> 32 3x3 1.65e-7 / 1.13e-7, 128 -> 64 1x1
-// 1.44e-7 / 1.04e-7, 128 -> 128 3x3 5.1e-7 / 2.3e-7, 256 -> 100 3x3 7.3e-7 / 3.1e-7, 64 -> 256 7x7 8.6e-7 / 3.6e-7.  Sums of up to 96 products, and the narrow tiles, whose six products in two
-// chains have 4e-8 - 3e-7, keep the three bfloat16 terms (cl_halves).  us per frame: full update of 256 -> 256 92x164 101.9 / 76.4, of 64 -> 64 480x640 193 / 167, 128 -> 128 1080p 2 % changed
-// 446 / 436, 10 % 828 / 745, ten-layer trunk 249 / 237.
-// float16's range is the price.  s is a power of two of each column, from its first values (cl_half_scale), and one of each filter row, from its largest weight.  A column that
-// outgrows its first values by 2^7 overflows and is recomputed like an infinity.  Values scaled below 2^-14 lose bits; they are counted, and a sum to which what its factors lost may
-// matter by more than 2^-22 of it (cl_half_doubt) is recomputed too: whatever the range of values and wherever there are zeros, a sum is that of float32 operands of at least 22 bits.
 #pragma once
 #include "cb_fused.h"
 #include "cb_cl_rules.h"
@@ -58,8 +46,6 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 // in front of both operands of a float32 product, and what takes them out of a sum of products
 constexpr float SPLIT_SCALE = 0x1p24f, SPLIT_UNSCALE = 0x1p-48f;
@@ -76,32 +62,6 @@ __device__ __forceinline__ void split2(float a, float b, unsigned& h, unsigned& 
     a -= __uint_as_float(m << 16);
     b -= __uint_as_float(m & 0xFFFF0000u);
     l = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, bf16x2));
-}
-
-// two neighbouring values times s -> a float16 and 2^11 times the rest (s11 = s * 2^11), packed
-__device__ __forceinline__ void halves2(float a, float b, float s, float s11, unsigned& h, unsigned& l)
-{
-    const f16x2 hh = __builtin_convertvector(floatx2{a * s, b * s}, f16x2);
-    h = __builtin_bit_cast(unsigned, hh);
-    l = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{__builtin_fmaf((float)hh.x, -2048.f, a * s11), __builtin_fmaf((float)hh.y, -2048.f, b * s11)}, f16x2));
-}
-// whether any of four values is not zero and, times the scale, below 2^-14 (cl_half_scale: magnitudes below the float32 2^-14 / scale)
-__device__ __forceinline__ bool halves_lose(const uint4& v, float s)
-{
-    auto key = [](unsigned bits) { return (bits << 1) - 1u; };       // (zero: the largest; without the sign)
-    auto least = [](unsigned a, unsigned b) { return a < b ? a : b; };
-    return least(least(key(v.x), key(v.y)), least(key(v.z), key(v.w))) < 0xEFFFFFFFu - (__float_as_uint(s) << 1);
-}
-// over aligned groups of W lanes (8 to 64), in all of them: COMBINE(a, b)
-template <int W, typename FN> __device__ __forceinline__ unsigned over_lanes(unsigned v, FN&& combine)
-{
-    v = combine(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));      // lane ^ 1
-    v = combine(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));      // lane ^ 2
-    v = combine(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));     // row_half_mirror
-    if constexpr (W >= 16) v = combine(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));     // row_mirror
-    if constexpr (W >= 32) v = combine(v, (unsigned)__shfl_xor((int)v, 16));
-    if constexpr (W >= 64) v = combine(v, (unsigned)__shfl_xor((int)v, 32));
-    return v;
 }
 
 // bits max(0, -o) .. min(k, size - o) - 1: which of a filter's k rows (columns), the first at o, lie inside the image
@@ -199,12 +159,11 @@ template <typename T> __host__ __device__ constexpr int cl_groups(int bn, int wg
     return sizeof(T) == 4 ? (bn >= 128 ? 1 : bn == 64 ? 2 : 4) : (bn >= 128 ? 2 : bn == 64 ? 4 : 8);
 }
 // bytes per column of a stage buffer, dynamic LDS (two buffers and the listed pixels; float32 three, bfloat16 four workgroups in 160 KB)
-template <typename T> __host__ __device__ constexpr unsigned cl_pitch(int bn, int wgk = 1, bool h2 = false)
+template <typename T> __host__ __device__ constexpr unsigned cl_pitch(int bn, int wgk = 1)
 {
-    return (unsigned)cl_groups<T>(bn, wgk) * (sizeof(T) == 4 ? (h2 ? 128u : 192u) : 64u) + 16u;
+    return (unsigned)cl_groups<T>(bn, wgk) * (sizeof(T) == 4 ? 192u : 64u) + 16u;
 }
 template <typename T> __host__ __device__ constexpr unsigned cl_lds(int bn, int wgk = 1) { return 2u * (unsigned)bn * cl_pitch<T>(bn, wgk) + 4u * (unsigned)bn; }
-static_assert(2u * 128u * cl_pitch<float>(128, 1, true) + 8u * 128u + 4u <= cl_lds<float>(128), "tiles of two terms have room for their columns' scales");
 constexpr unsigned CL_LDS_F32 = cl_lds<float>(128), CL_LDS_BF16 = cl_lds<uint16_t>(128);
 static_assert(3 * CL_LDS_F32 <= 163840 && cl_lds<float>(64) <= CL_LDS_F32 && cl_lds<float>(32) <= CL_LDS_F32 && cl_lds<float>(16) <= CL_LDS_F32 &&
               4 * CL_LDS_BF16 <= 163840 && cl_lds<uint16_t>(64) <= CL_LDS_BF16 && cl_lds<uint16_t>(32) <= CL_LDS_BF16 &&
@@ -214,7 +173,7 @@ static_assert(3 * CL_LDS_F32 <= 163840 && cl_lds<float>(64) <= CL_LDS_F32 && cl_
 // SPLIT: a tile's K is divided into `parts` ranges of stages, an item each.  An item leaves its sums in the workspace and counts itself; the
 // tile's last one adds them up, in the order of K, and writes the outputs.
 struct ClSplit { float* ws; int* count; unsigned parts; };
-template <typename T, bool P2, int FAR, bool HALF, int WGM, int WGN, int TM, int TN, int WGK = 1, bool SPLIT = false>
+template <typename T, bool P2, int FAR, int WGM, int WGN, int TM, int TN, int WGK = 1, bool SPLIT = false>
 __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, const T* __restrict__ S2,
                                                  const int32_t* __restrict__ idx, const int N,
                                                  const uint4* __restrict__ KF, const float* __restrict__ KT,
@@ -222,9 +181,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                                                  T* __restrict__ OUT2, const unsigned bx, const unsigned gx, const ClSplit& split = ClSplit())
 {
     constexpr bool F32 = sizeof(T) == 4;
-    // float32 in two float16 terms (the tiles whose sums would be one chain of six products; see above)
-    constexpr bool H2 = HALF && F32 && TM * TN >= 4 && !(SPLIT && TM * TN == 4);
-    constexpr int TERMS = H2 ? 2 : F32 ? 3 : 1;  // terms per value
+    constexpr int TERMS = F32 ? 3 : 1;           // bfloat16 terms per value
     constexpr int EPV = 16 / (int)sizeof(T);     // elements per 16-byte piece
     constexpr unsigned ESZ = (unsigned)sizeof(T);
     static_assert(WGM * WGN * WGK == 4, "four wavefronts per workgroup");
@@ -244,7 +201,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     // stages per round of the stage loop: ring slot and register set are compile-time indexes
     constexpr int UU = D / UKW > GD ? D / UKW : GD;
     static_assert(UU * UKW % D == 0 && UU % GD == 0, "a round of stages is whole rings");
-    constexpr unsigned PITCH = cl_pitch<T>(BN, WGK, H2), BUF = BN * PITCH;
+    constexpr unsigned PITCH = cl_pitch<T>(BN, WGK), BUF = BN * PITCH;
     constexpr unsigned PLANE = UKG * 64u;        // bytes of one term of a column
     // the largest tile has no registers for what can be fetched when it is used: the next tile's pixels, the bias, a longer ring
     constexpr bool LEAN = TM * TN > 8;
@@ -255,16 +212,12 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     // 240x320 29.9 / 28.6, a full update of 256 -> 256 92x164 107.0 / 102.5.  Wider bfloat16 tiles have the wavefronts and not the registers (128 x 128 spread: 458 / 544).
     constexpr bool SPREAD = F32 ? TM * TN <= (P2 ? 8 : 4) : TM * TN <= 2 && WGK == 1;
     constexpr int NF = UKW * TN, BR = !F32 && SPREAD ? 4 : 2;
-    constexpr bool TWO = H2 || TM * TN < 4 || (SPLIT && F32 && TM * TN == 4);     // second accumulator chain where a wavefront has few tiles (errors: cl_least_parts)
+    constexpr bool TWO = TM * TN < 4 || (SPLIT && F32 && TM * TN == 4);     // second accumulator chain where a wavefront has few tiles (errors: cl_least_parts)
     extern __shared__ uint4 dyn_lds4[];          // two stage buffers, then the listed pixel of every column
     char* const Bs = reinterpret_cast<char*>(dyn_lds4);
     int* const qs = reinterpret_cast<int*>(Bs + 2 * BUF);
 
     const int nkg = F32 ? (g.Cs * g.kh * g.kw + 63) / 64 * 2 : (g.Cs * g.kh * g.kw + 127) / 128 * 4;       // k-groups of the packed filter matrix
-    // behind the three terms of float32: the two, and of every row the exponent of its scale and the weights of which float16 loses bits
-    const size_t kf = (size_t)(((unsigned)g.O + 127u) / 128u * 8u) * (unsigned)nkg * 64u;
-    const uint4* const KH = KF + 3 * kf;
-    const int2* const rows_of = reinterpret_cast<const int2*>(KF + 5 * kf);
     const int stages = (nkg + UKG - 1) / UKG;
     const unsigned parts = SPLIT ? split.parts : 1u;
     const int lc = 31 - __builtin_clz((unsigned)g.Cs);       // (P2)
@@ -318,7 +271,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 
         // ring of filter fragments: [k-group mod D][row tile][term].  The resource covers this tile's rows.
         const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint4*>(H2 ? KH : KF) + (size_t)(m0 >> 4) * nkg * (TERMS * 64), 0,
+            const_cast<uint4*>(KF) + (size_t)(m0 >> 4) * nkg * (TERMS * 64), 0,
             (int)((unsigned)(BM / 16) * (unsigned)nkg * (TERMS * 1024u)), 0x00020000);
         uint4 areg[D][TM][TERMS];
         auto aload = [&](int kg, uint4 (&dst)[TM][TERMS]) {
@@ -369,18 +322,9 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             const unsigned out = (unsigned)(__builtin_amdgcn_sbfe((int)outr[p], w.j, 1u) | __builtin_amdgcn_sbfe((int)outc[p], w.i, 1u));
             return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(srsrc, (int)((out & NOWHERE) | (base[p] + w.off)), 0, 0));
         };
-        float sc[NP];                             // (H2) the columns' scales, and how many of their pieces have values of which float16 loses bits
-        unsigned lost = 0;
         auto lds_store = [&](int buf, int p, const uint4& v) {
             char* dst = Bs + buf * BUF + gc * PITCH + (F32 ? 8 : 16) * ch;
-            if constexpr (H2) {
-                uint2 h, l;
-                halves2(__uint_as_float(v.x), __uint_as_float(v.y), sc[p], sc[p] * 2048.f, h.x, l.x);
-                halves2(__uint_as_float(v.z), __uint_as_float(v.w), sc[p], sc[p] * 2048.f, h.y, l.y);
-                lost += halves_lose(v, sc[p]) ? 1u : 0u;
-                *reinterpret_cast<uint2*>(dst + CPP * p * PITCH) = h;
-                *reinterpret_cast<uint2*>(dst + CPP * p * PITCH + PLANE) = l;
-            } else if constexpr (F32) {
+            if constexpr (F32) {
                 uint2 h, m, l;
                 split2(__uint_as_float(v.x), __uint_as_float(v.y), h.x, m.x, l.x);
                 split2(__uint_as_float(v.z), __uint_as_float(v.w), h.y, m.y, l.y);
@@ -419,30 +363,10 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = m0 + (wm * TM + a) * 16 + lq * 4 + r;
-                bv[a][r] = LEAN || H2 ? 0.f : bias[m < g.O ? m : g.O - 1];
+                bv[a][r] = LEAN ? 0.f : bias[m < g.O ? m : g.O - 1];
             }
         __syncthreads();                          // the previous tile has read its last stage and its qs
         if (ch < NP) qs[mycol] = q;
-        if constexpr (H2) {
-            // Columns' scales from their first values; where these are zero (a tap outside the image) from the wavefront's other columns, and where all are (the image's first
-            // row), from the taps in the middle of the filter
-            auto most = [](unsigned a, unsigned b) { return a > b ? a : b; };
-            unsigned m[NP], all = 0u;
-            auto look = [&](int p, const uint4& v) {
-                m[p] = over_lanes<PPC>(most(most(v.x << 1, v.y << 1), most(v.z << 1, v.w << 1)), most) >> 1;
-                all = most(all, m[p]);
-            };
-#pragma unroll
-            for (int p = 0; p < NP; ++p) look(p, breg[0][p]);
-            if (!__ballot(all != 0u)) {
-                const Piece mid{(unsigned)g.kh / 2u, (unsigned)g.kw / 2u, pixels((unsigned)(g.kh / 2 * g.W + g.kw / 2)) * ESZ};
-#pragma unroll
-                for (int p = 0; p < NP; ++p) look(p, gload(mid, p));
-            }
-            all = over_lanes<64>(all, most);
-#pragma unroll
-            for (int p = 0; p < NP; ++p) sc[p] = __uint_as_float(cl_half_scale(m[p] ? m[p] : all) << 23);
-        }
 #pragma unroll
         for (int p = 0; p < NP; ++p) lds_store(0, p, breg[0][p]);
         gather(GD, breg[0]);
@@ -500,15 +424,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                             d[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[a][ea]),
                                                                               __builtin_bit_cast(bf16x8, bfr[f % BR][eb]), d[a][b], 0, 0, 0);
                     };
-                    if constexpr (H2) {
-                        auto mul16 = [&](int ea, int eb, floatx4 (&d)[TM][TN]) {
-#pragma unroll
-                            for (int a = 0; a < TM; ++a)
-                                d[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, af[a][ea]), __builtin_bit_cast(f16x8, bfr[f % BR][eb]), d[a][b], 0, 0, 0);
-                        };
-                        mul16(1, 0, acc1); mul16(0, 1, acc1);
-                        mul16(0, 0, acc);
-                    } else if constexpr (F32) {
+                    if constexpr (F32) {
                         // smallest terms first; a chain of their own where a wavefront has few tiles
                         floatx4 (&rest)[TM][TN] = TWO ? acc1 : acc;
                         mul(2, 0, rest); mul(1, 1, rest); mul(0, 2, rest); mul(1, 0, rest); mul(0, 1, rest);
@@ -536,33 +452,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             static_assert(UU == 1 || UU == 2 || UU == 4, "stages per round");
         }
 
-        if constexpr (H2) {
-            // Out of the scales; a sum to which lost bits may matter is left to the recomputation (cl_half_doubt)
-            int2 row[TM][4];
-#pragma unroll
-            for (int a = 0; a < TM; ++a)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) row[a][r] = rows_of[m0 + (wm * TM + a) * 16 + lq * 4 + r];
-            int* const cx = qs + BN + 1;          // exponent of a column's scale, and above it how many pieces lost bits
-            const unsigned n = over_lanes<PPC>(lost, [](unsigned a, unsigned b) { return a + b; });
-            if (ch == 0) {
-#pragma unroll
-                for (int p = 0; p < NP; ++p) cx[gc + CPP * p] = (int)(n << 8 | __float_as_uint(sc[p]) >> 23);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int b = 0; b < TN; ++b) {
-                const int col = cx[(wn * TN + b) * 16 + l16], ce = 127 - (col & 255);
-                const unsigned cn = 4u * ((unsigned)col >> 8);
-#pragma unroll
-                for (int a = 0; a < TM; ++a)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float t = acc[a][b][r] + acc1[a][b][r] * 0x1p-11f;
-                        acc[a][b][r] = fabsf(t) < cl_half_doubt(cn + (unsigned)row[a][r].y) ? __builtin_nanf("") : ldexpf(t, ce - row[a][r].x);
-                    }
-            }
-        } else if (TWO) {
+        if (TWO) {
 #pragma unroll
             for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -647,7 +537,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 #pragma unroll
                 for (int b = 0; b < TN; ++b) acc[a][b] = sum[a][b];
         }
-        if constexpr (LEAN || H2) {
+        if constexpr (LEAN) {
 #pragma unroll
             for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -673,7 +563,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                     float v4[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        float v = F32 && !H2 ? fmaf(acc[a][b][r], SPLIT_UNSCALE, bv[a][r]) : acc[a][b][r] + bv[a][r];
+                        float v = F32 ? fmaf(acc[a][b][r], SPLIT_UNSCALE, bv[a][r]) : acc[a][b][r] + bv[a][r];
                         if (F32 && !(fabsf(acc[a][b][r]) < __builtin_inff()) && (all || mb + r < g.O)) bad |= 1ull << ((b * TM + a) * 4 + r);
                         if (relu) v = v > 0.f ? v : 0.f;
                         if (all || mb + r < g.O) st_out(o + (size_t)(a * 16 + r) * g.Po, v);
@@ -687,16 +577,14 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             else rows(false);
         }
         if constexpr (F32) {
-            if (__ballot(bad != 0ull)) {
-                const __amdgpu_buffer_rsrc_t k3src = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(KF) + (size_t)(m0 >> 4) * nkg * 192, 0,
-                                                                                       (int)((unsigned)(BM / 16) * (unsigned)nkg * 3072u), 0x00020000);
+            if (__ballot(bad != 0ull))
 #pragma unroll 1
                 for (int b = 0; b < TN; ++b) {
                     const unsigned mine = (unsigned)(bad >> (4 * TM * b)) & ((1u << (4 * TM)) - 1u);
                     if (!__ballot(mine != 0u)) continue;
                     const int qn = qs[(wn * TN + b) * 16 + l16];
                     floatx4 sum[TM];
-                    exact_tiles<TM, P2>(g, div, srsrc, k3src, KT, nkg, wm_s * TM, lane, qn, mw + l16, sum);
+                    exact_tiles<TM, P2>(g, div, srsrc, krsrc, KT, nkg, wm_s * TM, lane, qn, mw + l16, sum);
 #pragma unroll
                     for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -709,7 +597,6 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                                 if (OUT2) OUT2[(size_t)qn * g.O + m] = v;
                             }
                 }
-            }
         }
     }
 }
@@ -731,7 +618,7 @@ __device__ __forceinline__ void hold_arguments(const Geom& g, const ClDiv& div, 
 constexpr unsigned CL_GRID = 1024;
 
 // workgroup bx of gx
-template <typename T, int SHAPE, bool P2, int FAR, bool HALF>
+template <typename T, int SHAPE, bool P2, int FAR>
 __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, const T* __restrict__ S2, const int32_t* __restrict__ idx,
                                              const int* __restrict__ count, const uint4* __restrict__ KF, const float* __restrict__ KT,
                                              const float* __restrict__ bias, int relu, T* __restrict__ OUT, T* __restrict__ OUT2,
@@ -744,12 +631,12 @@ __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, co
         const unsigned sp = cl_split<sizeof(T) == 4>(N, g.O, ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u, ws_bytes);
         if (sp) {
             const ClSplit split{ws, kcount, sp & 15u};
-            if (sp & 16u) fused_cl_body<T, P2, FAR, HALF, 4, 1, 2, 4, 1, true>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx, split);
-            else fused_cl_body<T, P2, FAR, HALF, 4, 1, 2, 2, 1, true>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx, split);
+            if (sp & 16u) fused_cl_body<T, P2, FAR, 4, 1, 2, 4, 1, true>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx, split);
+            else fused_cl_body<T, P2, FAR, 4, 1, 2, 2, 1, true>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx, split);
             return;
         }
     }
-#define CB_BODY(...) fused_cl_body<T, P2, FAR, HALF, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx)
+#define CB_BODY(...) fused_cl_body<T, P2, FAR, __VA_ARGS__>(g, div, S2, idx, N, KF, KT, bias, relu, OUT, OUT2, bx, gx)
     // (the tiles of cb_cl_rules.h)
     cl_tile<sizeof(T) == 4, SHAPE>(N, g.O, g.Cs, g.kh * g.kw, g.R, [&](auto tile) __attribute__((always_inline)) {
         constexpr int t = decltype(tile)::value;
@@ -766,14 +653,14 @@ __device__ __forceinline__ void fused_cl_run(const Geom& g, const ClDiv& div, co
 
 // (wavefronts per SIMD: as many as the widest tile's registers allow.  They are worth more than wider tiles: bfloat16, O > 64
 // at 76 800 listed pixels 45 us with two, 40 us with four.)
-template <typename T, int SHAPE, bool P2, int FAR, bool HALF>
+template <typename T, int SHAPE, bool P2, int FAR>
 __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_kernel(Geom g, ClDiv div, const T* __restrict__ S2,
                                                           const int32_t* __restrict__ idx, const int* __restrict__ count,
                                                           const uint4* __restrict__ KF, const float* __restrict__ KT,
                                                           const float* __restrict__ bias, int relu,
                                                           T* __restrict__ OUT, T* __restrict__ OUT2, float* ws, unsigned ws_bytes, int* kcount)
 {
-    fused_cl_run<T, SHAPE, P2, FAR, HALF>(g, div, S2, idx, count, KF, KT, bias, relu, OUT, OUT2, blockIdx.x, CL_GRID, ws, ws_bytes, kcount);
+    fused_cl_run<T, SHAPE, P2, FAR>(g, div, S2, idx, count, KF, KT, bias, relu, OUT, OUT2, blockIdx.x, CL_GRID, ws, ws_bytes, kcount);
 }
 
 // run(an integral constant: the kernel's instance) for a layer of this geometry; its arguments checked
@@ -807,27 +694,22 @@ hipError_t launch_fused_cl(const Geom& g, const FusedPlan& plan, const T* shadow
     const bool p2 = (g.Cs & (g.Cs - 1)) == 0;
     return fused_cl_instance<T>(g, plan, [&](auto shape) {
         constexpr int SHAPE = decltype(shape)::value;
-#define CB_CL(p, far, half) \
-    CB_LAUNCH_LDS((fused_cl_kernel<T, SHAPE, p, far, half>), dim3(CL_GRID), dim3(256), cl_lds_bytes<T>(), st, tm, g, div, shadow, \
+#define CB_CL(p, far) \
+    CB_LAUNCH_LDS((fused_cl_kernel<T, SHAPE, p, far>), dim3(CL_GRID), dim3(256), cl_lds_bytes<T>(), st, tm, g, div, shadow, \
                   idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2, work.ws, work.bytes, work.count)
-        constexpr bool halves = sizeof(T) == 4 && SHAPE > 16;       // (a kernel with tiles of two float16 terms)
-        const bool half = halves && cl_halves(g.O, ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u);
         const int far = fused_cl_far_mode(g, work);
         if constexpr (SHAPE == 128)
             if (far == 2) {
-                CB_CL(true, 2, halves);
+                CB_CL(true, 2);
                 return;
             }
         if constexpr (SHAPE >= 128)
             if (far) {
-                if (half) CB_CL(true, 1, halves);
-                else CB_CL(true, 1, false);
+                CB_CL(true, 1);
                 return;
             }
-        if (p2 && half) CB_CL(true, 0, halves);
-        else if (p2) CB_CL(true, 0, false);
-        else if (half) CB_CL(false, 0, halves);
-        else CB_CL(false, 0, false);
+        if (p2) CB_CL(true, 0);
+        else CB_CL(false, 0);
 #undef CB_CL
     });
 }

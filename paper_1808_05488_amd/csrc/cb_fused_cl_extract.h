@@ -12,7 +12,7 @@ namespace {
 // compute units work, and it needs nothing of the product: frames of the ten-layer trunk of 3 x 3
 // filters at 368x656 with propagated change maps, 5 % changed, us: bfloat16 203 -> 157, float32 343 -> 291; of the five-layer 7 x 7 net at
 // 480x640 110 -> 97.
-template <typename T, int SHAPE, int FAR, bool HALF>
+template <typename T, int SHAPE, int FAR>
 __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_extract_kernel(Geom g, ClDiv div, const T* __restrict__ S2,
                                                           const int32_t* __restrict__ idx, const int* __restrict__ count,
                                                           const uint4* __restrict__ KF, const float* __restrict__ KT,
@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void fused_cl_extract_
         if (blockIdx.x < (unsigned)job.nblk) extract_block(job, (int)blockIdx.x, reinterpret_cast<uint64_t*>(dyn_lds4));
         return;
     }
-    fused_cl_run<T, SHAPE, true, FAR, HALF>(g, div, S2, idx, count, KF, KT, bias, relu, OUT, OUT2, blockIdx.x - first, CL_GRID, ws, ws_bytes, kcount);
+    fused_cl_run<T, SHAPE, true, FAR>(g, div, S2, idx, count, KF, KT, bias, relu, OUT, OUT2, blockIdx.x - first, CL_GRID, ws, ws_bytes, kcount);
 }
 
 template <typename T>
@@ -37,25 +37,21 @@ hipError_t launch_fused_cl_extract(const Geom& g, const FusedPlan& plan, const T
     const ClDiv div = cl_div(g.Wo, g.Ho, g.kw, g.Cs);
     return fused_cl_instance<T>(g, plan, [&](auto shape) {
         constexpr int SHAPE = decltype(shape)::value;
-#define CB_CLX(far, half) \
-    CB_LAUNCH_LDS((fused_cl_extract_kernel<T, SHAPE, far, half>), dim3(CL_GRID + (((unsigned)job.nblk + 7u) & ~7u)), dim3(256), \
+#define CB_CLX(far) \
+    CB_LAUNCH_LDS((fused_cl_extract_kernel<T, SHAPE, far>), dim3(CL_GRID + (((unsigned)job.nblk + 7u) & ~7u)), dim3(256), \
                   cl_lds_bytes<T>(), st, tm, g, div, shadow, idx, count, (const uint4*)KF, KT, bias, relu, OUT, OUT2, job, work.ws, work.bytes, work.count)
-        constexpr bool halves = sizeof(T) == 4 && SHAPE > 16;
-        const bool half = halves && cl_halves(g.O, ((unsigned)(g.Cs * g.kh * g.kw) + 31u) / 32u);
         const int far = fused_cl_far_mode(g, work);
         if constexpr (SHAPE == 128)
             if (far == 2) {
-                CB_CLX(2, halves);
+                CB_CLX(2);
                 return;
             }
         if constexpr (SHAPE >= 128)
             if (far) {
-                if (half) CB_CLX(1, halves);
-                else CB_CLX(1, false);
+                CB_CLX(1);
                 return;
             }
-        if (half) CB_CLX(0, halves);
-        else CB_CLX(0, false);
+        CB_CLX(0);
 #undef CB_CLX
     });
 }
