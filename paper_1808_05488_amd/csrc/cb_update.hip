@@ -108,29 +108,36 @@ __global__ __launch_bounds__(256) void update_kernel(int O, int Opad, int R, int
     }
 }
 
-// The common window, 2 x 2: items of 256 listed pixels and OCH channels, the channels of a pixel in a row (which pixels an item has does not depend on their count then).
+// The common window, 2 x 2: items of 256 pixels, listed ones or those of the whole map in turn, and OCH channels.  (Which pixels an item of a list has does not depend on their count.)
 // Bound by its chain of loads (count and pixel together, then sixteen values a lane) and, with a pixel-major copy, by the number of its stores: a pixel's OCH
 // channels are one.  32-bit items, rows by reciprocal.  With 64-bit divisions, the pixel asked for behind the count and a store a channel, frames, us, before / now: ten-layer trunk
-// of 3 x 3 filters (three stages) bfloat16 141.2 / 137.6, float32 225 / 222, five-layer net (two) 71.4 / 70.6.  1 024 workgroups: 512 140.0, 4 096 of which most find nothing 143.8.
-template <typename T>
+// of 3 x 3 filters (three stages) bfloat16 141.2 / 137.6, float32 225 / 222, five-layer net (two) 71.4 / 70.6.  Whole maps walk a channel's tiles in a row: with the channels of a tile in
+// a row, 8 channels at 1080p 30.1 us, now 21.9, 64 at 540x960 bfloat16 52.9 / 41.8.  2 048 workgroups: with 1 024, whole 32 at 1080p bfloat16 95 / 77 us, 40 % of it listed 52.0 / 42.8.
+template <typename T, bool LISTED>
 __global__ __launch_bounds__(256) void pool2_kernel(int O, int Ho, int Wo, int Hp, int Wp, ClDiv div, const T* __restrict__ OUT,
                                                     const int32_t* __restrict__ idx, const int* __restrict__ count,
                                                     T* __restrict__ POOL, T* __restrict__ POOL2)
 {
     const unsigned Po = (unsigned)Ho * (unsigned)Wo, Pp = (unsigned)Hp * (unsigned)Wp;
     const unsigned och = (unsigned)(O + OCH - 1) / OCH;
+    // Lists, items of a round: the channels of one tile of 256 pixels in a row, so that with a multiple of eight of them each XCD keeps to its own maps, or few
+    // channels, that are none, of eight tiles.  us, channel after channel as in whole maps / so: 64 channels 480x640, 40 % of the pixels listed here and there 33.5 / 22.8,
+    // 32 at 1080p bfloat16, 10 % 47.1 / 29.6; one tile / eight: 16 at 480x640, 40 % 15.2 / 13.1, 48 at 240x321 bfloat16 10.7 / 9.2, but 100 at 120x160, 1 % 5.1 / 6.4.
+    const unsigned sh = (och & 7u) && och < 16u ? 3u : 0u, round = och << sh;
+    auto tile_of = [&](unsigned t) { return (t / round << sh) + (t & ((1u << sh) - 1u)); };
     // (the list has Po entries; those from the count on are stale but readable)
     auto entry = [&](unsigned t) {
-        const unsigned n = t / och * 256u + threadIdx.x;
-        return idx ? idx[n < Po ? n : Po - 1u] : (int)n;
+        const unsigned n = tile_of(t) * 256u + threadIdx.x;
+        return idx[n < Po ? n : Po - 1u];
     };
-    int q = entry(blockIdx.x);
-    const unsigned N = idx ? (unsigned)*count : Po;
-    for (unsigned t = blockIdx.x; t / och * 256u < N; t += gridDim.x) {
-        const int here = q;
-        q = entry(t + gridDim.x);
-        const unsigned tile = t / och;
-        const int o0 = (int)(t - tile * och) * OCH, on = O - o0 < OCH ? O - o0 : OCH;
+    const unsigned tiles = (Po + 255u) / 256u;             // (of a whole map)
+    int q = LISTED ? entry(blockIdx.x) : 0;
+    const unsigned N = LISTED ? (unsigned)*count : Po;
+    for (unsigned t = blockIdx.x; LISTED ? (t / round << sh) * 256u < N : t < tiles * och; t += gridDim.x) {
+        const unsigned tile = LISTED ? tile_of(t) : t % tiles, oc = LISTED ? t % round >> sh : t / tiles;
+        const int here = LISTED ? q : (int)(tile * 256u + threadIdx.x);
+        if (LISTED) q = entry(t + gridDim.x);
+        const int o0 = (int)oc * OCH, on = O - o0 < OCH ? O - o0 : OCH;
         if (tile * 256u + threadIdx.x >= N) continue;
         const T* const src = OUT + (size_t)o0 * Po;
         const int yo = cl_row(div, here, Wo), xo = here - yo * Wo;
@@ -257,12 +264,16 @@ hipError_t launch_pool(int O, int Ho, int Wo, int w, int bf16, const void* OUT, 
     const int Hp = (Ho + w - 1) / w, Wp = (Wo + w - 1) / w;
     if (w == 2) {
         const long items = (((long)Ho * Wo + 255) / 256) * ((O + OCH - 1) / OCH);
-        const dim3 grid((unsigned)(items < 1024 ? items : 1024));
+        const long most = 2048;
+        const dim3 grid((unsigned)(items < most ? items : most));
         const ClDiv div = cl_div(Wo, Ho, 1);
-        if (bf16)
-            hipLaunchKernelGGL(pool2_kernel<uint16_t>, grid, dim3(256), 0, st, O, Ho, Wo, Hp, Wp, div, (const uint16_t*)OUT, idx, count, (uint16_t*)POOL, (uint16_t*)POOL2);
-        else
-            hipLaunchKernelGGL(pool2_kernel<float>, grid, dim3(256), 0, st, O, Ho, Wo, Hp, Wp, div, (const float*)OUT, idx, count, (float*)POOL, (float*)POOL2);
+#define CB_POOL2(T, listed) \
+    hipLaunchKernelGGL((pool2_kernel<T, listed>), grid, dim3(256), 0, st, O, Ho, Wo, Hp, Wp, div, (const T*)OUT, idx, count, (T*)POOL, (T*)POOL2)
+        if (bf16 && idx) CB_POOL2(uint16_t, true);
+        else if (bf16) CB_POOL2(uint16_t, false);
+        else if (idx) CB_POOL2(float, true);
+        else CB_POOL2(float, false);
+#undef CB_POOL2
         return hipGetLastError();
     }
     long max_items = (long)(((long)Ho * Wo + 255) / 256) * ((O + OCH - 1) / OCH);

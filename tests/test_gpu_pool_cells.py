@@ -1,5 +1,5 @@
-"""2 x 2 pooling of a change-based layer against the dense pool of its output: maps of one row, one column and odd sizes, channel counts around the four that an item has, with
-and without a pixel-major copy, frames that list everything, something and nothing."""
+"""2 x 2 pooling of a change-based layer against the dense pool of its output: maps of one row, one column and odd sizes, channel counts around the four that an item has and the
+eight items that a round of a list is made of, with and without a pixel-major copy, frames that list everything, something and nothing."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +11,7 @@ if torch.cuda.is_available():
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 1, 7), (4, 9, 1), (5, 2, 2), (8, 7, 9), (13, 33, 65), (32, 61, 93), (64, 120, 161), (1, 700, 1100), (260, 17, 16)])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 1, 7), (4, 9, 1), (5, 2, 2), (8, 7, 9), (13, 33, 65), (32, 61, 93), (64, 120, 161), (1, 700, 1100), (260, 17, 16), (36, 61, 93), (48, 40, 200), (100, 50, 51)])
 def test_pooled_cells(shape, bf16):
     O, H, W = shape
     print("pool", shape, bf16, flush=True)
