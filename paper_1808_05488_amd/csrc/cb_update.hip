@@ -168,15 +168,9 @@ __global__ __launch_bounds__(256) void pool2_kernel(int O, int Ho, int Wo, int H
             if (j < on) POOL[(size_t)(o0 + j) * Pp + cell] = best[j];
         }
         if (POOL2) {
-            T* const d = POOL2 + (size_t)cell * O + o0;
-            if ((O & (OCH - 1)) == 0) {
-                typedef unsigned vec __attribute__((ext_vector_type(OCH * sizeof(T) / 4)));
-                *reinterpret_cast<vec*>(d) = *reinterpret_cast<const vec*>(best);
-            } else {
-#pragma unroll
-                for (int j = 0; j < OCH; ++j)
-                    if (j < on) d[j] = best[j];
-            }
+            // (producers that keep the pixel-major copy have a power of two of channels, at least 16)
+            typedef unsigned vec __attribute__((ext_vector_type(OCH * sizeof(T) / 4)));
+            *reinterpret_cast<vec*>(POOL2 + (size_t)cell * O + o0) = *reinterpret_cast<const vec*>(best);
         }
     }
 }
