@@ -38,6 +38,16 @@ def shifts_by_last_register(asm: str) -> list[tuple[str, str]]:
     return found
 
 
+def spilled_registers(asm: str) -> list[tuple[str, int]]:
+    """(kernel, how many) of every kernel that keeps vector registers in scratch memory, from the metadata behind its assembly."""
+    kernels = re.findall(r"^\s*\.name:\s+(_Z\S+)(?:(?!^\s*\.name:\s+_Z).)*?^\s*\.vgpr_spill_count:\s+(\d+)", asm, re.M | re.S)
+    return [(name, int(n)) for name, n in kernels if int(n)]
+
+
+# sources whose kernels have room for all they hold
+UNSPILLED = {"cb_fused_cl_f32.hip", "cb_fused_cl_extract_f32.hip"}
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(CSRC, src.replace(".hip", ".o"))
     with tempfile.TemporaryDirectory() as tmp:
@@ -52,9 +62,13 @@ def _compile(src: str) -> str:
             raise RuntimeError(f"no assembly of the kernels of {src}")
         for path in asm:
             with open(path) as f:
-                found = shifts_by_last_register(f.read())
+                text = f.read()
+            found = shifts_by_last_register(text)
             if found:
                 raise RuntimeError(f"{src}: 64-bit shifts by the last register of an allocation: {found[:3]}")
+            spilled = spilled_registers(text) if src in UNSPILLED else []
+            if spilled:
+                raise RuntimeError(f"{src}: kernels that spill vector registers: {spilled[:3]}")
         with open(made, "rb") as f, open(obj, "wb") as g:
             g.write(f.read())
     noise = "is not a recognized feature for this target"

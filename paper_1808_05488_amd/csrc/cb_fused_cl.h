@@ -246,14 +246,22 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     // Of the NP columns that a column group of lanes fetches, lane ch has the pixel of column ch % NP, and works out what the others need of it (one column after
     // the other in every lane took 0.3 us a tile)
     static_assert(PPC >= NP && (NP & (NP - 1)) == 0, "a lane for each column");
-    const int mycol = gc + CPP * (ch & (NP - 1));
-    auto fetch_q = [&](unsigned u) {
-        const unsigned n = (xcd0 + (SPLIT ? u / parts : u) / MTX) * BN + mycol;
+    // The thread's number as a value that the compiler does not know, so that what follows from it is worked out again for each tile, ahead of and behind its stages, and not held
+    // over them, for which there are no registers: with such numbers held 14 of the 16 float32 kernels spilled 1 - 12 of them (a reload ahead of a tile's first stage waits for
+    // every load in flight), now none, and bfloat16's with 128 x 128 tiles 13 - 21, now 7 - 12.  Frames are the same within 1 %.
+    auto thread_again = [&]() {
+        int t = (int)threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    auto column_of = [&](int t) { return t / PPC + CPP * (t % PPC & (NP - 1)); };
+    auto fetch_q = [&](unsigned u, int col) {
+        const unsigned n = (xcd0 + (SPLIT ? u / parts : u) / MTX) * BN + col;
         const int q = idx[n < (unsigned)N ? n : (unsigned)N - 1u];
         return u < total && n < (unsigned)N ? q : -1;
     };
     int qnext = -1;
-    if constexpr (!LEAN) qnext = fetch_q(bx >> 3);
+    if constexpr (!LEAN) qnext = fetch_q(bx >> 3, column_of(tid));
 
     for (unsigned uq = bx >> 3; uq < total; uq += gx >> 3) {
         const unsigned ut = SPLIT ? uq / parts : uq;
@@ -263,9 +271,10 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
         const unsigned part = SPLIT ? uq % parts : 0u;
         const int u0 = SPLIT ? (int)(part * (unsigned)stages / parts) : 0;
         const int nunits = SPLIT ? (int)((part + 1u) * (unsigned)stages / parts) - u0 : stages;
+        const int t0 = thread_again(), mycol = column_of(t0);
         int q = qnext;
-        if constexpr (LEAN) q = fetch_q(uq);
-        else qnext = fetch_q(uq + (gx >> 3));
+        if constexpr (LEAN) q = fetch_q(uq, mycol);
+        else qnext = fetch_q(uq + (gx >> 3), mycol);
         if (nt >= NT || (FAR && (unsigned)mt >= MT)) continue;
         const int m0 = mt * BM;
 
@@ -298,7 +307,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             const unsigned r = ~(colv ? taps_within(y0, g.kh, g.H) : 0u), c = ~taps_within(x0, g.kw, g.W), b = pixels((unsigned)(y0 * g.W + x0)) * ESZ;
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
-                const int from = (lane & ~(PPC - 1)) + p;      // (PPC: up to a wavefront)
+                const int from = (t0 & 63 & ~(PPC - 1)) + p;      // (PPC: up to a wavefront)
                 outr[p] = (unsigned)__shfl((int)r, from);
                 outc[p] = (unsigned)__shfl((int)c, from);
                 base[p] = (unsigned)__shfl((int)b, from) + (unsigned)cl * ESZ;
@@ -362,7 +371,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
         for (int a = 0; a < TM; ++a)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int m = m0 + (wm * TM + a) * 16 + lq * 4 + r;
+                const int m = m0 + (wm * TM + a) * 16 + (t0 & 63) / 16 * 4 + r;
                 bv[a][r] = LEAN ? 0.f : bias[m < g.O ? m : g.O - 1];
             }
         __syncthreads();                          // the previous tile has read its last stage and its qs
@@ -452,6 +461,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             static_assert(UU == 1 || UU == 2 || UU == 4, "stages per round");
         }
 
+        const int lane_o = thread_again() & 63, l16o = lane_o & 15, lqo = lane_o >> 4;
         if (TWO) {
 #pragma unroll
             for (int a = 0; a < TM; ++a)
@@ -460,7 +470,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
         }
         if constexpr (WGK > 1) {
             // the partial sums of the other wavefronts, through the (now free) stage buffers, added in their order
-            float* const red = reinterpret_cast<float*>(Bs) + lane;
+            float* const red = reinterpret_cast<float*>(Bs) + lane_o;
             constexpr int PER = TM * TN * 4 * 64;
             static_assert((unsigned)(4 * PER) * 4u <= 2u * BUF, "partial sums fit the stage buffers");
             if (wk) {
@@ -542,24 +552,24 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             for (int a = 0; a < TM; ++a)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int m = m0 + (wm * TM + a) * 16 + lq * 4 + r;
+                    const int m = m0 + (wm * TM + a) * 16 + lqo * 4 + r;
                     bv[a][r] = bias[m < g.O ? m : g.O - 1];
                 }
         }
         // output update: bias + ReLU, written at the listed pixels only
         unsigned long long bad = 0;               // float32: sums to recompute, bit (b*TM + a)*4 + r
         const int mw = m0 + wm_s * TM * 16;       // first row of this wavefront
-        T* const orow = OUT + (size_t)(mw + lq * 4) * g.Po;
+        T* const orow = OUT + (size_t)(mw + lqo * 4) * g.Po;
         const bool whole = mw + 16 * TM <= g.O;
 #pragma unroll
         for (int b = 0; b < TN; ++b) {
-            const int qn = qs[(wn * TN + b) * 16 + l16];
+            const int qn = qs[(wn * TN + b) * 16 + l16o];
             if (qn < 0) continue;
             T* const o = orow + qn;
             auto rows = [&](bool all) {
 #pragma unroll
                 for (int a = 0; a < TM; ++a) {
-                    const int mb = mw + a * 16 + lq * 4;
+                    const int mb = mw + a * 16 + lqo * 4;
                     float v4[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
@@ -582,15 +592,15 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                 for (int b = 0; b < TN; ++b) {
                     const unsigned mine = (unsigned)(bad >> (4 * TM * b)) & ((1u << (4 * TM)) - 1u);
                     if (!__ballot(mine != 0u)) continue;
-                    const int qn = qs[(wn * TN + b) * 16 + l16];
+                    const int qn = qs[(wn * TN + b) * 16 + l16o];
                     floatx4 sum[TM];
-                    exact_tiles<TM, P2>(g, div, srsrc, krsrc, KT, nkg, wm_s * TM, lane, qn, mw + l16, sum);
+                    exact_tiles<TM, P2>(g, div, srsrc, krsrc, KT, nkg, wm_s * TM, lane_o, qn, mw + l16o, sum);
 #pragma unroll
                     for (int a = 0; a < TM; ++a)
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
                             if (mine & (1u << (4 * a + r))) {
-                                const int m = mw + a * 16 + lq * 4 + r;
+                                const int m = mw + a * 16 + lqo * 4 + r;
                                 float v = sum[a][r] + bias[m];
                                 if (relu) v = v > 0.f ? v : 0.f;
                                 OUT[(size_t)m * g.Po + qn] = v;
