@@ -596,7 +596,7 @@ __device__ __forceinline__ void extract_own_block(const DetectJob& job, int* __r
     else {
         const int nvalid = g.Wo - 64 * wo < 64 ? g.Wo - 64 * wo : 64;
 #pragma unroll 1
-        for (int t = 0; t < g.s; ++t) {                                  // (the second half of a word beyond the map is masked)
+        for (int t = 0; t < g.s && 32 * t < g.Wo; ++t) {                 // (the same number for all lanes; the second half of a word beyond the map is masked)
             const uint64_t f = fires_shared(g, lds, first_bit, yo * g.s - g.p, 64 * wo * g.s - g.p + 64 * t, 6 - lper, lane >> lper);
             word |= g.s == 1 ? f : even_bits(f) << (32 * t);
         }

@@ -39,6 +39,13 @@ def test_dilated_words_and_list(geom):
         assert n == ref.sum() and np.array_equal(idx, np.flatnonzero(ref))
 
 
+@pytest.mark.parametrize("W", [1, 2, 61, 62, 63, 64, 65, 66, 67])
+@pytest.mark.parametrize("k", [1, 3])
+def test_strided_maps_of_half_a_word(k, W):
+    """Stride 2, outputs around 32 a row: rows of one half of a word, and of a half and a little more."""
+    test_dilated_words_and_list((k, k, k // 2, 2, 29, W))
+
+
 @pytest.mark.parametrize("channels", [16, 64, 128, 256, 512, 24, 300])
 @pytest.mark.parametrize("apart", [1, 3, 5, 33, 97])
 def test_bits_of_listed_pixels(channels, apart):
