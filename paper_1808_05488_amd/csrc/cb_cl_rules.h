@@ -171,11 +171,11 @@ CB_HD unsigned cl_xcd_rows(unsigned MT, unsigned NT, unsigned parts, unsigned fi
 // 30.3 / 24.2, but 120x160, 10 % 55.1 / 56.1; 128 -> 128, 9x9, 60x80 44.8 / 37.8; 256 -> 128 there 77.5 / 56.7; bfloat16 256 -> 256, 7x7, 60x80, 20 % 55.0 / 44.8.  Shorter filters
 // are not considered, for which the choice alone took 0.4 us: 256 -> 256, 3x3, 92x164 (72 groups) 29.7 / 30.6; bfloat16 512 -> 512, 3x3, 46x82 (144) 42.3 / 43.0.
 // float32: K is only divided where that rounds the sums no worse than the whole tile.  Relative errors of sums over a K of 4 608 against float64: one
-// chain of products 1.06e-6, two (the small terms in one of their own: up to two tiles a wavefront, and four in parts) 4.1e-7, two in each of four wavefronts
-// that share K 1.9e-7; in p parts they fall with the square root of p.  Without the rule 512 -> 260, 3x3, 46x82, every output: 4.1e-7 whole, 7.4e-7 in
-// two parts of one chain.
+// chain of products 1.06e-6, two (the small terms in one of their own: up to four tiles a wavefront) 4.1e-7, groups of six products added at once (128 x 64) 2.5e-7, two in each of four wavefronts
+// that share K 1.9e-7; in p parts they fall with the square root of p.  The numbers of parts are those for a 128 x 64 tile of one chain, which it was when they were fitted: 2 of its parts are as exact as any
+// whole tile now, and the costs of more layers in so few are not measured.
 constexpr unsigned CL_SPLIT_NS = 8500, CL_SPLIT_MAX = 8;     // (tiles: at most 256)
-// the fewest parts of one chain (or of two) that are as exact as a whole tile: 0: 64 x 16 and 64 x 32, 1: 16 x 16, 2: 128 x 32 and 128 x 64
+// the fewest parts of a 128 x 64 tile as one chain (or of 128 x 32, two) that are as exact as a whole tile: 0: 64 x 16 and 64 x 32, 1: 16 x 16, 2: 128 x 32 and 128 x 64
 CB_HD unsigned cl_least_parts(int whole, bool two) { return whole == 2 ? 2u : whole == 0 ? (two ? 2u : 7u) : two ? 5u : CL_SPLIT_MAX + 1u; }
 CB_HD bool cl_split_pays(unsigned nkg, bool f32) { return nkg >= (f32 ? 96u : 256u); }
 template <bool F32> CB_HD unsigned cl_split(int N, int O, unsigned nkg, unsigned ws_bytes)

@@ -25,9 +25,9 @@
 // leading one,
 //     h*h + (h*m + m*h) + (h*l + m*m + l*h),
 // are accumulated in float32: 6/16 of the matrix-core time.  What is left out (m*l, l*m, l*l) is below 2^-24 of the
-// product; the sum over K is rounded 6 times per 32 products instead of up to 32 times.  Error against float64 over
-// whole layers, before -> now: 64 -> 64 3x3 4.4e-7 -> 3.6e-7, 128 -> 128 3x3 5.7e-7 -> 4.8e-7, 256 -> 256 3x3 8.1e-7 ->
-// 7.0e-7.  The epilogue takes the 2^48 out again, exactly, together with the bias.  (Without the 2^24, values below 2^-110 lost
+// product; the sum over K is rounded once per 32 products instead of up to 32 times (TWO and GROUPED below).  Error against float64 over
+// whole layers, float32 instruction / now: 64 -> 64 3x3 4.4e-7 / 1.3e-7, 128 -> 128 3x3 5.7e-7 / 1.3e-7, 256 -> 256 3x3 8.1e-7 /
+// 1.7e-7.  The epilogue takes the 2^48 out again, exactly, together with the bias.  (Without the 2^24, values below 2^-110 lost
 // their last term: 4e-6 of the result at 2^-116, 1e-3 at 2^-124.)
 // The terms of an infinity, a NaN or a value of 2^104 and more do not add up to it, and sums beyond 2^80 overflow; any
 // such makes the accumulated sum non-finite, and the epilogue recomputes every non-finite sum in plain
@@ -212,10 +212,16 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     // 240x320 29.9 / 28.6, a full update of 256 -> 256 92x164 107.0 / 102.5.  Wider bfloat16 tiles have the wavefronts and not the registers (128 x 128 spread: 458 / 544).
     constexpr bool SPREAD = F32 ? TM * TN <= (P2 ? 8 : 4) : TM * TN <= 2 && WGK == 1;
     constexpr int NF = UKW * TN, BR = !F32 && SPREAD ? 4 : 2;
-    constexpr bool TWO = TM * TN < 4 || (SPLIT && F32 && TM * TN == 4);     // second accumulator chain where a wavefront has few tiles (errors: cl_least_parts)
+    // float32: what rounds a sum is every product that is added to it.  TWO: the five small ones of a group are a second chain, where there are registers for its sums.  GROUPED: the six
+    // of a group are summed from zero and added at once; 16 vector additions for 96 cycles of matrix instructions.  Relative errors of whole layers against float64, one chain of six / so:
+    // 128 -> 128 3x3 5.3e-7 / 1.3e-7, 256 -> 256 3x3 7.3e-7 / 1.7e-7, 64 -> 256 7x7 8.7e-7 / 1.9e-7, 32 -> 32 3x3 2.5e-7 / 0.9e-7.  us: full update of 256 -> 256 92x164 104.9 / 108.8, of 64 -> 256 7x7
+    // 120x160 172.3 / 179.6, of 64 -> 64 480x640 197.1 / 198.5, 128 -> 128 1080p 2 % changed 456.0 / 460.3, five-layer net 116.8 / 116.5.
+    constexpr bool TWO = TM * TN < 4 || (F32 && TM * TN == 4), GROUPED = F32 && !TWO;
     extern __shared__ uint4 dyn_lds4[];          // two stage buffers, then the listed pixel of every column
     char* const Bs = reinterpret_cast<char*>(dyn_lds4);
     int* const qs = reinterpret_cast<int*>(Bs + 2 * BUF);
+    float* const bs = reinterpret_cast<float*>(qs + BN + 4);      // (GROUPED: the tile's bias, for which there are no registers; behind it and the pixels SPLIT has a word)
+    static_assert(!GROUPED || 2 * BUF + 4 * (BN + 4 + BM) <= cl_lds<T>(128), "room for a tile's bias");
 
     const int nkg = F32 ? (g.Cs * g.kh * g.kw + 63) / 64 * 2 : (g.Cs * g.kh * g.kw + 127) / 128 * 4;       // k-groups of the packed filter matrix
     const int stages = (nkg + UKG - 1) / UKG;
@@ -372,9 +378,15 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = m0 + (wm * TM + a) * 16 + (t0 & 63) / 16 * 4 + r;
-                bv[a][r] = LEAN ? 0.f : bias[m < g.O ? m : g.O - 1];
+                bv[a][r] = LEAN || GROUPED ? 0.f : bias[m < g.O ? m : g.O - 1];
             }
-        __syncthreads();                          // the previous tile has read its last stage and its qs
+        float bias_of = 0.f;
+        if constexpr (GROUPED) bias_of = bias[m0 + t0 % BM < g.O ? m0 + t0 % BM : g.O - 1];
+        __syncthreads();                          // the previous tile has read its last stage, its qs and its bias
+        if constexpr (GROUPED) {
+            static_assert(BM <= 256, "a thread for each row");
+            if (t0 < BM) bs[t0] = bias_of;
+        }
         if (ch < NP) qs[mycol] = q;
 #pragma unroll
         for (int p = 0; p < NP; ++p) lds_store(0, p, breg[0][p]);
@@ -433,7 +445,21 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
                             d[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[a][ea]),
                                                                               __builtin_bit_cast(bf16x8, bfr[f % BR][eb]), d[a][b], 0, 0, 0);
                     };
-                    if constexpr (F32) {
+                    if constexpr (GROUPED) {
+                        floatx4 t[TM];
+                        auto term = [&](int ea, int eb, bool first) {
+#pragma unroll
+                            for (int a = 0; a < TM; ++a)
+                                t[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[a][ea]), __builtin_bit_cast(bf16x8, bfr[f % BR][eb]),
+                                                                               first ? floatx4{0.f, 0.f, 0.f, 0.f} : t[a], 0, 0, 0);
+                        };
+                        term(2, 0, true); term(1, 1, false); term(0, 2, false); term(1, 0, false); term(0, 1, false); term(0, 0, false);
+#pragma unroll
+                        for (int a = 0; a < TM; ++a) {
+                            acc[a][b] += t[a];
+                            asm volatile("" : "+v"(acc[a][b]));       // (here: moved to the end of the stage all additions' operands are held, and 66 - 126 registers spill)
+                        }
+                    } else if constexpr (F32) {
                         // smallest terms first; a chain of their own where a wavefront has few tiles
                         floatx4 (&rest)[TM][TN] = TWO ? acc1 : acc;
                         mul(2, 0, rest); mul(1, 1, rest); mul(0, 2, rest); mul(1, 0, rest); mul(0, 1, rest);
@@ -546,6 +572,14 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
             for (int a = 0; a < TM; ++a)
 #pragma unroll
                 for (int b = 0; b < TN; ++b) acc[a][b] = sum[a][b];
+        }
+        if constexpr (GROUPED) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a) {
+                const floatx4 v = *reinterpret_cast<const floatx4*>(bs + (wm * TM + a) * 16 + lqo * 4);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) bv[a][r] = v[r];
+            }
         }
         if constexpr (LEAN) {
 #pragma unroll
