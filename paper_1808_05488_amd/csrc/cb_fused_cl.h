@@ -213,7 +213,7 @@ __device__ __forceinline__ void fused_cl_body(const Geom& g, const ClDiv& div, c
     constexpr bool SPREAD = F32 ? TM * TN <= (P2 ? 8 : 4) : TM * TN <= 2 && WGK == 1;
     constexpr int NF = UKW * TN, BR = !F32 && SPREAD ? 4 : 2;
     // float32: what rounds a sum is every product that is added to it.  TWO: the five small ones of a group are a second chain, where there are registers for its sums.  GROUPED: the six
-    // of a group are summed from zero and added at once; 16 vector additions for 96 cycles of matrix instructions.  Relative errors of whole layers against float64, one chain of six / so:
+    // of a group are summed from zero and added at once; 4 vector additions, 16 cycles, for 96 of matrix instructions.  Relative errors of whole layers against float64, one chain of six / so:
     // 128 -> 128 3x3 5.3e-7 / 1.3e-7, 256 -> 256 3x3 7.3e-7 / 1.7e-7, 64 -> 256 7x7 8.7e-7 / 1.9e-7, 32 -> 32 3x3 2.5e-7 / 0.9e-7.  us: full update of 256 -> 256 92x164 104.9 / 108.8, of 64 -> 256 7x7
     // 120x160 172.3 / 179.6, of 64 -> 64 480x640 197.1 / 198.5, 128 -> 128 1080p 2 % changed 456.0 / 460.3, five-layer net 116.8 / 116.5.
     constexpr bool TWO = TM * TN < 4 || (F32 && TM * TN == 4), GROUPED = F32 && !TWO;
